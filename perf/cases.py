@@ -192,7 +192,8 @@ def prepare(case, seed):
         tensors.append(edgc.Tensor(t["G"], torch.empty_like(t["G"]), E, Q, P, case["residual"] == "zero"))
     single = case["calls"] == "single"
     rows, cols = (tensors[0].grad.shape if single else (64, 64))
-    ctx = edgc.Context(0, max_bins=case["bins"], max_rank=max(r, 4), max_rows=rows, max_cols=cols)
+    # a program sizes its context for the largest rank that the rule may decide on, not for the rank of the moment
+    ctx = edgc.Context(0, max_bins=case["bins"], max_rank=128, max_rows=rows, max_cols=cols)
     state = {"case": case, "ctx": ctx, "tensors": tensors, "flats": [t.grad.view(-1) for t in tensors],
              "result": torch.empty(ENTROPY_RESULT_BYTES, dtype=torch.uint8, pin_memory=True),
              "counts": torch.zeros(case["bins"], dtype=torch.int64, device="cuda"), "step": seed % 1000}
