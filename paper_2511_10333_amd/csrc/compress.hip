@@ -2314,7 +2314,7 @@ static int run_orthonormalise(edgc_ctx* ctx, Group& g, const TensorScratch* cap,
 {
     const uint32_t r = g.r;
     const uint32_t RP = rank_tiles(r) * 32;
-    const uint32_t t16 = r <= 16 ? 1 : r <= 32 ? 2 : r <= 64 ? 4 : 8;   // 16-wide tiles per side
+    const uint32_t t16 = gram_tiles(r);
     const uint32_t ntile = t16 * (t16 + 1) / 2, ne = ntile * 256;
     uint32_t tgt[kMaxGroup];
     share_targets(g, static_cast<uint32_t>(ctx->num_cu) * 2, tgt);

@@ -36,10 +36,14 @@ struct Scratch {
 
 constexpr int kMaxReduceBlocks = 4096;
 
-// Doubles behind `rinv`: the upper-triangle 16x16 tiles of R^-1 for a rank padded to a multiple of 16
-inline size_t rinv_elems(uint32_t max_rank)
+// 16-wide tiles per side of the Gram matrix and of R^-1 at a rank: the orthonormalisation kernels are built for
+// 1, 2, 4 and 8, and work on (and store) every tile of the size they are built for.
+constexpr uint32_t gram_tiles(uint32_t r) { return r <= 16 ? 1 : r <= 32 ? 2 : r <= 64 ? 4 : 8; }
+
+// Doubles behind `rinv`: the upper-triangle 16x16 tiles of R^-1 at any rank up to max_rank
+constexpr size_t rinv_elems(uint32_t max_rank)
 {
-    const size_t t = (static_cast<size_t>(max_rank) + 15) / 16;
+    const size_t t = gram_tiles(max_rank);
     return t * (t + 1) / 2 * 256;
 }
 

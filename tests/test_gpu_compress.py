@@ -127,6 +127,29 @@ def test_ranks_next_to_the_tile_edges_of_the_factorisation(r):
     assert np.abs(P64.T @ P64 - np.eye(r)).max() < 1e-5
 
 
+@pytest.mark.parametrize("r", [33, 48, 79, 112])
+def test_contexts_and_batch_slots_made_for_exactly_that_rank(r):
+    # the factorisation works on 64 or 128 columns here, and its scratch has to hold them all
+    m, n, ld = 256, 384, (r + 3) // 4 * 4
+    G = gen.lowrank_plus_noise(m, n, 160, 0.97, 1e-3, seed=r)
+    q0 = _q0(n, r)
+    Po, Qo, Do = orc.compress(G, None, q0[:, :r].copy(), r)
+    c = edgc.Context(0, 256, r, m, n)
+    c.reserve_batch([(m, n)])
+    for batch in (False, True):
+        E, P, Q = (torch.empty((m, n), device="cuda"), torch.zeros((m, ld), device="cuda"),
+                   torch.zeros((n, ld), device="cuda"))
+        Q[:, :r] = to_dev(q0[:, :r].copy())
+        Gd = to_dev(G)
+        if batch:
+            c.compress_batch([edgc.Tensor(Gd, torch.empty_like(Gd), E, Q, P, True)], r)
+        else:
+            c.compress(Gd, E, True, Q, P, r)
+        torch.cuda.synchronize()
+        assert rel_fro(to_host(P)[:, :r], Po) < 1e-3 and rel_fro(to_host(Q)[:, :r], Qo) < 1e-3
+    c.close()
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_strided_gradient_rows(dtype):
     G = gen.lowrank_plus_noise(192, 320, 32, 0.9, 1e-4, seed=5, dtype=dtype)

@@ -4,6 +4,7 @@ import ctypes
 import math
 import os
 import re
+import subprocess
 
 import numpy as np
 import pytest
@@ -38,6 +39,23 @@ def test_struct_sizes_match_the_header_layout():
     assert ctypes.sizeof(b._RankCost) == 32
     assert ctypes.sizeof(b._RankBounds) == 16
     assert ctypes.sizeof(b._DevicePeaks) == 40            # copy, read, mfma, bytes, write
+
+
+def test_scratch_of_the_inverse_factor_holds_every_tile_the_kernels_store(tmp_path):
+    """The orthonormalisation kernels exist for 1, 2, 4 and 8 tiles of 16 columns a side and store every upper-triangle
+    tile of that size: a context made for rank r needs that room for r and for every smaller rank."""
+    src = tmp_path / "rinv.cpp"
+    src.write_text('#include <cstdio>\n#include "edgc_internal.h"\n'
+                   'int main() { for (unsigned r = 1; r <= 128; ++r) '
+                   'std::printf("%zu\\n", edgc::rinv_elems(r)); }\n')
+    exe = tmp_path / "rinv"
+    subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-w", "-I/opt/rocm/include",
+                    "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(ROOT, "paper_2511_10333_amd", "csrc"),
+                    str(src), "-o", str(exe)], check=True)
+    sizes = [int(x) for x in subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.split()]
+    for r in range(1, 129):
+        t = next(t for t in (1, 2, 4, 8) if 16 * t >= r)
+        assert sizes[r - 1] >= t * (t + 1) // 2 * 256, f"rank {r}"
 
 
 def _both(prm_kwargs, windows):
