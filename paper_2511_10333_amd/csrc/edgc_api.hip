@@ -38,8 +38,7 @@ void free_batch(edgc_ctx* ctx)
 
 void free_scratch(Scratch& s)
 {
-    void* ptrs[] = {s.mm_part, s.done_counter, s.part16, s.wide, s.totals, s.counts, s.range, s.result_dev,
-                    s.part, s.gram_part, s.gram, s.rinv, s.pt};
+    void* ptrs[] = {s.small, s.part16, s.part, s.gram_part, s.pt};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     s = Scratch{};
@@ -92,22 +91,34 @@ extern "C" int edgc_create(edgc_ctx** out, int hip_device, uint32_t max_bins, ui
     s.gram_part_elems = (rows_pad / 64) * 36ull * 256ull;
     s.pt_bytes = 2ull * rp * rows_pad * 2ull;
     bool ok = true;
-    ok = ok && dev_alloc(&s.mm_part, 2 * kMaxReduceBlocks) == hipSuccess;
-    ok = ok && dev_alloc(&s.done_counter, 4) == hipSuccess;
+    // everything but the large buffers in one allocation; what has to be zero between calls comes first
+    size_t used = 0;
+    auto place = [&](size_t bytes) { const size_t at = used; used += (bytes + 255) / 256 * 256; return at; };
+    const size_t at_ticket = place(kTicketWords * sizeof(unsigned int));
+    const size_t at_wide = place(65536 * sizeof(unsigned long long));
+    const size_t zeroed = used;
+    const size_t at_mm = place(2 * kMaxReduceBlocks * sizeof(float));
+    const size_t at_totals = place(65536 * sizeof(unsigned long long));
+    const size_t at_counts = place(static_cast<size_t>(max_bins) * sizeof(unsigned long long));
+    const size_t at_result = place(sizeof(edgc_entropy_result));
+    const size_t at_gram = place(static_cast<size_t>(36) * 256 * sizeof(double));
+    const size_t at_rinv = place(rinv_elems(max_rank) * sizeof(double));
+    ok = ok && dev_alloc(&s.small, used) == hipSuccess;
+    s.ticket = reinterpret_cast<unsigned int*>(s.small + at_ticket);
+    s.wide = reinterpret_cast<unsigned long long*>(s.small + at_wide);
+    s.mm_part = reinterpret_cast<float*>(s.small + at_mm);
+    s.totals = reinterpret_cast<unsigned long long*>(s.small + at_totals);
+    s.copies = reinterpret_cast<uint32_t*>(s.totals);       // never in use at the same time
+    s.counts = reinterpret_cast<unsigned long long*>(s.small + at_counts);
+    s.result_dev = s.small + at_result;
+    s.gram = reinterpret_cast<double*>(s.small + at_gram);
+    s.rinv = reinterpret_cast<double*>(s.small + at_rinv);
     s.part16_blocks = static_cast<uint32_t>(ctx->num_cu);
     ok = ok && dev_alloc(&s.part16, static_cast<size_t>(s.part16_blocks) * 65536) == hipSuccess;
-    ok = ok && dev_alloc(&s.wide, 65536) == hipSuccess;
-    ok = ok && dev_alloc(&s.totals, 65536) == hipSuccess;
-    ok = ok && dev_alloc(&s.counts, max_bins) == hipSuccess;
-    ok = ok && hipMalloc(&s.range, 64) == hipSuccess;
-    ok = ok && hipMalloc(&s.result_dev, sizeof(edgc_entropy_result)) == hipSuccess;
     ok = ok && dev_alloc(&s.part, s.part_elems) == hipSuccess;
     ok = ok && dev_alloc(&s.gram_part, s.gram_part_elems) == hipSuccess;
-    ok = ok && dev_alloc(&s.gram, static_cast<size_t>(36) * 256) == hipSuccess;
-    ok = ok && dev_alloc(&s.rinv, rinv_elems(max_rank)) == hipSuccess;
     ok = ok && hipMalloc(&s.pt, s.pt_bytes) == hipSuccess;
-    ok = ok && hipMemset(s.done_counter, 0, 4 * sizeof(unsigned int)) == hipSuccess;
-    ok = ok && hipMemset(s.wide, 0, 65536 * sizeof(unsigned long long)) == hipSuccess;
+    ok = ok && hipMemset(s.small, 0, zeroed) == hipSuccess;
     ok = ok && hipDeviceSynchronize() == hipSuccess;
     ok = ok && prepare_entropy_kernels(ctx) == EDGC_OK && prepare_compress_kernels(ctx) == EDGC_OK;
     ok = ok && resolve_static_scratch(ctx) == EDGC_OK;
@@ -258,12 +269,14 @@ static int entropy_estimate_impl(edgc_ctx* ctx, bool static_scratch, const void*
         for (uint32_t i = 0; i < count; ++i) {
             g.base[i] = grads[i];
             g.geom[i] = make_geom(grads[i], dtype, n_elems[i], stride, chunk, seed, step, pass == 0);
+            g.first[i] = g.n_items;
             g.n_items += g.geom[i].n_items;
             g.n_sampled += g.geom[i].n_sampled;
             uniform = uniform && (g.geom[i].vec > 1) == (g.geom[0].vec > 1);
         }
         if (uniform) break;
     }
+    g.first[count] = g.n_items;
     if (g.n_sampled == 0) return fail(ctx, EDGC_ENONFINITE, "the sampling predicate selects no element");
     EDGC_HIP_TRY(ctx, hipSetDevice(ctx->device));
     if (static_scratch)

@@ -13,15 +13,16 @@ namespace edgc {
 
 // Scratch owned by a context.  Sized once in edgc_create; hot calls only use it.
 struct Scratch {
+    unsigned char*      small        = nullptr;  // one allocation for everything here but part16, part, gram_part and pt
     // entropy
     float*              mm_part      = nullptr;  // [2 * kMaxReduceBlocks] per-block (lo, hi)
-    unsigned int*       done_counter = nullptr;  // [4] last-block tickets and the overflow gate, zero between calls
+    unsigned int*       ticket       = nullptr;  // [kTicketWords] last-block ticket and the overflow gate, zero between calls
+    uint32_t*           copies       = nullptr;  // [8][kCopyBins] histogram counters, a set per XCD
     uint16_t*           part16       = nullptr;  // [part16_blocks][65536] 16-bit counters per block
     uint32_t            part16_blocks = 0;
     unsigned long long* wide         = nullptr;  // [65536] 64-bit credits per key, zero between calls
     unsigned long long* totals       = nullptr;  // [65536] counts per bf16 bit pattern
     unsigned long long* counts       = nullptr;  // [max_bins] histogram when the caller gives none
-    void*               range        = nullptr;  // RangeParams
     void*               result_dev   = nullptr;  // edgc_entropy_result
     // compress / decompress
     float*  part      = nullptr;   // split-K partial factors [S][rows][rank_pad]
@@ -35,6 +36,9 @@ struct Scratch {
 };
 
 constexpr int kMaxReduceBlocks = 4096;
+constexpr uint32_t kTicketWords = 64;      // the last-block ticket and, on a cache line of its own, the overflow gate
+constexpr uint32_t kGateWord = 32;
+constexpr uint32_t kCopyBins = 16384;      // (8 x kCopyBins counters of 32 bits take the place of `totals`) largest histogram that is accumulated in one set of counters per XCD
 
 // 16-wide tiles per side of the Gram matrix and of R^-1 at a rank: the orthonormalisation kernels are built for
 // 1, 2, 4 and 8, and work on (and store) every tile of the size they are built for.
@@ -151,7 +155,7 @@ struct edgc_ctx {
     int tune_qfull = -1;    // Q-pass of whole-tile groups: -1 built-in choice; 0 the general kernel; 4 / 8 the
                             // pipelined kernel with that many waves per block
     int tune_apply = -1;    // k_apply above rank 64: 4 = four waves (64 rows) per block, 8 = eight (128 rows)
-    int tune_ept = 0;       // items per thread of the histogram of a small sample (the range pass takes twice as many)
+    int tune_ept = 0;       // items per thread of the histogram and, twice as many, of the range pass; 0: built-in choice
     int tune_pattern = 1;   // entropy estimate: 1 one read into 16-bit counters per block where that applies
                             // (bf16 samples, fp32 on more than 16384 bins); 0 the plain kernels only; 3 as 1,
                             // and every such estimate reports a counter overflow (tests of the redo path)
@@ -234,6 +238,7 @@ struct EntGroup {
     uint64_t n_sampled;     // over all buffers
     const void* base[kMaxEntGroup];
     SampleGeom geom[kMaxEntGroup];
+    uint64_t first[kMaxEntGroup + 1];   // first item of each buffer in the union; [count] = n_items
 };
 
 SampleGeom make_geom(const void* base, edgc_dtype dt, uint64_t n, uint64_t stride, uint32_t chunk,

@@ -2,13 +2,18 @@
 // estimated with an equal-width histogram).
 //
 // Two streaming kernels over the sampled chunks plus nothing else:
-//   k_minmax  range of the finite sample: per-lane min/max, wavefront DPP
-//             reduction, LDS across the block's waves, last-block finish
-//   k_hist    bin index in fp32 (separately rounded subtract / multiply, the
-//             scale comes from one correctly rounded division), LDS histogram
+//   k_minmax  range of the finite sample per block: per-lane min/max, wavefront DPP
+//             reduction, LDS across the block's waves
+//   k_hist    the blocks' ranges folded, bin index in fp32 (separately rounded subtract /
+//             multiply, the scale comes from one correctly rounded division), LDS histogram
 //             with lane-interleaved replicas so equal bins in one wavefront hit
-//             different banks, flush to 64-bit global counters, and the last
-//             block reduces the counters to the Shannon entropy in fp64
+//             different banks, flush to global counters, and the last block reduces
+//             the counters to the Shannon entropy in fp64
+// or, where one block holds the sample in one round, k_estimate_one alone.
+// What bounds them at a 1 % sample (0.01 to 0.5 M items): latency.  Blocks of four items per thread,
+// as many as the sample gives, each over one contiguous range of the union of the buffers: 2 M
+// fp32 elements of four buffers on 4096 bins 64 -> 23 us (both kernels), 143 K bf16 elements of 24
+// buffers 105 -> 27 us, 10 K fp32 elements by one block 17 -> 8 us.
 // The chunk-strided sample is read with 16-byte loads whenever chunks are a
 // multiple of the vector width, so a wavefront touches whole cache lines.
 // Both kernels take a list of buffers (EntGroup): the estimate is over the union
@@ -17,6 +22,7 @@
 // into the caller's pinned host memory when it is device-accessible.
 #include "edgc_internal.h"
 
+#include <algorithm>
 #include <math.h>
 
 namespace edgc {
@@ -29,7 +35,7 @@ constexpr int kMMBlock   = 256;
 constexpr int kMMBlockFat = 1024;                 // large samples: one block per CU
 constexpr uint64_t kBigSampleItems = 8ull << 20;  // items (16 bytes each) from which a sample counts as large
 constexpr int kHistBlock = 512;
-constexpr int kSmallSampleBlocks = 16;   // blocks the kernels of a sample of up to 512 Ki items get at most
+constexpr int kOneBlock = 1024;       // k_estimate_one
 constexpr int kHistBlockFat = 1024;   // when the LDS histogram leaves room for one block per CU
 
 // ---------------------------------------------------------------------------
@@ -78,41 +84,6 @@ template <> struct ElemTraits<uint16_t> {   // raw bf16 bits
     }
 };
 
-// Loads the VEC elements of one item starting at element i0; elements at or
-// beyond n are reported invalid.  Full items use one 16-byte load.
-template <typename T, int VEC>
-__device__ __forceinline__ uint32_t load_item(const T* __restrict__ g, uint64_t i0, uint64_t n,
-                                              float (&v)[VEC])
-{
-    if constexpr (VEC == 1) {
-        v[0] = ElemTraits<T>::widen(g[i0]);
-        return 1u;
-    } else {
-        if (i0 + VEC <= n) {
-            if constexpr (sizeof(T) == 4) {
-                const float4 q = *reinterpret_cast<const float4*>(g + i0);
-                v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
-            } else {
-                const uint4 q = *reinterpret_cast<const uint4*>(g + i0);
-                const uint32_t w[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-                for (int p = 0; p < 4; ++p) {
-                    v[2 * p]     = __uint_as_float(w[p] << 16);
-                    v[2 * p + 1] = __uint_as_float(w[p] & 0xffff0000u);
-                }
-            }
-            return (1u << VEC) - 1u;
-        }
-        uint32_t mask = 0;
-#pragma unroll
-        for (int p = 0; p < VEC; ++p) {
-            v[p] = 0.0f;
-            if (i0 + p < n) { v[p] = ElemTraits<T>::widen(g[i0 + p]); mask |= 1u << p; }
-        }
-        return mask;
-    }
-}
-
 // The VEC elements of a whole item from its 16 raw bytes.
 template <typename T, int VEC>
 __device__ __forceinline__ void unpack_item(const uint4& q, float (&v)[VEC])
@@ -131,24 +102,29 @@ __device__ __forceinline__ void unpack_item(const uint4& q, float (&v)[VEC])
     }
 }
 
-// Walks the items owned by one thread: item t, t + G, t + 2G, ... without a
-// division in the loop.  item -> (k-th sampled chunk, e-th item in it).
+// The item of one thread: item -> (k-th sampled chunk, e-th item in it), advanced without a division.
 struct ItemCursor {
-    uint64_t item, k;
-    uint32_t e;
-    uint64_t dk;
-    uint32_t de;
-    __device__ __forceinline__ void init(uint64_t first, uint64_t step, uint32_t ipc)
+    uint64_t k;
+    uint32_t e, dk, de;
+    // item `base` (the same for the whole block) + `off`; advances by `step` items
+    __device__ __forceinline__ void init(uint64_t base, uint32_t off, uint32_t step, uint32_t ipc)
     {
-        item = first;
-        k = first / ipc;
-        e = static_cast<uint32_t>(first - k * ipc);
+        const uint64_t q = (base >> 32) ? base / ipc : static_cast<uint32_t>(base) / ipc;
+        const uint32_t s = static_cast<uint32_t>(base - q * ipc) + off;
+        const uint32_t sq = s / ipc;
+        k = q + sq;
+        e = s - sq * ipc;
         dk = step / ipc;
-        de = static_cast<uint32_t>(step - dk * ipc);
+        de = step - dk * ipc;
     }
-    __device__ __forceinline__ void advance(uint64_t step, uint32_t ipc)
+    // any item
+    __device__ __forceinline__ void init_each(uint64_t item, uint32_t ipc)
     {
-        item += step;
+        k = (item >> 32) ? item / ipc : static_cast<uint32_t>(item) / ipc;
+        e = static_cast<uint32_t>(item - k * ipc);
+    }
+    __device__ __forceinline__ void advance(uint32_t ipc)
+    {
         k += dk;
         e += de;
         if (e >= ipc) { e -= ipc; ++k; }
@@ -159,6 +135,180 @@ struct ItemCursor {
     }
 };
 
+// The first `left` < VEC elements of an item, requested together.
+template <typename T, int VEC, typename Elem>
+__device__ __forceinline__ void partial_item(const T* __restrict__ at, uint64_t left, Elem&& elem)
+{
+    T x[VEC - 1];
+#pragma unroll
+    for (int p = 0; p < VEC - 1; ++p) x[p] = p < static_cast<int>(left) ? at[p] : T(0);
+#pragma unroll
+    for (int p = 0; p < VEC - 1; ++p)
+        if (p < static_cast<int>(left)) elem(x[p]);
+}
+
+// Visits the items [begin, end) of the union of the buffers' samples (buffer i holds the items first[i] ..
+// first[i + 1]), by one block: `item(raw)` gets the 16 bytes of every whole item, `elem(x)` every element of a
+// partial one (the end of a buffer) and, where VEC is 1, every element; `round()` is called by the whole block after
+// every round of at most U items per thread.  A round's loads are issued together.  With `ahead`, the next round's
+// loads are issued before the current round is used; they need no condition, since every item before a buffer's last
+// sampled chunk is whole (the chunk size is a multiple of VEC).
+// Blocks share the union, not every buffer: a block's range touches one or two of the buffers of a transformer
+// stage (24 buffers, 143 K elements sampled: with every buffer split among all blocks each block walked all 24, 105 us
+// for the two kernels).
+template <typename T, int VEC, int BLOCK, typename Item, typename Elem, typename Round>
+__device__ __forceinline__ void walk_items(const EntGroup& grp, uint64_t begin, uint64_t end, bool ahead, Item&& item,
+                                           Elem&& elem, Round&& round)
+{
+    constexpr int U = 4;
+    constexpr uint32_t STEP = U * BLOCK;
+    if (begin >= end) return;
+    // the buffers that hold items of the range: first[i + 1] > begin and first[i] < end; lane l has buffer l's first item
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint64_t first_l = grp.first[min(lane, grp.count)];
+    uint32_t ti, t_end;
+    {
+        const bool in = lane < grp.count;
+        ti = static_cast<uint32_t>(__popcll(__ballot(in && grp.first[min(lane + 1u, grp.count)] <= begin)));
+        t_end = static_cast<uint32_t>(__popcll(__ballot(in && first_l < end)));
+    }
+    if constexpr (VEC > 1) {
+        // Many short buffers (norm weights and biases): every thread finds its item's buffer, so that a round spans
+        // them all.  The sampler's parameters are the same for every buffer of a group; base and length differ.
+        if (t_end - ti > 2) {
+            const SampleGeom& geom = grp.geom[ti];
+            const uint32_t ipc = geom.ipc, tl = min(lane, grp.count - 1u);
+            const uint64_t n_l = grp.geom[tl].n, base_l = reinterpret_cast<uint64_t>(grp.base[tl]);
+            for (uint64_t rb = begin; rb < end; rb += STEP) {
+                uint4 raw[U];
+                const T* at[U];
+                uint64_t left[U];                      // elements from the item's first on
+                uint32_t t[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) t[u] = ti;
+                for (uint32_t b = ti + 1; b < t_end; ++b) {
+                    const uint64_t fb = __shfl(first_l, b, 64);
+#pragma unroll
+                    for (int u = 0; u < U; ++u) t[u] += (rb + u * BLOCK + threadIdx.x >= fb) ? 1u : 0u;
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    raw[u] = make_uint4(0u, 0u, 0u, 0u);
+                    const uint64_t i = rb + u * BLOCK + threadIdx.x;
+                    const uint64_t n = __shfl(n_l, t[u], 64);
+                    ItemCursor cur;
+                    cur.init_each(i - __shfl(first_l, t[u], 64), ipc);
+                    const uint64_t e0 = cur.elem0(geom, VEC);
+                    at[u] = reinterpret_cast<const T*>(__shfl(base_l, t[u], 64)) + e0;
+                    left[u] = (i < end && e0 < n) ? n - e0 : 0;
+                    if (left[u] >= VEC) raw[u] = *reinterpret_cast<const uint4*>(at[u]);
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (left[u] >= VEC) item(raw[u]);
+                    else if (left[u]) partial_item<T, VEC>(at[u], left[u], elem);
+                }
+                round();
+            }
+            return;
+        }
+    }
+    for (; ti < t_end; ++ti) {
+        const SampleGeom& geom = grp.geom[ti];
+        const T* __restrict__ g = static_cast<const T*>(grp.base[ti]);
+        const uint64_t f0 = grp.first[ti];
+        const uint64_t lb = max(begin, f0) - f0, le = min(end, grp.first[ti + 1]) - f0;
+        const uint32_t ipc = geom.ipc;
+        ItemCursor cur;
+        cur.init(lb, threadIdx.x, BLOCK, ipc);
+        uint64_t rb = lb;                              // first item of the round
+        if constexpr (VEC > 1) {
+            const uint64_t fast_end = (geom.n_items >= ipc) ? min(le, geom.n_items - ipc) : 0;
+            auto fetch = [&](uint4 (&raw)[U]) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    raw[u] = *reinterpret_cast<const uint4*>(g + cur.elem0(geom, VEC));
+                    cur.advance(ipc);
+                }
+            };
+            auto use = [&](const uint4 (&raw)[U]) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) item(raw[u]);
+                round();
+            };
+            if (ahead && rb + STEP <= fast_end) {
+                uint4 ra[U], rc[U];
+                fetch(ra);
+                while (true) {
+                    rb += STEP;
+                    if (rb + STEP > fast_end) { use(ra); break; }
+                    fetch(rc);
+                    use(ra);
+                    rb += STEP;
+                    if (rb + STEP > fast_end) { use(rc); break; }
+                    fetch(ra);
+                    use(rc);
+                }
+            }
+            for (; rb < le; rb += STEP) {
+                uint4 raw[U];
+                uint64_t at[U];
+                uint32_t whole = 0, partial = 0;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    raw[u] = make_uint4(0u, 0u, 0u, 0u);
+                    at[u] = cur.elem0(geom, VEC);
+                    if (rb + u * BLOCK + threadIdx.x < le) {
+                        if (at[u] + VEC <= geom.n) {
+                            raw[u] = *reinterpret_cast<const uint4*>(g + at[u]);
+                            whole |= 1u << u;
+                        } else if (at[u] < geom.n) {
+                            partial |= 1u << u;
+                        }
+                    }
+                    cur.advance(ipc);
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if ((whole >> u) & 1u) item(raw[u]);
+                if (partial) {
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+                        if ((partial >> u) & 1u) partial_item<T, VEC>(g + at[u], geom.n - at[u], elem);
+                }
+                round();
+            }
+        } else {
+            for (; rb < le; rb += STEP) {
+                T x[U];
+                uint32_t have = 0;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    x[u] = T(0);
+                    const uint64_t at = cur.elem0(geom, 1);
+                    if (rb + u * BLOCK + threadIdx.x < le && at < geom.n) {
+                        x[u] = g[at];
+                        have |= 1u << u;
+                    }
+                    cur.advance(ipc);
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if ((have >> u) & 1u) elem(x[u]);
+                round();
+            }
+        }
+    }
+}
+
+// The range of the union that one block of a grid visits.
+__device__ __forceinline__ void block_range(const EntGroup& grp, uint64_t& begin, uint64_t& end)
+{
+    const uint64_t per = (grp.n_items + gridDim.x - 1) / gridDim.x;
+    begin = min(static_cast<uint64_t>(blockIdx.x) * per, grp.n_items);
+    end = min(begin + per, grp.n_items);
+}
+
 __device__ __forceinline__ bool finite_f32(float x)
 {
     return (__float_as_uint(x) & 0x7f800000u) != 0x7f800000u;
@@ -166,11 +316,11 @@ __device__ __forceinline__ bool finite_f32(float x)
 
 // The estimate from sum c log2 c (`acc`) and sum c (`tot`) over the bins, by one thread:
 // H = log2 n - (1/n) sum c log2 c in fp64, and the result record.
-__device__ __forceinline__ void emit_result(double acc, double tot, uint32_t bins, const RangeParams* rp,
+__device__ __forceinline__ void emit_result(double acc, double tot, uint32_t bins, const RangeParams& rp,
                                             unsigned long long n_sampled, edgc_entropy_result* res)
 {
     edgc_entropy_result r;
-    r.lo = rp->lo; r.hi = rp->hi;
+    r.lo = rp.lo; r.hi = rp.hi;
     r.n_sampled = n_sampled;
     // every finite element of the sample was counted in exactly one bin (values outside a caller's
     // range in the edge bins), so what the bins do not hold is the non-finite part; the counts are
@@ -180,7 +330,7 @@ __device__ __forceinline__ void emit_result(double acc, double tot, uint32_t bin
     if (tot > 0.0) {
         double H = log2(tot) - acc / tot;
         if (H < 0.0) H = 0.0;
-        const double w = static_cast<double>(rp->w);
+        const double w = static_cast<double>(rp.w);
         r.H_bits = H;
         r.h_diff_nats = (w > 0.0) ? H * 0.69314718055994530942 + log(w / static_cast<double>(bins))
                                   : -INFINITY;
@@ -218,190 +368,165 @@ __device__ __forceinline__ void block_sum_pair(double& acc, double& tot)
     }
 }
 
-// Shannon entropy of the 64-bit counters and the result record, by one whole block (the last one of a
-// grid).
-template <int BLOCK>
-__device__ __forceinline__ void finish_entropy(const unsigned long long* counts, uint32_t bins,
-                                               const RangeParams* rp, unsigned long long n_sampled,
-                                               edgc_entropy_result* res)
-{
-    double acc = 0.0, tot = 0.0;
-    for (uint32_t i = threadIdx.x; i < bins; i += BLOCK)
-        entropy_term(__hip_atomic_load(&counts[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), acc, tot);
-    block_sum_pair<BLOCK>(acc, tot);
-    if (threadIdx.x == 0) emit_result(acc, tot, bins, rp, n_sampled, res);
-}
-
 // ---------------------------------------------------------------------------
 // kernel 1: range of the finite sample
 // ---------------------------------------------------------------------------
+// (lo, hi) of the finite elements of the block's range, per thread
 template <typename T, int VEC, int BLOCK>
-__global__ __launch_bounds__(BLOCK) void k_minmax(const EntGroup grp,
-                                                     float* __restrict__ part,
-                                                     unsigned int* done, RangeParams* rp,
-                                                     float fbins, unsigned long long* counts,
-                                                     uint32_t bins, const unsigned int* gate)
+__device__ __forceinline__ void range_of_items(const EntGroup& grp, uint64_t begin, uint64_t end, float& lo, float& hi)
 {
-    // behind the one-pass kernel of bf16 samples: only when that one reported a counter overflow
-    if (gate && __hip_atomic_load(gate, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u) return;
-    const uint64_t G = static_cast<uint64_t>(gridDim.x) * BLOCK;
-    const uint64_t gtid = static_cast<uint64_t>(blockIdx.x) * BLOCK + threadIdx.x;
-    // the histogram kernel that follows on the stream accumulates into zeroed counters
-    for (uint64_t b = gtid; b < bins; b += G) counts[b] = 0ull;
-
-    float lo = INFINITY, hi = -INFINITY;
-    constexpr int U = 4;
-    for (uint32_t ti = 0; ti < grp.count; ++ti) {
-    const SampleGeom& geom = grp.geom[ti];
-    const T* __restrict__ g = static_cast<const T*>(grp.base[ti]);
-    // a block takes one contiguous range of the buffer's items (the sets are the same as with any
-    // other assignment; consecutive rounds of a block then read consecutive memory)
-    const uint64_t per = (geom.n_items + gridDim.x - 1) / gridDim.x;
-    const uint64_t begin = static_cast<uint64_t>(blockIdx.x) * per;
-    const uint64_t end = min(begin + per, geom.n_items);
-    ItemCursor cur;
-    cur.init(begin + threadIdx.x, BLOCK, geom.ipc);
-    if constexpr (VEC > 1) {
-        // rounds of U whole items per thread with the next round's loads in flight (see k_hist)
-        const uint64_t fast_end = (geom.n_items >= geom.ipc) ? min(end, geom.n_items - geom.ipc) : 0;
-        auto round_fits = [&]() { return cur.item + static_cast<uint64_t>(U - 1) * BLOCK < fast_end; };
-        auto fetch_raw = [&](uint4 (&raw)[U]) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                raw[u] = *reinterpret_cast<const uint4*>(g + cur.elem0(geom, VEC));
-                cur.advance(BLOCK, geom.ipc);
-            }
-        };
-        auto fold_raw = [&](const uint4 (&raw)[U]) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
+    auto fold = [&](float x) {
+        // no branch: a non-finite value stands in as the bound itself
+        const bool fin = finite_f32(x);
+        lo = fminf(lo, fin ? x : lo);
+        hi = fmaxf(hi, fin ? x : hi);
+    };
+    walk_items<T, VEC, BLOCK>(grp, begin, end, true,
+        [&](const uint4& raw) {
+            if constexpr (VEC > 1) {
                 float v[VEC];
-                unpack_item<T, VEC>(raw[u], v);
+                unpack_item<T, VEC>(raw, v);
 #pragma unroll
-                for (int p = 0; p < VEC; ++p) {
-                    const bool fin = finite_f32(v[p]);
-                    lo = fminf(lo, fin ? v[p] : lo);
-                    hi = fmaxf(hi, fin ? v[p] : hi);
-                }
+                for (int p = 0; p < VEC; ++p) fold(v[p]);
             }
-        };
-        if (round_fits()) {
-            uint4 ra[U], rb[U];
-            fetch_raw(ra);
-            while (true) {
-                if (!round_fits()) { fold_raw(ra); break; }
-                fetch_raw(rb);
-                fold_raw(ra);
-                if (!round_fits()) { fold_raw(rb); break; }
-                fetch_raw(ra);
-                fold_raw(rb);
-            }
-        }
-    }
-    while (cur.item < end) {
-        float v[U][VEC];
-        uint32_t mask[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            mask[u] = 0;
-            if (cur.item < end) {
-                const uint64_t i0 = cur.elem0(geom, VEC);
-                if (i0 < geom.n) mask[u] = load_item<T, VEC>(g, i0, geom.n, v[u]);
-            }
-            cur.advance(BLOCK, geom.ipc);
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (mask[u] == (1u << VEC) - 1u) {
-                // a whole item: no branch per element, a non-finite value stands in as the bound itself
-#pragma unroll
-                for (int p = 0; p < VEC; ++p) {
-                    const float x = v[u][p];
-                    const bool fin = finite_f32(x);
-                    lo = fminf(lo, fin ? x : lo);
-                    hi = fmaxf(hi, fin ? x : hi);
-                }
-            } else {
-#pragma unroll
-                for (int p = 0; p < VEC; ++p)
-                    if (((mask[u] >> p) & 1u) && finite_f32(v[u][p])) {
-                        lo = fminf(lo, v[u][p]);
-                        hi = fmaxf(hi, v[u][p]);
-                    }
-            }
-        }
-    }
-    }
-
-    __shared__ float s_lo[BLOCK / 64], s_hi[BLOCK / 64];
-    __shared__ bool s_last;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    lo = wave_reduce_minmax<true>(lo);
-    hi = wave_reduce_minmax<false>(hi);
-    if (lane == 0) { s_lo[wave] = lo; s_hi[wave] = hi; }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < BLOCK / 64; ++w) { lo = fminf(lo, s_lo[w]); hi = fmaxf(hi, s_hi[w]); }
-        part[2 * blockIdx.x]     = lo;
-        part[2 * blockIdx.x + 1] = hi;
-        __threadfence();
-        const unsigned int ticket = atomicAdd(done, 1u);
-        s_last = (ticket == gridDim.x - 1);
-    }
-    __syncthreads();
-    if (!s_last) return;
-
-    // last block: fold the per-block partials
-    __threadfence();
-    lo = INFINITY; hi = -INFINITY;
-    for (unsigned int b = threadIdx.x; b < gridDim.x; b += BLOCK) {
-        lo = fminf(lo, __hip_atomic_load(&part[2 * b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-        hi = fmaxf(hi, __hip_atomic_load(&part[2 * b + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-    }
-    lo = wave_reduce_minmax<true>(lo);
-    hi = wave_reduce_minmax<false>(hi);
-    __syncthreads();
-    if (lane == 0) { s_lo[wave] = lo; s_hi[wave] = hi; }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < BLOCK / 64; ++w) { lo = fminf(lo, s_lo[w]); hi = fmaxf(hi, s_hi[w]); }
-        RangeParams r;
-        if (lo <= hi) {
-            r.lo = lo; r.hi = hi;
-            r.w = __fsub_rn(hi, lo);
-            r.scale = (r.w > 0.0f) ? __fdiv_rn(fbins, r.w) : 0.0f;
-        } else {   // no finite sample at all
-            r.lo = NAN; r.hi = NAN; r.w = 0.0f; r.scale = 0.0f;
-        }
-        *rp = r;
-        *done = 0u;
-    }
+        },
+        [&](T x) { fold(ElemTraits<T>::widen(x)); }, [] {});
 }
 
-// Caller-supplied range: same derived quantities, no pass over the data; zeroes the counters.
-__global__ void k_set_range(RangeParams* rp, float lo, float hi, float fbins,
-                            unsigned long long* counts, uint32_t bins, const unsigned int* gate)
+__device__ __forceinline__ RangeParams make_range(float lo, float hi, float fbins)
 {
-    if (gate && __hip_atomic_load(gate, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u) return;
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < bins) counts[i] = 0ull;
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        RangeParams r;
+    RangeParams r;
+    if (lo <= hi) {
         r.lo = lo; r.hi = hi;
         r.w = __fsub_rn(hi, lo);
         r.scale = (r.w > 0.0f) ? __fdiv_rn(fbins, r.w) : 0.0f;
-        *rp = r;
+    } else {   // no finite sample at all
+        r.lo = NAN; r.hi = NAN; r.w = 0.0f; r.scale = 0.0f;
     }
+    return r;
+}
+
+// Folds (lo, hi) over the block; every thread returns the block's values.
+template <int BLOCK>
+__device__ __forceinline__ void block_range_minmax(float& lo, float& hi)
+{
+    __shared__ float s_lo[BLOCK / 64], s_hi[BLOCK / 64];
+    lo = wave_reduce_minmax<true>(lo);
+    hi = wave_reduce_minmax<false>(hi);
+    if ((threadIdx.x & 63) == 0) { s_lo[threadIdx.x >> 6] = lo; s_hi[threadIdx.x >> 6] = hi; }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < BLOCK / 64; ++w) { lo = fminf(lo, s_lo[w]); hi = fmaxf(hi, s_hi[w]); }
+}
+
+// The blocks' (lo, hi) go to `part` as they stand: every block of the histogram kernel folds them itself (a ticket and
+// a last block here cost some 4 us more than those 2 KB of loads there).  Zeroes the `zero_words` 32-bit words at
+// `zero`, the counters that kernel accumulates into.
+template <typename T, int VEC, int BLOCK>
+__global__ __launch_bounds__(BLOCK) void k_minmax(const EntGroup grp, float2* __restrict__ part,
+                                                  uint32_t* __restrict__ zero, uint32_t zero_words,
+                                                  const unsigned int* gate)
+{
+    // behind the one-pass kernel of bf16 samples: only when that one reported a counter overflow
+    if (gate && __hip_atomic_load(gate, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u) return;
+    for (uint32_t i = blockIdx.x * BLOCK + threadIdx.x; i < zero_words; i += gridDim.x * BLOCK) zero[i] = 0u;
+    float lo = INFINITY, hi = -INFINITY;
+    uint64_t begin, end;
+    block_range(grp, begin, end);
+    range_of_items<T, VEC, BLOCK>(grp, begin, end, lo, hi);
+    block_range_minmax<BLOCK>(lo, hi);
+    if (threadIdx.x == 0) part[blockIdx.x] = make_float2(lo, hi);
+}
+
+// Caller-supplied range: stands in as the one block's (lo, hi); zeroes the counters.
+__global__ void k_set_range(float2* part, float lo, float hi, uint32_t* __restrict__ zero, uint32_t zero_words,
+                            const unsigned int* gate)
+{
+    if (gate && __hip_atomic_load(gate, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u) return;
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < zero_words; i += gridDim.x * blockDim.x) zero[i] = 0u;
+    if (threadIdx.x == 0 && blockIdx.x == 0) part[0] = make_float2(lo, hi);
 }
 
 // ---------------------------------------------------------------------------
 // kernel 2: histogram + entropy
 // ---------------------------------------------------------------------------
+// Bins of the block's range into the LDS counters h[bin - bin_base][replica], bins [bin_base, bin_base + local_n).
+// bin = trunc((x - lo) * scale), each operation rounded on its own, clamped to [0, bins - 1].
+template <typename T, int VEC, int BLOCK>
+__device__ __forceinline__ void bin_items(const EntGroup& grp, uint64_t begin, uint64_t end, float lo, float scale,
+                                          uint32_t bins, uint32_t bin_base, uint32_t local_n, uint32_t rep_shift,
+                                          bool ahead, uint32_t* h)
+{
+    // largest float below the bin count: truncating a value clamped to [0, top] gives 0 .. bins - 1
+    const float top = __uint_as_float(__float_as_uint(static_cast<float>(bins)) - 1u);
+    const bool whole = local_n == bins;                                   // one slice holds every bin
+    uint32_t* const h_rep = h + (threadIdx.x & ((1u << rep_shift) - 1u)); // this lane's replica
+    // No branch per element: the bin of a non-finite value is some valid bin (the clamp maps NaN to 0) and it adds 0.
+    auto add = [&](float x) {
+        const float f = __builtin_amdgcn_fmed3f(__fmul_rn(__fsub_rn(x, lo), scale), 0.0f, top);
+        const uint32_t b = static_cast<uint32_t>(f), one = finite_f32(x) ? 1u : 0u;
+        if (whole) atomicAdd(&h_rep[b << rep_shift], one);
+        else if (b - bin_base < local_n) atomicAdd(&h_rep[(b - bin_base) << rep_shift], one);
+    };
+    walk_items<T, VEC, BLOCK>(grp, begin, end, ahead,
+        [&](const uint4& raw) {
+            if constexpr (VEC > 1) {
+                float v[VEC];
+                unpack_item<T, VEC>(raw, v);
+#pragma unroll
+                for (int p = 0; p < VEC; ++p) add(v[p]);
+            }
+        },
+        [&](T x) { add(ElemTraits<T>::widen(x)); }, [] {});
+}
+
+// (lo, hi) of the sample from the blocks' partials, by one block
+template <int BLOCK>
+__device__ __forceinline__ RangeParams fold_range(const float2* __restrict__ part, uint32_t nparts, float fbins)
+{
+    float lo = INFINITY, hi = -INFINITY;
+    for (uint32_t i = threadIdx.x; i < nparts; i += BLOCK) {
+        const float2 v = part[i];
+        lo = fminf(lo, v.x);
+        hi = fmaxf(hi, v.y);
+    }
+    block_range_minmax<BLOCK>(lo, hi);
+    return make_range(lo, hi, fbins);
+}
+
+// True in every thread of the block that finishes last of the grid (the ticket is zero before and after).
+// Every wave waits for its own stores and atomics, then ONE thread makes them visible device-wide: an agent-scope
+// release writes this XCD's L2 back, and with one in every wave of every block these queue up behind each other (the
+// histogram kernel of a 1 % sample: 384 blocks 59 us, 48 blocks 27 us; with one per block 20 and 18).
+template <int BLOCK>
+__device__ __forceinline__ bool last_block(unsigned int* ticket)
+{
+    __shared__ bool s_last;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        __threadfence();
+        const bool last = atomicAdd(ticket, 1u) == gridDim.x * gridDim.y - 1u;
+        if (last) *ticket = 0u;
+        s_last = last;
+    }
+    __syncthreads();
+    const bool last = s_last;
+    if (last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    return last;
+}
+
+__host__ __device__ constexpr uint32_t copy_stride(uint32_t bins) { return (bins + 3u) & ~3u; }   // words per set
+
+// `sets` = 8: the blocks of equal id modulo 8, which the dispatcher places on one XCD, share a set of 32-bit counters at
+// `copies`, and the last block adds the sets up: a counter line that all XCDs add to moves between their caches
+// (192 blocks 19.3 us, with eight sets 17.3; 384 blocks 24.5 and 20.2).  1: one set for all blocks.  0 (samples of 2^32
+// elements or more, or more bins than the sets hold): `counts` itself.
 template <typename T, int VEC, int BLOCK>
 __global__ __launch_bounds__(BLOCK) void k_hist(
-    const EntGroup grp, const RangeParams* __restrict__ rp, uint32_t bins,
-    uint32_t bins_local, uint32_t rep_shift, unsigned long long* counts,
-    unsigned int* done, edgc_entropy_result* res, const unsigned int* gate)
+    const EntGroup grp, const float2* __restrict__ part, uint32_t nparts, uint32_t bins,
+    uint32_t bins_local, uint32_t rep_shift, uint32_t* copies, uint32_t sets, unsigned long long* counts,
+    unsigned int* ticket, edgc_entropy_result* res, unsigned int* gate)
 {
     if (gate && __hip_atomic_load(gate, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u) return;
     extern __shared__ uint32_t h[];   // [bins_local << rep_shift], replica = lane & (R-1)
@@ -409,137 +534,106 @@ __global__ __launch_bounds__(BLOCK) void k_hist(
     const uint32_t local_n = min(bins_local, bins - bin_base);
     const uint32_t words = local_n << rep_shift;
     for (uint32_t i = threadIdx.x; i < words; i += BLOCK) h[i] = 0u;
+    const RangeParams rp = fold_range<BLOCK>(part, nparts, static_cast<float>(bins));
     __syncthreads();
 
-    const float lo = rp->lo, scale = rp->scale;
-    const float fbins = static_cast<float>(bins);
-    // largest float below the bin count: truncating a value clamped to [0, top] gives 0 .. bins - 1,
-    // the same index as min(trunc(max(f, 0)), bins - 1)
-    const float top = __uint_as_float(__float_as_uint(fbins) - 1u);
-    const uint32_t rep = threadIdx.x & ((1u << rep_shift) - 1u);
-    const bool whole = (gridDim.y == 1);      // one slice holds every bin
-    uint32_t* const h_rep = h + rep;          // this lane's replica of bin b is h_rep[b << rep_shift]
-
-    constexpr int U = 4;
-    for (uint32_t ti = 0; ti < grp.count; ++ti) {
-    const SampleGeom& geom = grp.geom[ti];
-    const T* __restrict__ g = static_cast<const T*>(grp.base[ti]);
-    const uint64_t per = (geom.n_items + gridDim.x - 1) / gridDim.x;      // one contiguous range per block
-    const uint64_t begin = static_cast<uint64_t>(blockIdx.x) * per;
-    const uint64_t end = min(begin + per, geom.n_items);
-    ItemCursor cur;
-    cur.init(begin + threadIdx.x, BLOCK, geom.ipc);
-    if constexpr (VEC > 1) {
-        // Rounds of U whole items per thread, the next round's loads issued before the current round is
-        // binned.  Every item before the buffer's last sampled chunk is whole (the chunk size is a multiple
-        // of VEC), so these loads need no condition and stay in flight across the binning.
-        const uint64_t fast_end = (geom.n_items >= geom.ipc) ? min(end, geom.n_items - geom.ipc) : 0;
-        auto round_fits = [&]() { return cur.item + static_cast<uint64_t>(U - 1) * BLOCK < fast_end; };
-        auto fetch_raw = [&](uint4 (&raw)[U]) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                raw[u] = *reinterpret_cast<const uint4*>(g + cur.elem0(geom, VEC));
-                cur.advance(BLOCK, geom.ipc);
-            }
-        };
-        auto bin_raw = [&](const uint4 (&raw)[U]) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                float v[VEC];
-                unpack_item<T, VEC>(raw[u], v);
-#pragma unroll
-                for (int p = 0; p < VEC; ++p) {
-                    const float t = __fsub_rn(v[p], lo);
-                    const float f = __builtin_amdgcn_fmed3f(__fmul_rn(t, scale), 0.0f, top);
-                    atomicAdd(&h_rep[static_cast<uint32_t>(f) << rep_shift], finite_f32(v[p]) ? 1u : 0u);
-                }
-            }
-        };
-        // (measured on a 1e9-element buffer: with every element sampled 0.86 instead of 0.91 ms on fp32 and
-        // 0.51 instead of 0.63 ms on bf16; on the 10 % sample, 256-byte runs 2.5 KB apart, 0.19 instead of
-        // 0.15 ms, so strided samples keep the plain loop below)
-        if (whole && geom.stride == 1 && round_fits()) {
-            uint4 ra[U], rb[U];
-            fetch_raw(ra);
-            while (true) {
-                if (!round_fits()) { bin_raw(ra); break; }
-                fetch_raw(rb);
-                bin_raw(ra);
-                if (!round_fits()) { bin_raw(rb); break; }
-                fetch_raw(ra);
-                bin_raw(rb);
-            }
-        }
-    }
-    while (cur.item < end) {
-        float v[U][VEC];
-        uint32_t mask[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            mask[u] = 0;
-            if (cur.item < end) {
-                const uint64_t i0 = cur.elem0(geom, VEC);
-                if (i0 < geom.n) mask[u] = load_item<T, VEC>(g, i0, geom.n, v[u]);
-            }
-            cur.advance(BLOCK, geom.ipc);
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (whole && mask[u] == (1u << VEC) - 1u) {
-                // a whole item with every bin in this block's slice: no branch per element.  The index
-                // of a non-finite value is some valid bin (the clamp maps NaN to 0) and it adds 0.
-#pragma unroll
-                for (int p = 0; p < VEC; ++p) {
-                    const float x = v[u][p];
-                    const float t = __fsub_rn(x, lo);
-                    const float f = __builtin_amdgcn_fmed3f(__fmul_rn(t, scale), 0.0f, top);
-                    atomicAdd(&h_rep[static_cast<uint32_t>(f) << rep_shift], finite_f32(x) ? 1u : 0u);
-                }
-                continue;
-            }
-#pragma unroll
-            for (int p = 0; p < VEC; ++p) {
-                if (!((mask[u] >> p) & 1u)) continue;
-                const float x = v[u][p];
-                if (!finite_f32(x)) continue;
-                // bin = trunc((x - lo) * scale), each operation rounded on its own
-                const float t = __fsub_rn(x, lo);
-                float f = __fmul_rn(t, scale);
-                f = fminf(fmaxf(f, 0.0f), fbins);          // also maps NaN (inf * 0) to 0
-                const uint32_t b = min(static_cast<uint32_t>(f), bins - 1u);
-                const uint32_t rel = b - bin_base;
-                if (rel < local_n) atomicAdd(&h_rep[rel << rep_shift], 1u);
-            }
-        }
-    }
-    }
+    uint64_t begin, end;
+    block_range(grp, begin, end);
+    // (loads one round ahead, measured on a 1e9-element buffer: with every element sampled 0.86 instead of 0.91 ms on
+    // fp32 and 0.51 instead of 0.63 ms on bf16; on the 10 % sample, 256-byte runs 2.5 KB apart, 0.19 instead of
+    // 0.15 ms, so strided samples go without)
+    bin_items<T, VEC, BLOCK>(grp, begin, end, rp.lo, rp.scale, bins, bin_base, local_n, rep_shift,
+                             gridDim.y == 1 && grp.geom[0].stride == 1, h);
     __syncthreads();
 
     // fold the replicas and flush non-empty bins
+    uint32_t* const copy = sets ? copies + static_cast<size_t>(blockIdx.x & (sets - 1u)) * copy_stride(bins) : nullptr;
     for (uint32_t i = threadIdx.x; i < local_n; i += BLOCK) {
         uint32_t s = 0;
         for (uint32_t r = 0; r < (1u << rep_shift); ++r) s += h[(i << rep_shift) | r];
-        if (s) atomicAdd(&counts[bin_base + i], static_cast<unsigned long long>(s));
+        if (!s) continue;
+        if (copy) atomicAdd(&copy[i], s);
+        else atomicAdd(&counts[bin_base + i], static_cast<unsigned long long>(s));
     }
-
-    __shared__ bool s_last;
-    __threadfence();                  // this thread's counter updates are visible device-wide
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const unsigned int ticket = atomicAdd(done, 1u);
-        s_last = (ticket == gridDim.x * gridDim.y - 1);
-    }
-    __syncthreads();
-    if (!s_last) return;
+    if (!last_block<BLOCK>(ticket)) return;
 
     // last block: H = log2 n - (1/n) sum c log2 c   (== -sum p log2 p)
-    __threadfence();
-    finish_entropy<BLOCK>(counts, bins, rp, grp.n_sampled, res);
-    if (threadIdx.x == 0) {
-        *done = 0u;
-        // every block of this grid has read the gate by now (each took its ticket after that)
-        if (gate) *const_cast<unsigned int*>(gate) = 0u;
+    double acc = 0.0, tot = 0.0;
+    auto four_bins = [&](uint32_t i, const unsigned long long (&c)[4]) {
+#pragma unroll
+        for (uint32_t e = 0; e < 4; ++e)
+            if (i + e < bins) {
+                counts[i + e] = c[e];
+                entropy_term(c[e], acc, tot);
+            }
+    };
+    // eight 16-byte loads in flight per thread: four bins of all eight sets, or eight times four bins of the one
+    if (sets == 8) {
+        for (uint32_t i = threadIdx.x * 4u; i < bins; i += BLOCK * 4u) {
+            uint4 x[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) x[k] = *reinterpret_cast<const uint4*>(copies + static_cast<size_t>(k) * copy_stride(bins) + i);
+            unsigned long long c[4] = {0, 0, 0, 0};
+#pragma unroll
+            for (int k = 0; k < 8; ++k) { c[0] += x[k].x; c[1] += x[k].y; c[2] += x[k].z; c[3] += x[k].w; }
+            four_bins(i, c);
+        }
+    } else if (sets == 1) {
+        for (uint32_t i0 = threadIdx.x * 4u; i0 < bins; i0 += BLOCK * 32u) {
+            uint4 x[8];
+#pragma unroll
+            for (uint32_t k = 0; k < 8; ++k) {
+                const uint32_t i = i0 + k * BLOCK * 4u;
+                x[k] = i < bins ? *reinterpret_cast<const uint4*>(copies + i) : make_uint4(0u, 0u, 0u, 0u);
+            }
+#pragma unroll
+            for (uint32_t k = 0; k < 8; ++k) {
+                const unsigned long long c[4] = {x[k].x, x[k].y, x[k].z, x[k].w};
+                four_bins(i0 + k * BLOCK * 4u, c);
+            }
+        }
+    } else {
+        for (uint32_t i = threadIdx.x; i < bins; i += BLOCK) entropy_term(counts[i], acc, tot);
     }
+    block_sum_pair<BLOCK>(acc, tot);
+    if (threadIdx.x == 0) {
+        emit_result(acc, tot, bins, rp, grp.n_sampled, res);
+        // every block of this grid has read the gate by now (each took its ticket after that)
+        if (gate) *gate = 0u;
+    }
+}
+
+// The whole estimate of a small sample by one block: range, histogram and entropy without a second launch, global
+// counters or a ticket.  Its latency chain is that of one block of k_hist without the device-wide part; the sample is
+// read twice, the second time from this CU's own cache.
+template <typename T, int VEC>
+__global__ __launch_bounds__(kOneBlock) void k_estimate_one(const EntGroup grp, int has_range, float range_lo,
+                                                            float range_hi, uint32_t bins, uint32_t rep_shift,
+                                                            unsigned long long* __restrict__ counts,
+                                                            edgc_entropy_result* res)
+{
+    extern __shared__ uint32_t h[];   // [bins << rep_shift]
+    for (uint32_t i = threadIdx.x; i < (bins << rep_shift); i += kOneBlock) h[i] = 0u;
+    float lo = INFINITY, hi = -INFINITY;
+    if (has_range) {
+        lo = range_lo; hi = range_hi;
+        __syncthreads();
+    } else {
+        range_of_items<T, VEC, kOneBlock>(grp, 0, grp.n_items, lo, hi);
+        block_range_minmax<kOneBlock>(lo, hi);
+    }
+    const RangeParams rp = make_range(lo, hi, static_cast<float>(bins));
+    bin_items<T, VEC, kOneBlock>(grp, 0, grp.n_items, rp.lo, rp.scale, bins, 0, bins, rep_shift, false, h);
+    __syncthreads();
+    double acc = 0.0, tot = 0.0;
+    for (uint32_t i = threadIdx.x; i < bins; i += kOneBlock) {
+        uint32_t s = 0;
+        for (uint32_t r = 0; r < (1u << rep_shift); ++r) s += h[(i << rep_shift) | r];
+        counts[i] = s;
+        entropy_term(s, acc, tot);
+    }
+    block_sum_pair<kOneBlock>(acc, tot);
+    if (threadIdx.x == 0) emit_result(acc, tot, bins, rp, grp.n_sampled, res);
 }
 
 // ---------------------------------------------------------------------------
@@ -580,7 +674,7 @@ __device__ __forceinline__ void field_add(uint32_t* h, unsigned long long* wide,
 
 template <typename T, int VEC, bool PATTERN>
 __global__ __launch_bounds__(kWideBlock) void k_wide_hist(
-    const EntGroup grp, const RangeParams* __restrict__ rp, uint32_t bins, uint16_t* __restrict__ part16,
+    const EntGroup grp, const float2* __restrict__ part, uint32_t nparts, uint32_t bins, uint16_t* __restrict__ part16,
     unsigned long long* __restrict__ wide, unsigned int* gate, int raise_gate)
 {
     static_assert(!PATTERN || sizeof(T) == 2, "the raw pattern is the key of 16-bit elements only");
@@ -590,8 +684,9 @@ __global__ __launch_bounds__(kWideBlock) void k_wide_hist(
 
     float lo = 0.0f, scale = 0.0f, top = 0.0f;
     if constexpr (!PATTERN) {
-        lo = rp->lo; scale = rp->scale;
         const float fbins = static_cast<float>(bins);
+        const RangeParams rp = fold_range<kWideBlock>(part, nparts, fbins);
+        lo = rp.lo; scale = rp.scale;
         top = __uint_as_float(__float_as_uint(fbins) - 1u);     // largest float below the bin count
     }
     // bin = trunc((x - lo) * scale), each operation rounded on its own, clamped to [0, bins - 1]
@@ -601,79 +696,38 @@ __global__ __launch_bounds__(kWideBlock) void k_wide_hist(
     };
 
     uint32_t overflow = 0;
-    constexpr int U = 4;
-    for (uint32_t ti = 0; ti < grp.count; ++ti) {
-        const SampleGeom& geom = grp.geom[ti];
-        const T* __restrict__ g = static_cast<const T*>(grp.base[ti]);
-        const uint64_t per = (geom.n_items + gridDim.x - 1) / gridDim.x;      // one contiguous range per block
-        const uint64_t begin = static_cast<uint64_t>(blockIdx.x) * per;
-        const uint64_t end = min(begin + per, geom.n_items);
-        ItemCursor cur;
-        cur.init(begin + threadIdx.x, kWideBlock, geom.ipc);
-        if constexpr (VEC > 1) {
-            // rounds of U whole items per thread, the next round's loads in flight behind the current one
-            const uint64_t fast_end = (geom.n_items >= geom.ipc) ? min(end, geom.n_items - geom.ipc) : 0;
-            auto round_fits = [&]() { return cur.item + static_cast<uint64_t>(U - 1) * kWideBlock < fast_end; };
-            auto fetch_raw = [&](uint4 (&raw)[U]) {
+    uint64_t begin, end;
+    block_range(grp, begin, end);
+    walk_items<T, VEC, kWideBlock>(grp, begin, end, true,
+        [&](const uint4& raw) {
+            if constexpr (PATTERN) {
+                const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    raw[u] = *reinterpret_cast<const uint4*>(g + cur.elem0(geom, VEC));
-                    cur.advance(kWideBlock, geom.ipc);
-                }
-            };
-            auto count_raw = [&](const uint4 (&raw)[U]) {
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    if constexpr (PATTERN) {
-                        const uint32_t w[4] = {raw[u].x, raw[u].y, raw[u].z, raw[u].w};
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const uint32_t a = w[q] & 0xffffu, b = w[q] >> 16;
-                            if (a == b) {                  // runs of equal values (zeros) in one add
-                                field_add(h, wide, a, 2u, overflow);
-                            } else {
-                                field_add(h, wide, a, 1u, overflow);
-                                field_add(h, wide, b, 1u, overflow);
-                            }
-                        }
+                for (int q = 0; q < 4; ++q) {
+                    const uint32_t a = w[q] & 0xffffu, b = w[q] >> 16;
+                    if (a == b) {                  // runs of equal values (zeros) in one add
+                        field_add(h, wide, a, 2u, overflow);
                     } else {
-                        float v[VEC];
-                        unpack_item<T, VEC>(raw[u], v);
-#pragma unroll
-                        for (int q = 0; q < VEC; ++q)
-                            field_add(h, wide, bin_of(v[q]), finite_f32(v[q]) ? 1u : 0u, overflow);
+                        field_add(h, wide, a, 1u, overflow);
+                        field_add(h, wide, b, 1u, overflow);
                     }
                 }
-            };
-            if (round_fits()) {
-                uint4 ra[U], rb[U];
-                fetch_raw(ra);
-                while (true) {
-                    if (!round_fits()) { count_raw(ra); break; }
-                    fetch_raw(rb);
-                    count_raw(ra);
-                    if (!round_fits()) { count_raw(rb); break; }
-                    fetch_raw(ra);
-                    count_raw(rb);
-                }
-            }
-        }
-        while (cur.item < end) {
-            const uint64_t i0 = cur.elem0(geom, VEC);
+            } else if constexpr (VEC > 1) {
+                float v[VEC];
+                unpack_item<T, VEC>(raw, v);
 #pragma unroll
-            for (int q = 0; q < VEC; ++q) {
-                if (i0 + q < geom.n) {
-                    if constexpr (PATTERN) {
-                        field_add(h, wide, g[i0 + q], 1u, overflow);
-                    } else {
-                        const float x = ElemTraits<T>::widen(g[i0 + q]);
-                        if (finite_f32(x)) field_add(h, wide, bin_of(x), 1u, overflow);
-                    }
-                }
+                for (int q = 0; q < VEC; ++q)
+                    field_add(h, wide, bin_of(v[q]), finite_f32(v[q]) ? 1u : 0u, overflow);
             }
-            cur.advance(kWideBlock, geom.ipc);
-        }
-    }
+        },
+        [&](T x) {
+            if constexpr (PATTERN) {
+                field_add(h, wide, x, 1u, overflow);
+            } else {
+                const float f = ElemTraits<T>::widen(x);
+                if (finite_f32(f)) field_add(h, wide, bin_of(f), 1u, overflow);
+            }
+        }, [] {});
     if (overflow || raise_gate) atomicOr(gate, 1u);   // raise_gate: the redo path under test
     __syncthreads();
     uint4* __restrict__ dst = reinterpret_cast<uint4*>(part16 + static_cast<size_t>(blockIdx.x) * kWideKeys);
@@ -693,14 +747,12 @@ template <bool PATTERN>
 __global__ __launch_bounds__(kWideBlock) void k_wide_reduce(
     const uint16_t* __restrict__ part16, uint32_t nblocks, unsigned long long* __restrict__ wide,
     unsigned long long* totals, uint32_t bins, int has_range, float range_lo, float range_hi,
-    unsigned long long* counts, RangeParams* rp, float* part, unsigned int* done, const unsigned int* gate,
+    unsigned long long* counts, const float2* __restrict__ mm_part, uint32_t nparts, float* part, unsigned int* ticket,
+    const unsigned int* gate,
     unsigned long long n_sampled, edgc_entropy_result* res)
 {
     extern __shared__ unsigned long long slice[];     // 32 KiB for the sums; PATTERN: [min(bins, kWideSliceBins)] as well
     constexpr uint32_t kMaxGrid = kWideKeys / kWideBlock;
-    __shared__ bool s_last;
-    __shared__ float s_lo[kWideBlock / 64], s_hi[kWideBlock / 64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint32_t key = blockIdx.x * kWideBlock + threadIdx.x;
     // after a counter overflow the kernels behind redo the estimate, on counters that start at zero
     const bool redo = __hip_atomic_load(gate, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
@@ -752,28 +804,18 @@ __global__ __launch_bounds__(kWideBlock) void k_wide_reduce(
         const float x = __uint_as_float(key << 16);
         float lo = INFINITY, hi = -INFINITY;
         if (c && finite_f32(x)) { lo = x; hi = x; }
-        lo = wave_reduce_minmax<true>(lo);
-        hi = wave_reduce_minmax<false>(hi);
-        if (lane == 0) { s_lo[wave] = lo; s_hi[wave] = hi; }
-        __syncthreads();
+        block_range_minmax<kWideBlock>(lo, hi);
         if (threadIdx.x == 0) {
-            for (int w = 1; w < kWideBlock / 64; ++w) { lo = fminf(lo, s_lo[w]); hi = fmaxf(hi, s_hi[w]); }
             part[2 * blockIdx.x]     = lo;            // lo > hi: none of this block's patterns occurs
             part[2 * blockIdx.x + 1] = hi;
         }
     }
-    __threadfence();
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const unsigned int ticket = atomicAdd(done, 1u);
-        s_last = (ticket == gridDim.x - 1);
-    }
-    __syncthreads();
-    if (!s_last) return;
-    __threadfence();
+    if (!last_block<kWideBlock>(ticket)) return;
 
+    RangeParams rp;
     double acc = 0.0, tot = 0.0;
     if constexpr (!PATTERN) {
+        rp = fold_range<kWideBlock>(mm_part, nparts, static_cast<float>(bins));
         if (threadIdx.x < gridDim.x) {
             acc = __hip_atomic_load(&part_d[2 * threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             tot = __hip_atomic_load(&part_d[2 * threadIdx.x + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -799,20 +841,11 @@ __global__ __launch_bounds__(kWideBlock) void k_wide_reduce(
             }
             s_nlist = nl;
             if (has_range) { lo = range_lo; hi = range_hi; }
-            const float fbins = static_cast<float>(bins);
-            RangeParams r;
-            if (has_range || lo <= hi) {
-                r.lo = lo; r.hi = hi;
-                r.w = __fsub_rn(hi, lo);
-                r.scale = (r.w > 0.0f) ? __fdiv_rn(fbins, r.w) : 0.0f;
-            } else {   // no finite sample at all
-                r.lo = NAN; r.hi = NAN; r.w = 0.0f; r.scale = 0.0f;
-            }
-            *rp = r;
-            s_range[0] = r.lo; s_range[1] = r.scale;
+            s_range[0] = lo; s_range[1] = hi;
         }
         __syncthreads();
-        const float rlo = s_range[0], scale = s_range[1];
+        rp = make_range(s_range[0], s_range[1], static_cast<float>(bins));
+        const float rlo = rp.lo, scale = rp.scale;
         const uint32_t nlist = s_nlist;
         const float fbins = static_cast<float>(bins);
         const float top = __uint_as_float(__float_as_uint(fbins) - 1u);   // largest float below the bin count
@@ -854,7 +887,6 @@ __global__ __launch_bounds__(kWideBlock) void k_wide_reduce(
     block_sum_pair<kWideBlock>(acc, tot);
     if (threadIdx.x == 0) {
         emit_result(acc, tot, bins, rp, n_sampled, res);
-        *done = 0u;
     }
 }
 
@@ -865,15 +897,15 @@ __global__ __launch_bounds__(256) void k_sample_indices(SampleGeom geom, uint64_
                                                         uint64_t cap)
 {
     const uint64_t G = static_cast<uint64_t>(gridDim.x) * 256;
-    ItemCursor cur;
-    cur.init(static_cast<uint64_t>(blockIdx.x) * 256 + threadIdx.x, G, geom.ipc);
     const int vec = static_cast<int>(geom.vec);
-    while (cur.item < geom.n_items) {
+    for (uint64_t item = static_cast<uint64_t>(blockIdx.x) * 256; item < geom.n_items; item += G) {
+        ItemCursor cur;
+        cur.init(item, threadIdx.x, 0, geom.ipc);
+        if (item + threadIdx.x >= geom.n_items) break;
         const uint64_t i0 = cur.elem0(geom, vec);
         const uint64_t pos0 = cur.k * geom.chunk + static_cast<uint64_t>(cur.e) * vec;
         for (int p = 0; p < vec; ++p)
             if (i0 + p < geom.n && pos0 + p < cap) idx[pos0 + p] = i0 + p;
-        cur.advance(G, geom.ipc);
     }
 }
 
@@ -922,32 +954,24 @@ static uint32_t grid_for(uint64_t n_items, int block, int per_thread, int max_bl
 // The device memory an estimate works in beyond its inputs and outputs: the context's own
 // allocations, or the file-scope array of the entry point that allocates nothing.
 struct EntScratch {
-    float*              mm_part;       // [2 * kMaxReduceBlocks] per-block (lo, hi)
-    unsigned int*       done_counter;  // [4] last-block tickets (0..2) and the overflow gate (3), zero between calls
+    float2*             mm_part;       // [kMaxReduceBlocks] per-block (lo, hi)
+    unsigned int*       ticket;        // [kTicketWords] last-block ticket and the overflow gate (kGateWord); zero between calls
+    uint32_t*           copies;        // [8][kCopyBins] histogram counters by XCD
     uint16_t*           part16;        // [part16_blocks][65536] 16-bit counters per block, or null: plain kernels only
     uint32_t            part16_blocks;
     unsigned long long* wide;          // [65536] 64-bit credits per key, zero between calls
     unsigned long long* totals;        // [65536] counts per bf16 bit pattern
     unsigned long long* counts;        // histogram when the caller gives none
-    void*               range;         // RangeParams
     void*               result_dev;    // edgc_entropy_result
 };
-
 template <typename T, int VEC>
 static int run_entropy(edgc_ctx* ctx, const EntScratch& s, const EntGroup& g, uint32_t bins, const float* range,
                        uint64_t* counts_out, edgc_entropy_result* res, hipStream_t st)
 {
     auto* counts = counts_out ? reinterpret_cast<unsigned long long*>(counts_out) : s.counts;
-    auto* rp = static_cast<RangeParams*>(s.range);
-    const float fbins = static_cast<float>(bins);
 
     const double sample_bytes = static_cast<double>(g.n_sampled) * sizeof(T);
-    const bool small_sample = g.n_items <= static_cast<uint64_t>(kHistBlock) * 4 * ctx->num_cu * 2;
-    // blocks a sample below 8 Mi items gets at most: 16 up to 1 Mi items; one per 32 Ki items from 2 Mi items on
-    // (1e7 fp32 elements, 2.5 Mi items: 0.068 instead of 0.082 ms alone); between the two the launch shapes of
-    // large samples (1e7 bf16 elements, 1.25 Mi items: 0.056 ms, with the cap 0.089)
-    const uint64_t few_blocks = small_sample ? kSmallSampleBlocks
-                              : (g.n_items >= (2ull << 20) ? (g.n_items >> 15) : ~0ull / (4 * kHistBlockFat));
+    const bool small = g.n_items <= static_cast<uint64_t>(kHistBlock) * 4 * ctx->num_cu * 2;
     // One read into 16-bit counters per block (the kernels above), where the context has the memory
     // for the blocks' fields: every bf16 sample of some size (no range pass, any number of bins), and
     // fp32 samples on more bins than 32-bit counters hold in LDS at once.  The plain kernels follow on
@@ -960,73 +984,28 @@ static int run_entropy(edgc_ctx* ctx, const EntScratch& s, const EntGroup& g, ui
     const bool by_pattern = sizeof(T) == 2 && wide_ok &&
                             (g.n_sampled >= pattern_min || (bins > 16384 && g.n_sampled >= pattern_min / 8));
     const bool by_wide_bins = sizeof(T) == 4 && wide_ok && bins > 16384 && bins <= kWideKeys;
-    unsigned int* gate = (by_pattern || by_wide_bins) ? s.done_counter + 3 : nullptr;
+    unsigned int* gate = (by_pattern || by_wide_bins) ? s.ticket + kGateWord : nullptr;
     const uint32_t wide_blocks = grid_for(g.n_items, kWideBlock, 4, min(ctx->num_cu, static_cast<int>(s.part16_blocks)));
+    uint32_t nparts = 0;                                   // blocks' (lo, hi) in s.mm_part
+    float* const pair_part = reinterpret_cast<float*>(s.mm_part + kMaxReduceBlocks / 2);
     if constexpr (sizeof(T) == 2) {
         if (by_pattern) {
             EDGC_LAUNCH(ctx, st, KID_WIDE_HIST, sample_bytes, 0.0,
                         k_wide_hist<T, VEC, true><<<wide_blocks, kWideBlock, kWideKeys * 2, st>>>(
-                            g, rp, bins, s.part16, s.wide, gate, ctx->tune_pattern == 3 ? 1 : 0));
+                            g, s.mm_part, nparts, bins, s.part16, s.wide, gate, ctx->tune_pattern == 3 ? 1 : 0));
             const size_t lds = max(static_cast<size_t>(min(bins, kWideSliceBins)) * sizeof(unsigned long long),
                                    kWideReduceLds);
             EDGC_LAUNCH(ctx, st, KID_WIDE_REDUCE, 2.0 * kWideKeys * wide_blocks, 0.0,
                         k_wide_reduce<true><<<kWideKeys / kWideBlock, kWideBlock, lds, st>>>(
                             s.part16, wide_blocks, s.wide, s.totals, bins, range ? 1 : 0, range ? range[0] : 0.0f,
-                            range ? range[1] : 0.0f, counts, rp, s.mm_part, s.done_counter + 2, gate,
+                            range ? range[1] : 0.0f, counts, nullptr, 0u, pair_part, s.ticket, gate,
                             g.n_sampled, res));
         }
     }
-    if (range) {
-        EDGC_LAUNCH(ctx, st, KID_SET_RANGE, 8.0 * bins, 0.0,
-                    k_set_range<<<(bins + 255) / 256, 256, 0, st>>>(rp, range[0], range[1], fbins, counts,
-                                                                     bins, by_pattern ? gate : nullptr));
-    } else {
-        // few blocks of four rounds of four 16-byte loads: the estimate runs beside the compressor's
-        // streaming passes, and every block of it that takes a CU slot delays those (measured on the
-        // bench workload: 16 items per thread cost 12 us of step time less than 4)
-        if (g.n_items >= kBigSampleItems) {
-            // a large sample: one block of 1024 threads per CU (1e8 fp32 elements out of 1e9: 0.08 instead
-            // of 0.12 ms, bf16 0.05 instead of 0.08; every element of 1e9: 0.70 instead of 0.71 ms)
-            const uint32_t gx = grid_for(g.n_items, kMMBlockFat, 16, ctx->num_cu);
-            EDGC_LAUNCH(ctx, st, KID_MINMAX, sample_bytes, 0.0,
-                        k_minmax<T, VEC, kMMBlockFat><<<gx, kMMBlockFat, 0, st>>>(g, s.mm_part, s.done_counter, rp,
-                                                                                  fbins, counts, bins,
-                                                                                  by_pattern ? gate : nullptr));
-        } else {
-            // a small sample (the 1 % sample of a transformer block's gradients, say) gets at most 16 blocks:
-            // beside the compressor's passes it is the number of CU slots the estimate takes that costs step
-            // time, not its own duration (hidden-5120 bf16 block at rank 128, 393 Ki items: 96 blocks of 16 items
-            // per thread 1.241 ms per step, 12 blocks 1.207 ms, though the two kernels alone take 88 instead of 44 us)
-            // (a 16 M-element sample of a 32-tensor stage, 4 Mi items: 983 and 491 blocks 6.90 ms per step and 87 + 123
-            // us alone, 123 blocks each 6.82 ms and 69 + 82 us)
-            const uint64_t few = static_cast<uint64_t>(kMMBlock) * few_blocks;
-            const int mm_items = ctx->tune_ept > 0 ? 2 * ctx->tune_ept
-                                                   : static_cast<int>(std::max<uint64_t>(16, (g.n_items + few - 1) / few));
-            const uint32_t gx = grid_for(g.n_items, kMMBlock, mm_items, min(kMaxReduceBlocks, ctx->num_cu * 4));
-            EDGC_LAUNCH(ctx, st, KID_MINMAX, sample_bytes, 0.0,
-                        k_minmax<T, VEC, kMMBlock><<<gx, kMMBlock, 0, st>>>(g, s.mm_part, s.done_counter, rp,
-                                                                            fbins, counts, bins,
-                                                                            by_pattern ? gate : nullptr));
-        }
-    }
-
-    if constexpr (sizeof(T) == 4) {
-        if (by_wide_bins) {
-            EDGC_LAUNCH(ctx, st, KID_WIDE_HIST, sample_bytes, 0.0,
-                        k_wide_hist<T, VEC, false><<<wide_blocks, kWideBlock, kWideKeys * 2, st>>>(
-                            g, rp, bins, s.part16, s.wide, gate, ctx->tune_pattern == 3 ? 1 : 0));
-            EDGC_LAUNCH(ctx, st, KID_WIDE_REDUCE, 2.0 * kWideKeys * wide_blocks, 0.0,
-                        k_wide_reduce<false><<<(bins + kWideBlock - 1) / kWideBlock, kWideBlock, kWideReduceLds, st>>>(
-                            s.part16, wide_blocks, s.wide, s.totals, bins, 0, 0.0f, 0.0f, counts, rp, s.mm_part,
-                            s.done_counter + 2, gate, g.n_sampled, res));
-        }
-    }
-
     // LDS plan: up to 64 KiB of 32-bit counters, replicated per lane where bins are few;
     // more than 16384 bins are covered in slices of 32768 (128 KiB), one slice per blockIdx.y
-    // small samples get few blocks of few items each, and then fewer replicas so that zeroing
+    // small samples get blocks of few items each, and then fewer replicas so that zeroing
     // and folding the LDS histogram does not outweigh the sampling itself
-    const bool small = small_sample;
     const uint32_t word_cap = small ? 4096u : 16384u;
     uint32_t bins_local = bins, rep_shift = 0;
     if (bins <= 16384) {
@@ -1036,27 +1015,66 @@ static int run_entropy(edgc_ctx* ctx, const EntScratch& s, const EntGroup& g, ui
     }
     const uint32_t ny = (bins + bins_local - 1) / bins_local;
     const size_t lds = static_cast<size_t>(bins_local << rep_shift) * sizeof(uint32_t);
-    // enough items per block that zeroing and flushing the LDS histogram stays small
-    const uint64_t few_h = static_cast<uint64_t>(kHistBlock) * few_blocks;
-    const int floor_items = small ? 8 : ((bins_local << rep_shift) > 16384 ? 64 : 16);
-    const int per_thread = ctx->tune_ept > 0 ? ctx->tune_ept
-                         : (g.n_items < kBigSampleItems
-                                ? static_cast<int>(std::max<uint64_t>(floor_items, (g.n_items + few_h - 1) / few_h))
-                                : floor_items);
+    if (bins <= 16384 && !by_pattern && g.n_items <= 4u * kOneBlock) {
+        EDGC_LAUNCH(ctx, st, KID_HIST, sample_bytes, 0.0,
+                    k_estimate_one<T, VEC><<<1, kOneBlock, lds, st>>>(g, range ? 1 : 0, range ? range[0] : 0.0f,
+                                                                      range ? range[1] : 0.0f, bins, rep_shift, counts, res));
+        EDGC_HIP_TRY(ctx, hipGetLastError());
+        return EDGC_OK;
+    }
     // One block of 1024 threads per CU when a histogram of more than 64 KiB leaves room for one block only
     // (1e9 fp32 elements on 65536 bins: 1.6 instead of 3.6 ms) and for samples of 8 Mi items or more (1e8
     // fp32 elements on 4096 bins: 0.13 instead of 0.18 ms; 1e9: 0.83 instead of 0.86 ms); two blocks of
     // 512 per CU otherwise (1e7 bf16 elements: 0.040 against 0.044 ms; two blocks of 1024: slower throughout)
-    if (lds > 65536 || g.n_items >= kBigSampleItems) {
-        const uint32_t gx = grid_for(g.n_items, kHistBlockFat, per_thread, ctx->num_cu);
+    const bool fat = lds > 65536 || g.n_items >= kBigSampleItems;
+    // enough items per block that zeroing and flushing the LDS histogram stays small
+    const int floor_items = small ? std::max(4, static_cast<int>((bins_local << rep_shift) / (kHistBlock * VEC / 2)))
+                                  : ((bins_local << rep_shift) > 16384 ? 64 : 16);
+    const int per_thread = ctx->tune_ept > 0 ? ctx->tune_ept : floor_items;
+    const uint32_t gx = fat ? grid_for(g.n_items, kHistBlockFat, per_thread, ctx->num_cu)
+                            : grid_for(g.n_items, kHistBlock, per_thread, ctx->num_cu * 2);
+    // the counters the histogram kernel accumulates into
+    const uint32_t sets = (bins <= kCopyBins && g.n_sampled < (1ull << 32)) ? (gx > 16 ? 8u : 1u) : 0u;
+    uint32_t* zero = sets ? s.copies : reinterpret_cast<uint32_t*>(counts);
+    const uint32_t zero_words = sets ? sets * copy_stride(bins) : 2u * bins;
+    const unsigned int* range_gate = by_pattern ? gate : nullptr;
+    if (range) {
+        nparts = 1;
+        EDGC_LAUNCH(ctx, st, KID_SET_RANGE, 4.0 * zero_words, 0.0,
+                    k_set_range<<<min((zero_words + 255) / 256, 1024u), 256, 0, st>>>(s.mm_part, range[0], range[1], zero,
+                                                                                    zero_words, range_gate));
+    } else if (g.n_items >= kBigSampleItems) {
+        // a large sample: one block of 1024 threads per CU (1e8 fp32 elements out of 1e9: 0.08 instead
+        // of 0.12 ms, bf16 0.05 instead of 0.08; every element of 1e9: 0.70 instead of 0.71 ms)
+        nparts = grid_for(g.n_items, kMMBlockFat, 16, ctx->num_cu);
+        EDGC_LAUNCH(ctx, st, KID_MINMAX, sample_bytes, 0.0,
+                    k_minmax<T, VEC, kMMBlockFat><<<nparts, kMMBlockFat, 0, st>>>(g, s.mm_part, zero, zero_words, range_gate));
+    } else {
+        nparts = grid_for(g.n_items, kMMBlock, ctx->tune_ept > 0 ? 2 * ctx->tune_ept : 8, ctx->num_cu * 4);
+        EDGC_LAUNCH(ctx, st, KID_MINMAX, sample_bytes, 0.0,
+                    k_minmax<T, VEC, kMMBlock><<<nparts, kMMBlock, 0, st>>>(g, s.mm_part, zero, zero_words, range_gate));
+    }
+
+    if constexpr (sizeof(T) == 4) {
+        if (by_wide_bins) {
+            EDGC_LAUNCH(ctx, st, KID_WIDE_HIST, sample_bytes, 0.0,
+                        k_wide_hist<T, VEC, false><<<wide_blocks, kWideBlock, kWideKeys * 2, st>>>(
+                            g, s.mm_part, nparts, bins, s.part16, s.wide, gate, ctx->tune_pattern == 3 ? 1 : 0));
+            EDGC_LAUNCH(ctx, st, KID_WIDE_REDUCE, 2.0 * kWideKeys * wide_blocks, 0.0,
+                        k_wide_reduce<false><<<(bins + kWideBlock - 1) / kWideBlock, kWideBlock, kWideReduceLds, st>>>(
+                            s.part16, wide_blocks, s.wide, s.totals, bins, 0, 0.0f, 0.0f, counts, s.mm_part, nparts,
+                            pair_part, s.ticket, gate, g.n_sampled, res));
+        }
+    }
+
+    if (fat) {
         EDGC_LAUNCH(ctx, st, KID_HIST, sample_bytes * ny, 0.0,
                     k_hist<T, VEC, kHistBlockFat><<<dim3(gx, ny), kHistBlockFat, lds, st>>>(
-                        g, rp, bins, bins_local, rep_shift, counts, s.done_counter + 1, res, gate));
+                        g, s.mm_part, nparts, bins, bins_local, rep_shift, s.copies, sets, counts, s.ticket, res, gate));
     } else {
-        const uint32_t gx = grid_for(g.n_items, kHistBlock, per_thread, ctx->num_cu * 2);
         EDGC_LAUNCH(ctx, st, KID_HIST, sample_bytes * ny, 0.0,
                     k_hist<T, VEC, kHistBlock><<<dim3(gx, ny), kHistBlock, lds, st>>>(
-                        g, rp, bins, bins_local, rep_shift, counts, s.done_counter + 1, res, gate));
+                        g, s.mm_part, nparts, bins, bins_local, rep_shift, s.copies, sets, counts, s.ticket, res, gate));
     }
     EDGC_HIP_TRY(ctx, hipGetLastError());
     return EDGC_OK;
@@ -1132,8 +1150,8 @@ int launch_entropy(edgc_ctx* ctx, const EntGroup& g, edgc_dtype dt, uint32_t bin
                    const float* range, edgc_entropy_result* out, uint64_t* counts_out, hipStream_t st)
 {
     const Scratch& c = ctx->s;
-    const EntScratch s{c.mm_part, c.done_counter, c.part16, c.part16_blocks, c.wide, c.totals,
-                       c.counts, c.range, c.result_dev};
+    const EntScratch s{reinterpret_cast<float2*>(c.mm_part), c.ticket, c.copies, c.part16, c.part16_blocks, c.wide,
+                       c.totals, c.counts, c.result_dev};
     return launch_entropy_on(ctx, s, g, dt, bins, range, out, counts_out, st);
 }
 
@@ -1144,11 +1162,11 @@ int launch_entropy(edgc_ctx* ctx, const EntGroup& g, edgc_dtype dt, uint32_t bin
 // edgc_create on that device (with that device current), and host code only ever uses that
 // pointer, never the array's name.
 // ---------------------------------------------------------------------------
-constexpr size_t kStaticOffDone   = sizeof(float) * 2 * kMaxReduceBlocks;             // 32 KiB of (lo, hi) pairs
-constexpr size_t kStaticOffRange  = kStaticOffDone + 256;
-constexpr size_t kStaticOffResult = kStaticOffRange + 256;
-constexpr size_t kStaticOffCounts = kStaticOffResult + 256;
-constexpr size_t kStaticBytes     = kStaticOffCounts + sizeof(unsigned long long) * kStaticMaxBins;
+constexpr size_t kStaticOffTicket = sizeof(float2) * kMaxReduceBlocks;
+constexpr size_t kStaticOffResult  = kStaticOffTicket + sizeof(unsigned int) * kTicketWords;
+constexpr size_t kStaticOffCopies  = kStaticOffResult + 256;
+constexpr size_t kStaticOffCounts  = kStaticOffCopies + sizeof(uint32_t) * 8 * kCopyBins;
+constexpr size_t kStaticBytes      = kStaticOffCounts + sizeof(unsigned long long) * kStaticMaxBins;
 static __device__ __align__(256) unsigned char scratch[kStaticBytes];
 
 constexpr int kMaxDevices = 64;
@@ -1162,9 +1180,9 @@ int resolve_static_scratch(edgc_ctx* ctx)
     unsigned char* ptr = nullptr;
     EDGC_HIP_TRY(ctx, hipGetSymbolAddress(reinterpret_cast<void**>(&ptr), HIP_SYMBOL(scratch)));
     if (!ptr) return fail(ctx, EDGC_EHIP, "hipGetSymbolAddress returned a null address");
-    // the tickets must start at zero; the array is zero-initialised when the code object is loaded
+    // the ticket must start at zero; the array is zero-initialised when the code object is loaded
     // and every estimate leaves them at zero, but a process may have been interrupted mid-call
-    EDGC_HIP_TRY(ctx, hipMemset(ptr + kStaticOffDone, 0, 256));
+    EDGC_HIP_TRY(ctx, hipMemset(ptr + kStaticOffTicket, 0, sizeof(unsigned int) * kTicketWords));
     EDGC_HIP_TRY(ctx, hipDeviceSynchronize());
     g_static_scratch[dev] = ptr;
     return EDGC_OK;
@@ -1175,11 +1193,11 @@ int launch_entropy_static(edgc_ctx* ctx, const EntGroup& g, edgc_dtype dt, uint3
 {
     unsigned char* base = (ctx->device >= 0 && ctx->device < kMaxDevices) ? g_static_scratch[ctx->device] : nullptr;
     if (!base) return fail(ctx, EDGC_EHIP, "the static scratch of this device was not set up");
-    const EntScratch s{reinterpret_cast<float*>(base),
-                       reinterpret_cast<unsigned int*>(base + kStaticOffDone),
+    const EntScratch s{reinterpret_cast<float2*>(base),
+                       reinterpret_cast<unsigned int*>(base + kStaticOffTicket),
+                       reinterpret_cast<uint32_t*>(base + kStaticOffCopies),
                        nullptr, 0u, nullptr, nullptr,     // no room for the blocks' 16-bit counters: plain kernels
-                       reinterpret_cast<unsigned long long*>(base + kStaticOffCounts),
-                       base + kStaticOffRange, base + kStaticOffResult};
+                       reinterpret_cast<unsigned long long*>(base + kStaticOffCounts), base + kStaticOffResult};
     return launch_entropy_on(ctx, s, g, dt, bins, range, out, counts_out, st);
 }
 

@@ -279,6 +279,33 @@ def test_stage_entropy_over_separate_buffers(dtype, stride, chunk, bins):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("stride,chunk,bins,given", [(1, 64, 257, False), (3, 64, 4096, False), (1, 64, 1024, True),
+                                                     (2, 8, 16384, False), (1, 24, 20000, False)])
+def test_stage_entropy_over_many_short_and_ragged_buffers(dtype, stride, chunk, bins, given):
+    """Blocks take ranges of the union of the buffers: ranges that span many buffers, ends inside an item, samples of
+    exactly one block's round (4096 items of 16 bytes) and one item more, and both sides of the bins that fit in LDS."""
+    vec = 4 if dtype == "f32" else 8
+    tail = vec - 1
+    lens = [1, 7, 64, 65, 127, 128, 129, 768, 2304, 3072, 100, 4095, 333, 64 * 9 + 3, 5, 5000]
+    groups = [lens, 2 * lens, [4096 * vec], [4096 * vec + tail], [4096 * vec - 64, 64, 1], 3 * [4096 * vec] + lens]
+    c = edgc.Context(0, max_bins=65536, max_rank=4, max_rows=64, max_cols=64)
+    counts = torch.zeros(bins, dtype=torch.int64, device="cuda")
+    value_range = (-2e-3, 3e-3) if given else None
+    for k, sizes in enumerate(groups):
+        bufs = [gen.laplace_mixture(n, 90 + i, dtype=dtype) for i, n in enumerate(sizes)]
+        bufs[0][-1] = 0x7fc0 if dtype == "bf16" else np.float32(np.nan)
+        if bufs[-1].size > 1:
+            bufs[-1][0] = 0xff80 if dtype == "bf16" else np.float32(-np.inf)
+        got = c.entropy_estimate([to_dev(b) for b in bufs], stride, chunk, 9, k, bins, value_range, counts_out=counts)
+        want, n_s = _oracle_union_entropy(bufs, stride, chunk, 9, k, bins, value_range)
+        assert (got.n_sampled, got.n_nonfinite) == (n_s, want.n_nonfinite), k
+        assert (got.lo, got.hi) == (want.lo, want.hi), k
+        assert np.array_equal(counts.cpu().numpy().astype(np.uint64), want.counts), k
+        # fp64 sums over the same integer counts in another order
+        assert abs(got.H_bits - want.H_bits) <= 1e-5, k
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_stage_entropy_large_union_sample(dtype):
     """A union sample large enough for the launch shapes of large samples (one block of 1024 threads
     per compute unit, whole-item rounds with the next loads in flight) over several buffers of
