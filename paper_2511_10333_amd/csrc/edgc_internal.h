@@ -16,7 +16,7 @@ struct Scratch {
     unsigned char*      small        = nullptr;  // one allocation for everything here but part16, part, gram_part and pt
     // entropy
     float*              mm_part      = nullptr;  // [2 * kMaxReduceBlocks] per-block (lo, hi)
-    unsigned int*       ticket       = nullptr;  // [kTicketWords] last-block ticket and the overflow gate, zero between calls
+    unsigned int*       ticket       = nullptr;  // [kTicketWords] last-block ticket, zero between calls
     uint32_t*           copies       = nullptr;  // [8][kCopyBins] histogram counters, a set per XCD
     uint16_t*           part16       = nullptr;  // [part16_blocks][65536] 16-bit counters per block
     uint32_t            part16_blocks = 0;
@@ -36,8 +36,7 @@ struct Scratch {
 };
 
 constexpr int kMaxReduceBlocks = 4096;
-constexpr uint32_t kTicketWords = 64;      // the last-block ticket and, on a cache line of its own, the overflow gate
-constexpr uint32_t kGateWord = 32;
+constexpr uint32_t kTicketWords = 64;      // the last-block ticket, on a cache line of its own
 constexpr uint32_t kCopyBins = 16384;      // (8 x kCopyBins counters of 32 bits take the place of `totals`) largest histogram that is accumulated in one set of counters per XCD
 
 // 16-wide tiles per side of the Gram matrix and of R^-1 at a rank: the orthonormalisation kernels are built for
@@ -157,8 +156,7 @@ struct edgc_ctx {
     int tune_apply = -1;    // k_apply above rank 64: 4 = four waves (64 rows) per block, 8 = eight (128 rows)
     int tune_ept = 0;       // items per thread of the histogram and, twice as many, of the range pass; 0: built-in choice
     int tune_pattern = 1;   // entropy estimate: 1 one read into 16-bit counters per block where that applies
-                            // (bf16 samples, fp32 on more than 16384 bins); 0 the plain kernels only; 3 as 1,
-                            // and every such estimate reports a counter overflow (tests of the redo path)
+                            // (bf16 samples, fp32 on more than 16384 bins); 0 the plain kernels only
     long long tune_pattern_min = 32 << 20;  // bf16 samples from this many elements on are counted by bit pattern
                                             // (on more than 16384 bins: from an eighth of it on)
     edgc::Scratch s;

@@ -424,11 +424,8 @@ __device__ __forceinline__ void block_range_minmax(float& lo, float& hi)
 // `zero`, the counters that kernel accumulates into.
 template <typename T, int VEC, int BLOCK>
 __global__ __launch_bounds__(BLOCK) void k_minmax(const EntGroup grp, float2* __restrict__ part,
-                                                  uint32_t* __restrict__ zero, uint32_t zero_words,
-                                                  const unsigned int* gate)
+                                                  uint32_t* __restrict__ zero, uint32_t zero_words)
 {
-    // behind the one-pass kernel of bf16 samples: only when that one reported a counter overflow
-    if (gate && __hip_atomic_load(gate, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u) return;
     for (uint32_t i = blockIdx.x * BLOCK + threadIdx.x; i < zero_words; i += gridDim.x * BLOCK) zero[i] = 0u;
     float lo = INFINITY, hi = -INFINITY;
     uint64_t begin, end;
@@ -439,10 +436,8 @@ __global__ __launch_bounds__(BLOCK) void k_minmax(const EntGroup grp, float2* __
 }
 
 // Caller-supplied range: stands in as the one block's (lo, hi); zeroes the counters.
-__global__ void k_set_range(float2* part, float lo, float hi, uint32_t* __restrict__ zero, uint32_t zero_words,
-                            const unsigned int* gate)
+__global__ void k_set_range(float2* part, float lo, float hi, uint32_t* __restrict__ zero, uint32_t zero_words)
 {
-    if (gate && __hip_atomic_load(gate, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u) return;
     for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < zero_words; i += gridDim.x * blockDim.x) zero[i] = 0u;
     if (threadIdx.x == 0 && blockIdx.x == 0) part[0] = make_float2(lo, hi);
 }
@@ -526,9 +521,8 @@ template <typename T, int VEC, int BLOCK>
 __global__ __launch_bounds__(BLOCK) void k_hist(
     const EntGroup grp, const float2* __restrict__ part, uint32_t nparts, uint32_t bins,
     uint32_t bins_local, uint32_t rep_shift, uint32_t* copies, uint32_t sets, unsigned long long* counts,
-    unsigned int* ticket, edgc_entropy_result* res, unsigned int* gate)
+    unsigned int* ticket, edgc_entropy_result* res)
 {
-    if (gate && __hip_atomic_load(gate, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u) return;
     extern __shared__ uint32_t h[];   // [bins_local << rep_shift], replica = lane & (R-1)
     const uint32_t bin_base = blockIdx.y * bins_local;
     const uint32_t local_n = min(bins_local, bins - bin_base);
@@ -596,11 +590,7 @@ __global__ __launch_bounds__(BLOCK) void k_hist(
         for (uint32_t i = threadIdx.x; i < bins; i += BLOCK) entropy_term(counts[i], acc, tot);
     }
     block_sum_pair<BLOCK>(acc, tot);
-    if (threadIdx.x == 0) {
-        emit_result(acc, tot, bins, rp, grp.n_sampled, res);
-        // every block of this grid has read the gate by now (each took its ticket after that)
-        if (gate) *gate = 0u;
-    }
+    if (threadIdx.x == 0) emit_result(acc, tot, bins, rp, grp.n_sampled, res);
 }
 
 // The whole estimate of a small sample by one block: range, histogram and entropy without a second launch, global
@@ -646,12 +636,11 @@ __global__ __launch_bounds__(kOneBlock) void k_estimate_one(const EntGroup grp, 
 //    the sample is read ONCE, with no range pass before it, and the rest (range of the finite
 //    sample, bin of every pattern by the same fp32 operations the binning kernel applies to
 //    every element, entropy) is derived from the 65536 pattern counts.
-// A field counts to 0x7fff; the add that takes it to 0x8000 or beyond sees that in the value the
-// atomic returns, and that thread alone credits 32768 to the key's 64-bit global counter
-// (`wide`) and takes 0x8000 off the field again.  A field could only carry into its neighbour if
-// 32767 more increments reached it between those two LDS operations of one thread; the add that
-// would do it sees 0xffff, and then the kernel raises `gate`, which lets the plain kernels queued
-// behind on the stream redo the estimate (they return at once otherwise).
+// A round of the block adds at most 32768 elements (1024 threads, four items of eight), so a field that is below 0x8000
+// when a round begins cannot carry into its neighbour; after every round each thread looks through its own 32 words and
+// moves fields that have reached 0x8000 off to the key's 64-bit global counter (`wide`), 32768 at a time.
+// (Adds that return the old value and move the field off at once need no such sweep, but every one of them waits for
+// the LDS: 134 M bf16 elements 90 us against 61, 4.4 TB/s.)
 // At its end a block stores its fields as they stand to its own 128 KiB of `part16` (plain
 // 16-byte stores: no atomics on global memory, of which 256 blocks x some thousand keys would be
 // the larger part of a small estimate), and k_wide_reduce sums them.
@@ -659,27 +648,16 @@ __global__ __launch_bounds__(kOneBlock) void k_estimate_one(const EntGroup grp, 
 constexpr int kWideBlock = 1024;
 constexpr uint32_t kWideKeys = 65536;
 
-__device__ __forceinline__ void field_add(uint32_t* h, unsigned long long* wide, uint32_t key, uint32_t k,
-                                          uint32_t& overflow)
-{
-    const uint32_t sh = (key & 1u) << 4;
-    const uint32_t old = atomicAdd(&h[key >> 1], k << sh);
-    const uint32_t fld = (old >> sh) & 0xffffu;
-    if (fld < 0x8000u && fld + k >= 0x8000u) {
-        atomicAdd(&wide[key], 32768ull);
-        atomicSub(&h[key >> 1], 0x8000u << sh);
-    }
-    if (fld + k > 0xffffu) overflow = 1u;
-}
-
 template <typename T, int VEC, bool PATTERN>
 __global__ __launch_bounds__(kWideBlock) void k_wide_hist(
     const EntGroup grp, const float2* __restrict__ part, uint32_t nparts, uint32_t bins, uint16_t* __restrict__ part16,
-    unsigned long long* __restrict__ wide, unsigned int* gate, int raise_gate)
+    unsigned long long* __restrict__ wide)
 {
     static_assert(!PATTERN || sizeof(T) == 2, "the raw pattern is the key of 16-bit elements only");
+    static_assert(kWideBlock * 4 * VEC <= 32768, "what a round can add to one field");
     extern __shared__ uint32_t h[];   // [kWideKeys / 2]
-    for (uint32_t i = threadIdx.x; i < kWideKeys / 2; i += kWideBlock) h[i] = 0u;
+    uint4* const h4 = reinterpret_cast<uint4*>(h);
+    for (uint32_t i = threadIdx.x; i < kWideKeys / 8; i += kWideBlock) h4[i] = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
 
     float lo = 0.0f, scale = 0.0f, top = 0.0f;
@@ -689,13 +667,13 @@ __global__ __launch_bounds__(kWideBlock) void k_wide_hist(
         lo = rp.lo; scale = rp.scale;
         top = __uint_as_float(__float_as_uint(fbins) - 1u);     // largest float below the bin count
     }
+    auto add = [&](uint32_t key, uint32_t k) { atomicAdd(&h[key >> 1], k << ((key & 1u) << 4)); };
     // bin = trunc((x - lo) * scale), each operation rounded on its own, clamped to [0, bins - 1]
-    auto bin_of = [&](float x) {
+    auto add_bin = [&](float x) {
         const float t = __fsub_rn(x, lo);
-        return static_cast<uint32_t>(__builtin_amdgcn_fmed3f(__fmul_rn(t, scale), 0.0f, top));
+        add(static_cast<uint32_t>(__builtin_amdgcn_fmed3f(__fmul_rn(t, scale), 0.0f, top)), finite_f32(x) ? 1u : 0u);
     };
 
-    uint32_t overflow = 0;
     uint64_t begin, end;
     block_range(grp, begin, end);
     walk_items<T, VEC, kWideBlock>(grp, begin, end, true,
@@ -705,75 +683,85 @@ __global__ __launch_bounds__(kWideBlock) void k_wide_hist(
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const uint32_t a = w[q] & 0xffffu, b = w[q] >> 16;
-                    if (a == b) {                  // runs of equal values (zeros) in one add
-                        field_add(h, wide, a, 2u, overflow);
-                    } else {
-                        field_add(h, wide, a, 1u, overflow);
-                        field_add(h, wide, b, 1u, overflow);
-                    }
+                    add(a, a == b ? 2u : 1u);                  // runs of equal values (zeros) in one add
+                    if (a != b) add(b, 1u);
                 }
             } else if constexpr (VEC > 1) {
                 float v[VEC];
                 unpack_item<T, VEC>(raw, v);
 #pragma unroll
-                for (int q = 0; q < VEC; ++q)
-                    field_add(h, wide, bin_of(v[q]), finite_f32(v[q]) ? 1u : 0u, overflow);
+                for (int q = 0; q < VEC; ++q) add_bin(v[q]);
             }
         },
         [&](T x) {
-            if constexpr (PATTERN) {
-                field_add(h, wide, x, 1u, overflow);
-            } else {
-                const float f = ElemTraits<T>::widen(x);
-                if (finite_f32(f)) field_add(h, wide, bin_of(f), 1u, overflow);
+            if constexpr (PATTERN) add(x, 1u);
+            else add_bin(ElemTraits<T>::widen(x));
+        },
+        [&] {
+            __syncthreads();
+#pragma unroll
+            for (uint32_t j = 0; j < kWideKeys / 8 / kWideBlock; ++j) {
+                const uint32_t at = threadIdx.x + j * kWideBlock;
+                const uint4 v = h4[at];
+                if (((v.x | v.y | v.z | v.w) & 0x80008000u) == 0u) continue;
+                const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                for (uint32_t q = 0; q < 4; ++q) {
+                    if (w[q] & 0x8000u) atomicAdd(&wide[at * 8 + 2 * q], 32768ull);
+                    if (w[q] & 0x80000000u) atomicAdd(&wide[at * 8 + 2 * q + 1], 32768ull);
+                }
+                h4[at] = make_uint4(v.x & 0x7fff7fffu, v.y & 0x7fff7fffu, v.z & 0x7fff7fffu, v.w & 0x7fff7fffu);
             }
-        }, [] {});
-    if (overflow || raise_gate) atomicOr(gate, 1u);   // raise_gate: the redo path under test
+            __syncthreads();
+        });
     __syncthreads();
     uint4* __restrict__ dst = reinterpret_cast<uint4*>(part16 + static_cast<size_t>(blockIdx.x) * kWideKeys);
-    const uint4* h4 = reinterpret_cast<const uint4*>(h);
     for (uint32_t i = threadIdx.x; i < kWideKeys / 8; i += kWideBlock) dst[i] = h4[i];
 }
 
-// Sums the blocks' 16-bit fields and the 64-bit credits per key (one thread per key, 1024 keys per
-// block), and the last block to finish turns the totals into the estimate.
+// Sums the blocks' 16-bit fields and the 64-bit credits per key, 256 keys per block, and the last block to finish
+// turns the totals into the estimate.
 //  fp32 (keys are bins): the totals are the histogram.
 //  bf16 (keys are bit patterns): the blocks also reduce the range of the patterns that occur; the
 //  last block bins the patterns' totals in LDS (slices of 16384 bins) and writes the histogram.
+// What bounds it: the latency of reading 128 KiB from each of up to 256 blocks' fields; all of a thread's eight 16-byte
+// loads are in flight together, on every CU (64 blocks of 1024 keys took 44 us for bf16 and 33 for fp32, a fence in
+// every wave included; these take 27 and 19).
 constexpr uint32_t kWideSliceBins = 16384;
-constexpr size_t kWideReduceLds = 8 * kWideBlock * sizeof(uint32_t);      // the eight groups' sums
+constexpr uint32_t kReduceKeys = 256;                                     // per block
+constexpr uint32_t kReduceGroups = kWideBlock / (kReduceKeys / 8);        // 32 groups of 32 threads
+constexpr size_t kWideReduceLds = (kReduceGroups + 4) * kReduceKeys * sizeof(uint32_t);
 
 template <bool PATTERN>
 __global__ __launch_bounds__(kWideBlock) void k_wide_reduce(
     const uint16_t* __restrict__ part16, uint32_t nblocks, unsigned long long* __restrict__ wide,
     unsigned long long* totals, uint32_t bins, int has_range, float range_lo, float range_hi,
     unsigned long long* counts, const float2* __restrict__ mm_part, uint32_t nparts, float* part, unsigned int* ticket,
-    const unsigned int* gate,
     unsigned long long n_sampled, edgc_entropy_result* res)
 {
-    extern __shared__ unsigned long long slice[];     // 32 KiB for the sums; PATTERN: [min(bins, kWideSliceBins)] as well
-    constexpr uint32_t kMaxGrid = kWideKeys / kWideBlock;
-    const uint32_t key = blockIdx.x * kWideBlock + threadIdx.x;
-    // after a counter overflow the kernels behind redo the estimate, on counters that start at zero
-    const bool redo = __hip_atomic_load(gate, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
+    extern __shared__ unsigned long long slice[];     // the groups' sums; PATTERN: [min(bins, kWideSliceBins)] as well
+    constexpr uint32_t kMaxGrid = kWideKeys / kReduceKeys;
+    const bool mine = threadIdx.x < kReduceKeys;      // one key per thread
+    const uint32_t key = blockIdx.x * kReduceKeys + threadIdx.x;
     // per block: (lo, hi) of the patterns that occur, or (sum c log2 c, sum c) of its bins
     double* const part_d = reinterpret_cast<double*>(part);
 
-    unsigned long long c = wide[key];
+    unsigned long long c = mine ? wide[key] : 0ull;
     if (c) wide[key] = 0ull;                          // zero between estimates
     {
-        // The block's 1024 keys are 128 columns of eight 16-bit fields (one 16-byte load); each of its
-        // eight groups of 128 threads sums every eighth block's fields, and the groups' sums meet in LDS.
-        uint32_t* const red = reinterpret_cast<uint32_t*>(slice);          // [8][kWideBlock]
-        const uint32_t col = threadIdx.x & 127u, grp = threadIdx.x >> 7;
-        const uint4* __restrict__ src = reinterpret_cast<const uint4*>(part16 + blockIdx.x * kWideBlock) + col;
+        // The block's keys are 32 columns of eight 16-bit fields (one 16-byte load); each of its 32 groups of 32 threads
+        // sums every 32nd block's fields, and the groups' sums meet in LDS.
+        uint32_t* const red = reinterpret_cast<uint32_t*>(slice);          // [kReduceGroups][kReduceKeys], then [4][kReduceKeys]
+        const uint32_t col = threadIdx.x & 31u, grp = threadIdx.x >> 5;
+        const uint4* __restrict__ src = reinterpret_cast<const uint4*>(part16 + blockIdx.x * kReduceKeys) + col;
         constexpr size_t kRow = kWideKeys / 8;                             // 16-byte items per block's fields
-        uint32_t sm[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};               // at most 32 blocks x 0xffff each
-        for (uint32_t b = grp; b < nblocks; b += 64) {
+        uint32_t sm[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};                 // fields are below 0x8000
+        for (uint32_t b = grp; b < nblocks; b += 8 * kReduceGroups) {
             uint4 v[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
-                v[u] = (b + 8 * u < nblocks) ? src[static_cast<size_t>(b + 8 * u) * kRow] : make_uint4(0u, 0u, 0u, 0u);
+            for (uint32_t u = 0; u < 8; ++u)
+                v[u] = (b + kReduceGroups * u < nblocks) ? src[static_cast<size_t>(b + kReduceGroups * u) * kRow]
+                                                         : make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 sm[0] += v[u].x & 0xffffu; sm[1] += v[u].x >> 16;
@@ -782,28 +770,36 @@ __global__ __launch_bounds__(kWideBlock) void k_wide_reduce(
                 sm[6] += v[u].w & 0xffffu; sm[7] += v[u].w >> 16;
             }
         }
-        uint4* const dst = reinterpret_cast<uint4*>(red + grp * kWideBlock + col * 8);
+        uint4* const dst = reinterpret_cast<uint4*>(red + grp * kReduceKeys + col * 8);
         dst[0] = make_uint4(sm[0], sm[1], sm[2], sm[3]);
         dst[1] = make_uint4(sm[4], sm[5], sm[6], sm[7]);
         __syncthreads();
+        const uint32_t k = threadIdx.x & (kReduceKeys - 1u), quarter = threadIdx.x / kReduceKeys;
         uint32_t sum = 0;
 #pragma unroll
-        for (int gI = 0; gI < 8; ++gI) sum += red[gI * kWideBlock + threadIdx.x];
-        c += sum;
+        for (uint32_t gI = 0; gI < kReduceGroups / 4; ++gI) sum += red[(quarter * (kReduceGroups / 4) + gI) * kReduceKeys + k];
+        uint32_t* const red2 = red + kReduceGroups * kReduceKeys;
+        red2[quarter * kReduceKeys + k] = sum;
+        __syncthreads();
+        if (mine) c += red2[k] + red2[kReduceKeys + k] + red2[2 * kReduceKeys + k] + red2[3 * kReduceKeys + k];
         __syncthreads();                              // `slice` is used again by the last block
     }
     if constexpr (!PATTERN) {
         // the totals are the histogram; this block's share of the entropy sums goes with them
-        if (key < bins) counts[key] = redo ? 0ull : c;
         double acc = 0.0, tot = 0.0;
-        if (key < bins) entropy_term(c, acc, tot);
+        if (mine && key < bins) {
+            counts[key] = c;
+            entropy_term(c, acc, tot);
+        }
         block_sum_pair<kWideBlock>(acc, tot);
         if (threadIdx.x == 0) { part_d[2 * blockIdx.x] = acc; part_d[2 * blockIdx.x + 1] = tot; }
     } else {
-        totals[key] = c;
-        const float x = __uint_as_float(key << 16);
         float lo = INFINITY, hi = -INFINITY;
-        if (c && finite_f32(x)) { lo = x; hi = x; }
+        if (mine) {
+            totals[key] = c;
+            const float x = __uint_as_float(key << 16);
+            if (c && finite_f32(x)) { lo = x; hi = x; }
+        }
         block_range_minmax<kWideBlock>(lo, hi);
         if (threadIdx.x == 0) {
             part[2 * blockIdx.x]     = lo;            // lo > hi: none of this block's patterns occurs
@@ -817,60 +813,46 @@ __global__ __launch_bounds__(kWideBlock) void k_wide_reduce(
     if constexpr (!PATTERN) {
         rp = fold_range<kWideBlock>(mm_part, nparts, static_cast<float>(bins));
         if (threadIdx.x < gridDim.x) {
-            acc = __hip_atomic_load(&part_d[2 * threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            tot = __hip_atomic_load(&part_d[2 * threadIdx.x + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            acc = part_d[2 * threadIdx.x];
+            tot = part_d[2 * threadIdx.x + 1];
         }
     } else {
-        // range of the finite sample from the blocks' partials, and the list of the blocks (of 1024
-        // patterns) in which any pattern occurs: a dense gradient touches a few of the 64
-        __shared__ float s_blo[kMaxGrid], s_bhi[kMaxGrid];
-        __shared__ uint32_t s_list[kMaxGrid];
-        __shared__ uint32_t s_nlist;
-        __shared__ float s_range[2];
-        if (threadIdx.x < gridDim.x) {
-            s_blo[threadIdx.x] = __hip_atomic_load(&part[2 * threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            s_bhi[threadIdx.x] = __hip_atomic_load(&part[2 * threadIdx.x + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+        // range of the finite sample from the blocks' partials, and the list of the blocks (of 256 patterns) in which
+        // any finite pattern occurs: a dense gradient touches a few of the 256
+        __shared__ uint32_t s_list[kMaxGrid], s_nlist;
+        float lo = INFINITY, hi = -INFINITY;
+        if (threadIdx.x < gridDim.x) { lo = part[2 * threadIdx.x]; hi = part[2 * threadIdx.x + 1]; }
+        const bool occurs = lo <= hi;
+        if (threadIdx.x == 0) s_nlist = 0u;
         __syncthreads();
-        if (threadIdx.x == 0) {
-            float lo = INFINITY, hi = -INFINITY;
-            uint32_t nl = 0;
-            for (uint32_t b = 0; b < gridDim.x; ++b) {
-                lo = fminf(lo, s_blo[b]); hi = fmaxf(hi, s_bhi[b]);
-                if (s_blo[b] <= s_bhi[b]) s_list[nl++] = b;
-            }
-            s_nlist = nl;
-            if (has_range) { lo = range_lo; hi = range_hi; }
-            s_range[0] = lo; s_range[1] = hi;
-        }
-        __syncthreads();
-        rp = make_range(s_range[0], s_range[1], static_cast<float>(bins));
-        const float rlo = rp.lo, scale = rp.scale;
-        const uint32_t nlist = s_nlist;
-        const float fbins = static_cast<float>(bins);
-        const float top = __uint_as_float(__float_as_uint(fbins) - 1u);   // largest float below the bin count
+        if (occurs) s_list[atomicAdd(&s_nlist, 1u)] = threadIdx.x;         // any order: the sums are of integers
+        block_range_minmax<kWideBlock>(lo, hi);
+        if (has_range) { lo = range_lo; hi = range_hi; }
+        rp = make_range(lo, hi, static_cast<float>(bins));
+        const uint32_t nlist = s_nlist, quarter = threadIdx.x / kReduceKeys, k = threadIdx.x & (kReduceKeys - 1u);
+        const float top = __uint_as_float(__float_as_uint(static_cast<float>(bins)) - 1u);   // largest float below the bin count
         for (uint32_t base = 0; base < bins; base += kWideSliceBins) {
             const uint32_t nb = min(kWideSliceBins, bins - base);
             for (uint32_t i = threadIdx.x; i < nb; i += kWideBlock) slice[i] = 0ull;
             __syncthreads();
-            // eight of the listed blocks at a time: their loads (from the other blocks' stores, past this
-            // CU's caches) are in flight together
-            for (uint32_t j = 0; j < nlist; j += 8) {
+            // 32 of the listed blocks at a time, eight per quarter of this one: their loads are in flight together
+            for (uint32_t j = 0; j < nlist; j += 32) {
                 unsigned long long cp[8];
                 uint32_t pp[8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    pp[u] = s_list[min(j + u, nlist - 1)] * kWideBlock + threadIdx.x;
-                    cp[u] = __hip_atomic_load(&totals[pp[u]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                for (uint32_t u = 0; u < 8; ++u) {
+                    const uint32_t l = j + 4 * u + quarter;
+                    pp[u] = s_list[min(l, nlist - 1)] * kReduceKeys + k;
+                    cp[u] = l < nlist ? totals[pp[u]] : 0ull;
                 }
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
                     const float x = __uint_as_float(pp[u] << 16);
-                    if (j + u < nlist && cp[u] && finite_f32(x)) {
+                    if (cp[u] && finite_f32(x)) {
                         // bin = trunc((x - lo) * scale), each operation rounded on its own, clamped to [0, bins - 1]
-                        const float t = __fsub_rn(x, rlo);
+                        const float t = __fsub_rn(x, rp.lo);
                         const uint32_t bin =
-                            static_cast<uint32_t>(__builtin_amdgcn_fmed3f(__fmul_rn(t, scale), 0.0f, top));
+                            static_cast<uint32_t>(__builtin_amdgcn_fmed3f(__fmul_rn(t, rp.scale), 0.0f, top));
                         if (bin - base < nb) atomicAdd(&slice[bin - base], cp[u]);
                     }
                 }
@@ -878,16 +860,14 @@ __global__ __launch_bounds__(kWideBlock) void k_wide_reduce(
             __syncthreads();
             for (uint32_t i = threadIdx.x; i < nb; i += kWideBlock) {
                 const unsigned long long cb = slice[i];
-                counts[base + i] = redo ? 0ull : cb;
+                counts[base + i] = cb;
                 entropy_term(cb, acc, tot);
             }
             __syncthreads();
         }
     }
     block_sum_pair<kWideBlock>(acc, tot);
-    if (threadIdx.x == 0) {
-        emit_result(acc, tot, bins, rp, n_sampled, res);
-    }
+    if (threadIdx.x == 0) emit_result(acc, tot, bins, rp, n_sampled, res);
 }
 
 // ---------------------------------------------------------------------------
@@ -955,7 +935,7 @@ static uint32_t grid_for(uint64_t n_items, int block, int per_thread, int max_bl
 // allocations, or the file-scope array of the entry point that allocates nothing.
 struct EntScratch {
     float2*             mm_part;       // [kMaxReduceBlocks] per-block (lo, hi)
-    unsigned int*       ticket;        // [kTicketWords] last-block ticket and the overflow gate (kGateWord); zero between calls
+    unsigned int*       ticket;        // [kTicketWords] last-block ticket; zero between calls
     uint32_t*           copies;        // [8][kCopyBins] histogram counters by XCD
     uint16_t*           part16;        // [part16_blocks][65536] 16-bit counters per block, or null: plain kernels only
     uint32_t            part16_blocks;
@@ -974,8 +954,7 @@ static int run_entropy(edgc_ctx* ctx, const EntScratch& s, const EntGroup& g, ui
     const bool small = g.n_items <= static_cast<uint64_t>(kHistBlock) * 4 * ctx->num_cu * 2;
     // One read into 16-bit counters per block (the kernels above), where the context has the memory
     // for the blocks' fields: every bf16 sample of some size (no range pass, any number of bins), and
-    // fp32 samples on more bins than 32-bit counters hold in LDS at once.  The plain kernels follow on
-    // the stream behind `gate` and return at once unless a 16-bit counter overflowed.
+    // fp32 samples on more bins than 32-bit counters hold in LDS at once.
     const bool wide_ok = s.part16 != nullptr && ctx->tune_pattern != 0;
     // (measured on samples of a 1e9-element bf16 buffer, 4096 bins, one read against two passes: 1e7
     // elements 0.067 against 0.061 ms, 1e8 0.115 against 0.171, 1e9 0.57 against 0.85; on 65536 bins: 1e7
@@ -984,7 +963,6 @@ static int run_entropy(edgc_ctx* ctx, const EntScratch& s, const EntGroup& g, ui
     const bool by_pattern = sizeof(T) == 2 && wide_ok &&
                             (g.n_sampled >= pattern_min || (bins > 16384 && g.n_sampled >= pattern_min / 8));
     const bool by_wide_bins = sizeof(T) == 4 && wide_ok && bins > 16384 && bins <= kWideKeys;
-    unsigned int* gate = (by_pattern || by_wide_bins) ? s.ticket + kGateWord : nullptr;
     const uint32_t wide_blocks = grid_for(g.n_items, kWideBlock, 4, min(ctx->num_cu, static_cast<int>(s.part16_blocks)));
     uint32_t nparts = 0;                                   // blocks' (lo, hi) in s.mm_part
     float* const pair_part = reinterpret_cast<float*>(s.mm_part + kMaxReduceBlocks / 2);
@@ -992,14 +970,16 @@ static int run_entropy(edgc_ctx* ctx, const EntScratch& s, const EntGroup& g, ui
         if (by_pattern) {
             EDGC_LAUNCH(ctx, st, KID_WIDE_HIST, sample_bytes, 0.0,
                         k_wide_hist<T, VEC, true><<<wide_blocks, kWideBlock, kWideKeys * 2, st>>>(
-                            g, s.mm_part, nparts, bins, s.part16, s.wide, gate, ctx->tune_pattern == 3 ? 1 : 0));
+                            g, s.mm_part, nparts, bins, s.part16, s.wide));
             const size_t lds = max(static_cast<size_t>(min(bins, kWideSliceBins)) * sizeof(unsigned long long),
                                    kWideReduceLds);
             EDGC_LAUNCH(ctx, st, KID_WIDE_REDUCE, 2.0 * kWideKeys * wide_blocks, 0.0,
-                        k_wide_reduce<true><<<kWideKeys / kWideBlock, kWideBlock, lds, st>>>(
+                        k_wide_reduce<true><<<kWideKeys / kReduceKeys, kWideBlock, lds, st>>>(
                             s.part16, wide_blocks, s.wide, s.totals, bins, range ? 1 : 0, range ? range[0] : 0.0f,
-                            range ? range[1] : 0.0f, counts, nullptr, 0u, pair_part, s.ticket, gate,
+                            range ? range[1] : 0.0f, counts, nullptr, 0u, pair_part, s.ticket,
                             g.n_sampled, res));
+            EDGC_HIP_TRY(ctx, hipGetLastError());
+            return EDGC_OK;
         }
     }
     // LDS plan: up to 64 KiB of 32-bit counters, replicated per lane where bins are few;
@@ -1036,45 +1016,46 @@ static int run_entropy(edgc_ctx* ctx, const EntScratch& s, const EntGroup& g, ui
     // the counters the histogram kernel accumulates into
     const uint32_t sets = (bins <= kCopyBins && g.n_sampled < (1ull << 32)) ? (gx > 16 ? 8u : 1u) : 0u;
     uint32_t* zero = sets ? s.copies : reinterpret_cast<uint32_t*>(counts);
-    const uint32_t zero_words = sets ? sets * copy_stride(bins) : 2u * bins;
-    const unsigned int* range_gate = by_pattern ? gate : nullptr;
+    const uint32_t zero_words = by_wide_bins ? 0u : sets ? sets * copy_stride(bins) : 2u * bins;
     if (range) {
         nparts = 1;
         EDGC_LAUNCH(ctx, st, KID_SET_RANGE, 4.0 * zero_words, 0.0,
-                    k_set_range<<<min((zero_words + 255) / 256, 1024u), 256, 0, st>>>(s.mm_part, range[0], range[1], zero,
-                                                                                    zero_words, range_gate));
+                    k_set_range<<<std::clamp((zero_words + 255) / 256, 1u, 1024u), 256, 0, st>>>(s.mm_part, range[0], range[1], zero,
+                                                                                    zero_words));
     } else if (g.n_items >= kBigSampleItems) {
         // a large sample: one block of 1024 threads per CU (1e8 fp32 elements out of 1e9: 0.08 instead
         // of 0.12 ms, bf16 0.05 instead of 0.08; every element of 1e9: 0.70 instead of 0.71 ms)
         nparts = grid_for(g.n_items, kMMBlockFat, 16, ctx->num_cu);
         EDGC_LAUNCH(ctx, st, KID_MINMAX, sample_bytes, 0.0,
-                    k_minmax<T, VEC, kMMBlockFat><<<nparts, kMMBlockFat, 0, st>>>(g, s.mm_part, zero, zero_words, range_gate));
+                    k_minmax<T, VEC, kMMBlockFat><<<nparts, kMMBlockFat, 0, st>>>(g, s.mm_part, zero, zero_words));
     } else {
         nparts = grid_for(g.n_items, kMMBlock, ctx->tune_ept > 0 ? 2 * ctx->tune_ept : 8, ctx->num_cu * 4);
         EDGC_LAUNCH(ctx, st, KID_MINMAX, sample_bytes, 0.0,
-                    k_minmax<T, VEC, kMMBlock><<<nparts, kMMBlock, 0, st>>>(g, s.mm_part, zero, zero_words, range_gate));
+                    k_minmax<T, VEC, kMMBlock><<<nparts, kMMBlock, 0, st>>>(g, s.mm_part, zero, zero_words));
     }
 
     if constexpr (sizeof(T) == 4) {
         if (by_wide_bins) {
             EDGC_LAUNCH(ctx, st, KID_WIDE_HIST, sample_bytes, 0.0,
                         k_wide_hist<T, VEC, false><<<wide_blocks, kWideBlock, kWideKeys * 2, st>>>(
-                            g, s.mm_part, nparts, bins, s.part16, s.wide, gate, ctx->tune_pattern == 3 ? 1 : 0));
+                            g, s.mm_part, nparts, bins, s.part16, s.wide));
             EDGC_LAUNCH(ctx, st, KID_WIDE_REDUCE, 2.0 * kWideKeys * wide_blocks, 0.0,
-                        k_wide_reduce<false><<<(bins + kWideBlock - 1) / kWideBlock, kWideBlock, kWideReduceLds, st>>>(
+                        k_wide_reduce<false><<<(bins + kReduceKeys - 1) / kReduceKeys, kWideBlock, kWideReduceLds, st>>>(
                             s.part16, wide_blocks, s.wide, s.totals, bins, 0, 0.0f, 0.0f, counts, s.mm_part, nparts,
-                            pair_part, s.ticket, gate, g.n_sampled, res));
+                            pair_part, s.ticket, g.n_sampled, res));
+            EDGC_HIP_TRY(ctx, hipGetLastError());
+            return EDGC_OK;
         }
     }
 
     if (fat) {
         EDGC_LAUNCH(ctx, st, KID_HIST, sample_bytes * ny, 0.0,
                     k_hist<T, VEC, kHistBlockFat><<<dim3(gx, ny), kHistBlockFat, lds, st>>>(
-                        g, s.mm_part, nparts, bins, bins_local, rep_shift, s.copies, sets, counts, s.ticket, res, gate));
+                        g, s.mm_part, nparts, bins, bins_local, rep_shift, s.copies, sets, counts, s.ticket, res));
     } else {
         EDGC_LAUNCH(ctx, st, KID_HIST, sample_bytes * ny, 0.0,
                     k_hist<T, VEC, kHistBlock><<<dim3(gx, ny), kHistBlock, lds, st>>>(
-                        g, s.mm_part, nparts, bins, bins_local, rep_shift, s.copies, sets, counts, s.ticket, res, gate));
+                        g, s.mm_part, nparts, bins, bins_local, rep_shift, s.copies, sets, counts, s.ticket, res));
     }
     EDGC_HIP_TRY(ctx, hipGetLastError());
     return EDGC_OK;
