@@ -2085,16 +2085,44 @@ __global__ __launch_bounds__(256, 2) void k_pass_p_deferred_narrow(const Group g
         }
 }
 
-// Strided row copy (a tensor that is sent as it stands: decompress hands the gradient on).
-__global__ __launch_bounds__(256) void k_copy_rows(const unsigned char* __restrict__ src, uint64_t ld_src,
-                                                   unsigned char* __restrict__ dst, uint64_t ld_dst,
-                                                   uint32_t m, uint64_t row_bytes)
+// Copies of the tensors that are sent as they stand (decompress hands the gradient on), all of them in one launch: a
+// transformer stage has a dozen norm weights and biases of some kilobytes each, and a launch costs more than any of
+// them (16 of them in the stage of two hidden-768 blocks: 16 launches 37 to 60 us, one 5).  A unit is the widest
+// access that the tensor's pointers, row length and strides allow; a contiguous tensor may end inside a unit.
+template <typename U>
+__device__ __forceinline__ void copy_units(const unsigned char* __restrict__ src, unsigned char* __restrict__ dst,
+                                           uint64_t row_bytes, uint64_t ld_src, uint64_t ld_dst, uint32_t m, uint64_t first)
 {
-    const uint64_t total = static_cast<uint64_t>(m) * row_bytes;
-    for (uint64_t i = static_cast<uint64_t>(blockIdx.x) * 256 + threadIdx.x; i < total;
-         i += static_cast<uint64_t>(gridDim.x) * 256) {
-        const uint64_t row = i / row_bytes, b = i % row_bytes;
-        dst[row * ld_dst + b] = src[row * ld_src + b];
+    constexpr int N = kCopyUnits / 256;
+    const uint64_t whole = row_bytes / sizeof(U), total = whole * m;      // units
+    U v[N] = {};
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        const uint64_t i = first + threadIdx.x + k * 256u, row = m == 1 ? 0 : i / whole;
+        if (i < total) v[k] = *reinterpret_cast<const U*>(src + row * ld_src + (i - row * whole) * sizeof(U));
+    }
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        const uint64_t i = first + threadIdx.x + k * 256u, row = m == 1 ? 0 : i / whole;
+        if (i < total) *reinterpret_cast<U*>(dst + row * ld_dst + (i - row * whole) * sizeof(U)) = v[k];
+    }
+    // what the last unit of a contiguous tensor leaves: 16-bit pieces, one per thread of its first block
+    const uint64_t at = whole * sizeof(U) + 2u * threadIdx.x;
+    if (first == 0 && m == 1 && at < row_bytes)
+        *reinterpret_cast<uint16_t*>(dst + at) = *reinterpret_cast<const uint16_t*>(src + at);
+}
+
+__global__ __launch_bounds__(256) void k_copy_rows(const CopyGroup grp)
+{
+    uint32_t t = 0;
+    for (uint32_t i = 1; i < grp.count; ++i) t += (blockIdx.x >= grp.t[i].first) ? 1u : 0u;
+    const CopyArgs& c = grp.t[t];
+    const uint64_t first = static_cast<uint64_t>(blockIdx.x - c.first) * kCopyUnits;
+    switch (c.unit) {
+    case 16: copy_units<uint4>(c.src, c.dst, c.row_bytes, c.ld_src, c.ld_dst, c.m, first); break;
+    case 8: copy_units<uint2>(c.src, c.dst, c.row_bytes, c.ld_src, c.ld_dst, c.m, first); break;
+    case 4: copy_units<uint32_t>(c.src, c.dst, c.row_bytes, c.ld_src, c.ld_dst, c.m, first); break;
+    default: copy_units<uint16_t>(c.src, c.dst, c.row_bytes, c.ld_src, c.ld_dst, c.m, first); break;
     }
 }
 
@@ -2175,15 +2203,39 @@ int launch_init_q(edgc_ctx* ctx, float* Q, uint32_t n, uint32_t ldq, uint32_t c0
     return EDGC_OK;
 }
 
-int launch_copy_rows(edgc_ctx* ctx, const void* src, uint64_t ld_src, void* dst, uint64_t ld_dst,
-                     uint32_t m, uint32_t n, uint32_t elem_bytes, hipStream_t st)
+int CopyList::add(const void* src, uint64_t ld_src, void* dst, uint64_t ld_dst, uint32_t m, uint32_t n,
+                  uint32_t elem_bytes, hipStream_t st)
 {
-    const uint64_t total = static_cast<uint64_t>(m) * n * elem_bytes;
-    if (total == 0 || src == dst) return EDGC_OK;
-    const uint32_t blocks = std::min<uint32_t>(cdiv(total, 256), static_cast<uint32_t>(ctx->num_cu) * 8);
-    k_copy_rows<<<blocks, 256, 0, st>>>(static_cast<const unsigned char*>(src), ld_src * elem_bytes,
-                                        static_cast<unsigned char*>(dst), ld_dst * elem_bytes, m,
-                                        static_cast<uint64_t>(n) * elem_bytes);
+    if (static_cast<uint64_t>(m) * n == 0 || src == dst) return EDGC_OK;
+    CopyArgs c{};
+    c.src = static_cast<const unsigned char*>(src);
+    c.dst = static_cast<unsigned char*>(dst);
+    c.m = m;
+    c.row_bytes = static_cast<uint64_t>(n) * elem_bytes;
+    c.ld_src = ld_src * elem_bytes;
+    c.ld_dst = ld_dst * elem_bytes;
+    if (ld_src == n && ld_dst == n) { c.row_bytes *= m; c.m = 1; }
+    uint64_t bits = reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst);
+    if (c.m > 1) bits |= c.row_bytes | c.ld_src | c.ld_dst;
+    c.unit = 16;
+    while (c.unit > elem_bytes && bits % c.unit) c.unit /= 2;
+    const uint64_t units = (c.row_bytes + c.unit - 1) / c.unit * c.m;
+    const uint64_t nb = (units + kCopyUnits - 1) / kCopyUnits;
+    if (nb > 0x7fffffffull) return fail(ctx, EDGC_EINVAL, "a tensor that is sent as it stands is too large");
+    if (g.count == kMaxCopies || blocks + nb > 0x7fffffffull)
+        if (int rc = flush(st)) return rc;
+    c.first = static_cast<uint32_t>(blocks);
+    blocks += nb;
+    g.t[g.count++] = c;
+    return EDGC_OK;
+}
+
+int CopyList::flush(hipStream_t st)
+{
+    if (g.count == 0) return EDGC_OK;
+    k_copy_rows<<<static_cast<uint32_t>(blocks), 256, 0, st>>>(g);
+    g.count = 0;
+    blocks = 0;
     EDGC_HIP_TRY(ctx, hipGetLastError());
     return EDGC_OK;
 }

@@ -617,11 +617,12 @@ int decompress_batch_impl(edgc_ctx* ctx, const edgc_tensor* tensors, uint32_t co
         return rc;
     };
     const uint32_t esz = dtype == EDGC_F32 ? 4 : 2;
+    CopyList copies{ctx};
     for (uint32_t i = 0; i < count; ++i) {
         const edgc_tensor& d = tensors[i];
         if (kind[i] == 1) {                      // sent as it stands: hand the gradient on
             if (with_out)
-                if (int rc = launch_copy_rows(ctx, d.grad, d.ld, d.grad_out, d.ld_out, d.m, d.n, esz, st)) return rc;
+                if (int rc = copies.add(d.grad, d.ld, d.grad_out, d.ld_out, d.m, d.n, esz, st)) return rc;
             continue;
         }
         TensorArgs& t = g.t[g.count];
@@ -630,6 +631,7 @@ int decompress_batch_impl(edgc_ctx* ctx, const edgc_tensor* tensors, uint32_t co
         if (++g.count == kMaxGroup)
             if (int rc = flush()) return rc;
     }
+    if (int rc = copies.flush(st)) return rc;
     return flush();
 }
 

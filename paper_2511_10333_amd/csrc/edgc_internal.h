@@ -261,8 +261,27 @@ int launch_init_q(edgc_ctx* ctx, float* Q, uint32_t n, uint32_t ldq, uint32_t c0
 int launch_compress(edgc_ctx* ctx, Group& g, const TensorScratch* cap, edgc_dtype dt,
                     uint32_t power_iters, hipStream_t st, int phase = 0);
 int launch_decompress(edgc_ctx* ctx, Group& g, edgc_dtype dt, hipStream_t st);
-int launch_copy_rows(edgc_ctx* ctx, const void* src, uint64_t ld_src, void* dst, uint64_t ld_dst,
-                     uint32_t m, uint32_t n, uint32_t elem_bytes, hipStream_t st);
+
+// Copies of tensors that are sent as they stand, collected and launched together (compress.hip).
+constexpr uint32_t kMaxCopies = 32, kCopyUnits = 1024;      // tensors per launch; units per block
+struct CopyArgs {
+    const unsigned char* src;
+    unsigned char* dst;
+    uint64_t row_bytes, ld_src, ld_dst;     // bytes
+    uint32_t m, unit, first;                // rows; bytes per access; first block
+};
+struct CopyGroup {
+    uint32_t count;
+    CopyArgs t[kMaxCopies];
+};
+struct CopyList {
+    edgc_ctx* ctx;
+    CopyGroup g{};
+    uint64_t blocks = 0;
+    int add(const void* src, uint64_t ld_src, void* dst, uint64_t ld_dst, uint32_t m, uint32_t n, uint32_t elem_bytes,
+            hipStream_t st);                // strides in elements
+    int flush(hipStream_t st);
+};
 int prepare_compress_kernels(edgc_ctx* ctx);
 int prepare_entropy_kernels(edgc_ctx* ctx);
 size_t compress_part_elems(uint64_t max_rows, uint64_t max_cols, uint32_t max_rank, int num_cu);

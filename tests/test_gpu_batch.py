@@ -306,6 +306,36 @@ def test_stage_entropy_over_many_short_and_ragged_buffers(dtype, stride, chunk, 
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("count", [1, 32, 33])
+def test_tensors_sent_as_they_stand_are_copied_whole_and_nothing_else(dtype, count):
+    """Vectors and matrices too small to compress, at every alignment and row stride the copy distinguishes, up to one
+    more than one launch takes: each reconstruction is the gradient, and nothing around it is written."""
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    shapes = [(768,), (1,), (3071,), (16384 + 3,), (5, 7), (6, 200), (40000, 1), (3, 24), (9, 16)]
+    g = torch.Generator(device="cuda").manual_seed(count)
+    ts, outs, pads = [], [], []
+    for i in range(count):
+        s = shapes[i % len(shapes)]
+        off, extra = [0, 1, 2, 3, 4, 8][i % 6], [0, 0, 1, 8][i % 4] if len(s) == 2 else 0
+        rows, cols = s if len(s) == 2 else (1, s[0])
+        def view(fill):
+            buf = torch.full((off + rows * (cols + extra) + 8,), fill, device="cuda", dtype=tdt)
+            v = buf[off:off + rows * (cols + extra)].view(rows, cols + extra)[:, :cols]
+            return buf, (v if len(s) == 2 else v[0])
+        _, grad = view(0.0)
+        grad.copy_(torch.randn(grad.shape, generator=g, device="cuda"))
+        buf, out = view(7.0)
+        ts.append(edgc.Tensor(grad, out)); outs.append(out); pads.append(buf)
+    c = edgc.Context(0, max_bins=16, max_rank=128, max_rows=64, max_cols=64)
+    c.reserve_batch([tuple(t.grad.shape) if t.grad.dim() == 2 else (1, t.grad.numel()) for t in ts])
+    c.decompress_batch(ts, 128)
+    for t, out, buf in zip(ts, outs, pads):
+        assert torch.equal(out, t.grad)
+        written = int((buf != 7.0).sum())
+        assert written == int((t.grad != 7.0).sum())
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_stage_entropy_large_union_sample(dtype):
     """A union sample large enough for the launch shapes of large samples (one block of 1024 threads
     per compute unit, whole-item rounds with the next loads in flight) over several buffers of
