@@ -348,6 +348,13 @@ __global__ __launch_bounds__(256) void k_reduce_gram(const Group grp, uint32_t R
             const uint32_t row = min(row0 + i, m - 1);       // rows past the end are loaded but not used
             v[it] = make_float4(0.f, 0.f, 0.f, 0.f);
             src[it] = part + static_cast<size_t>(row) * RP + c4;
+            if (S == 0 && static_cast<uint32_t>(c4) < r) {   // P as the caller holds it, columns from r on masked
+                const float4 x = *reinterpret_cast<const float4*>(P + static_cast<size_t>(row) * ldp + c4);
+                v[it].x = x.x;
+                if (static_cast<uint32_t>(c4) + 1 < r) v[it].y = x.y;
+                if (static_cast<uint32_t>(c4) + 2 < r) v[it].z = x.z;
+                if (static_cast<uint32_t>(c4) + 3 < r) v[it].w = x.w;
+            }
         }
         constexpr int DEP = T16 >= 4 ? 2 : 4;            // splits per round
         uint32_t sp = 0;
@@ -377,7 +384,7 @@ __global__ __launch_bounds__(256) void k_reduce_gram(const Group grp, uint32_t R
             const int idx = tid + 256 * it;
             const int i = idx / (CW / 4), c4 = (idx % (CW / 4)) * 4;
             const uint32_t row = row0 + i;
-            if (row < m) {
+            if (row < m && S != 0) {
                 // partial columns >= r are exact zeros (the Q tile is masked in the P-pass)
                 float* dst = P + static_cast<size_t>(row) * ldp + c4;
                 if (static_cast<uint32_t>(c4) + 4 <= r) {
@@ -387,7 +394,7 @@ __global__ __launch_bounds__(256) void k_reduce_gram(const Group grp, uint32_t R
                     if (static_cast<uint32_t>(c4) + 1 < r) dst[1] = v[it].y;
                     if (static_cast<uint32_t>(c4) + 2 < r) dst[2] = v[it].z;
                 }
-            } else {
+            } else if (row >= m) {
                 v[it] = make_float4(0.f, 0.f, 0.f, 0.f);
             }
             *reinterpret_cast<float4*>(Ps + i * LD + c4) = v[it];
@@ -416,23 +423,6 @@ __global__ __launch_bounds__(256) void k_reduce_gram(const Group grp, uint32_t R
             for (int v = 0; v < 4; ++v) out[((lane >> 4) + 4 * v) * 16 + (lane & 15)] = acc[q][v];
         }
     }
-}
-
-// The factor P as the caller holds it (m x ldp) in the layout of ONE column split of the
-// P-pass, [row][RP] with zeros from column r on: what the orthonormalisation starts from when
-// P comes from outside (the second phase of a split call: P after an exchange between ranks).
-__global__ __launch_bounds__(256) void k_p_to_part(const Group grp, uint32_t RP)
-{
-    const TensorArgs& ta = grp.t[locate(grp, blockIdx.x)];
-    const uint32_t q4 = RP / 4;
-    const uint64_t i = static_cast<uint64_t>(blockIdx.x - ta.first) * 256 + threadIdx.x;
-    if (i >= static_cast<uint64_t>(ta.m) * q4) return;
-    const uint32_t row = static_cast<uint32_t>(i / q4), c4 = static_cast<uint32_t>(i % q4) * 4;
-    const float* src = ta.P + static_cast<size_t>(row) * ta.ldp + c4;
-    float v[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = (c4 + e < grp.r) ? src[e] : 0.0f;
-    *reinterpret_cast<float4*>(ta.part + static_cast<size_t>(row) * RP + c4) = make_float4(v[0], v[1], v[2], v[3]);
 }
 
 // out[e] = sum over blocks of gp[b][e], in block order within each of four interleaved
@@ -1138,13 +1128,14 @@ __global__ __launch_bounds__(256, (NP == 2 && RT == 4) ? 2 : 1) void k_pass_q(co
             }
 }
 
-// Q = sum of the row-split partials, in split order (four independent loads in flight)
-__global__ __launch_bounds__(256) void k_reduce_q(const Group grp, uint32_t RP)
+// Q = sum of the row-split partials (or, of_p, P = sum of the column-split ones: the first phase of a split call,
+// which needs no Gram matrix), in split order, four independent loads in flight
+__global__ __launch_bounds__(256) void k_reduce_q(const Group grp, uint32_t RP, int of_p)
 {
     const TensorArgs& ta = grp.t[locate(grp, blockIdx.x)];
     const float* __restrict__ part = ta.part;
-    float* __restrict__ Q = ta.Q;
-    const uint32_t S = ta.sq, n = ta.n, r = grp.r, ldq = ta.ldq;
+    float* __restrict__ Q = of_p ? ta.P : ta.Q;
+    const uint32_t S = of_p ? ta.sp : ta.sq, n = of_p ? ta.m : ta.n, r = grp.r, ldq = of_p ? ta.ldp : ta.ldq;
     // one thread per four adjacent factor columns of one row of Q
     const uint32_t q4 = RP / 4;
     const uint64_t t = static_cast<uint64_t>(blockIdx.x - ta.first) * 256 + threadIdx.x;
@@ -2359,11 +2350,13 @@ static int run_pass_p(edgc_ctx* ctx, Group& g, const TensorScratch* cap, bool wi
     return EDGC_OK;
 }
 
-// sums_only: stop after P = sum of the partials (the first phase of a split call)
+// from_p: P is in the caller's buffer and not in partials (the second phase of a split call)
 template <int NP>
 static int run_orthonormalise(edgc_ctx* ctx, Group& g, const TensorScratch* cap, hipStream_t st,
-                              bool sums_only = false)
+                              bool from_p = false)
 {
+    if (from_p)
+        for (uint32_t i = 0; i < g.count; ++i) g.t[i].sp = 0;
     const uint32_t r = g.r;
     const uint32_t RP = rank_tiles(r) * 32;
     const uint32_t t16 = gram_tiles(r);
@@ -2399,7 +2392,6 @@ static int run_orthonormalise(edgc_ctx* ctx, Group& g, const TensorScratch* cap,
         }
     }
     EDGC_HIP_TRY(ctx, hipGetLastError());
-    if (sums_only) return EDGC_OK;
 
     // Gram = sum of the per-block tiles; the Cholesky block only sums a single tile itself
     blocks = 0;
@@ -2536,7 +2528,7 @@ static int run_pass_q(edgc_ctx* ctx, Group& g, const TensorScratch* cap, hipStre
         blocks += cdiv(static_cast<uint64_t>(t.n) * (RP / 4), 256);
         bytes += 4.0 * t.n * g.r * (t.sq + 1);
     }
-    EDGC_LAUNCH(ctx, st, KID_REDUCE_Q, bytes, 0.0, k_reduce_q<<<blocks, 256, 0, st>>>(g, RP));
+    EDGC_LAUNCH(ctx, st, KID_REDUCE_Q, bytes, 0.0, k_reduce_q<<<blocks, 256, 0, st>>>(g, RP, 0));
     EDGC_HIP_TRY(ctx, hipGetLastError());
     return EDGC_OK;
 }
@@ -2553,22 +2545,21 @@ static int compress_impl(edgc_ctx* ctx, Group& g, const TensorScratch* cap, uint
     if (phase == 1) {
         int rc = run_pass_p<NP, RT>(ctx, g, cap, true, st);
         if (rc != EDGC_OK) return rc;
-        return run_orthonormalise<NP>(ctx, g, cap, st, true);
-    }
-    if (phase == 2) {
         constexpr uint32_t RP = RT * 32;
         uint32_t blocks = 0;
+        double bytes = 0.0;
         for (uint32_t i = 0; i < g.count; ++i) {
             TensorArgs& t = g.t[i];
-            if (cap[i].part_elems < static_cast<uint64_t>(t.m) * RP)
-                return fail(ctx, EDGC_EINVAL, "partial-factor scratch too small for this shape");
-            t.sp = 1;
             t.first = blocks;
             blocks += cdiv(static_cast<uint64_t>(t.m) * (RP / 4), 256);
+            bytes += 4.0 * t.m * g.r * (t.sp + 1);
         }
-        k_p_to_part<<<blocks, 256, 0, st>>>(g, RP);
+        EDGC_LAUNCH(ctx, st, KID_REDUCE_Q, bytes, 0.0, k_reduce_q<<<blocks, 256, 0, st>>>(g, RP, 1));
         EDGC_HIP_TRY(ctx, hipGetLastError());
-        int rc = run_orthonormalise<NP>(ctx, g, cap, st);
+        return EDGC_OK;
+    }
+    if (phase == 2) {
+        int rc = run_orthonormalise<NP>(ctx, g, cap, st, true);
         if (rc != EDGC_OK) return rc;
         return run_pass_q<NP, RT, 2>(ctx, g, cap, st);
     }
