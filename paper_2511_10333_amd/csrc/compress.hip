@@ -178,12 +178,8 @@ __global__ __launch_bounds__(256) void k_pass_p(const Group grp)
                 if (G) ld_stream4(G + static_cast<uint64_t>(row) * ldg + col, g);
                 if (!e_zero) {
                     const float* pe = E + static_cast<uint64_t>(row) * n + col;
-                    if (grp.stream) {
-                        ld_stream4(pe, e);
-                    } else {                                  // the residual may still be cached: keep it so
-                        const float4 q4 = *reinterpret_cast<const float4*>(pe);
-                        e[0] = q4.x; e[1] = q4.y; e[2] = q4.z; e[3] = q4.w;
-                    }
+                    const float4 q4 = *reinterpret_cast<const float4*>(pe);
+                    e[0] = q4.x; e[1] = q4.y; e[2] = q4.z; e[3] = q4.w;
                 }
             } else {
                 load_grad4<NP, VECOK>(G, ldg, row, col, m, k_end, g);
@@ -1530,13 +1526,8 @@ __global__ __launch_bounds__(256, 2) void k_pass_p_deferred(const Group grp)
                     gv[B][v][1] = 0.0f;                  // that nothing here waits for the load
                 }
                 if (!e_zero) {
-                    if (grp.stream) {
-                        const vf2 x = __builtin_nontemporal_load(reinterpret_cast<const vf2*>(pd));
-                        dv[B][v][0] = x.x; dv[B][v][1] = x.y;
-                    } else {
-                        const float2 x = *reinterpret_cast<const float2*>(pd);
-                        dv[B][v][0] = x.x; dv[B][v][1] = x.y;
-                    }
+                    const float2 x = *reinterpret_cast<const float2*>(pd);
+                    dv[B][v][0] = x.x; dv[B][v][1] = x.y;
                 }
             } else {
                 const uint32_t row = rowu + 4 * g, col = col0 + 2 * jl;
@@ -1686,7 +1677,7 @@ __global__ __launch_bounds__(256, 2) void k_pass_p_deferred(const Group grp)
     // with a residual to add: every load is unconditional, so the compiler can count them and the
     // wait for the Q rows at the top of a stage leaves the G / D_prev loads behind them in flight
     // (with loads under conditions it waits for everything there).
-#define EDGC_DEFERRED_STAGE_FAST(ST, STREAM)                                                              \
+#define EDGC_DEFERRED_STAGE_FAST(ST)                                                                      \
     {                                                                                                     \
         __syncthreads();                                                                                  \
         stage_q();                                                                                        \
@@ -1694,7 +1685,7 @@ __global__ __launch_bounds__(256, 2) void k_pass_p_deferred(const Group grp)
         fetch_q_fast((ST) + 1);                                                                           \
         EDGC_DEFERRED_M_HAT()                                                                             \
         EDGC_DEFERRED_COMBINE(ST, 0, true)                                                                \
-        fetch_dg_fast((ST) + 1, std::integral_constant<bool, STREAM>{});                                  \
+        fetch_dg_fast((ST) + 1);                                                                          \
         __syncthreads();                                                                                  \
         EDGC_DEFERRED_P_PRODUCT()                                                                         \
     }
@@ -1713,8 +1704,7 @@ __global__ __launch_bounds__(256, 2) void k_pass_p_deferred(const Group grp)
             }
         }
     };
-    auto fetch_dg_fast = [&](uint32_t st, auto stream_tag) __attribute__((always_inline)) {
-        constexpr bool STREAM = decltype(stream_tag)::value;
+    auto fetch_dg_fast = [&](uint32_t st) __attribute__((always_inline)) {
         const uint32_t col0 = k_begin + st * 64;
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
@@ -1728,13 +1718,8 @@ __global__ __launch_bounds__(256, 2) void k_pass_p_deferred(const Group grp)
                 gv[0][v][0] = __uint_as_float(__builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(pg)));
                 gv[0][v][1] = 0.0f;
             }
-            if constexpr (STREAM) {
-                const vf2 x = __builtin_nontemporal_load(reinterpret_cast<const vf2*>(pd));
-                dv[0][v][0] = x.x; dv[0][v][1] = x.y;
-            } else {
-                const float2 x = *reinterpret_cast<const float2*>(pd);
-                dv[0][v][0] = x.x; dv[0][v][1] = x.y;
-            }
+            const float2 x = *reinterpret_cast<const float2*>(pd);
+            dv[0][v][0] = x.x; dv[0][v][1] = x.y;
         }
     };
 
@@ -1747,13 +1732,8 @@ __global__ __launch_bounds__(256, 2) void k_pass_p_deferred(const Group grp)
     if (FAST && n_fast) {
         if constexpr (FAST) {
             fetch_q_fast(0);
-            if (grp.stream) {
-                fetch_dg_fast(0, T{});
-                for (; st < n_fast; ++st) EDGC_DEFERRED_STAGE_FAST(st, true)
-            } else {
-                fetch_dg_fast(0, F{});
-                for (; st < n_fast; ++st) EDGC_DEFERRED_STAGE_FAST(st, false)
-            }
+            fetch_dg_fast(0);
+            for (; st < n_fast; ++st) EDGC_DEFERRED_STAGE_FAST(st)
         }
     } else {
         if (n_st) fetch_q(0);
@@ -1879,7 +1859,7 @@ __global__ __launch_bounds__(256, 2) void k_pass_p_deferred_narrow(const Group g
                 const float* pd = E + (static_cast<uint64_t>(rowu) * n + col0) + off_d;
                 if constexpr (NP == 2) gv[v] = __builtin_nontemporal_load(pg);
                 else gv[v] = __uint_as_float(static_cast<uint32_t>(__builtin_nontemporal_load(pg)));   // widened where used
-                if (!e_zero) dv[v] = grp.stream ? __builtin_nontemporal_load(pd) : *pd;
+                if (!e_zero) dv[v] = *pd;
             } else {
                 const uint32_t row = rowu + 4 * g, col = col0 + jl;
                 const bool in = row < m && col < k_end;
@@ -1975,8 +1955,7 @@ __global__ __launch_bounds__(256, 2) void k_pass_p_deferred_narrow(const Group g
             }
         }
     };
-    auto fetch_dg_fast = [&](uint32_t st, auto stream_tag) __attribute__((always_inline)) {
-        constexpr bool STREAM = decltype(stream_tag)::value;
+    auto fetch_dg_fast = [&](uint32_t st) __attribute__((always_inline)) {
         const uint32_t col0 = k_begin + st * 32;
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
@@ -1985,7 +1964,7 @@ __global__ __launch_bounds__(256, 2) void k_pass_p_deferred_narrow(const Group g
             const float* pd = E + (static_cast<uint64_t>(rowu) * n + col0) + off_d;
             if constexpr (NP == 2) gv[v] = __builtin_nontemporal_load(pg);
             else gv[v] = __uint_as_float(static_cast<uint32_t>(__builtin_nontemporal_load(pg)));
-            dv[v] = STREAM ? __builtin_nontemporal_load(pd) : *pd;
+            dv[v] = *pd;
         }
     };
 #define EDGC_NARROW_M_HAT()                                                                               \
@@ -2013,7 +1992,7 @@ __global__ __launch_bounds__(256, 2) void k_pass_p_deferred_narrow(const Group g
                 accp[ct] = mma<NP>(af, b, accp[ct]);                                                      \
             }                                                                                             \
         }
-#define EDGC_NARROW_STAGE_FAST(ST, STREAM)                                                                \
+#define EDGC_NARROW_STAGE_FAST(ST)                                                                        \
     {                                                                                                     \
         __syncthreads();                                                                                  \
         stage_q();                                                                                        \
@@ -2022,7 +2001,7 @@ __global__ __launch_bounds__(256, 2) void k_pass_p_deferred_narrow(const Group g
         EDGC_NARROW_M_HAT()                                                                               \
         if (e_zero) { _Pragma("unroll") for (int v = 0; v < 16; ++v) dv[v] = 0.0f; }                      \
         EDGC_NARROW_COMBINE(ST, true)                                                                     \
-        fetch_dg_fast((ST) + 1, std::integral_constant<bool, STREAM>{});                                  \
+        fetch_dg_fast((ST) + 1);                                                                          \
         __syncthreads();                                                                                  \
         EDGC_NARROW_P_PRODUCT()                                                                           \
     }
@@ -2036,13 +2015,8 @@ __global__ __launch_bounds__(256, 2) void k_pass_p_deferred_narrow(const Group g
     if (FAST && n_fast) {
         if constexpr (FAST) {
             fetch_q_fast(0);
-            if (grp.stream) {
-                fetch_dg_fast(0, T{});
-                for (; st < n_fast; ++st) EDGC_NARROW_STAGE_FAST(st, true)
-            } else {
-                fetch_dg_fast(0, F{});
-                for (; st < n_fast; ++st) EDGC_NARROW_STAGE_FAST(st, false)
-            }
+            fetch_dg_fast(0);
+            for (; st < n_fast; ++st) EDGC_NARROW_STAGE_FAST(st)
         }
     } else if (n_st) {
         fetch_q(0);
@@ -2233,17 +2207,19 @@ int CopyList::flush(hipStream_t st)
 
 // The blocks a pass aims at are shared among the tensors of a group in proportion to their
 // size (at least one each).
-// A group whose residual (= D) takes more than half of the 256 MB last-level cache streams it
-// (measured on 400 MB groups: the Q-pass reads D at 4.7 instead of 3.7 TB/s with non-temporal
-// loads); a smaller one is left cached: the decompress then finds D, and the next step's P-pass
-// E_new, largely still there (bench workload: 0.262 instead of 0.283 ms per step, together with
-// the non-temporal store of the reconstruction).
+// Whether the Q-pass reads D with non-temporal loads: D is not read again before the next step in the deferred form, and
+// in the stored form the decompress finds nothing of a D that exceeds the 256 MB last-level cache.  Per pass over cold
+// inputs, cached / streamed: deferred, hidden-2048 fp32 block (201 MB) 253 / 236 us, hidden-3584 shard (154 MB) 214 / 200,
+// hidden-1536 (113 MB) 200 / 195, two hidden-768 blocks (57 MB) 109 / 112; stored, 50257 x 1024 (206 MB) 334 / 339,
+// hidden-2048 at rank 64 (201 MB) 356 / 364, hidden-4096 fp32 block (805 MB) 1221 / 1186.
+// The P-pass reads the residual with ordinary loads in every case (non-temporal ones: hidden-2048 246 against 236 us,
+// the shard 210 against 200, 50257 x 1024 349 against 339, hidden-4096 1197 against 1186).
 static uint32_t group_streams(const edgc_ctx* ctx, const Group& g)
 {
     if (ctx->tune_stream >= 0) return ctx->tune_stream != 0 ? 1u : 0u;
     double bytes = 0.0;
     for (uint32_t i = 0; i < g.count; ++i) bytes += 4.0 * g.t[i].m * g.t[i].n;
-    return bytes > 128.0 * 1024 * 1024 ? 1u : 0u;
+    return bytes >= (g.defer ? 96.0 : 256.0) * 1024 * 1024 ? 1u : 0u;
 }
 
 static void share_targets(const Group& g, uint32_t target, uint32_t (&out)[kMaxGroup])
@@ -2254,6 +2230,26 @@ static void share_targets(const Group& g, uint32_t target, uint32_t (&out)[kMaxG
         const double f = static_cast<double>(g.t[i].m) * g.t[i].n / total;
         out[i] = std::max<uint32_t>(1u, static_cast<uint32_t>(f * target + 0.5));
     }
+}
+
+// How a pass cuts the tensors of a group into blocks that take equally long: tensor i is `across[i]` blocks wide, and
+// its `along[i]` stages are cut into runs of the returned number of stages, the smallest with which the launch has at
+// most `target` blocks (`blocks`: how many it has).
+static uint32_t uniform_step(uint32_t count, const uint32_t* across, const uint32_t* along, uint32_t target, uint64_t& blocks)
+{
+    uint32_t lo = 1, hi = 1;
+    for (uint32_t i = 0; i < count; ++i) hi = std::max(hi, along[i]);
+    auto count_blocks = [&](uint32_t step) {
+        uint64_t b = 0;
+        for (uint32_t i = 0; i < count; ++i) b += static_cast<uint64_t>(across[i]) * cdiv(along[i], step);
+        return b;
+    };
+    while (lo < hi) {
+        const uint32_t mid = lo + (hi - lo) / 2;
+        if (count_blocks(mid) <= target) hi = mid; else lo = mid + 1;
+    }
+    blocks = count_blocks(lo);
+    return lo;
 }
 
 template <int NP, int RT>
@@ -2277,22 +2273,53 @@ static int run_pass_p(edgc_ctx* ctx, Group& g, const TensorScratch* cap, bool wi
     // block, whose residual streams from HBM; 89 against 86 us on the hidden-2048 block, which the last-level cache
     // holds: there the general kernel stays)
     const bool fp32_wide = NP == 2 && RT == 4;
+    double d_all = 0.0;
+    for (uint32_t i = 0; i < g.count; ++i) d_all += 4.0 * g.t[i].m * g.t[i].n;
+    const bool big_d = d_all > 128.0 * 1024 * 1024;
     const bool use_full = with_grad && ctx->tune_full != 0 && pass_p_full_applies(g, DT, RT, pwaves) &&
-                          (!fp32_wide || g.stream || ctx->tune_full > 0);
+                          (!fp32_wide || big_d || ctx->tune_full > 0);
     const bool use_narrow = with_grad && g.defer && RT == 4;
     const bool use_wide = with_grad && RT <= 2 && (g.defer || NP == 1);
     const uint32_t per_cu = (use_narrow && !use_full) ? 2u : (use_full && pwaves == 8 ? 2u : 4u);
     const uint32_t rows_per_block = use_full ? 32u * pwaves : 128u;
-    const uint32_t target = static_cast<uint32_t>(ctx->num_cu) * (ctx->tune_p ? ctx->tune_p : per_cu);
+    const uint32_t cu = static_cast<uint32_t>(ctx->num_cu);
     uint32_t tgt[kMaxGroup];
-    share_targets(g, target, tgt);
+    share_targets(g, cu * (ctx->tune_p ? ctx->tune_p : per_cu), tgt);
+    // Blocks of equal length, a few per CU: fewer column splits mean fewer partials to write and sum, more blocks even out
+    // the load.  From two per CU on (four where the residual takes more than 192 MB and blocks are of four waves), until no
+    // CU would have many fewer blocks than others.  Per pass, four per CU in proportion to size / equal length from two on /
+    // from four on: two hidden-768 blocks 114.6 / 109.6 / 114.7 us, hidden-1536 block at rank 64 202 / 192 / 202, three odd
+    // matrices 149 / 143 / 148; hidden-4096 fp32 block at rank 64, stored 1214 / 1264 / 1184, deferred 935 / 1006 / 895;
+    // 50257 x 1024 (393 blocks across): two per CU 375, four 345, five 331.
+    uint32_t step = 0;
+    if (!ctx->tune_p) {
+        uint32_t across[kMaxGroup], along[kMaxGroup];
+        double d_bytes = 0.0;
+        for (uint32_t i = 0; i < g.count; ++i) {
+            across[i] = cdiv(g.t[i].m, rows_per_block);
+            along[i] = cdiv(g.t[i].n, BK);
+            d_bytes += 4.0 * g.t[i].m * g.t[i].n;
+        }
+        // what a plan keeps busy of the CUs' time: all blocks of a large group take `step` stages; in a small one it is the
+        // count of blocks per CU that matters
+        const bool large = rows_per_block == 128 && d_bytes > 192.0 * 1024 * 1024;
+        double total = 0.0, best = 0.0;
+        for (uint32_t i = 0; i < g.count; ++i) total += static_cast<double>(across[i]) * along[i];
+        for (uint32_t k = large ? 4 : 2; k <= 8 && best < 0.8; ++k) {
+            uint64_t nb = 0;
+            const uint32_t s = uniform_step(g.count, across, along, cu * k, nb);
+            const double slots = static_cast<double>(cdiv(nb, cu)) * cu;
+            const double eff = large ? total / (s * slots) : static_cast<double>(nb) / slots;
+            if (eff > best) { best = eff; step = s; }
+        }
+    }
     bool vec = true;
     uint32_t blocks = 0;
     double bytes = 0.0, flops = 0.0;
     for (uint32_t i = 0; i < g.count; ++i) {
         TensorArgs& t = g.t[i];
         const uint32_t RB = cdiv(t.m, rows_per_block), ksteps = cdiv(t.n, BK);
-        uint32_t S = std::max(1u, std::min(ksteps, tgt[i] / RB));
+        uint32_t S = step ? cdiv(ksteps, step) : std::max(1u, std::min(ksteps, tgt[i] / RB));
         const uint64_t lim = cap[i].part_elems / (static_cast<uint64_t>(t.m) * RP);
         if (lim == 0) return fail(ctx, EDGC_EINVAL, "partial-factor scratch too small for this shape");
         S = static_cast<uint32_t>(std::min<uint64_t>(S, lim));
@@ -2483,7 +2510,11 @@ static int run_pass_q(edgc_ctx* ctx, Group& g, const TensorScratch* cap, hipStre
     // with one row split) aim at three blocks per CU: 594 against 649 us
     uint64_t d_bytes = 0;
     for (uint32_t i = 0; i < g.count; ++i) d_bytes += 4ull * g.t[i].m * g.t[i].n;
-    const uint32_t per_cu = ctx->tune_q ? ctx->tune_q : (qwaves == 8 ? 1u : (d_bytes >= (1ull << 30) ? 3u : 2u));
+    // one block per CU where D is small and the partials of more row splits weigh: 4096 x 4096 fp32 at rank 32 (two
+    // iterations) 202 against 210 us, three odd matrices of 14 M elements 125 against 127, hidden-2048 block (201 MB) 237
+    // against 232
+    const uint32_t per_cu = ctx->tune_q ? ctx->tune_q
+                          : ((qwaves == 8 || d_bytes <= (80ull << 20)) ? 1u : (d_bytes >= (1ull << 30) ? 3u : 2u));
     const uint32_t target = static_cast<uint32_t>(ctx->num_cu) * per_cu;
     uint32_t tgt[kMaxGroup];
     share_targets(g, target, tgt);
@@ -2620,6 +2651,11 @@ static int decompress_impl(edgc_ctx* ctx, Group& g, hipStream_t st)
     const uint32_t target = static_cast<uint32_t>(ctx->num_cu) * per_cu;
     uint32_t tgt[kMaxGroup];
     share_targets(g, target, tgt);
+    // Short blocks for the general kernel: many rounds of them keep every CU busy to the end.  Stored form, per pass: hidden-4096
+    // fp32 block at rank 64 with 24 stages per block 1276 us, 8: 1208, 6: 1215, 4: 1199 (the kernel 498 -> 425 us, 5.7 TB/s,
+    // what a plain copy reaches); at rank 16 1229 / 1168 (8) / 1148 (4); 8192 x 8192 at rank 64 with 8 stages 396, 4: 400,
+    // 1: 411; hidden-3072 at rank 128 with 14 stages 866, 7: 844, 5: 862.
+    const uint32_t max_sps = use_full ? ~0u : 8u;
     bool vec = true;
     uint32_t blocks = 0;
     double bytes = 0.0, flops = 0.0;
@@ -2627,7 +2663,7 @@ static int decompress_impl(edgc_ctx* ctx, Group& g, hipStream_t st)
         TensorArgs& t = g.t[i];
         const uint32_t RB = cdiv(t.m, rows_per_block), stages = cdiv(t.n, 64);
         uint32_t JS = std::max(1u, std::min(stages, tgt[i] / RB));
-        const uint32_t sps = cdiv(stages, JS);
+        const uint32_t sps = std::min(cdiv(stages, JS), max_sps);
         JS = cdiv(stages, sps);
         t.d0 = sps;
         t.d1 = JS;

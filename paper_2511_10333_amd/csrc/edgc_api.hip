@@ -528,7 +528,9 @@ int compress_batch_impl(edgc_ctx* ctx, const edgc_tensor* tensors, uint32_t coun
         kind[i] = check_batch_tensor(ctx, tensors[i], i, dtype, r, phase != 2, false);
         if (kind[i] < 0) return kind[i];
     }
-    const int defer = phase == 2 ? 0 : batch_deferred(ctx, tensors, kind);   // the second phase reads D as it stands
+    // the second phase reads D as it stands, whichever form: an exchange between the ranks follows, so that D is treated as
+    // not read again soon
+    const int defer = phase == 2 ? 1 : batch_deferred(ctx, tensors, kind);
     if (defer < 0) return defer;
     EDGC_HIP_TRY(ctx, hipSetDevice(ctx->device));
     hipStream_t st = static_cast<hipStream_t>(hip_stream);

@@ -87,10 +87,7 @@ struct TensorArgs {
 struct Group {
     uint32_t count;
     uint32_t r;             // rank, the same for every tensor of a group
-    uint32_t stream;        // 1: the group's residual is too large to stay in the last-level cache:
-                            //    the Q-pass reads D, and the P-pass E_old, with non-temporal loads.
-                            //    0: both are ordinary loads, so that D is still cached when the
-                            //    decompress reads it again and E_new when the next step's P-pass does
+    uint32_t stream;        // 1: the Q-pass reads D with non-temporal loads (group_streams)
     uint32_t defer;         // 1: deferred subtraction: the residual buffer holds D between steps and the
                             //    next P-pass subtracts M^ = P^ Q^T itself; the decompress only writes M^
     TensorArgs t[kMaxGroup];
@@ -144,7 +141,7 @@ struct edgc_ctx {
     // launch-shape overrides for sweeps (blocks per CU aimed at by the P-pass, Q-pass and
     // decompress); 0 = the built-in choice
     uint32_t tune_p = 0, tune_q = 0, tune_d = 0;
-    int tune_stream = -1;   // -1: by size; 0 / 1: force cached / non-temporal reads of D in the Q-pass
+    int tune_stream = -1;   // -1: by size and form; 0 / 1: force cached / non-temporal reads of D in the Q-pass
     int tune_dfull = -1;    // write-only decompress of whole-tile groups: -1 built-in choice (above rank
                             // 64 the whole-tile kernel, 8 waves per block); 0 the general kernel; 4 / 8
                             // the whole-tile kernel with that many waves per block at every rank

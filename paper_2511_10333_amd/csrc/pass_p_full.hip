@@ -15,15 +15,19 @@
 
 namespace edgc {
 
-template <int NP, int RT, int WAVES>
+template <int NP, int RT, int WAVES, bool SUB>
 constexpr size_t pass_p_full_lds()
 {
-    return static_cast<size_t>(64) * (NP * RT * 32 * 2 + 16) + static_cast<size_t>(RT * 32 + 32 * WAVES) * (NP * 128 + 16);
+    return static_cast<size_t>(SUB ? 64 : 0) * (NP * RT * 32 * 2 + 16) + static_cast<size_t>(RT * 32 + 32 * WAVES) * (NP * 128 + 16);
 }
 
 // WAVES x 32 rows per block share the staged Q tiles (two LDS layouts per stage): eight waves halve that
 // staging work per row.
-template <int NP, int RT, bool STREAM, bool QLATE, int WAVES>
+// SUB = false: the residual buffer holds E itself (the stored form): the same sweep with nothing to subtract, without
+// the first product, its fragments and its LDS tile.  What bounds either form is HBM.  Used
+// for bf16 gradients and up to rank 32 for fp32 (per pass, general kernel / this: hidden-1024 bf16 block 126 / 118 us,
+// hidden-4096 block at rank 16 fp32 1149 / 1126; at rank 64 fp32 1179 / 1182, 8192 x 8192 425 / 430: not there).
+template <int NP, int RT, bool QLATE, int WAVES, bool SUB>
 __global__ __launch_bounds__(64 * WAVES, 2) void k_pass_p_deferred_full(const Group grp)
 {
     const TensorArgs& ta = grp.t[locate(grp, blockIdx.x)];
@@ -45,8 +49,8 @@ __global__ __launch_bounds__(64 * WAVES, 2) void k_pass_p_deferred_full(const Gr
     static_assert(32 * (RP / 4) % NTH == 0, "the Q stage divides evenly among the threads");
     constexpr int PQ = 32 * (RP / 4) / NTH;           // Q-stage items per thread: 2 rows x 4 ranks each
     extern __shared__ __attribute__((aligned(16))) unsigned char plds[];
-    unsigned char* ldsQ = plds;                       // 64 x ROWQ
-    unsigned char* ldsT = ldsQ + 64 * ROWQ;           // RP x ROWB: Q^T
+    unsigned char* ldsQ = plds;                       // 64 x ROWQ (SUB)
+    unsigned char* ldsT = ldsQ + (SUB ? 64 * ROWQ : 0);   // RP x ROWB: Q^T
     unsigned char* ldsA = ldsT + RP * ROWB;           // 32 WAVES x ROWB: D, 32 rows per wave
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -63,9 +67,9 @@ __global__ __launch_bounds__(64 * WAVES, 2) void k_pass_p_deferred_full(const Gr
     const uint32_t off_g = 4u * g * static_cast<uint32_t>(ldg) + 2u * jl;
 
     // A-fragments of P^_prev: row row0 + jl, k = kb*16 + 8g .. +8
-    bf16x8 a[KT][NP];
+    bf16x8 a[SUB ? KT : 1][NP];
 #pragma unroll
-    for (int kb = 0; kb < KT; ++kb) {
+    for (int kb = 0; kb < (SUB ? KT : 0); ++kb) {
         float v[8];
         const uint32_t row = row0 + jl, c0 = kb * 16 + 8 * g;
 #pragma unroll
@@ -121,13 +125,8 @@ __global__ __launch_bounds__(64 * WAVES, 2) void k_pass_p_deferred_full(const Gr
             } else {                                                                                      \
                 gv[v][0] = __uint_as_float(__builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(pg))); \
             }                                                                                             \
-            if constexpr (STREAM) {                                                                       \
-                const vf2 x = __builtin_nontemporal_load(reinterpret_cast<const vf2*>(pd));               \
-                dv[v][0] = x.x; dv[v][1] = x.y;                                                           \
-            } else {                                                                                      \
-                const float2 x = *reinterpret_cast<const float2*>(pd);                                    \
-                dv[v][0] = x.x; dv[v][1] = x.y;                                                           \
-            }                                                                                             \
+            const float2 x = *reinterpret_cast<const float2*>(pd);                                        \
+            dv[v][0] = x.x; dv[v][1] = x.y;                                                               \
         }                                                                                                 \
     }
     // ... into LDS twice: [column][rank] (row 2jp + h at LDS row h*32 + jp, so that a lane of the
@@ -148,7 +147,8 @@ __global__ __launch_bounds__(64 * WAVES, 2) void k_pass_p_deferred_full(const Gr
         _Pragma("unroll") for (int q = 0; q < NP; ++q) {                                                  \
             _Pragma("unroll") for (int h = 0; h < 2; ++h) {                                               \
                 const u32x2 two = {w[h][0][q], w[h][1][q]};                                               \
-                *reinterpret_cast<u32x2*>(ldsQ + (h * 32 + jp) * ROWQ + q * (RP * 2) + c4 * 2) = two;     \
+                if constexpr (SUB)                                                                        \
+                    *reinterpret_cast<u32x2*>(ldsQ + (h * 32 + jp) * ROWQ + q * (RP * 2) + c4 * 2) = two; \
             }                                                                                             \
             _Pragma("unroll") for (int e2 = 0; e2 < 2; ++e2) {                                            \
                 const uint32_t lo = __builtin_amdgcn_perm(w[1][e2][q], w[0][e2][q], 0x05040100u);         \
@@ -169,7 +169,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void k_pass_p_deferred_full(const Gr
         f32x16 acc[2];                                                                                    \
         _Pragma("unroll") for (int ct = 0; ct < 2; ++ct) {                                                \
             _Pragma("unroll") for (int v = 0; v < 16; ++v) acc[ct][v] = 0.0f;                             \
-            _Pragma("unroll") for (int kb = 0; kb < KT; ++kb) {                                           \
+            _Pragma("unroll") for (int kb = 0; kb < (SUB ? KT : 0); ++kb) {                               \
                 bf16x8 b[NP];                                                                             \
                 _Pragma("unroll") for (int p = 0; p < NP; ++p)                                            \
                     b[p] = *reinterpret_cast<const bf16x8*>(ldsQ + (ct * 32 + jl) * ROWQ + p * (RP * 2) + kb * 32 + g * 16); \
@@ -250,7 +250,6 @@ template <int NP>
 static bool group_is_full(const Group& g, uint32_t waves)
 {
     using GT = typename GradElem<NP>::type;
-    if (!g.defer) return false;
     for (uint32_t i = 0; i < g.count; ++i) {
         const TensorArgs& t = g.t[i];
         if (t.e_zero || !t.G) return false;
@@ -264,6 +263,7 @@ static bool group_is_full(const Group& g, uint32_t waves)
 
 bool pass_p_full_applies(const Group& g, edgc_dtype dt, int rt, uint32_t waves)
 {
+    if (!g.defer && dt != EDGC_BF16 && rt > 1) return false;       // (above)
     if (waves != 4 && !(waves == 8 && rt >= 2)) return false;
     if (dt == EDGC_BF16) return group_is_full<1>(g, waves);
     // fp32 gradients above rank 64: eight waves only (138 KB of LDS, one block per CU)
@@ -271,19 +271,23 @@ bool pass_p_full_applies(const Group& g, edgc_dtype dt, int rt, uint32_t waves)
     return group_is_full<2>(g, waves);
 }
 
+template <int NP, int RT, int WAVES, bool SUB>
+static hipError_t launch_full_sub(const Group& g, uint32_t blocks, bool qlate, hipStream_t st)
+{
+    constexpr size_t lds = pass_p_full_lds<NP, RT, WAVES, SUB>();
+    constexpr int NTH = 64 * WAVES;
+    if (qlate) k_pass_p_deferred_full<NP, RT, true, WAVES, SUB><<<blocks, NTH, lds, st>>>(g);
+    else k_pass_p_deferred_full<NP, RT, false, WAVES, SUB><<<blocks, NTH, lds, st>>>(g);
+    return hipGetLastError();
+}
+
 template <int NP, int RT, int WAVES>
 static hipError_t launch_full_w(const Group& g, uint32_t blocks, bool qlate, hipStream_t st)
 {
-    constexpr size_t lds = pass_p_full_lds<NP, RT, WAVES>();
-    constexpr int NTH = 64 * WAVES;
-    if (g.stream) {
-        if (qlate) k_pass_p_deferred_full<NP, RT, true, true, WAVES><<<blocks, NTH, lds, st>>>(g);
-        else k_pass_p_deferred_full<NP, RT, true, false, WAVES><<<blocks, NTH, lds, st>>>(g);
-    } else {
-        if (qlate) k_pass_p_deferred_full<NP, RT, false, true, WAVES><<<blocks, NTH, lds, st>>>(g);
-        else k_pass_p_deferred_full<NP, RT, false, false, WAVES><<<blocks, NTH, lds, st>>>(g);
+    if constexpr (NP == 1 || RT == 1) {
+        if (!g.defer) return launch_full_sub<NP, RT, WAVES, false>(g, blocks, qlate, st);
     }
-    return hipGetLastError();
+    return launch_full_sub<NP, RT, WAVES, true>(g, blocks, qlate, st);
 }
 
 template <int NP, int RT>
@@ -312,20 +316,28 @@ hipError_t launch_pass_p_full(const Group& g, edgc_dtype dt, int rt, uint32_t bl
     }
 }
 
-template <int NP, int RT, int WAVES>
-static hipError_t allow_lds_full()
+template <int NP, int RT, int WAVES, bool SUB>
+static hipError_t allow_lds_sub()
 {
-    constexpr int lds = static_cast<int>(pass_p_full_lds<NP, RT, WAVES>());
+    constexpr int lds = static_cast<int>(pass_p_full_lds<NP, RT, WAVES, SUB>());
     if (lds <= 64 * 1024) return hipSuccess;
-    const void* fns[4] = {reinterpret_cast<const void*>(&k_pass_p_deferred_full<NP, RT, true, true, WAVES>),
-                          reinterpret_cast<const void*>(&k_pass_p_deferred_full<NP, RT, true, false, WAVES>),
-                          reinterpret_cast<const void*>(&k_pass_p_deferred_full<NP, RT, false, true, WAVES>),
-                          reinterpret_cast<const void*>(&k_pass_p_deferred_full<NP, RT, false, false, WAVES>)};
+    const void* fns[2] = {reinterpret_cast<const void*>(&k_pass_p_deferred_full<NP, RT, true, WAVES, SUB>),
+                          reinterpret_cast<const void*>(&k_pass_p_deferred_full<NP, RT, false, WAVES, SUB>)};
     for (const void* f : fns) {
         hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
+}
+
+template <int NP, int RT, int WAVES>
+static hipError_t allow_lds_full()
+{
+    hipError_t e = allow_lds_sub<NP, RT, WAVES, true>();
+    if constexpr (NP == 1 || RT == 1) {
+        if (e == hipSuccess) e = allow_lds_sub<NP, RT, WAVES, false>();
+    }
+    return e;
 }
 
 hipError_t prepare_pass_p_full()
