@@ -464,8 +464,8 @@ __global__ __launch_bounds__(256) void k_gram_sum(const Group grps, uint32_t ne)
 // column that is numerically dependent on the previous ones: it is removed
 // from the factorisation (row and column of X zero), so its P^ column is zero
 // and later columns are not projected on it.
-// `tiles` holds nb sets of tiles (nb > 1 only for a single tile): tile t = (ta <= tb),
-// row-major over the triangle, is [i][j] = W[16 tb + i][16 ta + j].
+// `tiles`: tile t = (ta <= tb), row-major over the triangle, is [i][j] = W[16 tb + i][16 ta + j].
+// One tile, and two in launches of few blocks, every block of k_apply factors itself.
 // ---------------------------------------------------------------------------
 constexpr double kPivotEps = 1e-11;
 constexpr int kCholThreads = 1024;
@@ -621,15 +621,15 @@ __global__ __launch_bounds__(kCholThreads) void k_chol(const Group grp, uint32_t
     const TensorArgs& ta_ = grp.t[blockIdx.x];          // one block per tensor
     const double* __restrict__ tiles = ta_.tiles;
     double* __restrict__ rinv = ta_.rinv;
-    const uint32_t nb = ta_.nb, r = grp.r;
+    const uint32_t r = grp.r;
     extern __shared__ double sm[];
     const int T = static_cast<int>(T16);
     const int RPAD = 16 * T, LDA = RPAD + kCholPad;
     double* A = sm;                                   // [RPAD][LDA]: lower tiles L, upper tiles X^T
     double* Xd = A + RPAD * LDA;                      // [T][16][17]: inverses of the diagonal tiles
     double* wd = Xd + T * 16 * 17;                    // [RPAD] kPivotEps W[c][c]: what the pivot of column c must exceed
-    double* red = wd + RPAD;                          // [kCholThreads] partial sums (single tile only)
-    uint32_t* deadw = reinterpret_cast<uint32_t*>(red + kCholThreads);   // [4]: bit c of the 128 set for a removed column c
+    double* red = wd + RPAD;                          // [16] the diagonal block at hand
+    uint32_t* deadw = reinterpret_cast<uint32_t*>(red + 16);   // [4]: bit c of the 128 set for a removed column c
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     constexpr int NW = kCholThreads / 64;
     const uint32_t ntile = T16 * (T16 + 1) / 2, ne = ntile * 256;
@@ -640,7 +640,7 @@ __global__ __launch_bounds__(kCholThreads) void k_chol(const Group grp, uint32_t
     double wv[kMaxPerThread];
     f64x4 st = {0.0, 0.0, 0.0, 0.0};                  // wavefront 0: the diagonal tile of the step at hand
     if (tid < 4) deadw[tid] = 0u;
-    if (nb == 1) {
+    {
 #pragma unroll
         for (int u = 0; u < kMaxPerThread; ++u) {
             const uint32_t e = tid + u * kCholThreads;
@@ -658,31 +658,6 @@ __global__ __launch_bounds__(kCholThreads) void k_chol(const Group grp, uint32_t
             wd[j] = kPivotEps * tiles[ti * 256 + (j & 15) * 17];
         }
     }
-    if (nb > 1) {                                     // ne == 256: interleaved groups of blocks per entry
-        constexpr uint32_t NG = kCholThreads / 256;
-        const uint32_t e = tid & 255, grp = tid >> 8;
-        double sacc = 0.0;
-        uint32_t b = grp;
-        for (; b + 7 * NG < nb; b += 8 * NG) {
-            double xx[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) xx[u] = tiles[static_cast<size_t>(b + NG * u) * ne + e];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) sacc += xx[u];
-        }
-        for (; b < nb; b += NG) sacc += tiles[static_cast<size_t>(b) * ne + e];
-        red[tid] = sacc;
-        __syncthreads();
-        if (tid < 256) {
-            double t = red[tid];
-#pragma unroll
-            for (uint32_t g2 = 1; g2 < NG; ++g2) t += red[tid + 256 * g2];
-            red[tid] = t;
-        }
-        __syncthreads();
-        if (tid < 16) wd[tid] = kPivotEps * red[tid * 17];
-        wv[0] = red[tid & 255];
-    }
     // Entry tid + u * kCholThreads sits in tile (wave / 4) + 4u, the same for a whole wavefront: the
     // tile's place (ta <= tb) is kept in scalar registers and advanced four tiles at a time.  A tile
     // holds [i][j] = W[16 tb + i][16 ta + j]: consecutive lanes write consecutive words, one LDS
@@ -694,22 +669,10 @@ __global__ __launch_bounds__(kCholThreads) void k_chol(const Group grp, uint32_t
 #pragma unroll
         for (int u = 0; u < kMaxPerThread; ++u) {
             while (tb >= T && ta < T) { ++ta; tb = tb - T + ta; }   // row ta of the triangle has tiles tb = ta .. T-1
-            if (ta < T && (nb == 1 || u == 0)) A[(16 * tb + i) * LDA + 16 * ta + j] = wv[u];
+            if (ta < T) A[(16 * tb + i) * LDA + 16 * ta + j] = wv[u];
             tb += 4;
         }
     }
-    if (nb > 1) {
-        // a single tile summed in LDS: wavefront 0 takes it from there (its lower triangle mirrored)
-        __syncthreads();
-        if (wave == 0) {
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int a = lq + 4 * v, b = lr;                 // element [a][b]
-                st[v] = A[max(a, b) * LDA + min(a, b)];
-            }
-        }
-    }
-
     // ---- blocked right-looking Cholesky with the diagonal tile one step ahead ----
     // The serial part is the chain of diagonal tiles, so wavefront 0 does nothing else: it factors
     // tile (p, p), solves the one panel tile (p+1, p) below it, applies that tile's update to
@@ -852,12 +815,103 @@ __global__ __launch_bounds__(kCholThreads) void k_chol(const Group grp, uint32_t
     }
 }
 
+// The wave's own LDS writes are seen by all its lanes.
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// R^-1 of one or two 16-wide tiles by one wavefront, the same steps in the same order as k_chol: W[t] and Rs[t] are the
+// tiles in its order, in LDS; `bc`, `wd` and `Xd` are scratch for 16, 16 T and 272 T doubles.
+template <int T>
+__device__ __forceinline__ void small_factor(const double* W, double* Rs, double* bc, double* wd, double* Xd, uint32_t r,
+                                             int lane)
+{
+    static_assert(T == 1 || T == 2, "one or two tiles a side");
+    const int lr = lane & 15, lq = lane >> 4;
+    if (lane < 16 * T) wd[lane] = kPivotEps * W[(lane < 16 ? 0 : 2 * 256) + (lane & 15) * 17];
+    wave_sync();
+    auto diagonal = [&](const double* w, f64x4& st) {            // symmetric from its lower triangle
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int a = lq + 4 * v, b = lr;
+            st[v] = w[max(a, b) * 16 + min(a, b)];
+        }
+    };
+    auto store_diagonal = [&](const f64x4& x, int p, uint32_t dead, double* out) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int c = lq + 4 * v;
+            Xd[(p * 16 + c) * 17 + lr] = x[v];
+            const bool live = lr <= c && static_cast<uint32_t>(16 * p + c) < r && !((dead >> lr) & 1u) && !((dead >> c) & 1u);
+            out[lr * 16 + c] = live ? x[v] : 0.0;
+        }
+    };
+    f64x4 st, x;
+    diagonal(W, st);
+    const uint32_t dead0 = chol16_factor_invert(st, x, lane, bc, wd);
+    store_diagonal(x, 0, dead0, Rs);
+    if constexpr (T == 2) {
+        wave_sync();
+        const double* C = W + 256;
+        f64x4 lt = {0.0, 0.0, 0.0, 0.0}, lt2 = {0.0, 0.0, 0.0, 0.0};     // two chains: see chol_inverse_terms
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {                                  // L^T = X_00 C^T
+            const double av = Xd[lr * 17 + 4 * kk + lq], bv = C[lr * 16 + 4 * kk + lq];
+            if (kk & 1) lt2 = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, lt2, 0, 0, 0);
+            else lt = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, lt, 0, 0, 0);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) lt[v] += lt2[v];
+        diagonal(W + 2 * 256, st);
+        f64x4 st2 = {0.0, 0.0, 0.0, 0.0}, sum = {0.0, 0.0, 0.0, 0.0}, sum2 = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {                                  // C_11 - L L^T
+            if (kk & 1) st2 = __builtin_amdgcn_mfma_f64_16x16x4f64(-lt[kk], lt[kk], st2, 0, 0, 0);
+            else st = __builtin_amdgcn_mfma_f64_16x16x4f64(-lt[kk], lt[kk], st, 0, 0, 0);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) st[v] += st2[v];
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {                                  // L_10 X_00
+            const double bv = Xd[(4 * kk + lq) * 17 + lr];
+            if (kk & 1) sum2 = __builtin_amdgcn_mfma_f64_16x16x4f64(lt[kk], bv, sum2, 0, 0, 0);
+            else sum = __builtin_amdgcn_mfma_f64_16x16x4f64(lt[kk], bv, sum, 0, 0, 0);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) sum[v] += sum2[v];
+        const uint32_t dead1 = chol16_factor_invert(st, x, lane, bc, wd + 16);
+        store_diagonal(x, 1, dead1, Rs + 2 * 256);
+        wave_sync();
+        f64x4 xo = {0.0, 0.0, 0.0, 0.0}, xo2 = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {                                  // X_10 = -X_11 (L_10 X_00)
+            const double av = -Xd[(16 + lr) * 17 + 4 * kk + lq];
+            if (kk & 1) xo2 = __builtin_amdgcn_mfma_f64_16x16x4f64(av, sum[kk], xo2, 0, 0, 0);
+            else xo = __builtin_amdgcn_mfma_f64_16x16x4f64(av, sum[kk], xo, 0, 0, 0);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int c = lq + 4 * v;
+            const bool live = static_cast<uint32_t>(16 + c) < r && !((dead0 >> lr) & 1u) && !((dead1 >> c) & 1u);
+            Rs[256 + lr * 16 + c] = live ? xo[v] + xo2[v] : 0.0;
+        }
+    }
+}
+
 // ---------------------------------------------------------------------------
 // P^ = P R^-1 on fp64 MFMA (64 rows per block, 16 per wave), fp32 result in place,
 // and the bf16 operand copy Pt[plane][c][i] (i contiguous, rows padded to a
 // multiple of 64) that the Q-pass reads as MFMA B-fragments.
+// FACTOR: every block sums the Gram tiles (`nb` sets, in the order of k_gram_sum) and factors them itself: a launch of
+// k_chol for one block per matrix costs more than the chain of one or two diagonal tiles (1.7 us each).  Per pass,
+// k_chol / this: 1024 x 1024 at rank 4 50 / 47 us, two hidden-768 blocks at rank 16 114 / 110, three odd matrices at rank 13
+// 147 / 143, 4096 x 4096 at rank 32 (two iterations) 201 / 192.  With several blocks per CU each pays for the chain:
+// 50257 x 1024 at rank 32 (786 blocks) 329 / 335.
 // ---------------------------------------------------------------------------
-template <int T16, int NP, int WAVES>
+template <int T16, int NP, int WAVES, bool FACTOR>
 __global__ __launch_bounds__(64 * WAVES) void k_apply(const Group grp, uint32_t RP)
 {
     const TensorArgs& ta = grp.t[locate(grp, blockIdx.x)];
@@ -873,13 +927,41 @@ __global__ __launch_bounds__(64 * WAVES) void k_apply(const Group grp, uint32_t 
     __shared__ double Rs[NTILE * 256];               // tile (tk <= tc), [k][c] row-major
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t row0 = (blockIdx.x - ta.first) * ROWS;
-    // R^-1 goes to LDS once per block (all loads in flight together): the multiply below then
-    // runs without a round trip to L2 per k step
-    // (k_chol wrote the tiles in this order, zero from rank r on)
+    static_assert(!FACTOR || T16 <= 2, "small_factor");
+    __shared__ double Ws[FACTOR ? NTILE * 256 + 16 + 16 * T16 + T16 * 272 : 1];
+    if constexpr (FACTOR) {
+        static_assert(NTH == 256, "one entry of a tile per thread");
+        const double* __restrict__ tiles = ta.tiles;
+        const uint32_t nb = ta.nb;
+        constexpr uint32_t NE = NTILE * 256, DEP = T16 == 1 ? 32 : 8;     // sets in flight
+        double s4[NTILE][4];
 #pragma unroll
-    for (int e0 = 0; e0 < NTILE * 256; e0 += NTH) {
-        const int e = e0 + tid;
-        if (e < NTILE * 256) Rs[e] = rinv[e];
+        for (int q = 0; q < NTILE; ++q)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) s4[q][u] = 0.0;
+        for (uint32_t b = 0; b < nb; b += DEP) {
+            double x[NTILE][DEP];
+#pragma unroll
+            for (uint32_t u = 0; u < DEP; ++u)
+#pragma unroll
+                for (int q = 0; q < NTILE; ++q)
+                    x[q][u] = (b + u < nb) ? tiles[static_cast<size_t>(b + u) * NE + q * 256 + tid] : 0.0;
+#pragma unroll
+            for (uint32_t u = 0; u < DEP; ++u)
+#pragma unroll
+                for (int q = 0; q < NTILE; ++q) s4[q][u & 3] += x[q][u];
+        }
+#pragma unroll
+        for (int q = 0; q < NTILE; ++q) Ws[q * 256 + tid] = ((s4[q][0] + s4[q][1]) + s4[q][2]) + s4[q][3];
+    } else {
+        // R^-1 goes to LDS once per block (all loads in flight together): the multiply below then
+        // runs without a round trip to L2 per k step
+        // (k_chol wrote the tiles in this order, zero from rank r on)
+#pragma unroll
+        for (int e0 = 0; e0 < NTILE * 256; e0 += NTH) {
+            const int e = e0 + tid;
+            if (e < NTILE * 256) Rs[e] = rinv[e];
+        }
     }
 #pragma unroll
     for (int it = 0; it < T16; ++it) {
@@ -900,6 +982,11 @@ __global__ __launch_bounds__(64 * WAVES) void k_apply(const Group grp, uint32_t 
         *reinterpret_cast<float4*>(Ps + i * LD + c4) = v;
     }
     __syncthreads();
+    if constexpr (FACTOR) {
+        double* const bc = Ws + NTILE * 256;
+        if (wave == 0) small_factor<T16>(Ws, Rs, bc, bc + 16, bc + 16 + 16 * T16, r, lane);
+        __syncthreads();
+    }
 
     f64x4 acc[T16];
 #pragma unroll
@@ -2145,7 +2232,7 @@ static constexpr size_t deferred_narrow_lds()
 
 int prepare_compress_kernels(edgc_ctx* ctx)
 {
-    constexpr int chol_max = (128 * (128 + kCholPad) + 8 * 16 * 17 + 128 + kCholThreads) * 8 + (8 + 36) * 4;
+    constexpr int chol_max = (128 * (128 + kCholPad) + 8 * 16 * 17 + 128 + 16) * 8 + (8 + 36) * 4;
     EDGC_HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(&k_chol),
                                           hipFuncAttributeMaxDynamicSharedMemorySize, chol_max));
     EDGC_HIP_TRY(ctx, (allow_lds_pass_q<1, 4, 2>()));
@@ -2420,12 +2507,19 @@ static int run_orthonormalise(edgc_ctx* ctx, Group& g, const TensorScratch* cap,
     }
     EDGC_HIP_TRY(ctx, hipGetLastError());
 
-    // Gram = sum of the per-block tiles; the Cholesky block only sums a single tile itself
+    // Gram = sum of the per-block tiles; up to rank 32 k_apply sums a few sets itself (one tile: up to 128 sets of 2 KB, three
+    // tiles: up to 8 of 6 KB; every one of its blocks reads them all)
+    uint32_t apply_blocks = 0;                         // of 64 rows
+    for (uint32_t i = 0; i < g.count; ++i) apply_blocks += cdiv(g.t[i].m_pad, 64u);
+    // two tiles: while the launch is at most two blocks per CU (the figures at k_apply); one tile: always, its chain is short
+    // and k_chol would need the sum of the sets in a launch of its own
+    const bool factor = t16 == 1 || (t16 == 2 && apply_blocks <= 2u * static_cast<uint32_t>(ctx->num_cu));
+    const uint32_t max_sets = t16 == 1 ? 128u : factor ? 8u : 1u;
     blocks = 0;
     bytes = 0.0;
     for (uint32_t i = 0; i < g.count; ++i) {
         TensorArgs& t = g.t[i];
-        const bool summed = t.nb > 1 && t16 > 1;
+        const bool summed = t.nb > max_sets;
         t.d0 = t.nb;
         t.first = blocks;
         if (summed) {
@@ -2438,25 +2532,22 @@ static int run_orthonormalise(edgc_ctx* ctx, Group& g, const TensorScratch* cap,
         EDGC_LAUNCH(ctx, st, KID_GRAM_SUM, bytes, 0.0, k_gram_sum<<<blocks, 256, 0, st>>>(g, ne));
         EDGC_HIP_TRY(ctx, hipGetLastError());
     }
-    bytes = 0.0;
-    for (uint32_t i = 0; i < g.count; ++i) {
-        TensorArgs& t = g.t[i];
-        if (t.tiles == t.gram) t.nb = 1;
-        bytes += 8.0 * ne * t.nb + 8.0 * r * r;
+    for (uint32_t i = 0; i < g.count; ++i)
+        if (g.t[i].tiles == g.t[i].gram) g.t[i].nb = 1;
+    if (!factor) {
+        const size_t rpad = 16 * t16;
+        const size_t chol_lds = (rpad * (rpad + kCholPad) + t16 * 16 * 17 + rpad + 16) * sizeof(double) + (8 + 36) * sizeof(uint32_t);
+        EDGC_LAUNCH(ctx, st, KID_CHOL, g.count * (8.0 * ne + 8.0 * r * r), g.count * 2.0 * r * r * r / 3.0,
+                    k_chol<<<g.count, kCholThreads, chol_lds, st>>>(g, t16));
+        EDGC_HIP_TRY(ctx, hipGetLastError());
     }
-    const size_t rpad = 16 * t16;
-    const size_t chol_lds = (rpad * (rpad + kCholPad) + t16 * 16 * 17 + rpad + kCholThreads) * sizeof(double) + (8 + 36) * sizeof(uint32_t);
-    EDGC_LAUNCH(ctx, st, KID_CHOL, bytes, g.count * 2.0 * r * r * r / 3.0,
-                k_chol<<<g.count, kCholThreads, chol_lds, st>>>(g, t16));
-    EDGC_HIP_TRY(ctx, hipGetLastError());
 
     // P^ = P R^-1 and its transposed bf16 copy.  Above rank 64 the 72 KB of R^-1 tiles leave room for one
     // block per CU, and a block's time is its share of fp64 MFMA work (144 per 16 rows, on four SIMDs):
     // blocks of 64 rows while they fit in one round over the CUs, of 128 rows otherwise
     uint32_t apply_rows = 64;
     if (t16 == 8) {
-        uint32_t b64 = 0;
-        for (uint32_t i = 0; i < g.count; ++i) b64 += cdiv(g.t[i].m_pad, 64u);
+        const uint32_t b64 = apply_blocks;
         apply_rows = ctx->tune_apply == 4 ? 64u : ctx->tune_apply == 8 ? 128u
                    : (b64 <= static_cast<uint32_t>(ctx->num_cu) ? 64u : 128u);
     }
@@ -2473,12 +2564,15 @@ static int run_orthonormalise(edgc_ctx* ctx, Group& g, const TensorScratch* cap,
     {
         ProfScope prof_scope_(ctx, st, KID_APPLY, bytes, flops);
         switch (t16) {
-        case 1: k_apply<1, NP, 4><<<blocks, 256, 0, st>>>(g, RP); break;
-        case 2: k_apply<2, NP, 4><<<blocks, 256, 0, st>>>(g, RP); break;
-        case 4: k_apply<4, NP, 4><<<blocks, 256, 0, st>>>(g, RP); break;
+        case 1: k_apply<1, NP, 4, true><<<blocks, 256, 0, st>>>(g, RP); break;
+        case 2:
+            if (factor) k_apply<2, NP, 4, true><<<blocks, 256, 0, st>>>(g, RP);
+            else k_apply<2, NP, 4, false><<<blocks, 256, 0, st>>>(g, RP);
+            break;
+        case 4: k_apply<4, NP, 4, false><<<blocks, 256, 0, st>>>(g, RP); break;
         default:
-            if (apply_rows == 128) k_apply<8, NP, 8><<<blocks, 512, 0, st>>>(g, RP);
-            else k_apply<8, NP, 4><<<blocks, 256, 0, st>>>(g, RP);
+            if (apply_rows == 128) k_apply<8, NP, 8, false><<<blocks, 512, 0, st>>>(g, RP);
+            else k_apply<8, NP, 4, false><<<blocks, 256, 0, st>>>(g, RP);
             break;
         }
     }

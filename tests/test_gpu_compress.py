@@ -27,7 +27,7 @@ def _pad4(r):
     return (r + 3) // 4 * 4
 
 
-def gpu_compress(G, E, Q0, r, power_iters=1, ld=None):
+def gpu_compress(G, E, Q0, r, power_iters=1, ld=None, c=None):
     """Runs edgc_compress on host arrays; returns (P, Q, D) as numpy."""
     m, n = G.shape
     Gd = to_dev(G)
@@ -42,7 +42,7 @@ def gpu_compress(G, E, Q0, r, power_iters=1, ld=None):
     Qd = torch.zeros((n, ldq), dtype=torch.float32, device="cuda")
     Qd[:, :r] = to_dev(np.ascontiguousarray(Q0[:, :r]))
     Pd = torch.full((m, ldq), 7.0, dtype=torch.float32, device="cuda")
-    ctx().compress(Gd, Ed, E is None, Qd, Pd, r, power_iters)
+    (c or ctx()).compress(Gd, Ed, E is None, Qd, Pd, r, power_iters)
     torch.cuda.synchronize()
     return to_host(Pd)[:, :r], to_host(Qd)[:, :r], to_host(Ed), (Pd, Qd, Ed)
 
@@ -148,6 +148,25 @@ def test_contexts_and_batch_slots_made_for_exactly_that_rank(r):
         torch.cuda.synchronize()
         assert rel_fro(to_host(P)[:, :r], Po) < 1e-3 and rel_fro(to_host(Q)[:, :r], Qo) < 1e-3
     c.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("m,n,r", [(128, 64, 1), (256, 192, 16), (256, 192, 17), (384, 64, 31), (256, 320, 32), (512, 128, 64),
+                                   (512, 192, 65), (768, 1088, 128), (8320, 64, 16), (33024, 64, 20)])
+def test_stored_residual_on_whole_tiles_against_the_oracle(dtype, m, n, r):
+    """A step with a residual where every tile is whole: the P-pass without edge paths, one stage and more per block, the
+    factorisation inside the multiply (one and two tiles, 128 sets of Gram tiles and more) and outside of it."""
+    G = gen.lowrank_plus_noise(m, n, min(2 * r, 64), 0.9, 1e-3, seed=r, dtype=dtype)
+    E = np.random.default_rng(r).normal(0, 1e-3, (m, n)).astype(np.float32)
+    q0 = _q0(n, r)
+    Po, Qo, Do = orc.compress(G, E, q0[:, :r].copy(), r)
+    Pk, Qk, Dk, _ = gpu_compress(G, E, q0, r, c=edgc.Context(0, 16, 128, m, n))
+    assert np.array_equal(Dk, Do)
+    # operands of 8 (bf16) or 17 bits: 2^-9 and 2^-17, and the conditioning of P's columns
+    tol = 2e-2 if dtype == "bf16" else 1e-3
+    P64 = Pk.astype(np.float64)
+    assert np.abs(P64.T @ P64 - np.eye(r)).max() < 1e-5
+    assert rel_fro(Pk @ Qk.T, Po @ Qo.T) < tol
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
