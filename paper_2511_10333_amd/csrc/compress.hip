@@ -299,14 +299,16 @@ __host__ __device__ inline void tri_tile(int t, int T, int& ta, int& tb)
     tb = ta + t;
 }
 
-template <int T16>
+// FROM_P: P is in the caller's buffer and not in partials (the second phase of a split call).  A template: as a branch it
+// costs the rank-128 kernel 24 registers (46 against 42 us on the hidden-5120 block).
+template <int T16, bool FROM_P>
 __global__ __launch_bounds__(256) void k_reduce_gram(const Group grp, uint32_t RP)
 {
     const TensorArgs& ta_ = grp.t[locate(grp, blockIdx.x)];
     const float* __restrict__ part = ta_.part;
     float* __restrict__ P = ta_.P;
     double* __restrict__ gram_part = ta_.gram_part;
-    const uint32_t S = ta_.sp, m = ta_.m, r = grp.r, ldp = ta_.ldp, chunks_per_block = ta_.d0;
+    const uint32_t S = FROM_P ? 0 : ta_.sp, m = ta_.m, r = grp.r, ldp = ta_.ldp, chunks_per_block = ta_.d0;
     const uint32_t bid = blockIdx.x - ta_.first;
     constexpr int CW = 16 * T16;
     constexpr int LD = CW + 16;                      // floats; 4 rows x 16 columns per read: 2-way at worst
@@ -344,7 +346,7 @@ __global__ __launch_bounds__(256) void k_reduce_gram(const Group grp, uint32_t R
             const uint32_t row = min(row0 + i, m - 1);       // rows past the end are loaded but not used
             v[it] = make_float4(0.f, 0.f, 0.f, 0.f);
             src[it] = part + static_cast<size_t>(row) * RP + c4;
-            if (S == 0 && static_cast<uint32_t>(c4) < r) {   // P as the caller holds it, columns from r on masked
+            if (FROM_P && static_cast<uint32_t>(c4) < r) {   // P as the caller holds it, columns from r on masked
                 const float4 x = *reinterpret_cast<const float4*>(P + static_cast<size_t>(row) * ldp + c4);
                 v[it].x = x.x;
                 if (static_cast<uint32_t>(c4) + 1 < r) v[it].y = x.y;
@@ -380,7 +382,7 @@ __global__ __launch_bounds__(256) void k_reduce_gram(const Group grp, uint32_t R
             const int idx = tid + 256 * it;
             const int i = idx / (CW / 4), c4 = (idx % (CW / 4)) * 4;
             const uint32_t row = row0 + i;
-            if (row < m && S != 0) {
+            if (!FROM_P && row < m) {
                 // partial columns >= r are exact zeros (the Q tile is masked in the P-pass)
                 float* dst = P + static_cast<size_t>(row) * ldp + c4;
                 if (static_cast<uint32_t>(c4) + 4 <= r) {
@@ -1035,7 +1037,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_apply(const Group grp, uint32_t 
         }
     }
     // transposed operand copy: 8 consecutive rows of one column per 16-byte store (the copy's rows are
-    // padded to a multiple of 64, which a block of 128 rows may reach past)
+    // padded to a multiple of 64, which a block of more rows may reach past)
     constexpr uint32_t SEG = ROWS / 8;
     for (uint32_t idx = tid; idx < RP * SEG; idx += NTH) {
         const uint32_t cc = idx / SEG, q = idx % SEG;
@@ -2498,12 +2500,16 @@ static int run_orthonormalise(edgc_ctx* ctx, Group& g, const TensorScratch* cap,
     }
     {
         ProfScope prof_scope_(ctx, st, KID_REDUCE_GRAM, bytes, flops);
+#define EDGC_GRAM(T_)                                                       \
+    if (from_p) k_reduce_gram<T_, true><<<blocks, 256, 0, st>>>(g, RP);     \
+    else k_reduce_gram<T_, false><<<blocks, 256, 0, st>>>(g, RP);
         switch (t16) {
-        case 1: k_reduce_gram<1><<<blocks, 256, 0, st>>>(g, RP); break;
-        case 2: k_reduce_gram<2><<<blocks, 256, 0, st>>>(g, RP); break;
-        case 4: k_reduce_gram<4><<<blocks, 256, 0, st>>>(g, RP); break;
-        default: k_reduce_gram<8><<<blocks, 256, 0, st>>>(g, RP); break;
+        case 1: EDGC_GRAM(1) break;
+        case 2: EDGC_GRAM(2) break;
+        case 4: EDGC_GRAM(4) break;
+        default: EDGC_GRAM(8) break;
         }
+#undef EDGC_GRAM
     }
     EDGC_HIP_TRY(ctx, hipGetLastError());
 
@@ -2544,13 +2550,19 @@ static int run_orthonormalise(edgc_ctx* ctx, Group& g, const TensorScratch* cap,
 
     // P^ = P R^-1 and its transposed bf16 copy.  Above rank 64 the 72 KB of R^-1 tiles leave room for one
     // block per CU, and a block's time is its share of fp64 MFMA work (144 per 16 rows, on four SIMDs):
-    // blocks of 64 rows while they fit in one round over the CUs, of 128 rows otherwise
-    uint32_t apply_rows = 64;
-    if (t16 == 8) {
-        const uint32_t b64 = apply_blocks;
-        apply_rows = ctx->tune_apply == 4 ? 64u : ctx->tune_apply == 8 ? 128u
-                   : (b64 <= static_cast<uint32_t>(ctx->num_cu) ? 64u : 128u);
+    // blocks of 64 rows while they fit in one round over the CUs, otherwise of 128, or of 144 or 160 where that saves a
+    // second, nearly empty round (35840 rows of the hidden-5120 block: 280 blocks of 128 rows 42 us, 251 of 144 33)
+    uint32_t apply_waves = 4;
+    if (t16 == 8 && apply_blocks > static_cast<uint32_t>(ctx->num_cu)) {
+        apply_waves = 8;
+        for (uint32_t w = 8; w <= 10; ++w) {
+            uint32_t nb = 0;
+            for (uint32_t i = 0; i < g.count; ++i) nb += cdiv(g.t[i].m_pad, 16u * w);
+            if (nb <= static_cast<uint32_t>(ctx->num_cu)) { apply_waves = w; break; }
+        }
     }
+    if (t16 == 8 && (ctx->tune_apply == 4 || (ctx->tune_apply >= 8 && ctx->tune_apply <= 10))) apply_waves = ctx->tune_apply;
+    const uint32_t apply_rows = 16u * apply_waves;
     blocks = 0;
     bytes = flops = 0.0;
     for (uint32_t i = 0; i < g.count; ++i) {
@@ -2571,8 +2583,12 @@ static int run_orthonormalise(edgc_ctx* ctx, Group& g, const TensorScratch* cap,
             break;
         case 4: k_apply<4, NP, 4, false><<<blocks, 256, 0, st>>>(g, RP); break;
         default:
-            if (apply_rows == 128) k_apply<8, NP, 8, false><<<blocks, 512, 0, st>>>(g, RP);
-            else k_apply<8, NP, 4, false><<<blocks, 256, 0, st>>>(g, RP);
+            switch (apply_waves) {
+            case 4: k_apply<8, NP, 4, false><<<blocks, 256, 0, st>>>(g, RP); break;
+            case 9: k_apply<8, NP, 9, false><<<blocks, 576, 0, st>>>(g, RP); break;
+            case 10: k_apply<8, NP, 10, false><<<blocks, 640, 0, st>>>(g, RP); break;
+            default: k_apply<8, NP, 8, false><<<blocks, 512, 0, st>>>(g, RP); break;
+            }
             break;
         }
     }

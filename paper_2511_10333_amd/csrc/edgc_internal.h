@@ -150,7 +150,7 @@ struct edgc_ctx {
     int tune_pwaves = -1;   // waves per block of that kernel: -1 built-in choice (8 above rank 64), 4 or 8
     int tune_qfull = -1;    // Q-pass of whole-tile groups: -1 built-in choice; 0 the general kernel; 4 / 8 the
                             // pipelined kernel with that many waves per block
-    int tune_apply = -1;    // k_apply above rank 64: 4 = four waves (64 rows) per block, 8 = eight (128 rows)
+    int tune_apply = -1;    // k_apply above rank 64: waves (of 16 rows) per block, 4, 8, 9 or 10
     int tune_ept = 0;       // items per thread of the histogram and, twice as many, of the range pass; 0: built-in choice
     int tune_pattern = 1;   // entropy estimate: 1 one read into 16-bit counters per block where that applies
                             // (bf16 samples, fp32 on more than 16384 bins); 0 the plain kernels only
