@@ -58,8 +58,7 @@ def entropy_sweep(args, torch, edgc, metric, hbm_peak_gbs) -> int:
                         for k, v in ks.items() if v["launches"] and v["total_ms"] > 0}
                 sample_bytes = res.n_sampled * esz
                 # reads of the sample: the range pass (not for bf16 counted by bit pattern) and one binning pass
-                # (two for fp32 on more than 32768 bins without the 16-bit counters); kernels that only check
-                # the overflow gate and return (a few microseconds, no bytes) do not count
+                # (two for fp32 on more than 32768 bins without the 16-bit counters)
                 live = {k: v for k, v in kern.items() if v["avg_us"] >= 4.0 or k.startswith("k_wide")}
                 reads = (1 if "k_minmax" in live else 0) + (1 if "k_wide_hist" in live else 0) + \
                         ((2 if bins > 32768 else 1) if "k_hist" in live else 0)

@@ -4,7 +4,8 @@
 //   k_pass_p        D = G + E_old (written back), P_partial = D Q    (split over columns)
 //   k_reduce_gram   P = sum of partials; per-block Gram P^T P in fp64
 //   k_gram_sum      Gram = sum of the per-block Grams (only when there are many)
-//   k_chol          scaled Cholesky of the Gram in fp64, inverse factor R^-1
+//   k_chol          scaled Cholesky of the Gram in fp64, inverse factor R^-1 (above rank 32, or 16 in
+//                   launches of many blocks; otherwise k_apply's blocks do it themselves)
 //   k_apply         P^ = P R^-1 (fp64), plus a transposed bf16 operand copy of P^
 //   k_pass_q        Q_partial = D^T P^                                (split over rows)
 //   k_reduce_q      Q = sum of partials

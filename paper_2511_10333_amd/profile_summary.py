@@ -147,8 +147,7 @@ def cmd_counters(a) -> int:
     out.extend(a.command)
     out.extend(["```\n",
                 "Mean per launch over the launches that did work; `idle` counts launches whose first counter reads under "
-                "1 % of the kernel's largest (a kernel queued behind the overflow gate of the one-read estimate returns at "
-                "once).\n",
+                "1 % of the kernel's largest.\n",
                 "| kernel | launches | idle | " + " | ".join(names) + " |", "|---|---|---|" + "---|" * len(names)])
     def weight(k):
         return -max(val[k][names[0]].values() or [0.0])
@@ -184,7 +183,7 @@ def cmd_cells(a) -> int:
     out.extend(["```\n",
                 "`ms`: one whole estimate, from a pair of events around back-to-back estimates.  `reads`: how often the "
                 "estimate's kernels read the sample.  Kernel columns: microseconds per launch from a second pass with every "
-                "launch between its own events (a kernel that only checks the overflow gate and returns reads about 1.6).\n",
+                "launch between its own events.\n",
                 "| dtype | stride | bins | sampled | ms | reads | sample GB/s | buffer GB/s | kernels (us) |",
                 "|---|---|---|---|---|---|---|---|---|"])
     for c in d["cells"]:
