@@ -31,6 +31,7 @@
 // and B[k = 8*(l/32) .. +8][j = l%32]; accumulator register v of lane l holds
 // D[i = 8*(v/4) + 4*(l/32) + v%4][j = l%32].
 #include "compress_common.h"
+#include "pass_plan.h"
 
 #include <algorithm>
 #include <math.h>
@@ -2322,34 +2323,11 @@ static void share_targets(const Group& g, uint32_t target, uint32_t (&out)[kMaxG
     }
 }
 
-// How a pass cuts the tensors of a group into blocks that take equally long: tensor i is `across[i]` blocks wide, and
-// its `along[i]` stages are cut into runs of the returned number of stages, the smallest with which the launch has at
-// most `target` blocks (`blocks`: how many it has).
-static uint32_t uniform_step(uint32_t count, const uint32_t* across, const uint32_t* along, uint32_t target, uint64_t& blocks)
-{
-    uint32_t lo = 1, hi = 1;
-    for (uint32_t i = 0; i < count; ++i) hi = std::max(hi, along[i]);
-    auto count_blocks = [&](uint32_t step) {
-        uint64_t b = 0;
-        for (uint32_t i = 0; i < count; ++i) b += static_cast<uint64_t>(across[i]) * cdiv(along[i], step);
-        return b;
-    };
-    while (lo < hi) {
-        const uint32_t mid = lo + (hi - lo) / 2;
-        if (count_blocks(mid) <= target) hi = mid; else lo = mid + 1;
-    }
-    blocks = count_blocks(lo);
-    return lo;
-}
-
 template <int NP, int RT>
 static int run_pass_p(edgc_ctx* ctx, Group& g, const TensorScratch* cap, bool with_grad, hipStream_t st)
 {
     constexpr uint32_t BK = 64, RP = RT * 32;
     using GT = typename GradElem<NP>::type;
-    // measured: ~4 blocks per CU stream best (3 are resident; more splits only add partials).
-    // The deferred kernel above rank 64 starts every block with 64 KB of P^ fragments: there
-    // exactly the two blocks per CU that are resident (0 to 7 % faster per step than four).
     // the kernels of the deferred form: above rank 64 only for that form; up to rank 64 also for bf16
     // gradients with the residual stored (its sweep is the faster one there: 295 against 390 us on the
     // hidden-5120 block)
@@ -2363,53 +2341,28 @@ static int run_pass_p(edgc_ctx* ctx, Group& g, const TensorScratch* cap, bool wi
     // block, whose residual streams from HBM; 89 against 86 us on the hidden-2048 block, which the last-level cache
     // holds: there the general kernel stays)
     const bool fp32_wide = NP == 2 && RT == 4;
-    double d_all = 0.0;
-    for (uint32_t i = 0; i < g.count; ++i) d_all += 4.0 * g.t[i].m * g.t[i].n;
-    const bool big_d = d_all > 128.0 * 1024 * 1024;
+    double d_bytes = 0.0;
+    for (uint32_t i = 0; i < g.count; ++i) d_bytes += 4.0 * g.t[i].m * g.t[i].n;
+    const bool big_d = d_bytes > 128.0 * 1024 * 1024;
     const bool use_full = with_grad && ctx->tune_full != 0 && pass_p_full_applies(g, DT, RT, pwaves) &&
                           (!fp32_wide || big_d || ctx->tune_full > 0);
     const bool use_narrow = with_grad && g.defer && RT == 4;
     const bool use_wide = with_grad && RT <= 2 && (g.defer || NP == 1);
-    const uint32_t per_cu = (use_narrow && !use_full) ? 2u : (use_full && pwaves == 8 ? 2u : 4u);
     const uint32_t rows_per_block = use_full ? 32u * pwaves : 128u;
-    const uint32_t cu = static_cast<uint32_t>(ctx->num_cu);
-    uint32_t tgt[kMaxGroup];
-    share_targets(g, cu * (ctx->tune_p ? ctx->tune_p : per_cu), tgt);
-    // Blocks of equal length, a few per CU: fewer column splits mean fewer partials to write and sum, more blocks even out
-    // the load.  From two per CU on (four where the residual takes more than 192 MB and blocks are of four waves), until no
-    // CU would have many fewer blocks than others.  Per pass, four per CU in proportion to size / equal length from two on /
-    // from four on: two hidden-768 blocks 114.6 / 109.6 / 114.7 us, hidden-1536 block at rank 64 202 / 192 / 202, three odd
-    // matrices 149 / 143 / 148; hidden-4096 fp32 block at rank 64, stored 1214 / 1264 / 1184, deferred 935 / 1006 / 895;
-    // 50257 x 1024 (393 blocks across): two per CU 375, four 345, five 331.
-    uint32_t step = 0;
-    if (!ctx->tune_p) {
-        uint32_t across[kMaxGroup], along[kMaxGroup];
-        double d_bytes = 0.0;
-        for (uint32_t i = 0; i < g.count; ++i) {
-            across[i] = cdiv(g.t[i].m, rows_per_block);
-            along[i] = cdiv(g.t[i].n, BK);
-            d_bytes += 4.0 * g.t[i].m * g.t[i].n;
-        }
-        // what a plan keeps busy of the CUs' time: all blocks of a large group take `step` stages; in a small one it is the
-        // count of blocks per CU that matters
-        const bool large = rows_per_block == 128 && d_bytes > 192.0 * 1024 * 1024;
-        double total = 0.0, best = 0.0;
-        for (uint32_t i = 0; i < g.count; ++i) total += static_cast<double>(across[i]) * along[i];
-        for (uint32_t k = large ? 4 : 2; k <= 8 && best < 0.8; ++k) {
-            uint64_t nb = 0;
-            const uint32_t s = uniform_step(g.count, across, along, cu * k, nb);
-            const double slots = static_cast<double>(cdiv(nb, cu)) * cu;
-            const double eff = large ? total / (s * slots) : static_cast<double>(nb) / slots;
-            if (eff > best) { best = eff; step = s; }
-        }
+    uint32_t across[kMaxGroup], along[kMaxGroup];
+    for (uint32_t i = 0; i < g.count; ++i) {
+        across[i] = cdiv(g.t[i].m, rows_per_block);
+        along[i] = cdiv(g.t[i].n, BK);
     }
+    const uint32_t step = pass_p_step(g.count, across, along, rows_per_block, RP, d_bytes,
+                                      static_cast<uint32_t>(ctx->num_cu), ctx->tune_p);
     bool vec = true;
     uint32_t blocks = 0;
     double bytes = 0.0, flops = 0.0;
     for (uint32_t i = 0; i < g.count; ++i) {
         TensorArgs& t = g.t[i];
-        const uint32_t RB = cdiv(t.m, rows_per_block), ksteps = cdiv(t.n, BK);
-        uint32_t S = step ? cdiv(ksteps, step) : std::max(1u, std::min(ksteps, tgt[i] / RB));
+        const uint32_t RB = across[i], ksteps = along[i];
+        uint32_t S = cdiv(ksteps, step);
         const uint64_t lim = cap[i].part_elems / (static_cast<uint64_t>(t.m) * RP);
         if (lim == 0) return fail(ctx, EDGC_EINVAL, "partial-factor scratch too small for this shape");
         S = static_cast<uint32_t>(std::min<uint64_t>(S, lim));

@@ -1,0 +1,67 @@
+// How the P-pass cuts the tensors of a group into blocks.  Plain C++: the plan is checked on the CPU.
+#pragma once
+
+#include <algorithm>
+#include <cstdint>
+
+namespace edgc {
+
+// Blocks of equal length: tensor i is `across[i]` blocks wide, and its `along[i]` stages are cut into runs of the returned
+// number of stages, the smallest with which the launch has at most `target` blocks (`blocks`: how many it has).
+inline uint32_t uniform_step(uint32_t count, const uint32_t* across, const uint32_t* along, uint64_t target, uint64_t& blocks)
+{
+    uint32_t lo = 1, hi = 1;
+    for (uint32_t i = 0; i < count; ++i) hi = std::max(hi, along[i]);
+    auto count_blocks = [&](uint32_t step) {
+        uint64_t b = 0;
+        for (uint32_t i = 0; i < count; ++i) b += static_cast<uint64_t>(across[i]) * ((along[i] + step - 1) / step);
+        return b;
+    };
+    while (lo < hi) {
+        const uint32_t mid = lo + (hi - lo) / 2;
+        if (count_blocks(mid) <= target) hi = mid; else lo = mid + 1;
+    }
+    blocks = count_blocks(lo);
+    return lo;
+}
+
+// Stages (of 64 columns) per block of the P-pass.  `rp`: columns of a partial factor; `d_bytes`: the group's residual;
+// `per_cu`: blocks per CU to aim at, 0 for the rule.
+//
+// Fewer column splits mean fewer partials to write and to sum, more blocks even out the load and keep more loads in flight.
+// Measured per pass, against blocks in proportion to the tensors' size, four per CU (256-row blocks: two); fp32 and bf16,
+// ranks 16, 64 and 128, stored and deferred:
+//  * 256-row blocks (rank 128, whole tiles): two per CU.  Hidden-1024 to hidden-6144 blocks -9 to +1 %; three per CU +1 to
+//    +15 %, four +3 to +15 % (hidden-1024: 175 us with three, 156 with two).
+//  * 128-row blocks, residual up to 224 MB: two per CU, or three and four where that leaves CUs with one block while others
+//    have two.  Hidden-1280 block -5 to -9 %, hidden-2048 (201 MB) -4 to +1, 832 x 11584 -4 to -9, 600 x 12818 -9 to -17;
+//    four per CU 0 to +1.  What is left idle counts for more the longer the pass: at 3/4 of the places taken, 1381 x 9200
+//    (51 MB) -3 to -7 %, hidden-1024 (50 MB) -6 to +2, four hidden-1024 blocks (201 MB) 0 to +8, 50257 x 768 (154 MB) -3 to +7.
+//  * larger residuals: from four per CU on.  8192 x 8192 (268 MB) with two +4 to +7 %, 4000 x 16384 +2 to +6, hidden-3584
+//    +4 to +13, hidden-4096 +4 to +7 and with four -5 to -1.  The line lies between 201 and 262 MB.  Four where
+//    that fills nine tenths of the places, five and more otherwise: hidden-3072 (864 blocks) with four +1 to +5, with five
+//    (1152) -4 to 0; 50257 x 4096 (786 blocks) 0, with five -5 to -10.
+//  * more than four per CU only while the partials stay below a sixteenth of what a block reads and writes (8 rp bytes
+//    against 16 per column): 662 x 13048 with five (one stage per block) +12 to +17 %, hidden-2304 at rank 128 stored +3.
+inline uint32_t pass_p_step(uint32_t count, const uint32_t* across, const uint32_t* along, uint32_t rows_per_block, uint32_t rp,
+                            double d_bytes, uint32_t cu, uint32_t per_cu)
+{
+    constexpr double MB = 1024.0 * 1024.0;
+    uint64_t blocks = 0;
+    if (per_cu == 0 && rows_per_block == 256) per_cu = 2;
+    if (per_cu) return uniform_step(count, across, along, static_cast<uint64_t>(cu) * per_cu, blocks);
+    const bool large = d_bytes > 224.0 * MB;
+    const double enough = large ? 0.9 : d_bytes > 96.0 * MB ? 0.8 : 0.75;
+    uint32_t step = 1;
+    double best = 0.0;
+    for (uint32_t k = large ? 4 : 2; k <= 8 && best < enough; ++k) {
+        const uint32_t s = uniform_step(count, across, along, static_cast<uint64_t>(cu) * k, blocks);
+        if (k > 4 && 8u * s < rp) break;
+        const uint64_t places = (blocks + cu - 1) / cu * cu;
+        const double taken = static_cast<double>(blocks) / static_cast<double>(places);
+        if (taken > best) { best = taken; step = s; }
+    }
+    return step;
+}
+
+}  // namespace edgc

@@ -1,0 +1,79 @@
+"""Launch plans of the passes (host code without a GPU)."""
+import os
+import random
+import subprocess
+
+import pytest
+
+from conftest import ROOT
+
+SRC = r"""
+#include <cstdio>
+#include <vector>
+#include "pass_plan.h"
+int main()
+{
+    // per line: count rows_per_block rp per_cu, then across and along per tensor
+    unsigned count, rpb, rp, per_cu;
+    while (std::scanf("%u %u %u %u", &count, &rpb, &rp, &per_cu) == 4) {
+        std::vector<uint32_t> across(count), along(count);
+        double d_bytes = 0.0;
+        for (unsigned i = 0; i < count; ++i) {
+            if (std::scanf("%u %u", &across[i], &along[i]) != 2) return 1;
+            d_bytes += 4.0 * across[i] * rpb * along[i] * 64.0;
+        }
+        std::printf("%u\n", edgc::pass_p_step(count, across.data(), along.data(), rpb, rp, d_bytes, 256, per_cu));
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    d = tmp_path_factory.mktemp("plan")
+    (d / "plan.cpp").write_text(SRC)
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I" + os.path.join(ROOT, "paper_2511_10333_amd", "csrc"),
+                    str(d / "plan.cpp"), "-o", str(d / "plan")], check=True)
+
+    def run(groups):
+        text = "\n".join(" ".join(map(str, [len(t), rpb, rp, per_cu, *[v for s in t for v in s]])) for t, rpb, rp, per_cu in groups)
+        out = subprocess.run([str(d / "plan")], input=text, check=True, capture_output=True, text=True).stdout
+        return [int(x) for x in out.split()]
+    return run
+
+
+def _cdiv(a, b):
+    return -(-a // b)
+
+
+def _group(shapes, rpb, rp, per_cu=0):
+    return [(_cdiv(m, rpb), _cdiv(n, 64)) for m, n in shapes], rpb, rp, per_cu
+
+
+def _blocks(group, step):
+    return sum(a * _cdiv(k, step) for a, k in group[0])
+
+
+def test_p_pass_plan_bounds(plan):
+    rng = random.Random(3)
+    groups = []
+    for _ in range(3000):
+        shapes = [(int(2 ** rng.uniform(4, 17)), int(2 ** rng.uniform(4, 16))) for _ in range(rng.randint(1, 16))]
+        groups.append(_group(shapes, rng.choice([128, 128, 256]), rng.choice([32, 64, 128]), rng.choice([0, 0, 0, 1, 3])))
+    for g, step in zip(groups, plan(groups)):
+        tensors, rpb, rp, per_cu = g
+        assert 1 <= step <= max(k for _, k in tensors)
+        single = sum(a for a, _ in tensors)              # every tensor in one split
+        most = per_cu or (2 if rpb == 256 else 8)
+        assert _blocks(g, step) <= max(256 * most, single), g
+        if not per_cu and 8 * step < rp:
+            # blocks so short that their partials weigh: at most four per CU
+            assert _blocks(g, step) <= max(256 * 4, single), g
+
+
+@pytest.mark.parametrize("m,n,most", [(662, 13048, 612), (1381, 9200, 792), (5003, 777, 520), (1024, 50257, 1024)])
+def test_p_pass_plan_does_not_trade_partials_for_the_last_places(plan, m, n, most):
+    """Shapes at which no count of blocks fills the CUs evenly: not more splits than blocks in proportion (four per CU)."""
+    for rp in (32, 64, 128):
+        g = _group([(m, n)], 128, rp)
+        assert _blocks(g, plan([g])[0]) <= most
