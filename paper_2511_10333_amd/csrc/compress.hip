@@ -2350,11 +2350,14 @@ static int run_pass_p(edgc_ctx* ctx, Group& g, const TensorScratch* cap, bool wi
     const bool use_wide = with_grad && RT <= 2 && (g.defer || NP == 1);
     const uint32_t rows_per_block = use_full ? 32u * pwaves : 128u;
     uint32_t across[kMaxGroup], along[kMaxGroup];
+    uint64_t most[kMaxGroup];
     for (uint32_t i = 0; i < g.count; ++i) {
         across[i] = cdiv(g.t[i].m, rows_per_block);
         along[i] = cdiv(g.t[i].n, BK);
+        most[i] = cap[i].part_elems / (static_cast<uint64_t>(g.t[i].m) * RP);
+        if (most[i] == 0) return fail(ctx, EDGC_EINVAL, "partial-factor scratch too small for this shape");
     }
-    const uint32_t step = pass_p_step(g.count, across, along, rows_per_block, RP, d_bytes,
+    const uint32_t step = pass_p_step(g.count, across, along, most, rows_per_block, RP, d_bytes,
                                       static_cast<uint32_t>(ctx->num_cu), ctx->tune_p);
     bool vec = true;
     uint32_t blocks = 0;
@@ -2363,9 +2366,6 @@ static int run_pass_p(edgc_ctx* ctx, Group& g, const TensorScratch* cap, bool wi
         TensorArgs& t = g.t[i];
         const uint32_t RB = across[i], ksteps = along[i];
         uint32_t S = cdiv(ksteps, step);
-        const uint64_t lim = cap[i].part_elems / (static_cast<uint64_t>(t.m) * RP);
-        if (lim == 0) return fail(ctx, EDGC_EINVAL, "partial-factor scratch too small for this shape");
-        S = static_cast<uint32_t>(std::min<uint64_t>(S, lim));
         const uint32_t kper = cdiv(ksteps, S) * BK;
         S = cdiv(t.n, kper);
         t.d0 = kper;

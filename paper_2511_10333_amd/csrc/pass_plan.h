@@ -7,10 +7,12 @@
 namespace edgc {
 
 // Blocks of equal length: tensor i is `across[i]` blocks wide, and its `along[i]` stages are cut into runs of the returned
-// number of stages, the smallest with which the launch has at most `target` blocks (`blocks`: how many it has).
-inline uint32_t uniform_step(uint32_t count, const uint32_t* across, const uint32_t* along, uint64_t target, uint64_t& blocks)
+// number of stages, the smallest of at least `least` with which the launch has at most `target` blocks (`blocks`: how many
+// it has).
+inline uint32_t uniform_step(uint32_t count, const uint32_t* across, const uint32_t* along, uint32_t least, uint64_t target,
+                             uint64_t& blocks)
 {
-    uint32_t lo = 1, hi = 1;
+    uint32_t lo = least, hi = least;
     for (uint32_t i = 0; i < count; ++i) hi = std::max(hi, along[i]);
     auto count_blocks = [&](uint32_t step) {
         uint64_t b = 0;
@@ -26,7 +28,8 @@ inline uint32_t uniform_step(uint32_t count, const uint32_t* across, const uint3
 }
 
 // Stages (of 64 columns) per block of the P-pass.  `rp`: columns of a partial factor; `d_bytes`: the group's residual;
-// `per_cu`: blocks per CU to aim at, 0 for the rule.
+// `most`: how many splits the scratch of each tensor has room for (at least one): no plan with more is looked at, so that the
+// launch is the plan that was weighed; `per_cu`: blocks per CU to aim at, 0 for the rule.
 //
 // Fewer column splits mean fewer partials to write and to sum, more blocks even out the load and keep more loads in flight.
 // Measured per pass, against blocks in proportion to the tensors' size, four per CU (256-row blocks: two); fp32 and bf16,
@@ -43,19 +46,21 @@ inline uint32_t uniform_step(uint32_t count, const uint32_t* across, const uint3
 //    (1152) -4 to 0; 50257 x 4096 (786 blocks) 0, with five -5 to -10.
 //  * more than four per CU only while the partials stay below a sixteenth of what a block reads and writes (8 rp bytes
 //    against 16 per column): 662 x 13048 with five (one stage per block) +12 to +17 %, hidden-2304 at rank 128 stored +3.
-inline uint32_t pass_p_step(uint32_t count, const uint32_t* across, const uint32_t* along, uint32_t rows_per_block, uint32_t rp,
-                            double d_bytes, uint32_t cu, uint32_t per_cu)
+inline uint32_t pass_p_step(uint32_t count, const uint32_t* across, const uint32_t* along, const uint64_t* most,
+                            uint32_t rows_per_block, uint32_t rp, double d_bytes, uint32_t cu, uint32_t per_cu)
 {
     constexpr double MB = 1024.0 * 1024.0;
     uint64_t blocks = 0;
+    uint32_t least = 1;
+    for (uint32_t i = 0; i < count; ++i) least = std::max(least, static_cast<uint32_t>((along[i] + most[i] - 1) / most[i]));
     if (per_cu == 0 && rows_per_block == 256) per_cu = 2;
-    if (per_cu) return uniform_step(count, across, along, static_cast<uint64_t>(cu) * per_cu, blocks);
+    if (per_cu) return uniform_step(count, across, along, least, static_cast<uint64_t>(cu) * per_cu, blocks);
     const bool large = d_bytes > 224.0 * MB;
     const double enough = large ? 0.9 : d_bytes > 96.0 * MB ? 0.8 : 0.75;
-    uint32_t step = 1;
+    uint32_t step = least;
     double best = 0.0;
     for (uint32_t k = large ? 4 : 2; k <= 8 && best < enough; ++k) {
-        const uint32_t s = uniform_step(count, across, along, static_cast<uint64_t>(cu) * k, blocks);
+        const uint32_t s = uniform_step(count, across, along, least, static_cast<uint64_t>(cu) * k, blocks);
         if (k > 4 && 8u * s < rp) break;
         const uint64_t places = (blocks + cu - 1) / cu * cu;
         const double taken = static_cast<double>(blocks) / static_cast<double>(places);

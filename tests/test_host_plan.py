@@ -13,16 +13,17 @@ SRC = r"""
 #include "pass_plan.h"
 int main()
 {
-    // per line: count rows_per_block rp per_cu, then across and along per tensor
+    // per line: count rows_per_block rp per_cu, then across, along and room for splits per tensor
     unsigned count, rpb, rp, per_cu;
     while (std::scanf("%u %u %u %u", &count, &rpb, &rp, &per_cu) == 4) {
         std::vector<uint32_t> across(count), along(count);
+        std::vector<uint64_t> most(count);
         double d_bytes = 0.0;
         for (unsigned i = 0; i < count; ++i) {
-            if (std::scanf("%u %u", &across[i], &along[i]) != 2) return 1;
+            if (std::scanf("%u %u %lu", &across[i], &along[i], &most[i]) != 3) return 1;
             d_bytes += 4.0 * across[i] * rpb * along[i] * 64.0;
         }
-        std::printf("%u\n", edgc::pass_p_step(count, across.data(), along.data(), rpb, rp, d_bytes, 256, per_cu));
+        std::printf("%u\n", edgc::pass_p_step(count, across.data(), along.data(), most.data(), rpb, rp, d_bytes, 256, per_cu));
     }
 }
 """
@@ -46,12 +47,12 @@ def _cdiv(a, b):
     return -(-a // b)
 
 
-def _group(shapes, rpb, rp, per_cu=0):
-    return [(_cdiv(m, rpb), _cdiv(n, 64)) for m, n in shapes], rpb, rp, per_cu
+def _group(shapes, rpb, rp, per_cu=0, most=1 << 40):
+    return [(_cdiv(m, rpb), _cdiv(n, 64), most) for m, n in shapes], rpb, rp, per_cu
 
 
 def _blocks(group, step):
-    return sum(a * _cdiv(k, step) for a, k in group[0])
+    return sum(a * _cdiv(k, step) for a, k, _ in group[0])
 
 
 def test_p_pass_plan_bounds(plan):
@@ -62,8 +63,8 @@ def test_p_pass_plan_bounds(plan):
         groups.append(_group(shapes, rng.choice([128, 128, 256]), rng.choice([32, 64, 128]), rng.choice([0, 0, 0, 1, 3])))
     for g, step in zip(groups, plan(groups)):
         tensors, rpb, rp, per_cu = g
-        assert 1 <= step <= max(k for _, k in tensors)
-        single = sum(a for a, _ in tensors)              # every tensor in one split
+        assert 1 <= step <= max(k for _, k, _ in tensors)
+        single = sum(a for a, _, _ in tensors)              # every tensor in one split
         most = per_cu or (2 if rpb == 256 else 8)
         assert _blocks(g, step) <= max(256 * most, single), g
         if not per_cu and 8 * step < rp:
@@ -77,3 +78,17 @@ def test_p_pass_plan_does_not_trade_partials_for_the_last_places(plan, m, n, mos
     for rp in (32, 64, 128):
         g = _group([(m, n)], 128, rp)
         assert _blocks(g, plan([g])[0]) <= most
+
+
+def test_p_pass_plan_fits_the_scratch_it_was_given(plan):
+    """The partials of a context made for exactly the shape and rank hold about four blocks of 128 rows per CU: a plan with
+    more splits than that would be cut back to another one than was chosen."""
+    rng = random.Random(4)
+    groups = []
+    for _ in range(2000):
+        m, n, rp = int(2 ** rng.uniform(5, 17)), int(2 ** rng.uniform(5, 17)), rng.choice([32, 64, 128])
+        room = (max(m, 128 * 1024) + m) * rp // (m * rp) if rng.random() < 0.7 else rng.randint(1, 8)
+        groups.append(_group([(m, n)], rng.choice([128, 256]), rp, most=room))
+    for g, step in zip(groups, plan(groups)):
+        (_, k, room), = g[0]
+        assert _cdiv(k, step) <= room, g
