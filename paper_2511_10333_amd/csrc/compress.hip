@@ -4,8 +4,8 @@
 //   k_pass_p        D = G + E_old (written back), P_partial = D Q    (split over columns)
 //   k_reduce_gram   P = sum of partials; per-block Gram P^T P in fp64
 //   k_gram_sum      Gram = sum of the per-block Grams (only when there are many)
-//   k_chol          scaled Cholesky of the Gram in fp64, inverse factor R^-1 (above rank 32, or 16 in
-//                   launches of many blocks; otherwise k_apply's blocks do it themselves)
+//   k_chol          scaled Cholesky of the Gram in fp64, inverse factor R^-1 (above rank 32, and in launches
+//                   of many blocks; otherwise k_apply's blocks do it themselves)
 //   k_apply         P^ = P R^-1 (fp64), plus a transposed bf16 operand copy of P^
 //   k_pass_q        Q_partial = D^T P^                                (split over rows)
 //   k_reduce_q      Q = sum of partials
@@ -469,7 +469,7 @@ __global__ __launch_bounds__(256) void k_gram_sum(const Group grps, uint32_t ne)
 // from the factorisation (row and column of X zero), so its P^ column is zero
 // and later columns are not projected on it.
 // `tiles`: tile t = (ta <= tb), row-major over the triangle, is [i][j] = W[16 tb + i][16 ta + j].
-// One tile, and two in launches of few blocks, every block of k_apply factors itself.
+// One and two tiles in launches of few blocks every block of k_apply factors itself.
 // ---------------------------------------------------------------------------
 constexpr double kPivotEps = 1e-11;
 constexpr int kCholThreads = 1024;
@@ -912,8 +912,9 @@ __device__ __forceinline__ void small_factor(const double* W, double* Rs, double
 // FACTOR: every block sums the Gram tiles (`nb` sets, in the order of k_gram_sum) and factors them itself: a launch of
 // k_chol for one block per matrix costs more than the chain of one or two diagonal tiles (1.7 us each).  Per pass,
 // k_chol / this: 1024 x 1024 at rank 4 50 / 47 us, two hidden-768 blocks at rank 16 114 / 110, three odd matrices at rank 13
-// 147 / 143, 4096 x 4096 at rank 32 (two iterations) 201 / 192.  With several blocks per CU each pays for the chain:
-// 50257 x 1024 at rank 32 (786 blocks) 329 / 335.
+// 147 / 143, 4096 x 4096 at rank 32 (two iterations) 201 / 192.  With several blocks per CU each pays for the chain: at
+// rank 32 50257 x 1024 (786 blocks) 329 / 335; at ranks 8 and 16 50257 x 768 (786) 256 / 254, two hidden-4096 blocks (896)
+// the same, 131072 x 128 (2048) 152 / 155, eight 100000 x 96 (12500, 64 sets each) 533 / 605.
 // ---------------------------------------------------------------------------
 template <int T16, int NP, int WAVES, bool FACTOR>
 __global__ __launch_bounds__(64 * WAVES) void k_apply(const Group grp, uint32_t RP)
@@ -2471,10 +2472,9 @@ static int run_orthonormalise(edgc_ctx* ctx, Group& g, const TensorScratch* cap,
     // tiles: up to 8 of 6 KB; every one of its blocks reads them all)
     uint32_t apply_blocks = 0;                         // of 64 rows
     for (uint32_t i = 0; i < g.count; ++i) apply_blocks += cdiv(g.t[i].m_pad, 64u);
-    // two tiles: while the launch is at most two blocks per CU (the figures at k_apply); one tile: always, its chain is short
-    // and k_chol would need the sum of the sets in a launch of its own
-    const bool factor = t16 == 1 || (t16 == 2 && apply_blocks <= 2u * static_cast<uint32_t>(ctx->num_cu));
-    const uint32_t max_sets = t16 == 1 ? 128u : factor ? 8u : 1u;
+    // while the launch is at most four blocks per CU with one tile, two with two tiles (the figures at k_apply)
+    const bool factor = t16 <= 2 && apply_blocks <= (t16 == 1 ? 4u : 2u) * static_cast<uint32_t>(ctx->num_cu);
+    const uint32_t max_sets = !factor ? 1u : t16 == 1 ? 128u : 8u;
     blocks = 0;
     bytes = 0.0;
     for (uint32_t i = 0; i < g.count; ++i) {
@@ -2530,7 +2530,10 @@ static int run_orthonormalise(edgc_ctx* ctx, Group& g, const TensorScratch* cap,
     {
         ProfScope prof_scope_(ctx, st, KID_APPLY, bytes, flops);
         switch (t16) {
-        case 1: k_apply<1, NP, 4, true><<<blocks, 256, 0, st>>>(g, RP); break;
+        case 1:
+            if (factor) k_apply<1, NP, 4, true><<<blocks, 256, 0, st>>>(g, RP);
+            else k_apply<1, NP, 4, false><<<blocks, 256, 0, st>>>(g, RP);
+            break;
         case 2:
             if (factor) k_apply<2, NP, 4, true><<<blocks, 256, 0, st>>>(g, RP);
             else k_apply<2, NP, 4, false><<<blocks, 256, 0, st>>>(g, RP);

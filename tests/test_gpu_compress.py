@@ -170,6 +170,25 @@ def test_stored_residual_on_whole_tiles_against_the_oracle(dtype, m, n, r):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("m,n,r", [(65536, 40, 7), (65537, 40, 7), (65600, 64, 16), (66048, 64, 1)])
+def test_one_tile_factored_by_the_multiply_or_by_a_kernel_of_its_own(dtype, m, n, r):
+    """Up to rank 16 the multiply's blocks factor the Gram matrix while there are few of them (here up to 1024 of 64 rows,
+    four per CU), a kernel of its own does from there on."""
+    G = gen.lowrank_plus_noise(m, n, 20, 0.9, 1e-3, seed=r, dtype=dtype)
+    E = np.random.default_rng(r).normal(0, 1e-3, (m, n)).astype(np.float32)
+    q0 = _q0(n, r)
+    Po, Qo, Do = orc.compress(G, E, q0[:, :r].copy(), r)
+    c = edgc.Context(0, 16, 128, m, n)
+    Pk, Qk, Dk, _ = gpu_compress(G, E, q0, r, c=c)
+    c.close()
+    assert np.array_equal(Dk, Do)
+    P64 = Pk.astype(np.float64)
+    assert np.abs(P64.T @ P64 - np.eye(r)).max() < 1e-5
+    # the tolerances of the test above
+    assert rel_fro(Pk @ Qk.T, Po @ Qo.T) < (2e-2 if dtype == "bf16" else 1e-3)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_strided_gradient_rows(dtype):
     G = gen.lowrank_plus_noise(192, 320, 32, 0.9, 1e-4, seed=5, dtype=dtype)
     check_step(G, None, _q0(320, 8), 8, dtype, ld=352)
