@@ -156,68 +156,76 @@ __device__ __forceinline__ void partial_item(const T* __restrict__ at, uint64_t 
 // Blocks share the union, not every buffer: a block's range touches one or two of the buffers of a transformer
 // stage (24 buffers, 143 K elements sampled: with every buffer split among all blocks each block walked all 24, 105 us
 // for the two kernels).
+// A round that would touch more than two buffers (norm weights and biases) is one round over all of them, in which every
+// thread finds its item's buffer; only such a round: with 31 short buffers beside one of 134 M fp32 elements the block that
+// holds them takes the large one's part as every other block does (387 -> 210 us for the estimate).
 template <typename T, int VEC, int BLOCK, typename Item, typename Elem, typename Round>
 __device__ __forceinline__ void walk_items(const EntGroup& grp, uint64_t begin, uint64_t end, bool ahead, Item&& item,
                                            Elem&& elem, Round&& round)
 {
     constexpr int U = 4;
     constexpr uint32_t STEP = U * BLOCK;
-    if (begin >= end) return;
-    // the buffers that hold items of the range: first[i + 1] > begin and first[i] < end; lane l has buffer l's first item
+    // lane l has buffer l's first item and the one after its last
     const uint32_t lane = threadIdx.x & 63u;
-    const uint64_t first_l = grp.first[min(lane, grp.count)];
-    uint32_t ti, t_end;
-    {
-        const bool in = lane < grp.count;
-        ti = static_cast<uint32_t>(__popcll(__ballot(in && grp.first[min(lane + 1u, grp.count)] <= begin)));
-        t_end = static_cast<uint32_t>(__popcll(__ballot(in && first_l < end)));
-    }
-    if constexpr (VEC > 1) {
-        // Many short buffers (norm weights and biases): every thread finds its item's buffer, so that a round spans
-        // them all.  The sampler's parameters are the same for every buffer of a group; base and length differ.
+    const bool in = lane < grp.count;
+    const uint64_t first_l = grp.first[min(lane, grp.count)], next_l = grp.first[min(lane + 1u, grp.count)];
+    for (uint64_t pos = begin; pos < end;) {
+        const uint64_t round_end = min(end, pos + STEP);
+        const uint32_t ti = static_cast<uint32_t>(__popcll(__ballot(in && next_l <= pos)));
+        const uint32_t t_end = static_cast<uint32_t>(__popcll(__ballot(in && first_l < round_end)));
         if (t_end - ti > 2) {
+            // The sampler's parameters are the same for every buffer of a group; base and length differ.
             const SampleGeom& geom = grp.geom[ti];
             const uint32_t ipc = geom.ipc, tl = min(lane, grp.count - 1u);
             const uint64_t n_l = grp.geom[tl].n, base_l = reinterpret_cast<uint64_t>(grp.base[tl]);
-            for (uint64_t rb = begin; rb < end; rb += STEP) {
-                uint4 raw[U];
-                const T* at[U];
-                uint64_t left[U];                      // elements from the item's first on
-                uint32_t t[U];
+            uint4 raw[U];
+            T one[U];
+            const T* at[U];
+            uint64_t left[U];                          // elements from the item's first on
+            uint32_t t[U];
 #pragma unroll
-                for (int u = 0; u < U; ++u) t[u] = ti;
-                for (uint32_t b = ti + 1; b < t_end; ++b) {
-                    const uint64_t fb = __shfl(first_l, b, 64);
+            for (int u = 0; u < U; ++u) t[u] = ti;
+            for (uint32_t b = ti + 1; b < t_end; ++b) {
+                const uint64_t fb = __shfl(first_l, b, 64);
 #pragma unroll
-                    for (int u = 0; u < U; ++u) t[u] += (rb + u * BLOCK + threadIdx.x >= fb) ? 1u : 0u;
-                }
+                for (int u = 0; u < U; ++u) t[u] += (pos + u * BLOCK + threadIdx.x >= fb) ? 1u : 0u;
+            }
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    raw[u] = make_uint4(0u, 0u, 0u, 0u);
-                    const uint64_t i = rb + u * BLOCK + threadIdx.x;
-                    const uint64_t n = __shfl(n_l, t[u], 64);
-                    ItemCursor cur;
-                    cur.init_each(i - __shfl(first_l, t[u], 64), ipc);
-                    const uint64_t e0 = cur.elem0(geom, VEC);
-                    at[u] = reinterpret_cast<const T*>(__shfl(base_l, t[u], 64)) + e0;
-                    left[u] = (i < end && e0 < n) ? n - e0 : 0;
+            for (int u = 0; u < U; ++u) {
+                raw[u] = make_uint4(0u, 0u, 0u, 0u);
+                one[u] = T(0);
+                const uint64_t i = pos + u * BLOCK + threadIdx.x;
+                const uint64_t n = __shfl(n_l, t[u], 64);
+                ItemCursor cur;
+                cur.init_each(i - __shfl(first_l, t[u], 64), ipc);
+                const uint64_t e0 = cur.elem0(geom, VEC);
+                at[u] = reinterpret_cast<const T*>(__shfl(base_l, t[u], 64)) + e0;
+                left[u] = (i < round_end && e0 < n) ? n - e0 : 0;
+                if constexpr (VEC > 1) {
                     if (left[u] >= VEC) raw[u] = *reinterpret_cast<const uint4*>(at[u]);
+                } else {
+                    if (left[u]) one[u] = *at[u];
                 }
+            }
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
+            for (int u = 0; u < U; ++u) {
+                if constexpr (VEC > 1) {
                     if (left[u] >= VEC) item(raw[u]);
                     else if (left[u]) partial_item<T, VEC>(at[u], left[u], elem);
+                } else {
+                    if (left[u]) elem(one[u]);
                 }
-                round();
             }
-            return;
+            round();
+            pos = round_end;
+            continue;
         }
-    }
-    for (; ti < t_end; ++ti) {
+        // else: buffer `ti` from here to its end, or the range's
         const SampleGeom& geom = grp.geom[ti];
         const T* __restrict__ g = static_cast<const T*>(grp.base[ti]);
         const uint64_t f0 = grp.first[ti];
-        const uint64_t lb = max(begin, f0) - f0, le = min(end, grp.first[ti + 1]) - f0;
+        const uint64_t lb = pos - f0, le = min(end, grp.first[ti + 1]) - f0;
+        pos = f0 + le;
         const uint32_t ipc = geom.ipc;
         ItemCursor cur;
         cur.init(lb, threadIdx.x, BLOCK, ipc);

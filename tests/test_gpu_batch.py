@@ -306,6 +306,33 @@ def test_stage_entropy_over_many_short_and_ragged_buffers(dtype, stride, chunk, 
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("off", [0, 1])
+def test_stage_entropy_short_buffers_beside_a_large_one(dtype, off):
+    """A block's range of several rounds that holds many short buffers and a part of a large one, at its front, in its
+    middle and at its end; with `off` no buffer is aligned and items are single elements."""
+    short = [768, 1, 2304, 65, 3072, 127, 4095, 64, 5, 333]
+    big = 9_000_003
+    c = edgc.Context(0, max_bins=65536, max_rank=4, max_rows=64, max_cols=64)
+    for k, sizes in enumerate([short + [big], [big] + short, short + [big // 2] + 2 * short + [big // 2 + 64]]):
+        bufs = [gen.laplace_mixture(n, 60 + i, dtype=dtype, scale=1e-3 * (1 + i % 3)) for i, n in enumerate(sizes)]
+        dev = []
+        for b in bufs:
+            room = torch.zeros(b.size + 8, dtype=torch.bfloat16 if dtype == "bf16" else torch.float32, device="cuda")
+            room[off:off + b.size] = to_dev(b)
+            dev.append(room[off:off + b.size])
+        for stride, chunk, bins in [(1, 64, 4096), (3, 64, 65536)]:
+            counts = torch.zeros(bins, dtype=torch.int64, device="cuda")
+            got = c.entropy_estimate(dev, stride, chunk, 9, k, bins, counts_out=counts)
+            want, n_s = _oracle_union_entropy(bufs, stride, chunk, 9, k, bins)
+            assert got.n_sampled == n_s == want.n_sampled, (k, bins)
+            assert (got.lo, got.hi) == (want.lo, want.hi), (k, bins)
+            assert np.array_equal(counts.cpu().numpy().astype(np.uint64), want.counts), (k, bins)
+            # fp64 sums over the same integer counts in another order
+            assert abs(got.H_bits - want.H_bits) <= 1e-5, (k, bins)
+    c.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("count", [1, 32, 33])
 def test_tensors_sent_as_they_stand_are_copied_whole_and_nothing_else(dtype, count):
     """Vectors and matrices too small to compress, at every alignment and row stride the copy distinguishes, up to one
