@@ -245,18 +245,27 @@ __device__ __forceinline__ void walk_items(const EntGroup& grp, uint64_t begin, 
                 round();
             };
             if (ahead && rb + STEP <= fast_end) {
-                uint4 ra[U], rc[U];
+                // No array is left undefined on any path: with exits between the two halves of the loop body the compiler
+                // reused registers of loads that one of the paths had yet to use (words 1 to 3 of three loads in four lost).
+                uint4 ra[U];
                 fetch(ra);
-                while (true) {
-                    rb += STEP;
-                    if (rb + STEP > fast_end) { use(ra); break; }
+                for (; rb + 3 * STEP <= fast_end; rb += 2 * STEP) {
+                    uint4 rc[U];
                     fetch(rc);
                     use(ra);
-                    rb += STEP;
-                    if (rb + STEP > fast_end) { use(rc); break; }
                     fetch(ra);
                     use(rc);
                 }
+                if (rb + 2 * STEP <= fast_end) {
+                    uint4 rc[U];
+                    fetch(rc);
+                    use(ra);
+#pragma unroll
+                    for (int u = 0; u < U; ++u) ra[u] = rc[u];
+                    rb += STEP;
+                }
+                use(ra);
+                rb += STEP;
             }
             for (; rb < le; rb += STEP) {
                 uint4 raw[U];

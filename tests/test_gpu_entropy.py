@@ -300,6 +300,40 @@ def test_sixteen_bit_counters_under_the_heaviest_contention(dtype):
     assert np.array_equal(counts.cpu().numpy().astype(np.uint64), ref.counts)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("rounds", [1, 2, 3, 4, 5, 6])
+def test_every_element_of_every_round_is_seen(dtype, rounds):
+    """Blocks whose whole range is exactly `rounds` rounds of unconditional loads, and one item more: the range pass (256 and
+    1024 threads) finds an extreme value wherever it stands in a round, and the counts of the histogram kernels (512 and 1024
+    threads, 16-bit counters) are those of all elements."""
+    tdt, vec = (torch.bfloat16, 8) if dtype == "bf16" else (torch.float32, 4)
+    gen_ = torch.Generator(device="cuda").manual_seed(rounds)
+    plain, one_read = _context_with(EDGC_TUNE_PATTERN=0), _context_with(EDGC_TUNE_PATTERN_MIN=0)
+    counts = torch.empty(65536, dtype=torch.int64, device="cuda")
+    for blocks, threads, extra in [(1024, 256, 0), (1024, 256, 1), (256, 1024, 0), (256, 1024, 4096)]:
+        items = blocks * threads * 4 * rounds + 4096 + extra            # the last chunk is read with checks
+        x = (torch.rand(items * vec, generator=gen_, device="cuda") - 0.5).to(tdt)
+        for c, bins in [(plain, 4096), (plain, 40000), (one_read, 4096), (one_read, 65536)]:
+            got = c.entropy_estimate(x, 1, 64, 0, 0, bins, None, counts[:bins])
+            xf = x.float()
+            lo, hi = xf.min(), xf.max()
+            assert (got.lo, got.hi, got.n_sampled) == (float(lo), float(hi), x.numel())
+            scale = torch.tensor(float(bins), dtype=torch.float32) / (hi - lo).cpu()
+            want = torch.bincount(((xf - lo) * scale.cuda()).long().clamp_(0, bins - 1), minlength=bins)
+            assert torch.equal(counts[:bins], want), (blocks, threads, extra, bins)
+        if blocks == 1024:
+            for at in range(4 * rounds):                                # every load of a block's rounds, every element of it
+                for e in range(vec):
+                    k = ((3 * 4 * rounds + at) * threads + (37 * at + 11 * e) % threads) * vec + e
+                    old = x[k].clone()
+                    x[k] = -2.0 if e % 2 else 2.0
+                    got = plain.entropy_estimate(x, 1, 64, 0, 0, 256)
+                    assert (got.lo == -2.0) if e % 2 else (got.hi == 2.0), (at, e)
+                    x[k] = old
+    plain.close()
+    one_read.close()
+
+
 def to_host_any(x):
     if x.dtype == torch.bfloat16:
         return x.view(torch.int16).cpu().numpy().view(np.uint16)
