@@ -334,6 +334,33 @@ def test_every_element_of_every_round_is_seen(dtype, rounds):
     one_read.close()
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("off", [0, 1])
+def test_sixteen_bit_counters_swept_across_short_and_large_buffers(dtype, off):
+    """31 short buffers of one value with ragged ends, then a large one of two values: every round of a block, over one
+    buffer or over many, adds as much to one field as a round can, and the fields are swept several times per block.  With
+    `off` items are single elements, of which eight rounds go between two sweeps."""
+    c = _context_with(EDGC_TUNE_PATTERN_MIN=0)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    sizes = [4000 + 67 * i for i in range(31)] + [20_000_003]
+    dev = []
+    for n in sizes:
+        x = torch.full((n + 8,), 0.375, device="cuda", dtype=tdt)[off:off + n]
+        if n > 1 << 20:
+            x[1::3] = -2.5
+        dev.append(x)
+    host = [to_host_any(x) for x in dev]
+    for stride, chunk, bins in [(1, 64, 65536), (2, 64, 65536), (1, 64, 20000)]:
+        counts = torch.empty(bins, dtype=torch.int64, device="cuda")
+        got = c.entropy_estimate(dev, stride, chunk, 5, 1, bins, None, counts)
+        cat = np.concatenate([h[orc.sample_indices(h.size, stride, chunk, 5, 1)] for h in host])
+        ref = orc.entropy(cat, 1, 1, 0, 0, bins)
+        assert (got.lo, got.hi, got.n_sampled) == (ref.lo, ref.hi, cat.size)
+        assert np.array_equal(counts.cpu().numpy().astype(np.uint64), ref.counts), (stride, bins)
+        assert abs(got.H_bits - ref.H_bits) <= H_TOL
+    c.close()
+
+
 def to_host_any(x):
     if x.dtype == torch.bfloat16:
         return x.view(torch.int16).cpu().numpy().view(np.uint16)
