@@ -2148,25 +2148,28 @@ __global__ __launch_bounds__(256, 2) void k_pass_p_deferred_narrow(const Group g
 // access that the tensor's pointers, row length and strides allow; a contiguous tensor may end inside a unit.
 template <typename U>
 __device__ __forceinline__ void copy_units(const unsigned char* __restrict__ src, unsigned char* __restrict__ dst,
-                                           uint64_t row_bytes, uint64_t ld_src, uint64_t ld_dst, uint32_t m, uint64_t first)
+                                           uint64_t row_bytes, uint64_t ld_src, uint64_t ld_dst, uint32_t m, uint64_t first,
+                                           uint64_t stride)
 {
     constexpr int N = kCopyUnits / 256;
     const uint64_t whole = row_bytes / sizeof(U), total = whole * m;      // units
-    U v[N] = {};
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
-        const uint64_t i = first + threadIdx.x + k * 256u, row = m == 1 ? 0 : i / whole;
-        if (i < total) v[k] = *reinterpret_cast<const U*>(src + row * ld_src + (i - row * whole) * sizeof(U));
-    }
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
-        const uint64_t i = first + threadIdx.x + k * 256u, row = m == 1 ? 0 : i / whole;
-        if (i < total) *reinterpret_cast<U*>(dst + row * ld_dst + (i - row * whole) * sizeof(U)) = v[k];
-    }
     // what the last unit of a contiguous tensor leaves: 16-bit pieces, one per thread of its first block
     const uint64_t at = whole * sizeof(U) + 2u * threadIdx.x;
     if (first == 0 && m == 1 && at < row_bytes)
         *reinterpret_cast<uint16_t*>(dst + at) = *reinterpret_cast<const uint16_t*>(src + at);
+    for (; first < total; first += stride) {
+        U v[N] = {};
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            const uint64_t i = first + threadIdx.x + k * 256u, row = m == 1 ? 0 : i / whole;
+            if (i < total) v[k] = *reinterpret_cast<const U*>(src + row * ld_src + (i - row * whole) * sizeof(U));
+        }
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            const uint64_t i = first + threadIdx.x + k * 256u, row = m == 1 ? 0 : i / whole;
+            if (i < total) *reinterpret_cast<U*>(dst + row * ld_dst + (i - row * whole) * sizeof(U)) = v[k];
+        }
+    }
 }
 
 __global__ __launch_bounds__(256) void k_copy_rows(const CopyGroup grp)
@@ -2175,11 +2178,12 @@ __global__ __launch_bounds__(256) void k_copy_rows(const CopyGroup grp)
     for (uint32_t i = 1; i < grp.count; ++i) t += (blockIdx.x >= grp.t[i].first) ? 1u : 0u;
     const CopyArgs& c = grp.t[t];
     const uint64_t first = static_cast<uint64_t>(blockIdx.x - c.first) * kCopyUnits;
+    const uint64_t stride = static_cast<uint64_t>(c.blocks) * kCopyUnits;
     switch (c.unit) {
-    case 16: copy_units<uint4>(c.src, c.dst, c.row_bytes, c.ld_src, c.ld_dst, c.m, first); break;
-    case 8: copy_units<uint2>(c.src, c.dst, c.row_bytes, c.ld_src, c.ld_dst, c.m, first); break;
-    case 4: copy_units<uint32_t>(c.src, c.dst, c.row_bytes, c.ld_src, c.ld_dst, c.m, first); break;
-    default: copy_units<uint16_t>(c.src, c.dst, c.row_bytes, c.ld_src, c.ld_dst, c.m, first); break;
+    case 16: copy_units<uint4>(c.src, c.dst, c.row_bytes, c.ld_src, c.ld_dst, c.m, first, stride); break;
+    case 8: copy_units<uint2>(c.src, c.dst, c.row_bytes, c.ld_src, c.ld_dst, c.m, first, stride); break;
+    case 4: copy_units<uint32_t>(c.src, c.dst, c.row_bytes, c.ld_src, c.ld_dst, c.m, first, stride); break;
+    default: copy_units<uint16_t>(c.src, c.dst, c.row_bytes, c.ld_src, c.ld_dst, c.m, first, stride); break;
     }
 }
 
@@ -2276,13 +2280,12 @@ int CopyList::add(const void* src, uint64_t ld_src, void* dst, uint64_t ld_dst, 
     if (c.m > 1) bits |= c.row_bytes | c.ld_src | c.ld_dst;
     c.unit = 16;
     while (c.unit > elem_bytes && bits % c.unit) c.unit /= 2;
-    const uint64_t units = (c.row_bytes + c.unit - 1) / c.unit * c.m;
-    const uint64_t nb = (units + kCopyUnits - 1) / kCopyUnits;
-    if (nb > 0x7fffffffull) return fail(ctx, EDGC_EINVAL, "a tensor that is sent as it stands is too large");
-    if (g.count == kMaxCopies || blocks + nb > 0x7fffffffull)
+    static_assert(static_cast<uint64_t>(kMaxCopies) * copy_blocks(~0ull >> 16) * 256 < (1ull << 32), "threads of a launch");
+    c.blocks = copy_blocks((c.row_bytes + c.unit - 1) / c.unit * c.m);
+    if (g.count == kMaxCopies)
         if (int rc = flush(st)) return rc;
-    c.first = static_cast<uint32_t>(blocks);
-    blocks += nb;
+    c.first = blocks;
+    blocks += c.blocks;
     g.t[g.count++] = c;
     return EDGC_OK;
 }
@@ -2290,7 +2293,7 @@ int CopyList::add(const void* src, uint64_t ld_src, void* dst, uint64_t ld_dst, 
 int CopyList::flush(hipStream_t st)
 {
     if (g.count == 0) return EDGC_OK;
-    k_copy_rows<<<static_cast<uint32_t>(blocks), 256, 0, st>>>(g);
+    k_copy_rows<<<blocks, 256, 0, st>>>(g);
     g.count = 0;
     blocks = 0;
     EDGC_HIP_TRY(ctx, hipGetLastError());

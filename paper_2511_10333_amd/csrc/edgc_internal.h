@@ -260,12 +260,18 @@ int launch_compress(edgc_ctx* ctx, Group& g, const TensorScratch* cap, edgc_dtyp
 int launch_decompress(edgc_ctx* ctx, Group& g, edgc_dtype dt, hipStream_t st);
 
 // Copies of tensors that are sent as they stand, collected and launched together (compress.hip).
-constexpr uint32_t kMaxCopies = 32, kCopyUnits = 1024;      // tensors per launch; units per block
+constexpr uint32_t kMaxCopies = 32, kCopyUnits = 1024;      // tensors per launch; units that a block copies at a time
+// Blocks of 256 threads for one tensor: a launch takes fewer than 2^32 threads, so beyond 2^18 blocks each copies several runs.
+constexpr uint32_t copy_blocks(uint64_t units)
+{
+    const uint64_t runs = (units + kCopyUnits - 1) / kCopyUnits;
+    return runs < (1u << 18) ? static_cast<uint32_t>(runs) : 1u << 18;
+}
 struct CopyArgs {
     const unsigned char* src;
     unsigned char* dst;
     uint64_t row_bytes, ld_src, ld_dst;     // bytes
-    uint32_t m, unit, first;                // rows; bytes per access; first block
+    uint32_t m, unit, first, blocks;        // rows; bytes per access; first block; blocks
 };
 struct CopyGroup {
     uint32_t count;
@@ -274,7 +280,7 @@ struct CopyGroup {
 struct CopyList {
     edgc_ctx* ctx;
     CopyGroup g{};
-    uint64_t blocks = 0;
+    uint32_t blocks = 0;
     int add(const void* src, uint64_t ld_src, void* dst, uint64_t ld_dst, uint32_t m, uint32_t n, uint32_t elem_bytes,
             hipStream_t st);                // strides in elements
     int flush(hipStream_t st);

@@ -362,6 +362,22 @@ def test_tensors_sent_as_they_stand_are_copied_whole_and_nothing_else(dtype, cou
         assert written == int((t.grad != 7.0).sum())
 
 
+def test_a_tensor_of_more_runs_than_blocks_is_copied_whole():
+    """2^28 + 5 elements at 2-byte alignment: a run more than the 2^18 blocks a tensor gets, so one block copies two."""
+    n = (1 << 28) + 5
+    src, dst = (torch.empty(n + 8, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    src.view(torch.int16).random_(-30000, 30000)
+    dst.fill_(7.0)
+    t = edgc.Tensor(src[1:n + 1], dst[1:n + 1])
+    c = edgc.Context(0, max_bins=16, max_rank=4, max_rows=64, max_cols=64)
+    c.reserve_batch([(1, n)])
+    c.decompress_batch([t], 4)
+    torch.cuda.synchronize()
+    assert torch.equal(dst[1:n + 1].view(torch.int16), src[1:n + 1].view(torch.int16))
+    assert float(dst[0]) == 7.0 and bool((dst[n + 1:] == 7.0).all())
+    c.close()
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_stage_entropy_large_union_sample(dtype):
     """A union sample large enough for the launch shapes of large samples (one block of 1024 threads

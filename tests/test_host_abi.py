@@ -58,6 +58,22 @@ def test_scratch_of_the_inverse_factor_holds_every_tile_the_kernels_store(tmp_pa
         assert sizes[r - 1] >= t * (t + 1) // 2 * 256, f"rank {r}"
 
 
+def test_a_copy_launch_stays_below_the_limit_of_threads(tmp_path):
+    """Tensors of any size that are sent as they stand go into one launch, of fewer than 2^32 threads."""
+    src = tmp_path / "copies.cpp"
+    src.write_text('#include <cstdio>\n#include "edgc_internal.h"\n'
+                   'int main() { for (int k = 0; k < 48; ++k) for (unsigned long long u : {(1ull << k) - 1, 1ull << k, (1ull << k) + 1}) '
+                   'std::printf("%llu %u %u %u\\n", u, edgc::copy_blocks(u), edgc::kMaxCopies, edgc::kCopyUnits); }\n')
+    exe = tmp_path / "copies"
+    subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-w", "-I/opt/rocm/include",
+                    "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(ROOT, "paper_2511_10333_amd", "csrc"),
+                    str(src), "-o", str(exe)], check=True)
+    for line in subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.splitlines():
+        units, blocks, tensors, run = map(int, line.split())
+        assert blocks * 256 * tensors < 2 ** 32, line
+        assert (blocks > 0) == (units > 0) and (blocks - 1) * run < max(units, 1), line     # no block without work
+
+
 def _both(prm_kwargs, windows):
     st_o, st_p = orc.RankState(), edgc.RankState()
     out = []
