@@ -6,6 +6,14 @@ import json
 import time
 
 
+def reads_of_sample(kernels, bins: int) -> int:
+    """How often one estimate without a given range reads its sample, from the names of its kernels: the range pass (not
+    for bf16 counted by bit pattern) and one binning pass (two for fp32 on more than 32768 bins without the 16-bit
+    counters); a sample that one block holds is read by that block twice."""
+    return (("k_minmax" in kernels) + ("k_wide_hist" in kernels) + 2 * ("k_estimate_one" in kernels)
+            + ((2 if bins > 32768 else 1) if "k_hist" in kernels else 0))
+
+
 def entropy_sweep(args, torch, edgc, metric, hbm_peak_gbs) -> int:
     """The entropy-only workload: one flat buffer of 1e9 elements (fp32, then bf16), Laplace(0, 1e-3)
     with 0.1 % of the values at 100 times the scale, generated on the device; sampling strides 1000,
@@ -57,11 +65,7 @@ def entropy_sweep(args, torch, edgc, metric, hbm_peak_gbs) -> int:
                                 gbs=round(v["bytes"] / (v["total_ms"] * 1e-3) / 1e9, 1))
                         for k, v in ks.items() if v["launches"] and v["total_ms"] > 0}
                 sample_bytes = res.n_sampled * esz
-                # reads of the sample: the range pass (not for bf16 counted by bit pattern) and one binning pass
-                # (two for fp32 on more than 32768 bins without the 16-bit counters)
-                live = {k: v for k, v in kern.items() if v["avg_us"] >= 4.0 or k.startswith("k_wide")}
-                reads = (1 if "k_minmax" in live else 0) + (1 if "k_wide_hist" in live else 0) + \
-                        ((2 if bins > 32768 else 1) if "k_hist" in live else 0)
+                reads = reads_of_sample(kern, bins)
                 cell = dict(dtype=dtype, stride=stride, bins=bins, n_sampled=res.n_sampled, ms=round(ms, 4),
                             gradient_gbs=round(n * esz / (ms * 1e-3) / 1e9, 1), reads_of_sample=reads,
                             sample_gbs=round(reads * sample_bytes / (ms * 1e-3) / 1e9, 1),
@@ -70,7 +74,7 @@ def entropy_sweep(args, torch, edgc, metric, hbm_peak_gbs) -> int:
                 if (dtype == "f32" and stride == 1 and bins == 4096) or headline is None:
                     headline = (cell, ms, ks, reps)
     cell, ms, ks, reps = headline
-    dom = max((k for k in ("k_minmax", "k_hist", "k_wide_hist") if k in ks and ks[k]["launches"]),
+    dom = max((k for k in ("k_minmax", "k_hist", "k_wide_hist", "k_estimate_one") if k in ks and ks[k]["launches"]),
               key=lambda k: ks[k]["total_ms"])
     achieved = ks[dom]["bytes"] / (ks[dom]["total_ms"] * 1e-3) / 1e9
     pa = torch.ones(1 << 28, dtype=torch.float32, device="cuda")

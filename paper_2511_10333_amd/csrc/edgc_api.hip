@@ -12,7 +12,7 @@ namespace edgc {
 const char* const kKernelNames[KID_COUNT] = {
     "k_set_range", "k_minmax", "k_hist", "k_sample_indices", "k_init_q", "k_pass_p",
     "k_reduce_gram", "k_gram_sum", "k_chol", "k_apply", "k_pass_q", "k_reduce_q", "k_decompress",
-    "k_pass_p_deferred", "k_wide_hist", "k_wide_reduce"};
+    "k_pass_p_deferred", "k_wide_hist", "k_wide_reduce", "k_estimate_one"};
 }
 
 namespace {

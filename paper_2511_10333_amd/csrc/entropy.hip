@@ -1021,7 +1021,7 @@ static int run_entropy(edgc_ctx* ctx, const EntScratch& s, const EntGroup& g, ui
     const uint32_t ny = (bins + bins_local - 1) / bins_local;
     const size_t lds = static_cast<size_t>(bins_local << rep_shift) * sizeof(uint32_t);
     if (bins <= 16384 && !by_pattern && g.n_items <= 4u * kOneBlock) {
-        EDGC_LAUNCH(ctx, st, KID_HIST, sample_bytes, 0.0,
+        EDGC_LAUNCH(ctx, st, KID_ESTIMATE_ONE, sample_bytes * (range ? 1.0 : 2.0), 0.0,
                     k_estimate_one<T, VEC><<<1, kOneBlock, lds, st>>>(g, range ? 1 : 0, range ? range[0] : 0.0f,
                                                                       range ? range[1] : 0.0f, bins, rep_shift, counts, res));
         EDGC_HIP_TRY(ctx, hipGetLastError());

@@ -57,3 +57,14 @@ def test_counters_summary_separates_launches_that_did_nothing(tmp_path):
     assert r.returncode == 0, r.stderr
     row = [l for l in out.read_text().splitlines() if l.startswith("| `k_hist<float, 4, 1024>`")]
     assert row == ["| `k_hist<float, 4, 1024>` | 2 | 1 | 2000 |"]      # two live launches, one idle, mean of the live ones
+
+
+def test_reads_of_a_sample_follow_from_the_kernels_however_short_they_are():
+    sys.path.insert(0, ROOT)
+    from bench_entropy import reads_of_sample
+    short = {"avg_us": 2.0, "gbs": 1.0}
+    assert reads_of_sample({"k_minmax": short, "k_hist": short}, 4096) == 2
+    assert reads_of_sample({"k_minmax": short, "k_hist": short}, 65536) == 3
+    assert reads_of_sample({"k_minmax": short, "k_wide_hist": short, "k_wide_reduce": short}, 65536) == 2
+    assert reads_of_sample({"k_wide_hist": short, "k_wide_reduce": short}, 4096) == 1
+    assert reads_of_sample({"k_estimate_one": short}, 256) == 2
