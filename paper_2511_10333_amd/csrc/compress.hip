@@ -2721,11 +2721,6 @@ static int decompress_impl(edgc_ctx* ctx, Group& g, hipStream_t st)
     const uint32_t target = static_cast<uint32_t>(ctx->num_cu) * per_cu;
     uint32_t tgt[kMaxGroup];
     share_targets(g, target, tgt);
-    // Short blocks for the general kernel: many rounds of them keep every CU busy to the end.  Stored form, per pass: hidden-4096
-    // fp32 block at rank 64 with 24 stages per block 1276 us, 8: 1208, 6: 1215, 4: 1199 (the kernel 498 -> 425 us, 5.7 TB/s,
-    // what a plain copy reaches); at rank 16 1229 / 1168 (8) / 1148 (4); 8192 x 8192 at rank 64 with 8 stages 396, 4: 400,
-    // 1: 411; hidden-3072 at rank 128 with 14 stages 866, 7: 844, 5: 862.
-    const uint32_t max_sps = use_full ? ~0u : 8u;
     bool vec = true;
     uint32_t blocks = 0;
     double bytes = 0.0, flops = 0.0;
@@ -2733,7 +2728,7 @@ static int decompress_impl(edgc_ctx* ctx, Group& g, hipStream_t st)
         TensorArgs& t = g.t[i];
         const uint32_t RB = cdiv(t.m, rows_per_block), stages = cdiv(t.n, 64);
         uint32_t JS = std::max(1u, std::min(stages, tgt[i] / RB));
-        const uint32_t sps = std::min(cdiv(stages, JS), max_sps);
+        const uint32_t sps = decompress_step(stages, JS, use_full || ctx->tune_d != 0);
         JS = cdiv(stages, sps);
         t.d0 = sps;
         t.d1 = JS;

@@ -29,6 +29,19 @@ int main()
 """
 
 
+DECOMPRESS = r"""
+#include <cstdio>
+#include "pass_plan.h"
+int main()
+{
+    for (unsigned stages = 1; stages <= 300; ++stages)
+        for (unsigned splits = 1; splits <= stages; ++splits)
+            std::printf("%u %u %u %u\n", stages, splits, edgc::decompress_step(stages, splits, false),
+                        edgc::decompress_step(stages, splits, true));
+}
+"""
+
+
 @pytest.fixture(scope="module")
 def plan(tmp_path_factory):
     d = tmp_path_factory.mktemp("plan")
@@ -92,3 +105,13 @@ def test_p_pass_plan_fits_the_scratch_it_was_given(plan):
     for g, step in zip(groups, plan(groups)):
         (_, k, room), = g[0]
         assert _cdiv(k, step) <= room, g
+
+
+def test_decompress_plan_is_the_one_asked_for(tmp_path):
+    """Blocks of at most eight stages by the rule; with a count of blocks per CU asked for, its splits and no more."""
+    (tmp_path / "d.cpp").write_text(DECOMPRESS)
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I" + os.path.join(ROOT, "paper_2511_10333_amd", "csrc"),
+                    str(tmp_path / "d.cpp"), "-o", str(tmp_path / "d")], check=True)
+    for line in subprocess.run([str(tmp_path / "d")], check=True, capture_output=True, text=True).stdout.splitlines():
+        stages, splits, rule, asked = map(int, line.split())
+        assert asked == _cdiv(stages, splits) and rule == min(asked, 8)
