@@ -2508,7 +2508,9 @@ static int run_orthonormalise(edgc_ctx* ctx, Group& g, const TensorScratch* cap,
     // P^ = P R^-1 and its transposed bf16 copy.  Above rank 64 the 72 KB of R^-1 tiles leave room for one
     // block per CU, and a block's time is its share of fp64 MFMA work (144 per 16 rows, on four SIMDs):
     // blocks of 64 rows while they fit in one round over the CUs, otherwise of 128, or of 144 or 160 where that saves a
-    // second, nearly empty round (35840 rows of the hidden-5120 block: 280 blocks of 128 rows 42 us, 251 of 144 33)
+    // second, nearly empty round (35840 rows of the hidden-5120 block: 280 blocks of 128 rows 42 us, 251 of 144 33; per pass with
+    // 128 / 144 / 160 rows: 35000 x 1024 fp32 387 / 377 / 377 us, 40000 x 1024 439 / 449 / 430, bf16 420 / 430 / 410, hidden-5632
+    // bf16 block 1524 / 1535 / 1513; from 40961 rows on no height that LDS holds does: hidden-6144 fp32 2368 / 2384 / 2378)
     uint32_t apply_waves = 4;
     if (t16 == 8 && apply_blocks > static_cast<uint32_t>(ctx->num_cu)) {
         apply_waves = 8;

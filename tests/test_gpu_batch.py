@@ -362,6 +362,45 @@ def test_tensors_sent_as_they_stand_are_copied_whole_and_nothing_else(dtype, cou
         assert written == int((t.grad != 7.0).sum())
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("r", [65, 100, 128])
+def test_blocks_of_every_height_of_the_multiply_by_the_inverse_factor(dtype, r, monkeypatch):
+    """Above rank 64 that multiply takes 64, 128, 144 or 160 rows per block, by the rows of the launch.  A row's result does
+    not depend on the block it is in, so all four give the same bits: rows that end inside a block, inside the 64 rows that
+    a tensor is padded to, and at their edges."""
+    shapes = [(145, 2600), (161, 2500), (320, 1000), (333, 900), (576, 700), (641, 650)]
+    assert not any(edgc.tensor_bypassed(m, n, r) for m, n in shapes)
+    mats = [gen.lowrank_plus_noise(m, n, 140, 0.97, 1e-4, seed=m + r, dtype=dtype) for m, n in shapes]
+    q0 = []
+    for i, (m, n) in enumerate(shapes):
+        q = np.zeros((n, (r + 3) // 4 * 4), dtype=np.float32)
+        orc.init_q(q, 0, r, 50 + i)
+        q0.append(q)
+    first = None
+    for waves in (4, 8, 9, 10):
+        monkeypatch.setenv("EDGC_TUNE_APPLY", str(waves))
+        c = edgc.Context(0, max_bins=16, max_rank=128, max_rows=64, max_cols=64)
+        c.reserve_batch(shapes)
+        ts = []
+        for g, q in zip(mats, q0):
+            gd = to_dev(g)
+            P = torch.full((g.shape[0], q.shape[1]), 7.0, device="cuda")
+            ts.append(edgc.Tensor(gd, torch.empty_like(gd), torch.empty(g.shape, device="cuda"), to_dev(q), P, True))
+        c.compress_batch(ts, r)
+        torch.cuda.synchronize()
+        got = [(t.P[:, :r].clone(), t.Q[:, :r].clone()) for t in ts]
+        c.close()
+        if first is None:
+            first = got
+            for g, q, (P, Q) in zip(mats, q0, got):
+                Po, Qo, _ = orc.compress(g, None, q[:, :r].copy(), r)
+                P64 = to_host(P).astype(np.float64)
+                assert np.abs(P64.T @ P64 - np.eye(r)).max() < 1e-5
+                assert rel_fro(to_host(P) @ to_host(Q).T, Po @ Qo.T) <= TOL[dtype]
+        for a, b in zip(first, got):
+            assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1]), waves
+
+
 def test_a_tensor_of_more_runs_than_blocks_is_copied_whole():
     """2^28 + 5 elements at 2-byte alignment: a run more than the 2^18 blocks a tensor gets, so one block copies two."""
     n = (1 << 28) + 5
