@@ -187,7 +187,7 @@ def cmd_cells(a) -> int:
                 "| dtype | stride | bins | sampled | ms | reads | sample GB/s | buffer GB/s | kernels (us) |",
                 "|---|---|---|---|---|---|---|---|---|"])
     for c in d["cells"]:
-        ks = ", ".join("`%s` %.1f" % (k, v["avg_us"]) for k, v in c["kernels"].items() if v["avg_us"] >= 4.0)
+        ks = ", ".join("`%s` %.1f" % (k, v["avg_us"]) for k, v in c["kernels"].items())
         out.append("| %s | %d | %d | %d | %.4f | %d | %.0f | %.0f | %s |" % (
             c["dtype"], c["stride"], c["bins"], c["n_sampled"], c["ms"], c["reads_of_sample"], c["sample_gbs"],
             c["gradient_gbs"], ks))

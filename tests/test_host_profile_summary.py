@@ -59,6 +59,18 @@ def test_counters_summary_separates_launches_that_did_nothing(tmp_path):
     assert row == ["| `k_hist<float, 4, 1024>` | 2 | 1 | 2000 |"]      # two live launches, one idle, mean of the live ones
 
 
+def test_cells_summary_lists_every_kernel_however_short(tmp_path):
+    import json
+    cell = {"dtype": "f32", "stride": 1000, "bins": 256, "n_sampled": 10, "ms": 0.02, "reads_of_sample": 2, "sample_gbs": 1.0,
+            "gradient_gbs": 2.0, "kernels": {"k_minmax": {"avg_us": 3.9}, "k_hist": {"avg_us": 10.3}}}
+    (tmp_path / "c.json").write_text(json.dumps({"cells": [cell]}) + "\n")
+    out = tmp_path / "c.md"
+    r = subprocess.run([sys.executable, "-m", "paper_2511_10333_amd.profile_summary", "cells", "--json", str(tmp_path / "c.json"),
+                        "--title", "t", "--out", str(out)], cwd=ROOT, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    assert "| f32 | 1000 | 256 | 10 | 0.0200 | 2 | 1 | 2 | `k_minmax` 3.9, `k_hist` 10.3 |" in out.read_text()
+
+
 def test_reads_of_a_sample_follow_from_the_kernels_however_short_they_are():
     sys.path.insert(0, ROOT)
     from bench_entropy import reads_of_sample
