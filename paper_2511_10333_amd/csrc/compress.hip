@@ -2300,8 +2300,6 @@ int CopyList::flush(hipStream_t st)
     return EDGC_OK;
 }
 
-// The blocks a pass aims at are shared among the tensors of a group in proportion to their
-// size (at least one each).
 // Whether the Q-pass reads D with non-temporal loads: D is not read again before the next step in the deferred form, and
 // in the stored form the decompress finds nothing of a D that exceeds the 256 MB last-level cache.  Per pass over cold
 // inputs, cached / streamed: deferred, hidden-2048 fp32 block (201 MB) 253 / 236 us, hidden-3584 shard (154 MB) 214 / 200,
@@ -2317,6 +2315,8 @@ static uint32_t group_streams(const edgc_ctx* ctx, const Group& g)
     return bytes >= (g.defer ? 96.0 : 256.0) * 1024 * 1024 ? 1u : 0u;
 }
 
+// The blocks the Q-pass and the decompress aim at are shared among the tensors of a group in proportion to their
+// size (at least one each).
 static void share_targets(const Group& g, uint32_t target, uint32_t (&out)[kMaxGroup])
 {
     double total = 0.0;
