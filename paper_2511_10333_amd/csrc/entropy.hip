@@ -168,11 +168,18 @@ __device__ __forceinline__ void walk_items(const EntGroup& grp, uint64_t begin, 
     // lane l has buffer l's first item and the one after its last
     const uint32_t lane = threadIdx.x & 63u;
     const bool in = lane < grp.count;
-    const uint64_t first_l = grp.first[min(lane, grp.count)], next_l = grp.first[min(lane + 1u, grp.count)];
+    uint64_t first_l = 0, next_l = 0;
+    if (grp.count > 1) {                               // (one buffer: nothing to look up, and no load to wait for)
+        first_l = grp.first[min(lane, grp.count)];
+        next_l = grp.first[min(lane + 1u, grp.count)];
+    }
     for (uint64_t pos = begin; pos < end;) {
         const uint64_t round_end = min(end, pos + STEP);
-        const uint32_t ti = static_cast<uint32_t>(__popcll(__ballot(in && next_l <= pos)));
-        const uint32_t t_end = static_cast<uint32_t>(__popcll(__ballot(in && first_l < round_end)));
+        uint32_t ti = 0, t_end = 1;
+        if (grp.count > 1) {
+            ti = static_cast<uint32_t>(__popcll(__ballot(in && next_l <= pos)));
+            t_end = static_cast<uint32_t>(__popcll(__ballot(in && first_l < round_end)));
+        }
         if (t_end - ti > 2) {
             // The sampler's parameters are the same for every buffer of a group; base and length differ.
             const SampleGeom& geom = grp.geom[ti];
