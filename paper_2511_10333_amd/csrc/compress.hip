@@ -2175,7 +2175,8 @@ __device__ __forceinline__ void copy_units(const unsigned char* __restrict__ src
 __global__ __launch_bounds__(256) void k_copy_rows(const CopyGroup grp)
 {
     uint32_t t = 0;
-    for (uint32_t i = 1; i < grp.count; ++i) t += (blockIdx.x >= grp.t[i].first) ? 1u : 0u;
+#pragma unroll
+    for (uint32_t i = 1; i < kMaxCopies; ++i) t += (blockIdx.x >= grp.first[i]) ? 1u : 0u;
     const CopyArgs& c = grp.t[t];
     const uint64_t first = static_cast<uint64_t>(blockIdx.x - c.first) * kCopyUnits;
     const uint64_t stride = static_cast<uint64_t>(c.blocks) * kCopyUnits;
@@ -2284,7 +2285,7 @@ int CopyList::add(const void* src, uint64_t ld_src, void* dst, uint64_t ld_dst, 
     c.blocks = copy_blocks((c.row_bytes + c.unit - 1) / c.unit * c.m);
     if (g.count == kMaxCopies)
         if (int rc = flush(st)) return rc;
-    c.first = blocks;
+    c.first = g.first[g.count] = blocks;
     blocks += c.blocks;
     g.t[g.count++] = c;
     return EDGC_OK;
@@ -2293,6 +2294,7 @@ int CopyList::add(const void* src, uint64_t ld_src, void* dst, uint64_t ld_dst, 
 int CopyList::flush(hipStream_t st)
 {
     if (g.count == 0) return EDGC_OK;
+    std::fill(g.first + g.count, g.first + kMaxCopies, ~0u);
     k_copy_rows<<<blocks, 256, 0, st>>>(g);
     g.count = 0;
     blocks = 0;
@@ -2375,7 +2377,7 @@ static int run_pass_p(edgc_ctx* ctx, Group& g, const TensorScratch* cap, bool wi
         t.d0 = kper;
         t.d1 = S;
         t.sp = S;
-        t.first = blocks;
+        t.first = g.first[i] = blocks;
         blocks += RB * S;
         // 16-byte accesses; the kernel of the deferred form reads and writes two columns per lane
         const uint32_t w = (use_wide || use_full) ? 2u : 4u;
@@ -2450,7 +2452,7 @@ static int run_orthonormalise(edgc_ctx* ctx, Group& g, const TensorScratch* cap,
             return fail(ctx, EDGC_EINVAL, "Gram scratch too small for this shape");
         t.d0 = cpb;
         t.nb = NB;
-        t.first = blocks;
+        t.first = g.first[i] = blocks;
         blocks += NB;
         const double mr = static_cast<double>(t.m) * r;
         bytes += 4.0 * mr * (t.sp + 1);
@@ -2484,7 +2486,7 @@ static int run_orthonormalise(edgc_ctx* ctx, Group& g, const TensorScratch* cap,
         TensorArgs& t = g.t[i];
         const bool summed = t.nb > max_sets;
         t.d0 = t.nb;
-        t.first = blocks;
+        t.first = g.first[i] = blocks;
         if (summed) {
             blocks += cdiv(ne, 64);
             bytes += 8.0 * ne * t.nb;
@@ -2526,7 +2528,7 @@ static int run_orthonormalise(edgc_ctx* ctx, Group& g, const TensorScratch* cap,
     bytes = flops = 0.0;
     for (uint32_t i = 0; i < g.count; ++i) {
         TensorArgs& t = g.t[i];
-        t.first = blocks;
+        t.first = g.first[i] = blocks;
         blocks += cdiv(t.m_pad, apply_rows);
         const double mr = static_cast<double>(t.m) * r;
         bytes += 8.0 * mr + 2.0 * NP * RP * t.m_pad;
@@ -2605,7 +2607,7 @@ static int run_pass_q(edgc_ctx* ctx, Group& g, const TensorScratch* cap, hipStre
         t.d0 = sps;
         t.d1 = CB;
         t.sq = S;
-        t.first = blocks;
+        t.first = g.first[i] = blocks;
         blocks += CB * S;
         vec = vec && (t.n % NT == 0) && (reinterpret_cast<uintptr_t>(t.E) % 16 == 0);
         bytes += 4.0 * t.m * t.n;
@@ -2627,7 +2629,7 @@ static int run_pass_q(edgc_ctx* ctx, Group& g, const TensorScratch* cap, hipStre
     bytes = 0.0;
     for (uint32_t i = 0; i < g.count; ++i) {
         TensorArgs& t = g.t[i];
-        t.first = blocks;
+        t.first = g.first[i] = blocks;
         blocks += cdiv(static_cast<uint64_t>(t.n) * (RP / 4), 256);
         bytes += 4.0 * t.n * g.r * (t.sq + 1);
     }
@@ -2653,7 +2655,7 @@ static int compress_impl(edgc_ctx* ctx, Group& g, const TensorScratch* cap, uint
         double bytes = 0.0;
         for (uint32_t i = 0; i < g.count; ++i) {
             TensorArgs& t = g.t[i];
-            t.first = blocks;
+            t.first = g.first[i] = blocks;
             blocks += cdiv(static_cast<uint64_t>(t.m) * (RP / 4), 256);
             bytes += 4.0 * t.m * g.r * (t.sp + 1);
         }
@@ -2688,6 +2690,7 @@ int launch_compress(edgc_ctx* ctx, Group& g, const TensorScratch* cap, edgc_dtyp
                     uint32_t power_iters, hipStream_t st, int phase)
 {
     const int rt = rank_tiles(g.r);
+    std::fill(g.first + g.count, g.first + kMaxGroup, ~0u);
 #define EDGC_DISPATCH(NP_)                                                        \
     switch (rt) {                                                                 \
     case 1: return compress_impl<NP_, 1>(ctx, g, cap, power_iters, phase, st);    \
@@ -2734,7 +2737,7 @@ static int decompress_impl(edgc_ctx* ctx, Group& g, hipStream_t st)
         JS = cdiv(stages, sps);
         t.d0 = sps;
         t.d1 = JS;
-        t.first = blocks;
+        t.first = g.first[i] = blocks;
         blocks += RB * JS;
         vec = vec && (t.n % 2 == 0) && (t.ldo % 2 == 0) && (reinterpret_cast<uintptr_t>(t.E) % 8 == 0) &&
               (reinterpret_cast<uintptr_t>(t.out) % (2 * esz) == 0);
@@ -2763,6 +2766,7 @@ static int decompress_impl(edgc_ctx* ctx, Group& g, hipStream_t st)
 int launch_decompress(edgc_ctx* ctx, Group& g, edgc_dtype dt, hipStream_t st)
 {
     const int rt = rank_tiles(g.r);
+    std::fill(g.first + g.count, g.first + kMaxGroup, ~0u);
 #define EDGC_DISPATCH(NP_)                                              \
     switch (rt) {                                                       \
     case 1: return decompress_impl<NP_, 1>(ctx, g, st);                 \

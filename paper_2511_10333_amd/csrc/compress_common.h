@@ -90,7 +90,8 @@ __device__ __forceinline__ f32x16 mma(const bf16x8 (&a)[NP], const bf16x8 (&b)[N
 __device__ __forceinline__ uint32_t locate(const Group& g, uint32_t bid)
 {
     uint32_t t = 0;
-    for (uint32_t i = 1; i < g.count; ++i) t += (bid >= g.t[i].first) ? 1u : 0u;
+#pragma unroll
+    for (int i = 1; i < kMaxGroup; ++i) t += (bid >= g.first[i]) ? 1u : 0u;
     return t;
 }
 

@@ -85,6 +85,10 @@ struct TensorArgs {
 };
 
 struct Group {
+    // First block of every tensor, ~0 beyond the last: a block finds its tensor from one 64-byte scalar load.  (A walk over
+    // the tensors' own `first` fields is a chain of dependent loads, each of a line of kernel arguments that no cache holds
+    // yet.)  The launchers set it next to the tensors' fields.
+    uint32_t first[kMaxGroup];
     uint32_t count;
     uint32_t r;             // rank, the same for every tensor of a group
     uint32_t stream;        // 1: the Q-pass reads D with non-temporal loads (group_streams)
@@ -274,6 +278,7 @@ struct CopyArgs {
     uint32_t m, unit, first, blocks;        // rows; bytes per access; first block; blocks
 };
 struct CopyGroup {
+    uint32_t first[kMaxCopies];             // as in Group
     uint32_t count;
     CopyArgs t[kMaxCopies];
 };
