@@ -262,21 +262,27 @@ static int entropy_estimate_impl(edgc_ctx* ctx, bool static_scratch, const void*
     }
     EntGroup g{};
     g.count = count;
-    // one vector width for the whole group: scalar loads as soon as one buffer needs them
+    // one vector width for the whole group: scalar loads as soon as one buffer needs them (the rest of the sampler's
+    // parameters is then the same for every buffer too: the chunk depends on the width and the call's arguments only)
     for (int pass = 0; pass < 2; ++pass) {
         bool uniform = true;
         g.n_items = g.n_sampled = 0;
         for (uint32_t i = 0; i < count; ++i) {
+            const SampleGeom geom = make_geom(grads[i], dtype, n_elems[i], stride, chunk, seed, step, pass == 0);
+            if (i == 0) {
+                g.ipc = geom.ipc; g.chunk = geom.chunk; g.vec = geom.vec;
+                g.stride = geom.stride; g.slot = geom.slot;
+            }
             g.base[i] = grads[i];
-            g.geom[i] = make_geom(grads[i], dtype, n_elems[i], stride, chunk, seed, step, pass == 0);
+            g.n[i] = n_elems[i];
             g.first[i] = g.n_items;
-            g.n_items += g.geom[i].n_items;
-            g.n_sampled += g.geom[i].n_sampled;
-            uniform = uniform && (g.geom[i].vec > 1) == (g.geom[0].vec > 1);
+            g.n_items += geom.n_items;
+            g.n_sampled += geom.n_sampled;
+            uniform = uniform && (geom.vec > 1) == (g.vec > 1);
         }
         if (uniform) break;
     }
-    g.first[count] = g.n_items;
+    for (uint32_t i = count; i <= static_cast<uint32_t>(kMaxEntGroup); ++i) g.first[i] = g.n_items;
     if (g.n_sampled == 0) return fail(ctx, EDGC_ENONFINITE, "the sampling predicate selects no element");
     EDGC_HIP_TRY(ctx, hipSetDevice(ctx->device));
     if (static_scratch)

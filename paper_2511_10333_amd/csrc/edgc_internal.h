@@ -232,12 +232,13 @@ struct SampleGeom {
 constexpr int kMaxEntGroup = 32;
 struct EntGroup {
     uint32_t count;
-    uint32_t _pad;
-    uint64_t n_items;       // over all buffers
-    uint64_t n_sampled;     // over all buffers
+    uint32_t ipc, chunk, vec;           // of the sampler: the same for every buffer of a group
+    uint64_t stride, slot;
+    uint64_t n_items;                   // over all buffers
+    uint64_t n_sampled;                 // over all buffers
+    uint64_t first[kMaxEntGroup + 1];   // first item of each buffer in the union; n_items from [count] on
     const void* base[kMaxEntGroup];
-    SampleGeom geom[kMaxEntGroup];
-    uint64_t first[kMaxEntGroup + 1];   // first item of each buffer in the union; [count] = n_items
+    uint64_t n[kMaxEntGroup];           // elements of each buffer
 };
 
 SampleGeom make_geom(const void* base, edgc_dtype dt, uint64_t n, uint64_t stride, uint32_t chunk,

@@ -9,11 +9,11 @@
 //             with lane-interleaved replicas so equal bins in one wavefront hit
 //             different banks, flush to global counters, and the last block reduces
 //             the counters to the Shannon entropy in fp64
-// or, where one block holds the sample in one round, k_estimate_one alone.
-// What bounds them at a 1 % sample (0.01 to 0.5 M items): latency.  Blocks of four items per thread,
-// as many as the sample gives, each over one contiguous range of the union of the buffers: 2 M
-// fp32 elements of four buffers on 4096 bins 64 -> 23 us (both kernels), 143 K bf16 elements of 24
-// buffers 105 -> 27 us, 10 K fp32 elements by one block 17 -> 8 us.
+// or, where one block holds the sample in one round, k_estimate_one alone; where every block of a grid takes one round
+// (1 % of a transformer block), k_minmax_small and k_hist_small.
+// What bounds them at a 1 % sample (0.01 to 0.5 M items): latency.  Both kernels, one after the other, for 2 M fp32
+// elements of four buffers on 4096 bins: 20.3 us (22.8 before they had kernels of their own); in the passes that they are a part
+// of: two hidden-768 bf16 blocks, 24 buffers, 100 -> 87 us per pass, hidden-2048 block 232 -> 228, hidden-5120 1173 -> 1164.
 // The chunk-strided sample is read with 16-byte loads whenever chunks are a
 // multiple of the vector width, so a wavefront touches whole cache lines.
 // Both kernels take a list of buffers (EntGroup): the estimate is over the union
@@ -24,6 +24,7 @@
 
 #include <algorithm>
 #include <math.h>
+#include <type_traits>
 
 namespace edgc {
 
@@ -36,6 +37,12 @@ constexpr int kMMBlockFat = 1024;                 // large samples: one block pe
 constexpr uint64_t kBigSampleItems = 8ull << 20;  // items (16 bytes each) from which a sample counts as large
 constexpr int kHistBlock = 512;
 constexpr int kOneBlock = 1024;       // k_estimate_one
+// k_minmax_small, k_hist_small: blocks of 512 threads, of four items each; of two up to 64 Ki items, where there are so few
+// blocks that more of them do not queue up at the ticket.  Per pass, two / four items: two hidden-768 blocks (18 K items) 88.4 /
+// 90.2 us, three odd matrices (35 K) 134.3 / 135.5, hidden-2048 block (126 K) 229.8 / 229.1, four buffers of 0.5 M items 23.4 /
+// 20.9; 1024 threads of four items (22.4, and 94.8 on the hidden-768 blocks), 256 of four (26.6) and 512 of eight (22.5) are slower.
+constexpr int kSmallBlock = 512;
+constexpr uint64_t kSmallTwo = 64 << 10;
 constexpr int kHistBlockFat = 1024;   // when the LDS histogram leaves room for one block per CU
 
 // ---------------------------------------------------------------------------
@@ -64,10 +71,23 @@ __device__ __forceinline__ float wave_reduce_minmax(float v)
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ double dpp_add(double v)          // v + (v of the lane that CTRL names; 0 where there is none)
+{
+    const uint64_t b = static_cast<uint64_t>(__double_as_longlong(v));
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0u, static_cast<uint32_t>(b), CTRL, ROW_MASK, 0xf, false);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0u, static_cast<uint32_t>(b >> 32), CTRL, ROW_MASK, 0xf, false);
+    return v + __longlong_as_double(static_cast<long long>((static_cast<uint64_t>(hi) << 32) | lo));
+}
 __device__ __forceinline__ double wave_sum_f64(double v)
 {
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-    return v;   // lane 0
+    v = dpp_add<0x111, 0xf>(v);
+    v = dpp_add<0x112, 0xf>(v);
+    v = dpp_add<0x114, 0xf>(v);
+    v = dpp_add<0x118, 0xf>(v);
+    v = dpp_add<0x142, 0xa>(v);
+    v = dpp_add<0x143, 0xc>(v);
+    return v;   // lane 63
 }
 
 // ---------------------------------------------------------------------------
@@ -102,42 +122,67 @@ __device__ __forceinline__ void unpack_item(const uint4& q, float (&v)[VEC])
     }
 }
 
-// The item of one thread: item -> (k-th sampled chunk, e-th item in it), advanced without a division.
+// Element index of the e-th item of the k-th sampled chunk
+template <typename Sampler>      // SampleGeom or EntGroup
+__device__ __forceinline__ uint64_t item_elem(const Sampler& g, uint64_t k, uint32_t e, int vec)
+{
+    return (g.slot + k * g.stride) * g.chunk + static_cast<uint64_t>(e) * vec;
+}
+
+// The item of one thread: item -> (k-th sampled chunk, e-th item in it), and from there in steps of a constant number of items
+// without a division or a product: the element index grows by the same amount every step, and by what the sampler leaves
+// out where the step ends in a later chunk.
 struct ItemCursor {
-    uint64_t k;
-    uint32_t e, dk, de;
+    uint64_t at;            // element index
+    uint64_t dat, jump;
+    uint32_t e, de;
     // item `base` (the same for the whole block) + `off`; advances by `step` items
-    __device__ __forceinline__ void init(uint64_t base, uint32_t off, uint32_t step, uint32_t ipc)
+    template <typename Sampler>
+    __device__ __forceinline__ void init(const Sampler& g, uint64_t base, uint32_t off, uint32_t step, int vec)
     {
+        const uint32_t ipc = g.ipc;
         const uint64_t q = (base >> 32) ? base / ipc : static_cast<uint32_t>(base) / ipc;
         const uint32_t s = static_cast<uint32_t>(base - q * ipc) + off;
         const uint32_t sq = s / ipc;
-        k = q + sq;
         e = s - sq * ipc;
-        dk = step / ipc;
+        at = item_elem(g, q + sq, e, vec);
+        const uint32_t dk = step / ipc;
         de = step - dk * ipc;
-    }
-    // any item
-    __device__ __forceinline__ void init_each(uint64_t item, uint32_t ipc)
-    {
-        k = (item >> 32) ? item / ipc : static_cast<uint32_t>(item) / ipc;
-        e = static_cast<uint32_t>(item - k * ipc);
+        dat = dk * (g.stride * g.chunk) + static_cast<uint64_t>(de) * vec;
+        jump = (g.stride - 1u) * g.chunk;
     }
     __device__ __forceinline__ void advance(uint32_t ipc)
     {
-        k += dk;
+        at += dat;
         e += de;
-        if (e >= ipc) { e -= ipc; ++k; }
-    }
-    __device__ __forceinline__ uint64_t elem0(const SampleGeom& g, int vec) const
-    {
-        return (g.slot + k * g.stride) * g.chunk + static_cast<uint64_t>(e) * vec;
+        if (e >= ipc) { e -= ipc; at += jump; }
     }
 };
+// any item
+template <typename Sampler>
+__device__ __forceinline__ uint64_t elem_of_item(const Sampler& g, uint64_t item, int vec)
+{
+    const uint64_t k = (item >> 32) ? item / g.ipc : static_cast<uint32_t>(item) / g.ipc;
+    return item_elem(g, k, static_cast<uint32_t>(item - k * g.ipc), vec);
+}
+
+// Memory at an address that went through integer registers: without the address space the compiler takes it for flat memory,
+// whose loads count as LDS accesses too (k_wide_hist 69 against 62 us).
+template <typename T> using GlobalPtr = const __attribute__((address_space(1))) T*;
+template <typename T>
+__device__ __forceinline__ GlobalPtr<T> global_ptr(uint64_t address) { return reinterpret_cast<GlobalPtr<T>>(address); }
+
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+template <typename T>
+__device__ __forceinline__ uint4 load_item(GlobalPtr<T> p)
+{
+    const u32x4_t v = *reinterpret_cast<GlobalPtr<u32x4_t>>(p);
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
 
 // The first `left` < VEC elements of an item, requested together.
 template <typename T, int VEC, typename Elem>
-__device__ __forceinline__ void partial_item(const T* __restrict__ at, uint64_t left, Elem&& elem)
+__device__ __forceinline__ void partial_item(GlobalPtr<T> at, uint64_t left, Elem&& elem)
 {
     T x[VEC - 1];
 #pragma unroll
@@ -146,6 +191,92 @@ __device__ __forceinline__ void partial_item(const T* __restrict__ at, uint64_t 
     for (int p = 0; p < VEC - 1; ++p)
         if (p < static_cast<int>(left)) elem(x[p]);
 }
+
+// What a wave needs to know of a group's buffers, lane l holding buffer l's (lanes past the last: an empty one at the end of
+// the union): one round of loads whose addresses depend on nothing, where a walk over the argument's fields is a chain of
+// them, each of a line that no cache holds yet.
+__device__ __forceinline__ uint64_t readlane64(uint64_t v, uint32_t lane)
+{
+    const uint32_t lo = __builtin_amdgcn_readlane(static_cast<uint32_t>(v), lane);
+    const uint32_t hi = __builtin_amdgcn_readlane(static_cast<uint32_t>(v >> 32), lane);
+    return (static_cast<uint64_t>(hi) << 32) | lo;
+}
+struct BufferTable {
+    uint64_t first, next, base, n;
+    __device__ __forceinline__ void load(const EntGroup& grp)
+    {
+        const uint32_t lane = threadIdx.x & 63u;
+        constexpr uint32_t kLast = kMaxEntGroup;
+        first = grp.first[min(lane, kLast)];
+        next = grp.first[min(lane + 1u, kLast)];
+        base = reinterpret_cast<uint64_t>(grp.base[min(lane, kLast - 1u)]);
+        n = grp.n[min(lane, kLast - 1u)];
+    }
+    // buffer of item `pos`, and the number of buffers that begin before item `end`
+    __device__ __forceinline__ uint32_t at(uint64_t pos) const { return static_cast<uint32_t>(__popcll(__ballot(next <= pos))); }
+    __device__ __forceinline__ uint32_t before(uint64_t end) const { return static_cast<uint32_t>(__popcll(__ballot(first < end))); }
+};
+
+// Up to U items per thread of a block, items [pos, end) of the union whatever buffers they are in, all requested at once.
+template <typename T, int VEC, int BLOCK, int U>
+struct ItemRound {
+    uint4 raw[U];
+    T one[U];
+    GlobalPtr<T> at[U];
+    uint64_t left[U];                                  // elements from the item's first on; 0: no item
+    __device__ __forceinline__ void request(const EntGroup& grp, const BufferTable& tab, uint64_t pos, uint64_t end)
+    {
+        const uint32_t ti = tab.at(pos), t_end = tab.before(end);
+        uint64_t f[U], base[U], n[U];
+        if (t_end - ti <= 1) {
+            const uint64_t f0 = readlane64(tab.first, ti), b0 = readlane64(tab.base, ti), n0 = readlane64(tab.n, ti);
+#pragma unroll
+            for (int u = 0; u < U; ++u) { f[u] = f0; base[u] = b0; n[u] = n0; }
+        } else {
+            uint32_t t[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) t[u] = ti;
+            for (uint32_t b = ti + 1; b < t_end; ++b) {
+                const uint64_t fb = readlane64(tab.first, b);
+#pragma unroll
+                for (int u = 0; u < U; ++u) t[u] += (pos + u * BLOCK + threadIdx.x >= fb) ? 1u : 0u;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                f[u] = __shfl(tab.first, t[u], 64);
+                base[u] = __shfl(tab.base, t[u], 64);
+                n[u] = __shfl(tab.n, t[u], 64);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            raw[u] = make_uint4(0u, 0u, 0u, 0u);
+            one[u] = T(0);
+            const uint64_t i = pos + u * BLOCK + threadIdx.x;
+            const uint64_t e0 = elem_of_item(grp, i - f[u], VEC);
+            at[u] = global_ptr<T>(base[u]) + e0;
+            left[u] = (i < end && e0 < n[u]) ? n[u] - e0 : 0;
+            if constexpr (VEC > 1) {
+                if (left[u] >= VEC) raw[u] = load_item(at[u]);
+            } else {
+                if (left[u]) one[u] = *at[u];
+            }
+        }
+    }
+    template <typename Item, typename Elem>
+    __device__ __forceinline__ void visit(Item&& item, Elem&& elem) const
+    {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if constexpr (VEC > 1) {
+                if (left[u] >= VEC) item(raw[u]);
+                else if (left[u]) partial_item<T, VEC>(at[u], left[u], elem);
+            } else {
+                if (left[u]) elem(one[u]);
+            }
+        }
+    }
+};
 
 // Visits the items [begin, end) of the union of the buffers' samples (buffer i holds the items first[i] ..
 // first[i + 1]), by one block: `item(raw)` gets the 16 bytes of every whole item, `elem(x)` every element of a
@@ -165,84 +296,34 @@ __device__ __forceinline__ void walk_items(const EntGroup& grp, uint64_t begin, 
 {
     constexpr int U = 4;
     constexpr uint32_t STEP = U * BLOCK;
-    // lane l has buffer l's first item and the one after its last
-    const uint32_t lane = threadIdx.x & 63u;
-    const bool in = lane < grp.count;
-    uint64_t first_l = 0, next_l = 0;
-    if (grp.count > 1) {                               // (one buffer: nothing to look up, and no load to wait for)
-        first_l = grp.first[min(lane, grp.count)];
-        next_l = grp.first[min(lane + 1u, grp.count)];
-    }
+    BufferTable tab;
+    tab.load(grp);
     for (uint64_t pos = begin; pos < end;) {
         const uint64_t round_end = min(end, pos + STEP);
-        uint32_t ti = 0, t_end = 1;
-        if (grp.count > 1) {
-            ti = static_cast<uint32_t>(__popcll(__ballot(in && next_l <= pos)));
-            t_end = static_cast<uint32_t>(__popcll(__ballot(in && first_l < round_end)));
-        }
-        if (t_end - ti > 2) {
-            // The sampler's parameters are the same for every buffer of a group; base and length differ.
-            const SampleGeom& geom = grp.geom[ti];
-            const uint32_t ipc = geom.ipc, tl = min(lane, grp.count - 1u);
-            const uint64_t n_l = grp.geom[tl].n, base_l = reinterpret_cast<uint64_t>(grp.base[tl]);
-            uint4 raw[U];
-            T one[U];
-            const T* at[U];
-            uint64_t left[U];                          // elements from the item's first on
-            uint32_t t[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) t[u] = ti;
-            for (uint32_t b = ti + 1; b < t_end; ++b) {
-                const uint64_t fb = __shfl(first_l, b, 64);
-#pragma unroll
-                for (int u = 0; u < U; ++u) t[u] += (pos + u * BLOCK + threadIdx.x >= fb) ? 1u : 0u;
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                raw[u] = make_uint4(0u, 0u, 0u, 0u);
-                one[u] = T(0);
-                const uint64_t i = pos + u * BLOCK + threadIdx.x;
-                const uint64_t n = __shfl(n_l, t[u], 64);
-                ItemCursor cur;
-                cur.init_each(i - __shfl(first_l, t[u], 64), ipc);
-                const uint64_t e0 = cur.elem0(geom, VEC);
-                at[u] = reinterpret_cast<const T*>(__shfl(base_l, t[u], 64)) + e0;
-                left[u] = (i < round_end && e0 < n) ? n - e0 : 0;
-                if constexpr (VEC > 1) {
-                    if (left[u] >= VEC) raw[u] = *reinterpret_cast<const uint4*>(at[u]);
-                } else {
-                    if (left[u]) one[u] = *at[u];
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if constexpr (VEC > 1) {
-                    if (left[u] >= VEC) item(raw[u]);
-                    else if (left[u]) partial_item<T, VEC>(at[u], left[u], elem);
-                } else {
-                    if (left[u]) elem(one[u]);
-                }
-            }
+        const uint32_t ti = tab.at(pos);
+        if (tab.before(round_end) - ti > 2) {
+            ItemRound<T, VEC, BLOCK, U> r;
+            r.request(grp, tab, pos, round_end);
+            r.visit(item, elem);
             round();
             pos = round_end;
             continue;
         }
         // else: buffer `ti` from here to its end, or the range's
-        const SampleGeom& geom = grp.geom[ti];
-        const T* __restrict__ g = static_cast<const T*>(grp.base[ti]);
-        const uint64_t f0 = grp.first[ti];
-        const uint64_t lb = pos - f0, le = min(end, grp.first[ti + 1]) - f0;
+        const GlobalPtr<T> g = global_ptr<T>(readlane64(tab.base, ti));
+        const uint64_t n = readlane64(tab.n, ti), f0 = readlane64(tab.first, ti), next = readlane64(tab.next, ti);
+        const uint64_t lb = pos - f0, le = min(end, next) - f0, items = next - f0;
         pos = f0 + le;
-        const uint32_t ipc = geom.ipc;
+        const uint32_t ipc = grp.ipc;
         ItemCursor cur;
-        cur.init(lb, threadIdx.x, BLOCK, ipc);
+        cur.init(grp, lb, threadIdx.x, BLOCK, VEC);
         uint64_t rb = lb;                              // first item of the round
         if constexpr (VEC > 1) {
-            const uint64_t fast_end = (geom.n_items >= ipc) ? min(le, geom.n_items - ipc) : 0;
+            const uint64_t fast_end = (items >= ipc) ? min(le, items - ipc) : 0;
             auto fetch = [&](uint4 (&raw)[U]) {
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    raw[u] = *reinterpret_cast<const uint4*>(g + cur.elem0(geom, VEC));
+                    raw[u] = load_item(g + cur.at);
                     cur.advance(ipc);
                 }
             };
@@ -281,12 +362,12 @@ __device__ __forceinline__ void walk_items(const EntGroup& grp, uint64_t begin, 
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     raw[u] = make_uint4(0u, 0u, 0u, 0u);
-                    at[u] = cur.elem0(geom, VEC);
+                    at[u] = cur.at;
                     if (rb + u * BLOCK + threadIdx.x < le) {
-                        if (at[u] + VEC <= geom.n) {
-                            raw[u] = *reinterpret_cast<const uint4*>(g + at[u]);
+                        if (at[u] + VEC <= n) {
+                            raw[u] = load_item(g + at[u]);
                             whole |= 1u << u;
-                        } else if (at[u] < geom.n) {
+                        } else if (at[u] < n) {
                             partial |= 1u << u;
                         }
                     }
@@ -298,7 +379,7 @@ __device__ __forceinline__ void walk_items(const EntGroup& grp, uint64_t begin, 
                 if (partial) {
 #pragma unroll
                     for (int u = 0; u < U; ++u)
-                        if ((partial >> u) & 1u) partial_item<T, VEC>(g + at[u], geom.n - at[u], elem);
+                        if ((partial >> u) & 1u) partial_item<T, VEC>(g + at[u], n - at[u], elem);
                 }
                 round();
             }
@@ -309,8 +390,8 @@ __device__ __forceinline__ void walk_items(const EntGroup& grp, uint64_t begin, 
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     x[u] = T(0);
-                    const uint64_t at = cur.elem0(geom, 1);
-                    if (rb + u * BLOCK + threadIdx.x < le && at < geom.n) {
+                    const uint64_t at = cur.at;
+                    if (rb + u * BLOCK + threadIdx.x < le && at < n) {
                         x[u] = g[at];
                         have |= 1u << u;
                     }
@@ -338,9 +419,17 @@ __device__ __forceinline__ bool finite_f32(float x)
     return (__float_as_uint(x) & 0x7f800000u) != 0x7f800000u;
 }
 
+// log of a bin's width: what the differential entropy adds.  Formed before the sums are there (a lone wave's fp64 logarithm
+// takes some 0.3 us, its code from a cold cache included).
+__device__ __forceinline__ double log_bin_width(const RangeParams& rp, uint32_t bins)
+{
+    const double w = static_cast<double>(rp.w);
+    return w > 0.0 ? log(w / static_cast<double>(bins)) : 0.0;
+}
+
 // The estimate from sum c log2 c (`acc`) and sum c (`tot`) over the bins, by one thread:
-// H = log2 n - (1/n) sum c log2 c in fp64, and the result record.
-__device__ __forceinline__ void emit_result(double acc, double tot, uint32_t bins, const RangeParams& rp,
+// H = log2 n - (1/n) sum c log2 c in fp64, and the result record.  `log_w`: log_bin_width.
+__device__ __forceinline__ void emit_result(double acc, double tot, double log_w, const RangeParams& rp,
                                             unsigned long long n_sampled, edgc_entropy_result* res)
 {
     edgc_entropy_result r;
@@ -354,10 +443,8 @@ __device__ __forceinline__ void emit_result(double acc, double tot, uint32_t bin
     if (tot > 0.0) {
         double H = log2(tot) - acc / tot;
         if (H < 0.0) H = 0.0;
-        const double w = static_cast<double>(rp.w);
         r.H_bits = H;
-        r.h_diff_nats = (w > 0.0) ? H * 0.69314718055994530942 + log(w / static_cast<double>(bins))
-                                  : -INFINITY;
+        r.h_diff_nats = (rp.w > 0.0f) ? H * 0.69314718055994530942 + log_w : -INFINITY;
         r.status = EDGC_OK;
     } else {
         r.H_bits = NAN; r.h_diff_nats = NAN;
@@ -376,45 +463,62 @@ __device__ __forceinline__ void entropy_term(unsigned long long c, double& acc, 
     }
 }
 
-// Sums the threads' (acc, tot) over the block; thread 0 returns the totals.
+// Sums the threads' (acc, tot) over the block; thread BLOCK - 1 returns the totals.
 template <int BLOCK>
 __device__ __forceinline__ void block_sum_pair(double& acc, double& tot)
 {
-    __shared__ double s_a[BLOCK / 64], s_b[BLOCK / 64];
+    constexpr uint32_t W = BLOCK / 64;
+    static_assert(W <= 16, "one row of lanes sums the waves'");
+    __shared__ double s_a[16], s_b[16];
     acc = wave_sum_f64(acc);
     tot = wave_sum_f64(tot);
     __syncthreads();              // the arrays may still be read from an earlier call
-    if ((threadIdx.x & 63) == 0) { s_a[threadIdx.x >> 6] = acc; s_b[threadIdx.x >> 6] = tot; }
+    if ((threadIdx.x & 63u) == 63u) { s_a[threadIdx.x >> 6] = acc; s_b[threadIdx.x >> 6] = tot; }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        acc = 0.0; tot = 0.0;
-        for (int w = 0; w < BLOCK / 64; ++w) { acc += s_a[w]; tot += s_b[w]; }
+    if (threadIdx.x >= BLOCK - 64) {
+        const uint32_t l = threadIdx.x & 63u;
+        acc = wave_sum_f64(l < W ? s_a[l] : 0.0);
+        tot = wave_sum_f64(l < W ? s_b[l] : 0.0);
     }
 }
 
 // ---------------------------------------------------------------------------
 // kernel 1: range of the finite sample
 // ---------------------------------------------------------------------------
-// (lo, hi) of the finite elements of the block's range, per thread
-template <typename T, int VEC, int BLOCK>
-__device__ __forceinline__ void range_of_items(const EntGroup& grp, uint64_t begin, uint64_t end, float& lo, float& hi)
-{
-    auto fold = [&](float x) {
+// What folds the items and elements that a walk or a round hands out into (lo, hi), per thread
+template <typename T, int VEC>
+struct RangeFold {
+    float &lo, &hi;
+    __device__ __forceinline__ void value(float x)
+    {
         // no branch: a non-finite value stands in as the bound itself
         const bool fin = finite_f32(x);
         lo = fminf(lo, fin ? x : lo);
         hi = fmaxf(hi, fin ? x : hi);
-    };
-    walk_items<T, VEC, BLOCK>(grp, begin, end, true,
-        [&](const uint4& raw) {
-            if constexpr (VEC > 1) {
-                float v[VEC];
-                unpack_item<T, VEC>(raw, v);
+    }
+    __device__ __forceinline__ void operator()(const uint4& raw)
+    {
+        if constexpr (VEC > 1) {
+            float v[VEC];
+            unpack_item<T, VEC>(raw, v);
 #pragma unroll
-                for (int p = 0; p < VEC; ++p) fold(v[p]);
-            }
-        },
-        [&](T x) { fold(ElemTraits<T>::widen(x)); }, [] {});
+            for (int p = 0; p < VEC; ++p) value(v[p]);
+        }
+    }
+    __device__ __forceinline__ void operator()(T x) { value(ElemTraits<T>::widen(x)); }
+};
+// (lo, hi) of the finite elements of the block's range, of its one round, per thread
+template <typename T, int VEC, int BLOCK>
+__device__ __forceinline__ void range_of_items(const EntGroup& grp, uint64_t begin, uint64_t end, float& lo, float& hi)
+{
+    RangeFold<T, VEC> fold{lo, hi};
+    walk_items<T, VEC, BLOCK>(grp, begin, end, true, fold, fold, [] {});
+}
+template <typename T, int VEC, int BLOCK, int U>
+__device__ __forceinline__ void range_of_round(const ItemRound<T, VEC, BLOCK, U>& items, float& lo, float& hi)
+{
+    RangeFold<T, VEC> fold{lo, hi};
+    items.visit(fold, fold);
 }
 
 __device__ __forceinline__ RangeParams make_range(float lo, float hi, float fbins)
@@ -469,34 +573,56 @@ __global__ void k_set_range(float2* part, float lo, float hi, uint32_t* __restri
 // ---------------------------------------------------------------------------
 // kernel 2: histogram + entropy
 // ---------------------------------------------------------------------------
-// Bins of the block's range into the LDS counters h[bin - bin_base][replica], bins [bin_base, bin_base + local_n).
+// What bins the items and elements that a walk or a round hands out into the LDS counters h[bin - bin_base][replica], bins
+// [bin_base, bin_base + local_n).
 // bin = trunc((x - lo) * scale), each operation rounded on its own, clamped to [0, bins - 1].
+template <typename T, int VEC, bool WHOLE>           // WHOLE: one slice holds every bin
+struct Binner {
+    float lo, scale, top;                            // top: largest float below the bin count; truncating a value clamped to
+    uint32_t bin_base, local_n, rep_shift;           // [0, top] gives 0 .. bins - 1
+    uint32_t* h_rep;                                 // this lane's replica
+    __device__ __forceinline__ Binner(float lo_, float scale_, uint32_t bins, uint32_t bin_base_, uint32_t local_n_,
+                                      uint32_t rep_shift_, uint32_t* h)
+        : lo(lo_), scale(scale_), top(__uint_as_float(__float_as_uint(static_cast<float>(bins)) - 1u)), bin_base(bin_base_),
+          local_n(local_n_), rep_shift(rep_shift_), h_rep(h + (threadIdx.x & ((1u << rep_shift_) - 1u))) {}
+    // No branch per element: the bin of a non-finite value is some valid bin (the clamp maps NaN to 0) and it adds 0.
+    __device__ __forceinline__ void value(float x)
+    {
+        const float f = __builtin_amdgcn_fmed3f(__fmul_rn(__fsub_rn(x, lo), scale), 0.0f, top);
+        const uint32_t b = static_cast<uint32_t>(f), one = finite_f32(x) ? 1u : 0u;
+        if (WHOLE) atomicAdd(&h_rep[b << rep_shift], one);
+        else if (b - bin_base < local_n) atomicAdd(&h_rep[(b - bin_base) << rep_shift], one);
+    }
+    __device__ __forceinline__ void operator()(const uint4& raw)
+    {
+        if constexpr (VEC > 1) {
+            float v[VEC];
+            unpack_item<T, VEC>(raw, v);
+#pragma unroll
+            for (int p = 0; p < VEC; ++p) value(v[p]);
+        }
+    }
+    __device__ __forceinline__ void operator()(T x) { value(ElemTraits<T>::widen(x)); }
+};
 template <typename T, int VEC, int BLOCK>
 __device__ __forceinline__ void bin_items(const EntGroup& grp, uint64_t begin, uint64_t end, float lo, float scale,
                                           uint32_t bins, uint32_t bin_base, uint32_t local_n, uint32_t rep_shift,
                                           bool ahead, uint32_t* h)
 {
-    // largest float below the bin count: truncating a value clamped to [0, top] gives 0 .. bins - 1
-    const float top = __uint_as_float(__float_as_uint(static_cast<float>(bins)) - 1u);
-    const bool whole = local_n == bins;                                   // one slice holds every bin
-    uint32_t* const h_rep = h + (threadIdx.x & ((1u << rep_shift) - 1u)); // this lane's replica
-    // No branch per element: the bin of a non-finite value is some valid bin (the clamp maps NaN to 0) and it adds 0.
-    auto add = [&](float x) {
-        const float f = __builtin_amdgcn_fmed3f(__fmul_rn(__fsub_rn(x, lo), scale), 0.0f, top);
-        const uint32_t b = static_cast<uint32_t>(f), one = finite_f32(x) ? 1u : 0u;
-        if (whole) atomicAdd(&h_rep[b << rep_shift], one);
-        else if (b - bin_base < local_n) atomicAdd(&h_rep[(b - bin_base) << rep_shift], one);
-    };
-    walk_items<T, VEC, BLOCK>(grp, begin, end, ahead,
-        [&](const uint4& raw) {
-            if constexpr (VEC > 1) {
-                float v[VEC];
-                unpack_item<T, VEC>(raw, v);
-#pragma unroll
-                for (int p = 0; p < VEC; ++p) add(v[p]);
-            }
-        },
-        [&](T x) { add(ElemTraits<T>::widen(x)); }, [] {});
+    if (local_n == bins) {
+        Binner<T, VEC, true> bin(lo, scale, bins, bin_base, local_n, rep_shift, h);
+        walk_items<T, VEC, BLOCK>(grp, begin, end, ahead, bin, bin, [] {});
+    } else {
+        Binner<T, VEC, false> bin(lo, scale, bins, bin_base, local_n, rep_shift, h);
+        walk_items<T, VEC, BLOCK>(grp, begin, end, ahead, bin, bin, [] {});
+    }
+}
+template <typename T, int VEC, int BLOCK, int U>
+__device__ __forceinline__ void bin_round(const ItemRound<T, VEC, BLOCK, U>& items, float lo, float scale, uint32_t bins,
+                                          uint32_t rep_shift, uint32_t* h)
+{
+    Binner<T, VEC, true> bin(lo, scale, bins, 0, bins, rep_shift, h);
+    items.visit(bin, bin);
 }
 
 // (lo, hi) of the sample from the blocks' partials, by one block
@@ -537,6 +663,52 @@ __device__ __forceinline__ bool last_block(unsigned int* ticket)
 
 __host__ __device__ constexpr uint32_t copy_stride(uint32_t bins) { return (bins + 3u) & ~3u; }   // words per set
 
+// The last block's part: the histogram from the sets of counters, H = log2 n - (1/n) sum c log2 c (== -sum p log2 p) and the
+// result.  Its code is fetched from a cold cache by one block, so it is short (with a loop over 32 bins written out 32 times
+// this took 7.7 us where one set of counters was summed); a thread has the counters of four bins in flight, bins BLOCK
+// apart, so that few bins are spread over all threads.
+template <int BLOCK>
+__device__ __forceinline__ void finish_hist(const uint32_t* copies, uint32_t sets, unsigned long long* counts, uint32_t bins,
+                                            const RangeParams& rp, unsigned long long n_sampled, edgc_entropy_result* res)
+{
+    constexpr uint32_t B = 4;
+    double acc = 0.0, tot = 0.0;
+    for (uint32_t i0 = threadIdx.x; i0 < bins; i0 += BLOCK * B) {
+        unsigned long long c[B] = {0, 0, 0, 0};
+        if (sets) {
+            uint32_t x[8][B];
+#pragma unroll
+            for (uint32_t k = 0; k < 8; ++k) {
+#pragma unroll
+                for (uint32_t e = 0; e < B; ++e) x[k][e] = 0u;
+                if (k < sets) {
+#pragma unroll
+                    for (uint32_t e = 0; e < B; ++e)
+                        x[k][e] = copies[static_cast<size_t>(k) * copy_stride(bins) + min(i0 + e * BLOCK, bins - 1u)];
+                }
+            }
+#pragma unroll
+            for (uint32_t k = 0; k < 8; ++k)
+#pragma unroll
+                for (uint32_t e = 0; e < B; ++e) c[e] += x[k][e];
+        } else {
+#pragma unroll
+            for (uint32_t e = 0; e < B; ++e) c[e] = counts[min(i0 + e * BLOCK, bins - 1u)];
+        }
+#pragma unroll 1
+        for (uint32_t e = 0; e < B; ++e) {
+            const uint32_t i = i0 + e * BLOCK;
+            if (i >= bins) break;
+            const unsigned long long v = e == 0 ? c[0] : e == 1 ? c[1] : e == 2 ? c[2] : c[3];
+            if (sets) counts[i] = v;
+            entropy_term(v, acc, tot);
+        }
+    }
+    const double log_w = log_bin_width(rp, bins);
+    block_sum_pair<BLOCK>(acc, tot);
+    if (threadIdx.x == BLOCK - 1) emit_result(acc, tot, log_w, rp, n_sampled, res);
+}
+
 // `sets` = 8: the blocks of equal id modulo 8, which the dispatcher places on one XCD, share a set of 32-bit counters at
 // `copies`, and the last block adds the sets up: a counter line that all XCDs add to moves between their caches
 // (192 blocks 19.3 us, with eight sets 17.3; 384 blocks 24.5 and 20.2).  1: one set for all blocks.  0 (samples of 2^32
@@ -561,7 +733,7 @@ __global__ __launch_bounds__(BLOCK) void k_hist(
     // fp32 and 0.51 instead of 0.63 ms on bf16; on the 10 % sample, 256-byte runs 2.5 KB apart, 0.19 instead of
     // 0.15 ms, so strided samples go without)
     bin_items<T, VEC, BLOCK>(grp, begin, end, rp.lo, rp.scale, bins, bin_base, local_n, rep_shift,
-                             gridDim.y == 1 && grp.geom[0].stride == 1, h);
+                             gridDim.y == 1 && grp.stride == 1, h);
     __syncthreads();
 
     // fold the replicas and flush non-empty bins
@@ -574,52 +746,59 @@ __global__ __launch_bounds__(BLOCK) void k_hist(
         else atomicAdd(&counts[bin_base + i], static_cast<unsigned long long>(s));
     }
     if (!last_block<BLOCK>(ticket)) return;
+    finish_hist<BLOCK>(copies, sets, counts, bins, rp, grp.n_sampled, res);
+}
 
-    // last block: H = log2 n - (1/n) sum c log2 c   (== -sum p log2 p)
-    double acc = 0.0, tot = 0.0;
-    auto four_bins = [&](uint32_t i, const unsigned long long (&c)[4]) {
-#pragma unroll
-        for (uint32_t e = 0; e < 4; ++e)
-            if (i + e < bins) {
-                counts[i + e] = c[e];
-                entropy_term(c[e], acc, tot);
-            }
-    };
-    // eight 16-byte loads in flight per thread: four bins of all eight sets, or eight times four bins of the one
-    if (sets == 8) {
-        for (uint32_t i = threadIdx.x * 4u; i < bins; i += BLOCK * 4u) {
-            uint4 x[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) x[k] = *reinterpret_cast<const uint4*>(copies + static_cast<size_t>(k) * copy_stride(bins) + i);
-            unsigned long long c[4] = {0, 0, 0, 0};
-#pragma unroll
-            for (int k = 0; k < 8; ++k) { c[0] += x[k].x; c[1] += x[k].y; c[2] += x[k].z; c[3] += x[k].w; }
-            four_bins(i, c);
-        }
-    } else if (sets == 1) {
-        for (uint32_t i0 = threadIdx.x * 4u; i0 < bins; i0 += BLOCK * 32u) {
-            uint4 x[8];
-#pragma unroll
-            for (uint32_t k = 0; k < 8; ++k) {
-                const uint32_t i = i0 + k * BLOCK * 4u;
-                x[k] = i < bins ? *reinterpret_cast<const uint4*>(copies + i) : make_uint4(0u, 0u, 0u, 0u);
-            }
-#pragma unroll
-            for (uint32_t k = 0; k < 8; ++k) {
-                const unsigned long long c[4] = {x[k].x, x[k].y, x[k].z, x[k].w};
-                four_bins(i0 + k * BLOCK * 4u, c);
-            }
-        }
-    } else {
-        for (uint32_t i = threadIdx.x; i < bins; i += BLOCK) entropy_term(counts[i], acc, tot);
+// The same for a sample of which every block takes one round of loads: 1 % of a transformer block and less.  What bounds it
+// is a chain of latencies, and the kernels of one round are cut for that: the items are requested before the range that they
+// are binned with is folded, nothing is divided that the host can divide, and the code is short, since every
+// instruction of it is fetched once, by one wave, from a cold cache.
+template <typename T, int VEC, int BLOCK, int U>
+__global__ __launch_bounds__(BLOCK) void k_minmax_small(const EntGroup grp, float2* __restrict__ part,
+                                                        uint32_t* __restrict__ zero, uint32_t zero_words)
+{
+    BufferTable tab;
+    tab.load(grp);
+    const uint64_t begin = static_cast<uint64_t>(blockIdx.x) * (BLOCK * U);
+    ItemRound<T, VEC, BLOCK, U> items;
+    items.request(grp, tab, begin, min(begin + BLOCK * U, grp.n_items));
+    for (uint32_t i = blockIdx.x * BLOCK + threadIdx.x; i < zero_words; i += gridDim.x * BLOCK) zero[i] = 0u;
+    float lo = INFINITY, hi = -INFINITY;
+    range_of_round(items, lo, hi);
+    block_range_minmax<BLOCK>(lo, hi);
+    if (threadIdx.x == 0) part[blockIdx.x] = make_float2(lo, hi);
+}
+
+template <typename T, int VEC, int BLOCK, int U>
+__global__ __launch_bounds__(BLOCK) void k_hist_small(const EntGroup grp, const float2* __restrict__ part, uint32_t nparts,
+                                                      uint32_t bins, uint32_t rep_shift, uint32_t* copies, uint32_t sets,
+                                                      unsigned long long* counts, unsigned int* ticket,
+                                                      edgc_entropy_result* res)
+{
+    extern __shared__ uint32_t h[];   // [bins << rep_shift]
+    BufferTable tab;
+    tab.load(grp);
+    const uint64_t begin = static_cast<uint64_t>(blockIdx.x) * (BLOCK * U);
+    ItemRound<T, VEC, BLOCK, U> items;
+    items.request(grp, tab, begin, min(begin + BLOCK * U, grp.n_items));
+    for (uint32_t i = threadIdx.x; i < (bins << rep_shift); i += BLOCK) h[i] = 0u;
+    const RangeParams rp = fold_range<BLOCK>(part, nparts, static_cast<float>(bins));
+    __syncthreads();
+    bin_round(items, rp.lo, rp.scale, bins, rep_shift, h);
+    __syncthreads();
+    uint32_t* const copy = copies + static_cast<size_t>(blockIdx.x & (sets - 1u)) * copy_stride(bins);
+    for (uint32_t i = threadIdx.x; i < bins; i += BLOCK) {
+        uint32_t s = 0;
+        for (uint32_t r = 0; r < (1u << rep_shift); ++r) s += h[(i << rep_shift) | r];
+        if (s) atomicAdd(&copy[i], s);
     }
-    block_sum_pair<BLOCK>(acc, tot);
-    if (threadIdx.x == 0) emit_result(acc, tot, bins, rp, grp.n_sampled, res);
+    if (!last_block<BLOCK>(ticket)) return;
+    finish_hist<BLOCK>(copies, sets, counts, bins, rp, grp.n_sampled, res);
 }
 
 // The whole estimate of a small sample by one block: range, histogram and entropy without a second launch, global
-// counters or a ticket.  Its latency chain is that of one block of k_hist without the device-wide part; the sample is
-// read twice, the second time from this CU's own cache.
+// counters or a ticket.  Its latency chain is that of one block of k_hist_small without the device-wide part; the items stay in
+// registers between the range and the bins.
 template <typename T, int VEC>
 __global__ __launch_bounds__(kOneBlock) void k_estimate_one(const EntGroup grp, int has_range, float range_lo,
                                                             float range_hi, uint32_t bins, uint32_t rep_shift,
@@ -628,16 +807,20 @@ __global__ __launch_bounds__(kOneBlock) void k_estimate_one(const EntGroup grp, 
 {
     extern __shared__ uint32_t h[];   // [bins << rep_shift]
     for (uint32_t i = threadIdx.x; i < (bins << rep_shift); i += kOneBlock) h[i] = 0u;
+    BufferTable tab;
+    tab.load(grp);
+    ItemRound<T, VEC, kOneBlock, 4> items;
+    items.request(grp, tab, 0, grp.n_items);
     float lo = INFINITY, hi = -INFINITY;
     if (has_range) {
         lo = range_lo; hi = range_hi;
         __syncthreads();
     } else {
-        range_of_items<T, VEC, kOneBlock>(grp, 0, grp.n_items, lo, hi);
+        range_of_round(items, lo, hi);
         block_range_minmax<kOneBlock>(lo, hi);
     }
     const RangeParams rp = make_range(lo, hi, static_cast<float>(bins));
-    bin_items<T, VEC, kOneBlock>(grp, 0, grp.n_items, rp.lo, rp.scale, bins, 0, bins, rep_shift, false, h);
+    bin_round(items, rp.lo, rp.scale, bins, rep_shift, h);
     __syncthreads();
     double acc = 0.0, tot = 0.0;
     for (uint32_t i = threadIdx.x; i < bins; i += kOneBlock) {
@@ -646,8 +829,9 @@ __global__ __launch_bounds__(kOneBlock) void k_estimate_one(const EntGroup grp, 
         counts[i] = s;
         entropy_term(s, acc, tot);
     }
+    const double log_w = log_bin_width(rp, bins);
     block_sum_pair<kOneBlock>(acc, tot);
-    if (threadIdx.x == 0) emit_result(acc, tot, bins, rp, grp.n_sampled, res);
+    if (threadIdx.x == kOneBlock - 1) emit_result(acc, tot, log_w, rp, grp.n_sampled, res);
 }
 
 // ---------------------------------------------------------------------------
@@ -824,7 +1008,7 @@ __global__ __launch_bounds__(kWideBlock) void k_wide_reduce(
             entropy_term(c, acc, tot);
         }
         block_sum_pair<kWideBlock>(acc, tot);
-        if (threadIdx.x == 0) { part_d[2 * blockIdx.x] = acc; part_d[2 * blockIdx.x + 1] = tot; }
+        if (threadIdx.x == kWideBlock - 1) { part_d[2 * blockIdx.x] = acc; part_d[2 * blockIdx.x + 1] = tot; }
     } else {
         float lo = INFINITY, hi = -INFINITY;
         if (mine) {
@@ -898,8 +1082,9 @@ __global__ __launch_bounds__(kWideBlock) void k_wide_reduce(
             __syncthreads();
         }
     }
+    const double log_w = log_bin_width(rp, bins);
     block_sum_pair<kWideBlock>(acc, tot);
-    if (threadIdx.x == 0) emit_result(acc, tot, bins, rp, n_sampled, res);
+    if (threadIdx.x == kWideBlock - 1) emit_result(acc, tot, log_w, rp, n_sampled, res);
 }
 
 // ---------------------------------------------------------------------------
@@ -911,11 +1096,10 @@ __global__ __launch_bounds__(256) void k_sample_indices(SampleGeom geom, uint64_
     const uint64_t G = static_cast<uint64_t>(gridDim.x) * 256;
     const int vec = static_cast<int>(geom.vec);
     for (uint64_t item = static_cast<uint64_t>(blockIdx.x) * 256; item < geom.n_items; item += G) {
-        ItemCursor cur;
-        cur.init(item, threadIdx.x, 0, geom.ipc);
-        if (item + threadIdx.x >= geom.n_items) break;
-        const uint64_t i0 = cur.elem0(geom, vec);
-        const uint64_t pos0 = cur.k * geom.chunk + static_cast<uint64_t>(cur.e) * vec;
+        const uint64_t it = item + threadIdx.x;
+        if (it >= geom.n_items) break;
+        const uint64_t i0 = elem_of_item(geom, it, vec);
+        const uint64_t pos0 = it * vec;               // (a chunk is ipc items of vec elements)
         for (int p = 0; p < vec; ++p)
             if (i0 + p < geom.n && pos0 + p < cap) idx[pos0 + p] = i0 + p;
     }
@@ -1034,6 +1218,29 @@ static int run_entropy(edgc_ctx* ctx, const EntScratch& s, const EntGroup& g, ui
         EDGC_HIP_TRY(ctx, hipGetLastError());
         return EDGC_OK;
     }
+    if constexpr (VEC > 1) {
+        if (bins <= 4096 && small && ctx->tune_ept == 0) {
+            auto launch = [&](auto u_tag) {
+                constexpr int U = decltype(u_tag)::value;
+                const uint32_t gx = static_cast<uint32_t>((g.n_items + kSmallBlock * U - 1) / (kSmallBlock * U));
+                const uint32_t sets = gx > 16 ? 2u : 1u, zero_words = sets * copy_stride(bins);
+                nparts = range ? 1u : gx;
+                if (range)
+                    EDGC_LAUNCH(ctx, st, KID_SET_RANGE, 4.0 * zero_words, 0.0,
+                                k_set_range<<<(zero_words + 255) / 256, 256, 0, st>>>(s.mm_part, range[0], range[1], s.copies, zero_words));
+                else
+                    EDGC_LAUNCH(ctx, st, KID_MINMAX, sample_bytes, 0.0,
+                                k_minmax_small<T, VEC, kSmallBlock, U><<<gx, kSmallBlock, 0, st>>>(g, s.mm_part, s.copies, zero_words));
+                EDGC_LAUNCH(ctx, st, KID_HIST, sample_bytes, 0.0,
+                            k_hist_small<T, VEC, kSmallBlock, U><<<gx, kSmallBlock, lds, st>>>(
+                                g, s.mm_part, nparts, bins, rep_shift, s.copies, sets, counts, s.ticket, res));
+            };
+            if (g.n_items <= kSmallTwo) launch(std::integral_constant<int, 2>{});
+            else launch(std::integral_constant<int, 4>{});
+            EDGC_HIP_TRY(ctx, hipGetLastError());
+            return EDGC_OK;
+        }
+    }
     // One block of 1024 threads per CU when a histogram of more than 64 KiB leaves room for one block only
     // (1e9 fp32 elements on 65536 bins: 1.6 instead of 3.6 ms) and for samples of 8 Mi items or more (1e8
     // fp32 elements on 4096 bins: 0.13 instead of 0.18 ms; 1e9: 0.83 instead of 0.86 ms); two blocks of
@@ -1043,6 +1250,7 @@ static int run_entropy(edgc_ctx* ctx, const EntScratch& s, const EntGroup& g, ui
     const int floor_items = small ? std::max(4, static_cast<int>((bins_local << rep_shift) / (kHistBlock * VEC / 2)))
                                   : ((bins_local << rep_shift) > 16384 ? 64 : 16);
     const int per_thread = ctx->tune_ept > 0 ? ctx->tune_ept : floor_items;
+    // (EDGC_TUNE_EPT given: these kernels at every size)
     const uint32_t gx = fat ? grid_for(g.n_items, kHistBlockFat, per_thread, ctx->num_cu)
                             : grid_for(g.n_items, kHistBlock, per_thread, ctx->num_cu * 2);
     // the counters the histogram kernel accumulates into
@@ -1131,8 +1339,7 @@ static int launch_entropy_on(edgc_ctx* ctx, const EntScratch& s, const EntGroup&
                              const float* range, edgc_entropy_result* out, uint64_t* counts_out, hipStream_t st)
 {
     // the kernels are compiled for one vector width: every buffer of the group was given the same
-    bool vec = true;
-    for (uint32_t i = 0; i < g.count; ++i) vec = vec && g.geom[i].vec > 1;
+    const bool vec = g.vec > 1;
     // Pinned (device-accessible) host memory takes the result straight from the kernel; any
     // other host memory gets it through a copy on the stream.
     auto* res = static_cast<edgc_entropy_result*>(s.result_dev);

@@ -360,6 +360,61 @@ def test_sixteen_bit_counters_swept_across_short_and_large_buffers(dtype, off):
     c.close()
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("items", [1, 4095, 4096, 4097, 16 * 1024, 16 * 1024 + 1, 64 * 1024, 64 * 1024 + 1, 1024 * 1024,
+                                   1024 * 1024 + 1])
+def test_one_round_kernels_at_the_edges_of_their_blocks(dtype, items):
+    """Samples at the line between one block and several, one and two sets of counters, two and four items per thread, one round
+    and several; in one buffer and in many, of which a block reads whole ones, parts and ragged ends; non-finite
+    values, bin counts on both sides of the line and a caller's range.  Counts and range as plain fp32 arithmetic gives them."""
+    tdt, vec = (torch.bfloat16, 8) if dtype == "bf16" else (torch.float32, 4)
+    gen_ = torch.Generator(device="cuda").manual_seed(items)
+    c, n = ctx(), items * vec
+    cuts = [[n], [n - n // 3, n // 3], [64 * vec * (1 + k % 3) - k % vec for k in range(20)]]
+    cuts[2].append(max(1, n - sum(-(-k // vec) for k in cuts[2]) * vec))     # (as many items, whole or not)
+    for sizes in cuts:
+        if min(sizes) < 1 or (len(sizes) > 2 and items < 4095):
+            continue
+        # every buffer begins on a 16-byte boundary, as torch allocates it
+        bufs = [((torch.rand(k, generator=gen_, device="cuda") - 0.25) ** 3).to(tdt) for k in sizes]
+        flat = torch.cat(bufs).float()
+        if flat.numel() > 100:
+            bufs[0][7], bufs[-1][-1] = float("nan"), float("inf")
+            flat[7], flat[-1] = float("nan"), float("inf")
+        fin = flat[torch.isfinite(flat)]
+        for bins, rng in [(1, None), (255, None), (4096, None), (4097, None), (1024, (-0.01, 0.2))]:
+            counts = torch.full((bins,), -1, dtype=torch.int64, device="cuda")
+            got = c.entropy_estimate(bufs if len(bufs) > 1 else bufs[0], 1, 64, 0, 0, bins, rng, counts)
+            lo, hi = (fin.min(), fin.max()) if rng is None else (torch.tensor(v, device="cuda") for v in rng)
+            scale = torch.tensor(float(bins), dtype=torch.float32) / (hi - lo).cpu()
+            at = (fin - lo) * scale.cuda() if float(hi) > float(lo) else torch.zeros_like(fin)
+            want = torch.bincount(at.clamp(0, bins).long().clamp_(0, bins - 1), minlength=bins)
+            assert (got.lo, got.hi) == (float(lo), float(hi))
+            assert (got.n_sampled, got.n_nonfinite) == (flat.numel(), flat.numel() - fin.numel())
+            assert torch.equal(counts, want), (sizes[:3], bins, rng)
+            p = want[want > 0].double() / fin.numel()
+            assert abs(got.H_bits - float(-(p * torch.log2(p)).sum())) <= H_TOL
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("stride,chunk", [(3, 64), (10, 64), (100, 64), (7, 200)])
+def test_one_round_kernels_on_strided_samples_of_many_buffers(dtype, stride, chunk):
+    """Strided samples of 1 to 32 buffers of ragged lengths, against the oracle's samples of the same buffers."""
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    rng = np.random.default_rng(stride)
+    for count in (1, 2, 3, 24, 32):
+        sizes = [int(rng.integers(1, 60_000)) for _ in range(count - 1)] + [1_000_003]
+        dev = [torch.from_numpy(rng.laplace(0, 1e-3, k).astype(np.float32)).cuda().to(tdt) for k in sizes]
+        for step in range(3):
+            parts = [x.float().cpu().numpy()[orc.sample_indices(x.numel(), stride, chunk, 7, step).astype(np.int64)] for x in dev]
+            ref = orc.entropy(np.concatenate(parts), 1, 64, 0, 0, 1024)
+            counts = torch.full((1024,), -1, dtype=torch.int64, device="cuda")
+            got = ctx().entropy_estimate(dev if count > 1 else dev[0], stride, chunk, 7, step, 1024, None, counts)
+            assert (got.n_sampled, got.lo, got.hi) == (ref.n_sampled, ref.lo, ref.hi)
+            assert np.array_equal(counts.cpu().numpy().astype(np.uint64), ref.counts)
+            assert abs(got.H_bits - ref.H_bits) <= H_TOL
+
+
 def to_host_any(x):
     if x.dtype == torch.bfloat16:
         return x.view(torch.int16).cpu().numpy().view(np.uint16)
