@@ -98,8 +98,10 @@ extern "C" int edgc_create(edgc_ctx** out, int hip_device, uint32_t max_bins, ui
     const size_t at_wide = place(65536 * sizeof(unsigned long long));
     const size_t zeroed = used;
     const size_t at_mm = place(2 * kMaxReduceBlocks * sizeof(float));
-    const size_t at_totals = place(65536 * sizeof(unsigned long long));
+    const size_t at_copies = place(8 * kCopyBins * sizeof(uint32_t));
     const size_t at_counts = place(static_cast<size_t>(max_bins) * sizeof(unsigned long long));
+    s.part16_blocks = static_cast<uint32_t>(std::min(ctx->num_cu, 1024));
+    const size_t at_occupied = place(static_cast<size_t>(s.part16_blocks) * 8 * sizeof(uint32_t));
     const size_t at_result = place(sizeof(edgc_entropy_result));
     const size_t at_gram = place(static_cast<size_t>(36) * 256 * sizeof(double));
     const size_t at_rinv = place(rinv_elems(max_rank) * sizeof(double));
@@ -107,13 +109,12 @@ extern "C" int edgc_create(edgc_ctx** out, int hip_device, uint32_t max_bins, ui
     s.ticket = reinterpret_cast<unsigned int*>(s.small + at_ticket);
     s.wide = reinterpret_cast<unsigned long long*>(s.small + at_wide);
     s.mm_part = reinterpret_cast<float*>(s.small + at_mm);
-    s.totals = reinterpret_cast<unsigned long long*>(s.small + at_totals);
-    s.copies = reinterpret_cast<uint32_t*>(s.totals);       // never in use at the same time
+    s.copies = reinterpret_cast<uint32_t*>(s.small + at_copies);
     s.counts = reinterpret_cast<unsigned long long*>(s.small + at_counts);
     s.result_dev = s.small + at_result;
     s.gram = reinterpret_cast<double*>(s.small + at_gram);
     s.rinv = reinterpret_cast<double*>(s.small + at_rinv);
-    s.part16_blocks = static_cast<uint32_t>(ctx->num_cu);
+    s.occupied = reinterpret_cast<uint32_t*>(s.small + at_occupied);
     ok = ok && dev_alloc(&s.part16, static_cast<size_t>(s.part16_blocks) * 65536) == hipSuccess;
     ok = ok && dev_alloc(&s.part, s.part_elems) == hipSuccess;
     ok = ok && dev_alloc(&s.gram_part, s.gram_part_elems) == hipSuccess;

@@ -19,9 +19,9 @@ struct Scratch {
     unsigned int*       ticket       = nullptr;  // [kTicketWords] last-block ticket, zero between calls
     uint32_t*           copies       = nullptr;  // [8][kCopyBins] histogram counters, a set per XCD
     uint16_t*           part16       = nullptr;  // [part16_blocks][65536] 16-bit counters per block
-    uint32_t            part16_blocks = 0;
+    uint32_t            part16_blocks = 0;       // at most 1024: k_wide_reduce looks at one block's marks per thread
+    uint32_t*           occupied     = nullptr;  // [part16_blocks][8] which of a block's fields were stored, a bit per 256 keys
     unsigned long long* wide         = nullptr;  // [65536] 64-bit credits per key, zero between calls
-    unsigned long long* totals       = nullptr;  // [65536] counts per bf16 bit pattern
     unsigned long long* counts       = nullptr;  // [max_bins] histogram when the caller gives none
     void*               result_dev   = nullptr;  // edgc_entropy_result
     // compress / decompress
@@ -37,7 +37,7 @@ struct Scratch {
 
 constexpr int kMaxReduceBlocks = 4096;
 constexpr uint32_t kTicketWords = 64;      // the last-block ticket, on a cache line of its own
-constexpr uint32_t kCopyBins = 16384;      // (8 x kCopyBins counters of 32 bits take the place of `totals`) largest histogram that is accumulated in one set of counters per XCD
+constexpr uint32_t kCopyBins = 16384;      // largest histogram that is accumulated in one set of counters per XCD
 
 // 16-wide tiles per side of the Gram matrix and of R^-1 at a rank: the orthonormalisation kernels are built for
 // 1, 2, 4 and 8, and work on (and store) every tile of the size they are built for.

@@ -853,26 +853,52 @@ __global__ __launch_bounds__(kOneBlock) void k_estimate_one(const EntGroup grp, 
 // the LDS: 134 M bf16 elements 90 us against 61, 4.4 TB/s.)
 // At its end a block stores its fields as they stand to its own 128 KiB of `part16` (plain
 // 16-byte stores: no atomics on global memory, of which 256 blocks x some thousand keys would be
-// the larger part of a small estimate), and k_wide_reduce sums them.
+// the larger part of a small estimate), and k_wide_reduce sums them.  Only the runs of 256 fields that hold anything are
+// stored, and marked in `occupied`: the values of a gradient touch some thirty of the 256 runs of bf16 patterns, and the
+// middle and a few outliers of 65536 bins.
 // ---------------------------------------------------------------------------
 constexpr int kWideBlock = 1024;
 constexpr uint32_t kWideKeys = 65536;
+constexpr uint32_t kReduceKeys = 256;                                     // keys that one block of k_wide_reduce sums
+constexpr uint32_t kOccupiedWords = kWideKeys / kReduceKeys / 32;         // 32-bit words of a block's marks
+static_assert(kReduceKeys / 8 == 32 && kWideKeys / 8 == kOccupiedWords * kWideBlock && kWideBlock / 32 == 32,
+              "k_wide_hist: half a wave stores the fields of one block of k_wide_reduce, each of 32 half waves one of each word");
+
+__device__ __forceinline__ void note_pattern(uint32_t key, float& lo, float& hi)     // key: of a bf16 value that occurs
+{
+    const float x = __uint_as_float(key << 16);
+    if (finite_f32(x)) { lo = fminf(lo, x); hi = fmaxf(hi, x); }
+}
 
 template <typename T, int VEC, bool PATTERN>
 __global__ __launch_bounds__(kWideBlock) void k_wide_hist(
-    const EntGroup grp, const float2* __restrict__ part, uint32_t nparts, uint32_t bins, uint16_t* __restrict__ part16,
-    unsigned long long* __restrict__ wide)
+    const EntGroup grp, float2* __restrict__ part, uint32_t nparts, uint32_t bins, uint16_t* __restrict__ part16,
+    uint32_t* __restrict__ occupied, unsigned long long* __restrict__ wide, unsigned long long* __restrict__ counts)
 {
     static_assert(!PATTERN || sizeof(T) == 2, "the raw pattern is the key of 16-bit elements only");
     constexpr uint32_t kRounds = 32768 / (kWideBlock * 4 * VEC);   // rounds that together add at most 32768 to a field
     static_assert(kRounds >= 1, "what a round can add to one field");
-    extern __shared__ uint32_t h[];   // [kWideKeys / 2]
+    extern __shared__ __align__(256) uint32_t h[];   // [kWideKeys / 2]
+    __shared__ uint32_t s_occupied[kOccupiedWords];
     uint4* const h4 = reinterpret_cast<uint4*>(h);
+    // PATTERN: range of the finite patterns whose fields were moved off (they may be zero at the end), in the order of their
+    // values.  In LDS: kept in registers it slows the loop over the sample down (57 to 67 us for 134 M elements).
+    __shared__ uint32_t s_moved_lo, s_moved_hi;
+    auto note_moved = [&](uint32_t key) {
+        if (!PATTERN || (key & 0x7f80u) == 0x7f80u) return;
+        const uint32_t order = key & 0x8000u ? 0xffffu - key : key | 0x8000u;
+        atomicMin(&s_moved_lo, order);
+        atomicMax(&s_moved_hi, order);
+    };
+    if (threadIdx.x < kOccupiedWords) s_occupied[threadIdx.x] = 0u;
+    if (threadIdx.x == 0) { s_moved_lo = 0xffffu; s_moved_hi = 0u; }
     for (uint32_t i = threadIdx.x; i < kWideKeys / 8; i += kWideBlock) h4[i] = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
 
     float lo = 0.0f, scale = 0.0f, top = 0.0f;
-    if constexpr (!PATTERN) {
+    if constexpr (PATTERN) {
+        for (uint32_t i = blockIdx.x * kWideBlock + threadIdx.x; i < bins; i += gridDim.x * kWideBlock) counts[i] = 0ull;
+    } else {
         const float fbins = static_cast<float>(bins);
         const RangeParams rp = fold_range<kWideBlock>(part, nparts, fbins);
         lo = rp.lo; scale = rp.scale;
@@ -915,69 +941,116 @@ __global__ __launch_bounds__(kWideBlock) void k_wide_hist(
                 since = 0;
             }
             __syncthreads();
+            uint32_t full = 0;                                     // which of this thread's 16-byte words hold such a field
 #pragma unroll
-            for (uint32_t j = 0; j < kWideKeys / 8 / kWideBlock; ++j) {
-                const uint32_t at = threadIdx.x + j * kWideBlock;
-                const uint4 v = h4[at];
-                if (((v.x | v.y | v.z | v.w) & 0x80008000u) == 0u) continue;
-                const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                for (uint32_t q = 0; q < 4; ++q) {
-                    if (w[q] & 0x8000u) atomicAdd(&wide[at * 8 + 2 * q], 32768ull);
-                    if (w[q] & 0x80000000u) atomicAdd(&wide[at * 8 + 2 * q + 1], 32768ull);
+            for (uint32_t j = 0; j < kOccupiedWords; ++j) {
+                const uint4 v = h4[threadIdx.x + j * kWideBlock];
+                full |= ((v.x | v.y | v.z | v.w) & 0x80008000u) ? 1u << j : 0u;
+            }
+            // rare, and compiled into every call of this function: short code, not fast code (written out, 8 x 8 fields per
+            // call, the kernel was 150 KB and its few rounds ran from a cold instruction cache)
+#pragma unroll 1
+            for (; full; full &= full - 1u) {
+                const uint32_t at = (threadIdx.x + (__ffs(full) - 1) * kWideBlock) * 4;
+#pragma unroll 1
+                for (uint32_t q = at; q < at + 4; ++q) {
+                    const uint32_t w = h[q];
+                    if (w & 0x8000u) { atomicAdd(&wide[2 * q], 32768ull); note_moved(2 * q); }
+                    if (w & 0x80000000u) { atomicAdd(&wide[2 * q + 1], 32768ull); note_moved(2 * q + 1); }
+                    h[q] = w & 0x7fff7fffu;
                 }
-                h4[at] = make_uint4(v.x & 0x7fff7fffu, v.y & 0x7fff7fffu, v.z & 0x7fff7fffu, v.w & 0x7fff7fffu);
             }
             __syncthreads();
         });
     __syncthreads();
     uint4* __restrict__ dst = reinterpret_cast<uint4*>(part16 + static_cast<size_t>(blockIdx.x) * kWideKeys);
-    for (uint32_t i = threadIdx.x; i < kWideKeys / 8; i += kWideBlock) dst[i] = h4[i];
+    float key_lo = INFINITY, key_hi = -INFINITY;
+    if constexpr (PATTERN) {
+        if (threadIdx.x == 0 && s_moved_lo <= s_moved_hi) {
+            const uint32_t a = s_moved_lo, b = s_moved_hi;
+            note_pattern(a & 0x8000u ? a & 0x7fffu : 0xffffu - a, key_lo, key_hi);
+            note_pattern(b & 0x8000u ? b & 0x7fffu : 0xffffu - b, key_lo, key_hi);
+        }
+    }
+#pragma unroll
+    for (uint32_t j = 0; j < kOccupiedWords; ++j) {
+        const uint32_t i = threadIdx.x + j * kWideBlock;
+        const uint4 v = h4[i];
+        const uint64_t any = __ballot((v.x | v.y | v.z | v.w) != 0u);
+        if (static_cast<uint32_t>(threadIdx.x & 32u ? any >> 32 : any) == 0u) continue;
+        dst[i] = v;
+        if constexpr (PATTERN) {
+            // values of one sign rise or fall with the pattern: the first and the last that occurs of the eight
+            const uint32_t m = ((v.x & 0xffffu) ? 1u : 0u) | ((v.x >> 16) ? 2u : 0u) | ((v.y & 0xffffu) ? 4u : 0u) |
+                               ((v.y >> 16) ? 8u : 0u) | ((v.z & 0xffffu) ? 16u : 0u) | ((v.z >> 16) ? 32u : 0u) |
+                               ((v.w & 0xffffu) ? 64u : 0u) | ((v.w >> 16) ? 128u : 0u);
+            if (m) {
+                note_pattern(i * 8 + __ffs(m) - 1, key_lo, key_hi);
+                note_pattern(i * 8 + 31 - __clz(m), key_lo, key_hi);
+            }
+        }
+        if ((threadIdx.x & 31u) == 0u) atomicOr(&s_occupied[j], 1u << (threadIdx.x >> 5));
+    }
+    if constexpr (PATTERN) {
+        block_range_minmax<kWideBlock>(key_lo, key_hi);
+        if (threadIdx.x == 0) part[blockIdx.x] = make_float2(key_lo, key_hi);
+    }
+    __syncthreads();
+    if (threadIdx.x < kOccupiedWords) occupied[blockIdx.x * kOccupiedWords + threadIdx.x] = s_occupied[threadIdx.x];
 }
 
 // Sums the blocks' 16-bit fields and the 64-bit credits per key, 256 keys per block, and the last block to finish
-// turns the totals into the estimate.
+// turns the histogram into the estimate.
 //  fp32 (keys are bins): the totals are the histogram.
-//  bf16 (keys are bit patterns): the blocks also reduce the range of the patterns that occur; the
-//  last block bins the patterns' totals in LDS (slices of 16384 bins) and writes the histogram.
-// What bounds it: the latency of reading 128 KiB from each of up to 256 blocks' fields; all of a thread's eight 16-byte
-// loads are in flight together, on every CU (64 blocks of 1024 keys took 44 us for bf16 and 33 for fp32, a fence in
-// every wave included; these take 27 and 19).
-constexpr uint32_t kWideSliceBins = 16384;
-constexpr uint32_t kReduceKeys = 256;                                     // per block
+//  bf16 (keys are bit patterns): every block folds the range of the patterns that k_wide_hist's blocks saw and adds its
+//  256 totals to the bins of their patterns.
+// What bounds it: latency, of the marks, the marked blocks' fields (all of a thread's eight 16-byte loads in flight together),
+// the one release per block and the last block's loads of the bins.  134 M bf16 elements of a gradient, both kernels: all of
+// 33 MB of fields read and the patterns binned by the last block alone 86.0 us, marked fields only 80.4, binned by every block
+// and k_wide_hist's short sweep 73.8; 10 M fp32 elements on 65536 bins (range kernel included) 43.7 us, marked fields only 35.5.
 constexpr uint32_t kReduceGroups = kWideBlock / (kReduceKeys / 8);        // 32 groups of 32 threads
 constexpr size_t kWideReduceLds = (kReduceGroups + 4) * kReduceKeys * sizeof(uint32_t);
 
 template <bool PATTERN>
 __global__ __launch_bounds__(kWideBlock) void k_wide_reduce(
-    const uint16_t* __restrict__ part16, uint32_t nblocks, unsigned long long* __restrict__ wide,
-    unsigned long long* totals, uint32_t bins, int has_range, float range_lo, float range_hi,
-    unsigned long long* counts, const float2* __restrict__ mm_part, uint32_t nparts, float* part, unsigned int* ticket,
-    unsigned long long n_sampled, edgc_entropy_result* res)
+    const uint16_t* __restrict__ part16, const uint32_t* __restrict__ occupied, uint32_t nblocks, unsigned long long* __restrict__ wide,
+    uint32_t bins, int has_range, float range_lo, float range_hi, unsigned long long* counts,
+    const float2* __restrict__ mm_part, uint32_t nparts, double* part_d, unsigned int* ticket, unsigned long long n_sampled,
+    edgc_entropy_result* res)
 {
-    extern __shared__ unsigned long long slice[];     // the groups' sums; PATTERN: [min(bins, kWideSliceBins)] as well
-    constexpr uint32_t kMaxGrid = kWideKeys / kReduceKeys;
+    extern __shared__ __align__(256) uint32_t red[];                  // the groups' sums: [kReduceGroups][kReduceKeys], then [4][kReduceKeys]
     const bool mine = threadIdx.x < kReduceKeys;      // one key per thread
     const uint32_t key = blockIdx.x * kReduceKeys + threadIdx.x;
-    // per block: (lo, hi) of the patterns that occur, or (sum c log2 c, sum c) of its bins
-    double* const part_d = reinterpret_cast<double*>(part);
-
+    __shared__ uint32_t s_from[kWideBlock], s_nfrom;  // the blocks that counted any of this block's keys, in any order
+    if (threadIdx.x == 0) s_nfrom = 0u;
     unsigned long long c = mine ? wide[key] : 0ull;
+    const uint32_t marks = threadIdx.x < nblocks ? occupied[threadIdx.x * kOccupiedWords + (blockIdx.x >> 5)] : 0u;
+    __syncthreads();
+    if ((marks >> (blockIdx.x & 31u)) & 1u) s_from[atomicAdd(&s_nfrom, 1u)] = threadIdx.x;
     if (c) wide[key] = 0ull;                          // zero between estimates
-    {
+    RangeParams rp{};
+    if constexpr (PATTERN) {
+        float lo = INFINITY, hi = -INFINITY;
+        if (threadIdx.x < nblocks) { lo = mm_part[threadIdx.x].x; hi = mm_part[threadIdx.x].y; }
+        block_range_minmax<kWideBlock>(lo, hi);
+        if (has_range) { lo = range_lo; hi = range_hi; }
+        rp = make_range(lo, hi, static_cast<float>(bins));
+    }
+    __syncthreads();
+    const uint32_t nfrom = s_nfrom;
+    if (nfrom) {
         // The block's keys are 32 columns of eight 16-bit fields (one 16-byte load); each of its 32 groups of 32 threads
-        // sums every 32nd block's fields, and the groups' sums meet in LDS.
-        uint32_t* const red = reinterpret_cast<uint32_t*>(slice);          // [kReduceGroups][kReduceKeys], then [4][kReduceKeys]
+        // sums the fields of every 32nd listed block, and the groups' sums meet in LDS.
         const uint32_t col = threadIdx.x & 31u, grp = threadIdx.x >> 5;
         const uint4* __restrict__ src = reinterpret_cast<const uint4*>(part16 + blockIdx.x * kReduceKeys) + col;
         constexpr size_t kRow = kWideKeys / 8;                             // 16-byte items per block's fields
         uint32_t sm[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};                 // at most 256 fields of 16 bits
-        for (uint32_t b = grp; b < nblocks; b += 8 * kReduceGroups) {
+        for (uint32_t b = grp; b < nfrom; b += 8 * kReduceGroups) {
             uint4 v[8];
 #pragma unroll
             for (uint32_t u = 0; u < 8; ++u)
-                v[u] = (b + kReduceGroups * u < nblocks) ? src[static_cast<size_t>(b + kReduceGroups * u) * kRow]
-                                                         : make_uint4(0u, 0u, 0u, 0u);
+                v[u] = (b + kReduceGroups * u < nfrom) ? src[static_cast<size_t>(s_from[b + kReduceGroups * u]) * kRow]
+                                                       : make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 sm[0] += v[u].x & 0xffffu; sm[1] += v[u].x >> 16;
@@ -998,7 +1071,6 @@ __global__ __launch_bounds__(kWideBlock) void k_wide_reduce(
         red2[quarter * kReduceKeys + k] = sum;
         __syncthreads();
         if (mine) c += red2[k] + red2[kReduceKeys + k] + red2[2 * kReduceKeys + k] + red2[3 * kReduceKeys + k];
-        __syncthreads();                              // `slice` is used again by the last block
     }
     if constexpr (!PATTERN) {
         // the totals are the histogram; this block's share of the entropy sums goes with them
@@ -1009,78 +1081,41 @@ __global__ __launch_bounds__(kWideBlock) void k_wide_reduce(
         }
         block_sum_pair<kWideBlock>(acc, tot);
         if (threadIdx.x == kWideBlock - 1) { part_d[2 * blockIdx.x] = acc; part_d[2 * blockIdx.x + 1] = tot; }
-    } else {
-        float lo = INFINITY, hi = -INFINITY;
-        if (mine) {
-            totals[key] = c;
-            const float x = __uint_as_float(key << 16);
-            if (c && finite_f32(x)) { lo = x; hi = x; }
+    } else if (threadIdx.x < kReduceKeys) {           // whole waves
+        const float x = __uint_as_float(key << 16);
+        if (!finite_f32(x)) c = 0ull;
+        // bin = trunc((x - lo) * scale), each operation rounded on its own, clamped to [0, bins - 1]
+        const float top = __uint_as_float(__float_as_uint(static_cast<float>(bins)) - 1u);   // largest float below the bin count
+        const uint32_t bin = static_cast<uint32_t>(
+            __builtin_amdgcn_fmed3f(__fmul_rn(__fsub_rn(x, rp.lo), rp.scale), 0.0f, top));
+        // Patterns next to each other share a bin wherever values are small: one addition per run of equal bins in a wave,
+        // of the difference of two running sums.
+        const uint32_t lane = threadIdx.x & 63u;
+        unsigned long long sum = c;
+#pragma unroll
+        for (uint32_t d = 1; d < 64; d <<= 1) {
+            const unsigned long long below = __shfl_up(sum, d, 64);
+            if (lane >= d) sum += below;
         }
-        block_range_minmax<kWideBlock>(lo, hi);
-        if (threadIdx.x == 0) {
-            part[2 * blockIdx.x]     = lo;            // lo > hi: none of this block's patterns occurs
-            part[2 * blockIdx.x + 1] = hi;
-        }
+        const uint32_t bin_below = __shfl_up(bin, 1, 64);
+        const uint64_t heads = __ballot(lane == 0 || bin != bin_below);
+        const uint32_t head = 63u - __clzll(heads & (~0ull >> (63u - lane)));
+        const unsigned long long before = __shfl(sum, static_cast<int>(head) - 1, 64);
+        const bool tail = lane == 63u || ((heads >> lane >> 1) & 1u);
+        const unsigned long long run = sum - (head ? before : 0ull);
+        if (tail && run) atomicAdd(&counts[bin], run);
     }
     if (!last_block<kWideBlock>(ticket)) return;
+    if constexpr (PATTERN) {
+        finish_hist<kWideBlock>(nullptr, 0u, counts, bins, rp, n_sampled, res);
+        return;
+    }
 
-    RangeParams rp;
+    rp = fold_range<kWideBlock>(mm_part, nparts, static_cast<float>(bins));
     double acc = 0.0, tot = 0.0;
-    if constexpr (!PATTERN) {
-        rp = fold_range<kWideBlock>(mm_part, nparts, static_cast<float>(bins));
-        if (threadIdx.x < gridDim.x) {
-            acc = part_d[2 * threadIdx.x];
-            tot = part_d[2 * threadIdx.x + 1];
-        }
-    } else {
-        // range of the finite sample from the blocks' partials, and the list of the blocks (of 256 patterns) in which
-        // any finite pattern occurs: a dense gradient touches a few of the 256
-        __shared__ uint32_t s_list[kMaxGrid], s_nlist;
-        float lo = INFINITY, hi = -INFINITY;
-        if (threadIdx.x < gridDim.x) { lo = part[2 * threadIdx.x]; hi = part[2 * threadIdx.x + 1]; }
-        const bool occurs = lo <= hi;
-        if (threadIdx.x == 0) s_nlist = 0u;
-        __syncthreads();
-        if (occurs) s_list[atomicAdd(&s_nlist, 1u)] = threadIdx.x;         // any order: the sums are of integers
-        block_range_minmax<kWideBlock>(lo, hi);
-        if (has_range) { lo = range_lo; hi = range_hi; }
-        rp = make_range(lo, hi, static_cast<float>(bins));
-        const uint32_t nlist = s_nlist, quarter = threadIdx.x / kReduceKeys, k = threadIdx.x & (kReduceKeys - 1u);
-        const float top = __uint_as_float(__float_as_uint(static_cast<float>(bins)) - 1u);   // largest float below the bin count
-        for (uint32_t base = 0; base < bins; base += kWideSliceBins) {
-            const uint32_t nb = min(kWideSliceBins, bins - base);
-            for (uint32_t i = threadIdx.x; i < nb; i += kWideBlock) slice[i] = 0ull;
-            __syncthreads();
-            // 32 of the listed blocks at a time, eight per quarter of this one: their loads are in flight together
-            for (uint32_t j = 0; j < nlist; j += 32) {
-                unsigned long long cp[8];
-                uint32_t pp[8];
-#pragma unroll
-                for (uint32_t u = 0; u < 8; ++u) {
-                    const uint32_t l = j + 4 * u + quarter;
-                    pp[u] = s_list[min(l, nlist - 1)] * kReduceKeys + k;
-                    cp[u] = l < nlist ? totals[pp[u]] : 0ull;
-                }
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const float x = __uint_as_float(pp[u] << 16);
-                    if (cp[u] && finite_f32(x)) {
-                        // bin = trunc((x - lo) * scale), each operation rounded on its own, clamped to [0, bins - 1]
-                        const float t = __fsub_rn(x, rp.lo);
-                        const uint32_t bin =
-                            static_cast<uint32_t>(__builtin_amdgcn_fmed3f(__fmul_rn(t, rp.scale), 0.0f, top));
-                        if (bin - base < nb) atomicAdd(&slice[bin - base], cp[u]);
-                    }
-                }
-            }
-            __syncthreads();
-            for (uint32_t i = threadIdx.x; i < nb; i += kWideBlock) {
-                const unsigned long long cb = slice[i];
-                counts[base + i] = cb;
-                entropy_term(cb, acc, tot);
-            }
-            __syncthreads();
-        }
+    if (threadIdx.x < gridDim.x) {
+        acc = part_d[2 * threadIdx.x];
+        tot = part_d[2 * threadIdx.x + 1];
     }
     const double log_w = log_bin_width(rp, bins);
     block_sum_pair<kWideBlock>(acc, tot);
@@ -1155,8 +1190,8 @@ struct EntScratch {
     uint32_t*           copies;        // [8][kCopyBins] histogram counters by XCD
     uint16_t*           part16;        // [part16_blocks][65536] 16-bit counters per block, or null: plain kernels only
     uint32_t            part16_blocks;
+    uint32_t*           occupied;      // [part16_blocks][kOccupiedWords] which of a block's fields hold anything, a bit per 256 keys
     unsigned long long* wide;          // [65536] 64-bit credits per key, zero between calls
-    unsigned long long* totals;        // [65536] counts per bf16 bit pattern
     unsigned long long* counts;        // histogram when the caller gives none
     void*               result_dev;    // edgc_entropy_result
 };
@@ -1181,19 +1216,16 @@ static int run_entropy(edgc_ctx* ctx, const EntScratch& s, const EntGroup& g, ui
     const bool by_wide_bins = sizeof(T) == 4 && wide_ok && bins > 16384 && bins <= kWideKeys;
     const uint32_t wide_blocks = grid_for(g.n_items, kWideBlock, 4, min(ctx->num_cu, static_cast<int>(s.part16_blocks)));
     uint32_t nparts = 0;                                   // blocks' (lo, hi) in s.mm_part
-    float* const pair_part = reinterpret_cast<float*>(s.mm_part + kMaxReduceBlocks / 2);
+    double* const pair_part = reinterpret_cast<double*>(s.mm_part + kMaxReduceBlocks / 2);
     if constexpr (sizeof(T) == 2) {
         if (by_pattern) {
             EDGC_LAUNCH(ctx, st, KID_WIDE_HIST, sample_bytes, 0.0,
                         k_wide_hist<T, VEC, true><<<wide_blocks, kWideBlock, kWideKeys * 2, st>>>(
-                            g, s.mm_part, nparts, bins, s.part16, s.wide));
-            const size_t lds = max(static_cast<size_t>(min(bins, kWideSliceBins)) * sizeof(unsigned long long),
-                                   kWideReduceLds);
+                            g, s.mm_part, nparts, bins, s.part16, s.occupied, s.wide, counts));
             EDGC_LAUNCH(ctx, st, KID_WIDE_REDUCE, 2.0 * kWideKeys * wide_blocks, 0.0,
-                        k_wide_reduce<true><<<kWideKeys / kReduceKeys, kWideBlock, lds, st>>>(
-                            s.part16, wide_blocks, s.wide, s.totals, bins, range ? 1 : 0, range ? range[0] : 0.0f,
-                            range ? range[1] : 0.0f, counts, nullptr, 0u, pair_part, s.ticket,
-                            g.n_sampled, res));
+                        k_wide_reduce<true><<<kWideKeys / kReduceKeys, kWideBlock, kWideReduceLds, st>>>(
+                            s.part16, s.occupied, wide_blocks, s.wide, bins, range ? 1 : 0, range ? range[0] : 0.0f,
+                            range ? range[1] : 0.0f, counts, s.mm_part, wide_blocks, pair_part, s.ticket, g.n_sampled, res));
             EDGC_HIP_TRY(ctx, hipGetLastError());
             return EDGC_OK;
         }
@@ -1278,10 +1310,10 @@ static int run_entropy(edgc_ctx* ctx, const EntScratch& s, const EntGroup& g, ui
         if (by_wide_bins) {
             EDGC_LAUNCH(ctx, st, KID_WIDE_HIST, sample_bytes, 0.0,
                         k_wide_hist<T, VEC, false><<<wide_blocks, kWideBlock, kWideKeys * 2, st>>>(
-                            g, s.mm_part, nparts, bins, s.part16, s.wide));
+                            g, s.mm_part, nparts, bins, s.part16, s.occupied, s.wide, counts));
             EDGC_LAUNCH(ctx, st, KID_WIDE_REDUCE, 2.0 * kWideKeys * wide_blocks, 0.0,
                         k_wide_reduce<false><<<(bins + kReduceKeys - 1) / kReduceKeys, kWideBlock, kWideReduceLds, st>>>(
-                            s.part16, wide_blocks, s.wide, s.totals, bins, 0, 0.0f, 0.0f, counts, s.mm_part, nparts,
+                            s.part16, s.occupied, wide_blocks, s.wide, bins, 0, 0.0f, 0.0f, counts, s.mm_part, nparts,
                             pair_part, s.ticket, g.n_sampled, res));
             EDGC_HIP_TRY(ctx, hipGetLastError());
             return EDGC_OK;
@@ -1313,9 +1345,6 @@ int prepare_entropy_kernels(edgc_ctx* ctx)
                                           hipFuncAttributeMaxDynamicSharedMemorySize, wide_lds));
     EDGC_HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(&k_wide_hist<float, 1, false>),
                                           hipFuncAttributeMaxDynamicSharedMemorySize, wide_lds));
-    EDGC_HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(&k_wide_reduce<true>),
-                                          hipFuncAttributeMaxDynamicSharedMemorySize,
-                                          static_cast<int>(kWideSliceBins * sizeof(unsigned long long))));
     EDGC_HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(&k_hist<float, 4, kHistBlock>),
                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds));
     EDGC_HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(&k_hist<float, 4, kHistBlockFat>),
@@ -1370,8 +1399,8 @@ int launch_entropy(edgc_ctx* ctx, const EntGroup& g, edgc_dtype dt, uint32_t bin
                    const float* range, edgc_entropy_result* out, uint64_t* counts_out, hipStream_t st)
 {
     const Scratch& c = ctx->s;
-    const EntScratch s{reinterpret_cast<float2*>(c.mm_part), c.ticket, c.copies, c.part16, c.part16_blocks, c.wide,
-                       c.totals, c.counts, c.result_dev};
+    const EntScratch s{reinterpret_cast<float2*>(c.mm_part), c.ticket, c.copies, c.part16, c.part16_blocks, c.occupied, c.wide,
+                       c.counts, c.result_dev};
     return launch_entropy_on(ctx, s, g, dt, bins, range, out, counts_out, st);
 }
 

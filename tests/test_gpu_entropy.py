@@ -272,6 +272,23 @@ def test_sixteen_bit_counter_kernels_on_small_and_ragged_samples(mode, dtype):
     c.close()
 
 
+@pytest.mark.parametrize("a,b", [(0.375, 0.375), (-2.5, 2.0 ** -20), (-3.0, -0.5), (0.0, 1.0), (2.0 ** 100, -2.0 ** -100)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_sixteen_bit_counters_that_end_at_zero(dtype, a, b):
+    """Every block counts a whole multiple of 32768 of one value, so that all of it has been moved off and the field is
+    zero at the end: range, counts and entropy still hold the value.  Few values: most runs of fields are not stored."""
+    n, bins = 1 << 26, 65536 if dtype == "f32" else 4096
+    x = torch.full((n,), a, device="cuda", dtype=torch.bfloat16 if dtype == "bf16" else torch.float32)
+    x[n // 2:] = b
+    counts = torch.empty(bins, dtype=torch.int64, device="cuda")
+    got = ctx().entropy_estimate(x, 1, 64, 0, 0, bins, None, counts)
+    assert got.status == 0 and (got.lo, got.hi, got.n_sampled) == (min(a, b), max(a, b), n)
+    if a == b:
+        assert got.H_bits == 0.0 and int(counts[0]) == n
+    else:
+        assert got.H_bits == 1.0 and int(counts[0]) == n // 2 and int(counts[bins - 1]) == n // 2
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_sixteen_bit_counters_under_the_heaviest_contention(dtype):
     """Every thread of every block hits the same one or two 16-bit fields: a constant buffer and a
