@@ -60,7 +60,7 @@ __global__ void k_init_q(float* Q, uint32_t n, uint32_t ldq, uint32_t c0, uint32
 // P-pass:  D = G + E_old,  P_partial[s] = D[:, k-range s] * Q[k-range s, :]
 // Block: 4 waves x 32 rows = 128 rows; k-step of 64 columns.
 // ---------------------------------------------------------------------------
-template <int NP, bool VECOK>
+template <int NP>
 __device__ __forceinline__ void load_grad4(const typename GradElem<NP>::type* __restrict__ G,
                                            uint64_t ldg, uint32_t row, uint32_t col, uint32_t m,
                                            uint32_t col_end, float (&v)[4])
@@ -68,12 +68,12 @@ __device__ __forceinline__ void load_grad4(const typename GradElem<NP>::type* __
     v[0] = v[1] = v[2] = v[3] = 0.0f;
     if (G == nullptr || row >= m || col >= col_end) return;   // null gradient: D is re-read as it stands
     const auto* p = G + static_cast<uint64_t>(row) * ldg + col;
-    if (VECOK && col + 4 <= col_end) {
+    if (col + 4 <= col_end) {
         if constexpr (NP == 2) {
-            const float4 q = *reinterpret_cast<const float4*>(p);
+            const Floats4 q = at_any<Floats4>(p);
             v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
         } else {
-            const uint2 q = *reinterpret_cast<const uint2*>(p);
+            const Bf16Quad q = at_any<Bf16Quad>(p);
             v[0] = __uint_as_float(q.x << 16); v[1] = __uint_as_float(q.x & 0xffff0000u);
             v[2] = __uint_as_float(q.y << 16); v[3] = __uint_as_float(q.y & 0xffff0000u);
         }
@@ -87,15 +87,14 @@ __device__ __forceinline__ void load_grad4(const typename GradElem<NP>::type* __
     }
 }
 
-template <bool VECOK>
 __device__ __forceinline__ void load_f32x4(const float* __restrict__ base, uint64_t ld, uint32_t row,
                                            uint32_t col, uint32_t rows, uint32_t col_end, float (&v)[4])
 {
     v[0] = v[1] = v[2] = v[3] = 0.0f;
     if (row >= rows || col >= col_end) return;
     const float* p = base + static_cast<uint64_t>(row) * ld + col;
-    if (VECOK && col + 4 <= col_end) {
-        const float4 q = *reinterpret_cast<const float4*>(p);
+    if (col + 4 <= col_end) {
+        const Floats4 q = at_any<Floats4>(p);
         v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
     } else {
 #pragma unroll
@@ -103,37 +102,34 @@ __device__ __forceinline__ void load_f32x4(const float* __restrict__ base, uint6
     }
 }
 
-template <bool VECOK>
 __device__ __forceinline__ void store_f32x4(float* __restrict__ base, uint64_t ld, uint32_t row,
                                             uint32_t col, uint32_t rows, uint32_t col_end,
                                             const float (&v)[4])
 {
     if (row >= rows || col >= col_end) return;
     float* p = base + static_cast<uint64_t>(row) * ld + col;
-    if (VECOK && col + 4 <= col_end) {
-        *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
+    if (col + 4 <= col_end) {
+        put_any(p, Floats4{v[0], v[1], v[2], v[3]});
     } else {
 #pragma unroll
         for (int e = 0; e < 4; ++e) if (col + e < col_end) p[e] = v[e];
     }
 }
 
-// 16-byte streaming load that does not pollute the caches (the matrix is read once per pass)
-typedef float vf4 __attribute__((ext_vector_type(4)));
-typedef uint32_t vu2 __attribute__((ext_vector_type(2)));
+// streaming load of four elements that does not pollute the caches (the matrix is read once per pass)
 __device__ __forceinline__ void ld_stream4(const float* __restrict__ p, float (&v)[4])
 {
-    const vf4 q = __builtin_nontemporal_load(reinterpret_cast<const vf4*>(p));
+    const f32x4_any q = __builtin_nontemporal_load(reinterpret_cast<const f32x4_any*>(p));
     v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
 }
 __device__ __forceinline__ void ld_stream4(const uint16_t* __restrict__ p, float (&v)[4])
 {
-    const vu2 q = __builtin_nontemporal_load(reinterpret_cast<const vu2*>(p));
+    const bf16x4_any q = __builtin_nontemporal_load(reinterpret_cast<const bf16x4_any*>(p));
     v[0] = __uint_as_float(q.x << 16); v[1] = __uint_as_float(q.x & 0xffff0000u);
     v[2] = __uint_as_float(q.y << 16); v[3] = __uint_as_float(q.y & 0xffff0000u);
 }
 
-template <int NP, int RT, bool VECOK>
+template <int NP, int RT>
 __global__ __launch_bounds__(256) void k_pass_p(const Group grp)
 {
     const TensorArgs& ta = grp.t[locate(grp, blockIdx.x)];
@@ -169,7 +165,7 @@ __global__ __launch_bounds__(256) void k_pass_p(const Group grp)
     float d[PA][4];
     float qv[PQ][8];
 
-    // FULL: the whole 128 x 64 tile is inside the matrix and vector accesses are allowed
+    // FULL: the whole 128 x 64 tile is inside the matrix
     auto fetch = [&](uint32_t k0, auto full_tag) {
         constexpr bool FULL = decltype(full_tag)::value;
 #pragma unroll
@@ -180,12 +176,12 @@ __global__ __launch_bounds__(256) void k_pass_p(const Group grp)
                 if (G) ld_stream4(G + static_cast<uint64_t>(row) * ldg + col, g);
                 if (!e_zero) {
                     const float* pe = E + static_cast<uint64_t>(row) * n + col;
-                    const float4 q4 = *reinterpret_cast<const float4*>(pe);
+                    const Floats4 q4 = at_any<Floats4>(pe);
                     e[0] = q4.x; e[1] = q4.y; e[2] = q4.z; e[3] = q4.w;
                 }
             } else {
-                load_grad4<NP, VECOK>(G, ldg, row, col, m, k_end, g);
-                if (!e_zero) load_f32x4<VECOK>(E, n, row, col, m, k_end, e);
+                load_grad4<NP>(G, ldg, row, col, m, k_end, g);
+                if (!e_zero) load_f32x4(E, n, row, col, m, k_end, e);
             }
 #pragma unroll
             for (int x = 0; x < 4; ++x) d[p][x] = g[x] + e[x];
@@ -209,10 +205,9 @@ __global__ __launch_bounds__(256) void k_pass_p(const Group grp)
         for (int p = 0; p < PA; ++p) {
             const uint32_t row = row0 + p * RPP + a_row, col = k0 + a_col;
             if constexpr (FULL)
-                *reinterpret_cast<float4*>(E + static_cast<uint64_t>(row) * n + col) =
-                    make_float4(d[p][0], d[p][1], d[p][2], d[p][3]);
+                put_any(E + static_cast<uint64_t>(row) * n + col, Floats4{d[p][0], d[p][1], d[p][2], d[p][3]});
             else
-                store_f32x4<VECOK>(E, n, row, col, m, k_end, d[p]);
+                store_f32x4(E, n, row, col, m, k_end, d[p]);
             bf16x4 w[NP];
             pack4<NP>(d[p], w);
 #pragma unroll
@@ -232,7 +227,7 @@ __global__ __launch_bounds__(256) void k_pass_p(const Group grp)
             }
         }
     };
-    auto tile_full = [&](uint32_t k0) { return VECOK && rows_full && k0 + BK <= k_end; };
+    auto tile_full = [&](uint32_t k0) { return rows_full && k0 + BK <= k_end; };
     using T = std::true_type;
     using F = std::false_type;
 
@@ -1075,14 +1070,14 @@ __device__ __forceinline__ void load_d_rows(const float* __restrict__ D, uint32_
         const float* p = D + static_cast<uint64_t>(row) * n + col;
         if constexpr (FULL) {
             if constexpr (NT == 4) {
-                const float4 x = *reinterpret_cast<const float4*>(p);
+                const Floats4 x = at_any<Floats4>(p);
                 v[q][0] = x.x; v[q][1] = x.y; v[q][2] = x.z; v[q][3] = x.w;
             } else if constexpr (NT == 2) {
                 if constexpr (STREAM) {
-                    const vf2 x = __builtin_nontemporal_load(reinterpret_cast<const vf2*>(p));
+                    const f32x2_any x = __builtin_nontemporal_load(reinterpret_cast<const f32x2_any*>(p));
                     v[q][0] = x.x; v[q][1] = x.y;
                 } else {
-                    const float2 x = *reinterpret_cast<const float2*>(p);
+                    const Floats2 x = at_any<Floats2>(p);
                     v[q][0] = x.x; v[q][1] = x.y;
                 }
             } else {
@@ -1095,7 +1090,7 @@ __device__ __forceinline__ void load_d_rows(const float* __restrict__ D, uint32_
     }
 }
 
-template <int NP, int RT, int NT, bool VECOK>
+template <int NP, int RT, int NT>
 __global__ __launch_bounds__(256, (NP == 2 && RT == 4) ? 2 : 1) void k_pass_q(const Group grp)
 {
     const TensorArgs& ta = grp.t[locate(grp, blockIdx.x)];
@@ -1119,7 +1114,7 @@ __global__ __launch_bounds__(256, (NP == 2 && RT == 4) ? 2 : 1) void k_pass_q(co
     const uint32_t col = jw0 + NT * jl;
     const uint32_t st_begin = s * stages_per_split;
     const uint32_t st_end = min(m_pad / 64, st_begin + stages_per_split);
-    const bool cols_full = VECOK && (jw0 + W <= n);
+    const bool cols_full = jw0 + W <= n;
 
     f32x16 acc[RT][NT];
 #pragma unroll
@@ -1270,7 +1265,7 @@ __global__ __launch_bounds__(256) void k_reduce_q(const Group grp, uint32_t RP, 
 // M^ itself (k_pass_p_deferred).  Without DEFER a null `out` leaves the reconstruction unwritten
 // (E_new alone: the deferred subtraction carried out after all).
 // ---------------------------------------------------------------------------
-template <int NP, int RT, bool VECOK, bool DEFER>
+template <int NP, int RT, bool DEFER, bool PAST>
 __global__ __launch_bounds__(256) void k_decompress(const Group grp)
 {
     const TensorArgs& ta = grp.t[locate(grp, blockIdx.x)];
@@ -1352,7 +1347,7 @@ __global__ __launch_bounds__(256) void k_decompress(const Group grp)
                 *reinterpret_cast<bf16x4*>(dlds + lrow * ROWB + q * (RP * 2) + c4 * 2) = w[q];
         }
     };
-    auto stage_full = [&](uint32_t st) { return VECOK && rows_full && st * 64 + 64 <= n; };
+    auto stage_full = [&](uint32_t st) { return rows_full && st * 64 + 64 <= n; };
     // D of this lane's 16 rows x 2 adjacent columns
     auto fetch_d = [&](uint32_t st, float (&d)[16][2], auto full_tag) {
         constexpr bool FULL = decltype(full_tag)::value;
@@ -1363,7 +1358,7 @@ __global__ __launch_bounds__(256) void k_decompress(const Group grp)
             const uint32_t row = row0 + 8 * (v / 4) + 4 * g + (v % 4);
             const float* p = E + static_cast<size_t>(row) * n + col;
             if constexpr (FULL) {
-                const float2 x = *reinterpret_cast<const float2*>(p);
+                const Floats2 x = at_any<Floats2>(p);
                 d[v][0] = x.x; d[v][1] = x.y;
             } else {
                 d[v][0] = (row < m && col < n) ? p[0] : 0.0f;
@@ -1384,9 +1379,10 @@ __global__ __launch_bounds__(256) void k_decompress(const Group grp)
                 w0 = static_cast<float>(h0); w1 = static_cast<float>(h1);
                 __bf16* o = static_cast<__bf16*>(out_) + static_cast<size_t>(row) * ldo + col;
                 if (!DEFER && out_ == nullptr) {
-                } else if constexpr (FULL) {      // the reconstruction is not read again here: past the caches
-                    bf16x2 hh = {h0, h1};
-                    __builtin_nontemporal_store(hh, reinterpret_cast<bf16x2*>(o));
+                } else if constexpr (FULL) {
+                    const bf16x2 hh = {h0, h1};
+                    if constexpr (PAST) __builtin_nontemporal_store(__builtin_bit_cast(bf16x2_any, hh), reinterpret_cast<bf16x2_any*>(o));
+                    else put_any(o, Bf16Pair{__builtin_bit_cast(uint32_t, hh)});
                 } else if (row < m) {
                     if (col < n) o[0] = h0;
                     if (col + 1 < n) o[1] = h1;
@@ -1395,8 +1391,9 @@ __global__ __launch_bounds__(256) void k_decompress(const Group grp)
                 float* o = static_cast<float*>(out_) + static_cast<size_t>(row) * ldo + col;
                 if (!DEFER && out_ == nullptr) {
                 } else if constexpr (FULL) {
-                    const vf2 q2 = {w0, w1};
-                    __builtin_nontemporal_store(q2, reinterpret_cast<vf2*>(o));
+                    const f32x2_any q2 = {w0, w1};
+                    if constexpr (PAST) __builtin_nontemporal_store(q2, reinterpret_cast<f32x2_any*>(o));
+                    else put_any(o, Floats2{w0, w1});
                 } else if (row < m) {
                     if (col < n) o[0] = w0;
                     if (col + 1 < n) o[1] = w1;
@@ -1405,7 +1402,7 @@ __global__ __launch_bounds__(256) void k_decompress(const Group grp)
             if constexpr (DEFER) continue;
             const float e0 = d[v][0] - w0, e1 = d[v][1] - w1;
             if constexpr (FULL) {
-                *reinterpret_cast<float2*>(e) = make_float2(e0, e1);
+                put_any(e, Floats2{e0, e1});
             } else if (row < m) {
                 if (col < n) e[0] = e0;
                 if (col + 1 < n) e[1] = e1;
@@ -1473,7 +1470,7 @@ __global__ __launch_bounds__(256) void k_decompress(const Group grp)
     // (fp32 above rank 64: the second copy of the loop costs the two registers that let two waves
     // share a SIMD, 128 instead of 103 us on the hidden-4096 layer: left out there)
     constexpr bool FAST = !(NP == 2 && RT == 4);
-    const uint32_t whole_end = (FAST && VECOK && rows_full) ? min(st_end, n / 64) : 0;
+    const uint32_t whole_end = (FAST && rows_full) ? min(st_end, n / 64) : 0;
     uint32_t st = st_begin;
     if (FAST && whole_end > st_begin + 2) {
         if constexpr (FAST) {
@@ -1508,7 +1505,7 @@ __global__ __launch_bounds__(256) void k_decompress(const Group grp)
 // (B operand of M^) and [rank][column] (B operand of D Q); D goes through a wave-private LDS
 // tile to become the A operand.
 // ---------------------------------------------------------------------------
-template <int NP, int RT, bool VECOK>
+template <int NP, int RT, bool PAST>
 __global__ __launch_bounds__(256, 2) void k_pass_p_deferred(const Group grp)
 {
     // Two blocks share a CU and each keeps one stage of G and D_prev in flight.  Above rank 64
@@ -1549,7 +1546,7 @@ __global__ __launch_bounds__(256, 2) void k_pass_p_deferred(const Group grp)
     const uint32_t k_end = min(n, k_begin + kper);
     const uint32_t n_st = k_begin < k_end ? (k_end - k_begin + 63) / 64 : 0;
     const bool rows_full = row0 + 32 <= m;
-    // per-lane element offsets inside a 32-row x 64-column stage (vector path: both fit 32 bits)
+    // per-lane element offsets inside a 32-row x 64-column stage (rows are at most kMaxDim long: both fit 32 bits)
     const uint32_t off_d = 4u * g * n + 2u * jl;
     const uint32_t off_g = 4u * g * static_cast<uint32_t>(ldg) + 2u * jl;
 
@@ -1577,7 +1574,7 @@ __global__ __launch_bounds__(256, 2) void k_pass_p_deferred(const Group grp)
 
     float qv[PQ][2][4];
     float dv[1][16][2], gv[1][16][2];
-    auto stage_full = [&](uint32_t st) __attribute__((always_inline)) { return VECOK && rows_full && k_begin + st * 64 + 64 <= k_end; };
+    auto stage_full = [&](uint32_t st) __attribute__((always_inline)) { return rows_full && k_begin + st * 64 + 64 <= k_end; };
     // Q rows of a stage: item (jp, c4) holds rows 2jp and 2jp+1 (two adjacent columns of the
     // matrix), ranks c4 .. c4+3; lanes run along jp
     auto fetch_q = [&](uint32_t st) __attribute__((always_inline)) {
@@ -1610,15 +1607,15 @@ __global__ __launch_bounds__(256, 2) void k_pass_p_deferred(const Group grp)
                 const GT* pg = G + (static_cast<uint64_t>(rowu) * ldg + col0) + off_g;
                 const float* pd = E + (static_cast<uint64_t>(rowu) * n + col0) + off_d;
                 if constexpr (NP == 2) {
-                    const vf2 x = __builtin_nontemporal_load(reinterpret_cast<const vf2*>(pg));
+                    const Floats2 x = load_pair<PAST>(pg);
                     gv[B][v][0] = x.x; gv[B][v][1] = x.y;
                 } else {
-                    const uint32_t x = __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(pg));
+                    const uint32_t x = load_pair<PAST>(pg);
                     gv[B][v][0] = __uint_as_float(x);    // the pair as loaded: widened where it is used, so
                     gv[B][v][1] = 0.0f;                  // that nothing here waits for the load
                 }
                 if (!e_zero) {
-                    const float2 x = *reinterpret_cast<const float2*>(pd);
+                    const Floats2 x = at_any<Floats2>(pd);
                     dv[B][v][0] = x.x; dv[B][v][1] = x.y;
                 }
             } else {
@@ -1707,7 +1704,7 @@ __global__ __launch_bounds__(256, 2) void k_pass_p_deferred(const Group grp)
             const float d0 = g0 + (dv[CUR][v][0] - w0), d1 = g1 + (dv[CUR][v][1] - w1);                   \
             if constexpr (FULL) {                                                                         \
                 float* pd = E + (static_cast<uint64_t>(row0 + rl) * n + col0) + off_d;                    \
-                *reinterpret_cast<float2*>(pd) = make_float2(d0, d1);                                     \
+                put_any(pd, Floats2{d0, d1});                                                             \
             } else {                                                                                      \
                 const uint32_t row = row0 + rl + 4 * g, col = col0 + 2 * jl;                              \
                 float* pd = E + static_cast<uint64_t>(row) * n + col;                                     \
@@ -1804,13 +1801,13 @@ __global__ __launch_bounds__(256, 2) void k_pass_p_deferred(const Group grp)
             const GT* pg = G + (static_cast<uint64_t>(rowu) * ldg + col0) + off_g;
             const float* pd = E + (static_cast<uint64_t>(rowu) * n + col0) + off_d;
             if constexpr (NP == 2) {
-                const vf2 x = __builtin_nontemporal_load(reinterpret_cast<const vf2*>(pg));
+                const Floats2 x = load_pair<PAST>(pg);
                 gv[0][v][0] = x.x; gv[0][v][1] = x.y;
             } else {
-                gv[0][v][0] = __uint_as_float(__builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(pg)));
+                gv[0][v][0] = __uint_as_float(load_pair<PAST>(pg));
                 gv[0][v][1] = 0.0f;
             }
-            const float2 x = *reinterpret_cast<const float2*>(pd);
+            const Floats2 x = at_any<Floats2>(pd);
             dv[0][v][0] = x.x; dv[0][v][1] = x.y;
         }
     };
@@ -1818,7 +1815,7 @@ __global__ __launch_bounds__(256, 2) void k_pass_p_deferred(const Group grp)
     // stages [0, n_fast) are full and followed by a full stage.  (fp32 at ranks 33 to 64 has no
     // registers to spare for the second copy of the loop: it spills there and gets slower.)
     constexpr bool FAST = !(NP == 2 && RT == 2);
-    const uint32_t n_whole = (FAST && VECOK && rows_full && !e_zero) ? (k_end - k_begin) / 64 : 0;
+    const uint32_t n_whole = (FAST && rows_full && !e_zero) ? (k_end - k_begin) / 64 : 0;
     const uint32_t n_fast = n_whole > 1 ? n_whole - 1 : 0;
     uint32_t st = 0;
     if (FAST && n_fast) {
@@ -1857,7 +1854,7 @@ __global__ __launch_bounds__(256, 2) void k_pass_p_deferred(const Group grp)
 // and row); neighbouring lanes swap their values (DPP) to write D into LDS as 32-bit pairs.
 // Same products in the same order as k_pass_p_deferred, hence the same bits.
 // ---------------------------------------------------------------------------
-template <int NP, int RT, bool VECOK>
+template <int NP, int RT>
 __global__ __launch_bounds__(256, 2) void k_pass_p_deferred_narrow(const Group grp)
 {
     static_assert(RT == 4, "built for ranks above 64");
@@ -1918,9 +1915,8 @@ __global__ __launch_bounds__(256, 2) void k_pass_p_deferred_narrow(const Group g
 
     float qv[PQ][2][4];
     float dv[16], gv[16];
-    // VECOK here: n and ldg are below 2^28, so that the 32-bit lane offsets hold
     auto stage_full = [&](uint32_t st) __attribute__((always_inline)) {
-        return VECOK && rows_full && k_begin + st * 32 + 32 <= k_end;
+        return rows_full && k_begin + st * 32 + 32 <= k_end;
     };
     auto fetch_q = [&](uint32_t st) __attribute__((always_inline)) {
         const uint32_t col0 = k_begin + st * 32;
@@ -2101,7 +2097,7 @@ __global__ __launch_bounds__(256, 2) void k_pass_p_deferred_narrow(const Group g
     // stages [0, n_fast) are full and followed by a full stage.  (With fp32 gradients the second
     // copy of the loop costs more in spilled registers than the waits it removes: bf16 only.)
     constexpr bool FAST = (NP == 1);
-    const uint32_t n_whole = (FAST && VECOK && rows_full) ? (k_end - k_begin) / 32 : 0;
+    const uint32_t n_whole = (FAST && rows_full) ? (k_end - k_begin) / 32 : 0;
     const uint32_t n_fast = n_whole > 1 ? n_whole - 1 : 0;
     uint32_t st = 0;
     if (FAST && n_fast) {
@@ -2211,10 +2207,7 @@ template <int NP, int RT, int NT>
 static hipError_t allow_lds_pass_q()
 {
     constexpr int lds = 2 * RT * 32 * (NP * 128 + 16);
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pass_q<NP, RT, NT, true>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e != hipSuccess) return e;
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pass_q<NP, RT, NT, false>),
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pass_q<NP, RT, NT>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, lds);
 }
 
@@ -2365,7 +2358,11 @@ static int run_pass_p(edgc_ctx* ctx, Group& g, const TensorScratch* cap, bool wi
     }
     const uint32_t step = pass_p_step(g.count, across, along, most, rows_per_block, RP, d_bytes,
                                       static_cast<uint32_t>(ctx->num_cu), ctx->tune_p);
-    bool vec = true;
+    // The kernels of the deferred form read G past the caches if its rows are whole cache lines: the two stages that share a
+    // line would fetch it twice (per pass, past them always / by this rule: 373 x 7423 bf16 76.8 / 73.6 us, 8191 x 4097 fp32
+    // 230.4 / 223.5, hidden-3001 bf16 block 567 / 548).  k_pass_p reads four columns per lane, and gains nothing by it (hidden-2056
+    // fp32 block stored 344 / 353, hidden-1000 112.8 / 116.9).
+    bool past = true;
     uint32_t blocks = 0;
     double bytes = 0.0, flops = 0.0;
     for (uint32_t i = 0; i < g.count; ++i) {
@@ -2379,12 +2376,7 @@ static int run_pass_p(edgc_ctx* ctx, Group& g, const TensorScratch* cap, bool wi
         t.sp = S;
         t.first = g.first[i] = blocks;
         blocks += RB * S;
-        // 16-byte accesses; the kernel of the deferred form reads and writes two columns per lane
-        const uint32_t w = (use_wide || use_full) ? 2u : 4u;
-        if (w == 2u) vec = vec && t.ldg < (1ull << 28) && t.n < (1u << 28);   // its per-lane offsets are 32-bit
-        vec = vec && (t.n % w == 0) && (t.ldg % w == 0) &&
-              (reinterpret_cast<uintptr_t>(t.G) % (w * sizeof(GT)) == 0) &&
-              (reinterpret_cast<uintptr_t>(t.E) % (4 * w) == 0);
+        past = past && (t.ldg * sizeof(GT)) % 128 == 0 && reinterpret_cast<uintptr_t>(t.G) % 128 == 0;
         // algorithmic traffic: read G (if any) and E_old (if any), write D
         const double mn = static_cast<double>(t.m) * t.n;
         bytes += mn * ((with_grad ? sizeof(GT) : 0) + (t.e_zero ? 0 : 4) + 4);
@@ -2401,27 +2393,17 @@ static int run_pass_p(edgc_ctx* ctx, Group& g, const TensorScratch* cap, bool wi
         // D_prev is read where the other form reads E_old: the same bytes; two products per element
         const double fl = g.defer ? 2.0 * flops : flops;
         if constexpr (RT == 4) {
-            // above rank 64: 32-column stages, 4-byte accesses (no alignment beyond the element's);
-            // `vec` here: the kernel's 32-bit lane offsets hold
+            // above rank 64: 32-column stages, 4-byte accesses
             constexpr size_t lds = deferred_narrow_lds<NP>();
-            bool off32 = true;
-            for (uint32_t i = 0; i < g.count; ++i)
-                off32 = off32 && g.t[i].ldg < (1ull << 28) && g.t[i].n < (1u << 28);
-            if (off32)
-                EDGC_LAUNCH(ctx, st, KID_PASS_P_DEFERRED, bytes, fl, (k_pass_p_deferred_narrow<NP, RT, true><<<blocks, 256, lds, st>>>(g)));
-            else
-                EDGC_LAUNCH(ctx, st, KID_PASS_P_DEFERRED, bytes, fl, (k_pass_p_deferred_narrow<NP, RT, false><<<blocks, 256, lds, st>>>(g)));
+            EDGC_LAUNCH(ctx, st, KID_PASS_P_DEFERRED, bytes, fl, (k_pass_p_deferred_narrow<NP, RT><<<blocks, 256, lds, st>>>(g)));
         } else {
             constexpr size_t lds = deferred_lds<NP, RT>();
-            if (vec)
-                EDGC_LAUNCH(ctx, st, KID_PASS_P_DEFERRED, bytes, fl, (k_pass_p_deferred<NP, RT, true><<<blocks, 256, lds, st>>>(g)));
-            else
-                EDGC_LAUNCH(ctx, st, KID_PASS_P_DEFERRED, bytes, fl, (k_pass_p_deferred<NP, RT, false><<<blocks, 256, lds, st>>>(g)));
+            ProfScope prof_scope_(ctx, st, KID_PASS_P_DEFERRED, bytes, fl);
+            if (past) k_pass_p_deferred<NP, RT, true><<<blocks, 256, lds, st>>>(g);
+            else k_pass_p_deferred<NP, RT, false><<<blocks, 256, lds, st>>>(g);
         }
-    } else if (vec)
-        EDGC_LAUNCH(ctx, st, KID_PASS_P, bytes, flops, (k_pass_p<NP, RT, true><<<blocks, 256, 0, st>>>(g)));
-    else
-        EDGC_LAUNCH(ctx, st, KID_PASS_P, bytes, flops, (k_pass_p<NP, RT, false><<<blocks, 256, 0, st>>>(g)));
+    } else
+        EDGC_LAUNCH(ctx, st, KID_PASS_P, bytes, flops, (k_pass_p<NP, RT><<<blocks, 256, 0, st>>>(g)));
     EDGC_HIP_TRY(ctx, hipGetLastError());
     return EDGC_OK;
 }
@@ -2592,7 +2574,6 @@ static int run_pass_q(edgc_ctx* ctx, Group& g, const TensorScratch* cap, hipStre
     const uint32_t target = static_cast<uint32_t>(ctx->num_cu) * per_cu;
     uint32_t tgt[kMaxGroup];
     share_targets(g, target, tgt);
-    bool vec = true;
     uint32_t blocks = 0;
     double bytes = 0.0, flops = 0.0;
     for (uint32_t i = 0; i < g.count; ++i) {
@@ -2609,18 +2590,14 @@ static int run_pass_q(edgc_ctx* ctx, Group& g, const TensorScratch* cap, hipStre
         t.sq = S;
         t.first = g.first[i] = blocks;
         blocks += CB * S;
-        vec = vec && (t.n % NT == 0) && (reinterpret_cast<uintptr_t>(t.E) % 16 == 0);
         bytes += 4.0 * t.m * t.n;
         flops += 2.0 * t.m * t.n * g.r;
     }
     if (qwaves) {
         ProfScope prof_scope_(ctx, st, KID_PASS_Q, bytes, flops);
         EDGC_HIP_TRY(ctx, launch_pass_q_full(g, DT, RT, blocks, qwaves, st));
-    } else if (vec) {
-        auto kern = &k_pass_q<NP, RT, NT, true>;
-        EDGC_LAUNCH(ctx, st, KID_PASS_Q, bytes, flops, kern<<<blocks, 256, lds, st>>>(g));
     } else {
-        auto kern = &k_pass_q<NP, RT, NT, false>;
+        auto kern = &k_pass_q<NP, RT, NT>;
         EDGC_LAUNCH(ctx, st, KID_PASS_Q, bytes, flops, kern<<<blocks, 256, lds, st>>>(g));
     }
     EDGC_HIP_TRY(ctx, hipGetLastError());
@@ -2726,7 +2703,15 @@ static int decompress_impl(edgc_ctx* ctx, Group& g, hipStream_t st)
     const uint32_t target = static_cast<uint32_t>(ctx->num_cu) * per_cu;
     uint32_t tgt[kMaxGroup];
     share_targets(g, target, tgt);
-    bool vec = true;
+    // The reconstruction is not read again here and goes past the caches, unless its rows are not whole cache lines: then half
+    // a line written past them at a time costs more (the kernel alone, deferred hidden-2056 fp32 block 73.5 past them, 41.8 us
+    // through them).  In the stored form lines of the reconstruction push out D, which the kernel reads from the last-level cache,
+    // so that only small groups take them through (past / through, per pass: hidden-500 fp32 block, 12 MB, 68.5 / 66.7 us;
+    // hidden-1000, 48 MB, 113 / 127; hidden-2056 344 / 391).
+    bool past = true;
+    uint64_t d_bytes = 0;
+    for (uint32_t i = 0; i < g.count; ++i) d_bytes += 4ull * g.t[i].m * g.t[i].n;
+    const bool by_line = g.defer || d_bytes <= (24ull << 20);
     uint32_t blocks = 0;
     double bytes = 0.0, flops = 0.0;
     for (uint32_t i = 0; i < g.count; ++i) {
@@ -2739,8 +2724,7 @@ static int decompress_impl(edgc_ctx* ctx, Group& g, hipStream_t st)
         t.d1 = JS;
         t.first = g.first[i] = blocks;
         blocks += RB * JS;
-        vec = vec && (t.n % 2 == 0) && (t.ldo % 2 == 0) && (reinterpret_cast<uintptr_t>(t.E) % 8 == 0) &&
-              (reinterpret_cast<uintptr_t>(t.out) % (2 * esz) == 0);
+        if (by_line) past = past && (t.ldo * esz) % 128 == 0 && reinterpret_cast<uintptr_t>(t.out) % 128 == 0;
         // algorithmic traffic: write M^ (if asked for); read D and write E_new unless deferred
         bytes += static_cast<double>(t.m) * t.n * ((g.defer ? 0 : 8) + (t.out ? esz : 0));
         flops += 2.0 * t.m * t.n * g.r;
@@ -2750,15 +2734,11 @@ static int decompress_impl(edgc_ctx* ctx, Group& g, hipStream_t st)
         EDGC_HIP_TRY(ctx, launch_decompress_full(g, DT, RT, blocks, waves, st));
         return EDGC_OK;
     }
-    if (g.defer) {
-        if (vec)
-            EDGC_LAUNCH(ctx, st, KID_DECOMPRESS, bytes, flops, (k_decompress<NP, RT, true, true><<<blocks, 256, lds, st>>>(g)));
-        else
-            EDGC_LAUNCH(ctx, st, KID_DECOMPRESS, bytes, flops, (k_decompress<NP, RT, false, true><<<blocks, 256, lds, st>>>(g)));
-    } else if (vec)
-        EDGC_LAUNCH(ctx, st, KID_DECOMPRESS, bytes, flops, (k_decompress<NP, RT, true, false><<<blocks, 256, lds, st>>>(g)));
-    else
-        EDGC_LAUNCH(ctx, st, KID_DECOMPRESS, bytes, flops, (k_decompress<NP, RT, false, false><<<blocks, 256, lds, st>>>(g)));
+    ProfScope prof_scope_(ctx, st, KID_DECOMPRESS, bytes, flops);
+    if (g.defer && past) k_decompress<NP, RT, true, true><<<blocks, 256, lds, st>>>(g);
+    else if (g.defer) k_decompress<NP, RT, true, false><<<blocks, 256, lds, st>>>(g);
+    else if (past) k_decompress<NP, RT, false, true><<<blocks, 256, lds, st>>>(g);
+    else k_decompress<NP, RT, false, false><<<blocks, 256, lds, st>>>(g);
     EDGC_HIP_TRY(ctx, hipGetLastError());
     return EDGC_OK;
 }

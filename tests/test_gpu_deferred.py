@@ -231,3 +231,44 @@ def test_deferred_with_the_reconstruction_written_over_the_gradient(dtype):
         for i, (x, y) in enumerate(zip(a.t, b.t)):
             assert torch.equal(x.grad_out, y.grad), (step, i)
             assert torch.equal(x.residual, y.residual) and torch.equal(x.P, y.P) and torch.equal(x.Q, y.Q), (step, i)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("r,deferred", [(13, True), (13, False), (40, True), (100, False), (100, True)])
+def test_any_element_address_gives_the_same_bits(dtype, r, deferred):
+    """Gradient, reconstruction and residual one element past an aligned address, in rows of an odd leading dimension, against
+    the same numbers in aligned rows: wide accesses serve both.  Nothing beside the matrices is written."""
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    gen_ = torch.Generator(device="cuda").manual_seed(31 * r)
+    shapes = [(512, 512), (512, 511), (385, 577), (450, 770), (1024, 257)]
+    pair = ([], [])
+    around = []
+    for m, n in shapes:
+        G = (torch.randn(m, n, device="cuda", generator=gen_) * 1e-2).to(tdt)
+        D = torch.randn(m, n, device="cuda", generator=gen_) * 1e-2
+        P, Q = (torch.randn(k, (r + 3) // 4 * 4, device="cuda", generator=gen_) for k in (m, n))
+        P[:, r:] = 0
+        Q[:, r:] = 0
+        for which, (ld, off) in enumerate([((n + 63) // 64 * 64, 0), ((n + 1) // 2 * 2 + 3, 1)]):
+            def rows(dt, src, ld, off):
+                flat = torch.full((m * ld + off + 64,), 7.0, device="cuda", dtype=dt)
+                view = flat[off:off + m * ld].view(m, ld)[:, :n]
+                if src is not None:
+                    view.copy_(src)
+                around.append((flat, view))
+                return view
+            pair[which].append(edgc.Tensor(rows(tdt, G, ld, off), rows(tdt, None, ld, off), rows(torch.float32, D, n, off),
+                                           Q.clone(), P.clone(), False))
+    c = edgc.Context(0, max_bins=256, max_rank=128, max_rows=1024, max_cols=1024)
+    c.reserve_batch(shapes)
+    for group in pair:
+        c.compress_batch(group, r, deferred=deferred)
+        c.decompress_batch(group, r, deferred=deferred)
+    torch.cuda.synchronize()
+    for a, b in zip(*pair):
+        for x, y in ((a.grad_out, b.grad_out), (a.residual, b.residual), (a.P, b.P), (a.Q, b.Q)):
+            assert torch.isfinite(x.float()).all() and torch.equal(x, y), tuple(a.grad.shape)
+    for flat, view in around:
+        view.fill_(7.0)
+        assert bool((flat == 7.0).all())
+    c.close()
