@@ -422,33 +422,40 @@ __global__ __launch_bounds__(256) void k_reduce_gram(const Group grp, uint32_t R
     }
 }
 
-// out[e] = sum over blocks of gp[b][e], in block order within each of four interleaved
-// groups and then over the groups: a fixed tree, so the result is reproducible.
+// out[e] = sum over blocks of gp[b][e], in block order within each of GROUPS interleaved
+// groups and then over the groups: a fixed tree, so the result is reproducible.  256 / GROUPS entries per block.
+template <uint32_t GROUPS>
 __global__ __launch_bounds__(256) void k_gram_sum(const Group grps, uint32_t ne)
 {
+    constexpr uint32_t W = 256 / GROUPS;
     const TensorArgs& ta = grps.t[locate(grps, blockIdx.x)];
     const double* __restrict__ gp = ta.gram_part;
     double* __restrict__ out = ta.gram;
     const uint32_t nb = ta.d0;
-    __shared__ double red[4][64];
-    const uint32_t e = (blockIdx.x - ta.first) * 64 + (threadIdx.x & 63);
-    const uint32_t grp = threadIdx.x >> 6;
+    __shared__ double red[GROUPS][W];
+    const uint32_t e = (blockIdx.x - ta.first) * W + threadIdx.x % W;
+    const uint32_t grp = threadIdx.x / W;
     double s = 0.0;
     if (e < ne) {
         const double* p = gp + e;
         uint32_t b = grp;
-        for (; b + 28 < nb; b += 32) {
+        for (; b + 7 * GROUPS < nb; b += 8 * GROUPS) {
             double x[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) x[u] = p[static_cast<size_t>(b + 4 * u) * ne];
+            for (uint32_t u = 0; u < 8; ++u) x[u] = p[static_cast<size_t>(b + GROUPS * u) * ne];
 #pragma unroll
             for (int u = 0; u < 8; ++u) s += x[u];
         }
-        for (; b < nb; b += 4) s += p[static_cast<size_t>(b) * ne];
+        for (; b < nb; b += GROUPS) s += p[static_cast<size_t>(b) * ne];
     }
-    red[grp][threadIdx.x & 63] = s;
+    red[grp][threadIdx.x % W] = s;
     __syncthreads();
-    if (grp == 0 && e < ne) out[e] = ((red[0][threadIdx.x] + red[1][threadIdx.x]) + red[2][threadIdx.x]) + red[3][threadIdx.x];
+    if (grp == 0 && e < ne) {
+        double sum = red[0][threadIdx.x];
+#pragma unroll
+        for (uint32_t q = 1; q < GROUPS; ++q) sum += red[q][threadIdx.x];
+        out[e] = sum;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1214,36 +1221,52 @@ __global__ __launch_bounds__(256, (NP == 2 && RT == 4) ? 2 : 1) void k_pass_q(co
 }
 
 // Q = sum of the row-split partials (or, of_p, P = sum of the column-split ones: the first phase of a split call,
-// which needs no Gram matrix), in split order, four independent loads in flight
+// which needs no Gram matrix), four independent loads in flight.  GROUPS 1: in split order.  8: every eighth split by one group
+// of 32 threads, the groups' sums in their order.
+template <uint32_t GROUPS>
 __global__ __launch_bounds__(256) void k_reduce_q(const Group grp, uint32_t RP, int of_p)
 {
+    constexpr uint32_t W = 256 / GROUPS;
     const TensorArgs& ta = grp.t[locate(grp, blockIdx.x)];
     const float* __restrict__ part = ta.part;
     float* __restrict__ Q = of_p ? ta.P : ta.Q;
     const uint32_t S = of_p ? ta.sp : ta.sq, n = of_p ? ta.m : ta.n, r = grp.r, ldq = of_p ? ta.ldp : ta.ldq;
-    // one thread per four adjacent factor columns of one row of Q
-    const uint32_t q4 = RP / 4;
-    const uint64_t t = static_cast<uint64_t>(blockIdx.x - ta.first) * 256 + threadIdx.x;
-    if (t >= static_cast<uint64_t>(n) * q4) return;
+    // one thread (of each group) per four adjacent factor columns of one row of Q
+    const uint32_t q4 = RP / 4, at = threadIdx.x % W, group = threadIdx.x / W;
+    const uint64_t t = static_cast<uint64_t>(blockIdx.x - ta.first) * W + at;
     const uint32_t j = static_cast<uint32_t>(t / q4), c = static_cast<uint32_t>(t % q4) * 4;
-    if (c >= r) return;
+    const bool live = t < static_cast<uint64_t>(n) * q4 && c < r;
+    if (GROUPS == 1 && !live) return;
     const size_t stride = static_cast<size_t>(n) * RP;
     const float* p = part + static_cast<size_t>(j) * RP + c;
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    uint32_t s = 0;
-    for (; s + 4 <= S; s += 4) {
-        const float4 x0 = *reinterpret_cast<const float4*>(p + (s + 0) * stride);
-        const float4 x1 = *reinterpret_cast<const float4*>(p + (s + 1) * stride);
-        const float4 x2 = *reinterpret_cast<const float4*>(p + (s + 2) * stride);
-        const float4 x3 = *reinterpret_cast<const float4*>(p + (s + 3) * stride);
-        v.x += x0.x; v.y += x0.y; v.z += x0.z; v.w += x0.w;
-        v.x += x1.x; v.y += x1.y; v.z += x1.z; v.w += x1.w;
-        v.x += x2.x; v.y += x2.y; v.z += x2.z; v.w += x2.w;
-        v.x += x3.x; v.y += x3.y; v.z += x3.z; v.w += x3.w;
+    if (live) {
+        uint32_t s = group;
+        for (; s + 3 * GROUPS < S; s += 4 * GROUPS) {
+            const float4 x0 = *reinterpret_cast<const float4*>(p + (s + 0 * GROUPS) * stride);
+            const float4 x1 = *reinterpret_cast<const float4*>(p + (s + 1 * GROUPS) * stride);
+            const float4 x2 = *reinterpret_cast<const float4*>(p + (s + 2 * GROUPS) * stride);
+            const float4 x3 = *reinterpret_cast<const float4*>(p + (s + 3 * GROUPS) * stride);
+            v.x += x0.x; v.y += x0.y; v.z += x0.z; v.w += x0.w;
+            v.x += x1.x; v.y += x1.y; v.z += x1.z; v.w += x1.w;
+            v.x += x2.x; v.y += x2.y; v.z += x2.z; v.w += x2.w;
+            v.x += x3.x; v.y += x3.y; v.z += x3.z; v.w += x3.w;
+        }
+        for (; s < S; s += GROUPS) {
+            const float4 x0 = *reinterpret_cast<const float4*>(p + s * stride);
+            v.x += x0.x; v.y += x0.y; v.z += x0.z; v.w += x0.w;
+        }
     }
-    for (; s < S; ++s) {
-        const float4 x0 = *reinterpret_cast<const float4*>(p + s * stride);
-        v.x += x0.x; v.y += x0.y; v.z += x0.z; v.w += x0.w;
+    if constexpr (GROUPS > 1) {
+        __shared__ float4 red[GROUPS][W];
+        red[group][at] = v;
+        __syncthreads();
+        if (group != 0 || !live) return;
+#pragma unroll
+        for (uint32_t q = 1; q < GROUPS; ++q) {
+            const float4 x = red[q][at];
+            v.x += x.x; v.y += x.y; v.z += x.z; v.w += x.w;
+        }
     }
     float* dst = Q + static_cast<size_t>(j) * ldq + c;
     if (c + 4 <= r) {
@@ -2464,6 +2487,11 @@ static int run_orthonormalise(edgc_ctx* ctx, Group& g, const TensorScratch* cap,
     // while the launch is at most four blocks per CU with one tile, two with two tiles (the figures at k_apply)
     const bool factor = t16 <= 2 && apply_blocks <= (t16 == 1 ? 4u : 2u) * static_cast<uint32_t>(ctx->num_cu);
     const uint32_t max_sets = !factor ? 1u : t16 == 1 ? 128u : 8u;
+    // One block sums 64 entries, or 16 in 16 groups where that leaves most CUs idle: a CU fetches some 40 bytes a ns
+    // (50257 x 1024 at rank 32, 786 sets of 6 KB: 12 blocks 12.4 us, 48 5.6)
+    uint32_t summed_tensors = 0;
+    for (uint32_t i = 0; i < g.count; ++i) summed_tensors += g.t[i].nb > max_sets ? 1u : 0u;
+    const bool narrow = summed_tensors * cdiv(ne, 64) * 4u <= static_cast<uint32_t>(ctx->num_cu);
     blocks = 0;
     bytes = 0.0;
     for (uint32_t i = 0; i < g.count; ++i) {
@@ -2472,13 +2500,15 @@ static int run_orthonormalise(edgc_ctx* ctx, Group& g, const TensorScratch* cap,
         t.d0 = t.nb;
         t.first = g.first[i] = blocks;
         if (summed) {
-            blocks += cdiv(ne, 64);
+            blocks += cdiv(ne, narrow ? 16 : 64);
             bytes += 8.0 * ne * t.nb;
         }
         t.tiles = summed ? t.gram : t.gram_part;
     }
     if (blocks) {
-        EDGC_LAUNCH(ctx, st, KID_GRAM_SUM, bytes, 0.0, k_gram_sum<<<blocks, 256, 0, st>>>(g, ne));
+        ProfScope prof_scope_(ctx, st, KID_GRAM_SUM, bytes, 0.0);
+        if (narrow) k_gram_sum<16><<<blocks, 256, 0, st>>>(g, ne);
+        else k_gram_sum<4><<<blocks, 256, 0, st>>>(g, ne);
         EDGC_HIP_TRY(ctx, hipGetLastError());
     }
     for (uint32_t i = 0; i < g.count; ++i)
@@ -2604,15 +2634,25 @@ static int run_pass_q(edgc_ctx* ctx, Group& g, const TensorScratch* cap, hipStre
     }
     EDGC_HIP_TRY(ctx, hipGetLastError());
 
+    // 256 items (four columns of a row of Q) per block, or 32 in eight groups where that leaves most CUs idle and there are
+    // sums to share (50257 x 1024 at rank 32, 113 splits: 32 blocks 12.0 us, 256 5.5)
+    uint32_t whole_blocks = 0, most_splits = 0;
+    for (uint32_t i = 0; i < g.count; ++i) {
+        whole_blocks += cdiv(static_cast<uint64_t>(g.t[i].n) * (RP / 4), 256);
+        most_splits = std::max(most_splits, g.t[i].sq);
+    }
+    const bool narrow = most_splits >= 16 && whole_blocks * 4u <= static_cast<uint32_t>(ctx->num_cu);
     blocks = 0;
     bytes = 0.0;
     for (uint32_t i = 0; i < g.count; ++i) {
         TensorArgs& t = g.t[i];
         t.first = g.first[i] = blocks;
-        blocks += cdiv(static_cast<uint64_t>(t.n) * (RP / 4), 256);
+        blocks += cdiv(static_cast<uint64_t>(t.n) * (RP / 4), narrow ? 32 : 256);
         bytes += 4.0 * t.n * g.r * (t.sq + 1);
     }
-    EDGC_LAUNCH(ctx, st, KID_REDUCE_Q, bytes, 0.0, k_reduce_q<<<blocks, 256, 0, st>>>(g, RP, 0));
+    ProfScope prof_scope_(ctx, st, KID_REDUCE_Q, bytes, 0.0);
+    if (narrow) k_reduce_q<8><<<blocks, 256, 0, st>>>(g, RP, 0);
+    else k_reduce_q<1><<<blocks, 256, 0, st>>>(g, RP, 0);
     EDGC_HIP_TRY(ctx, hipGetLastError());
     return EDGC_OK;
 }
@@ -2638,7 +2678,7 @@ static int compress_impl(edgc_ctx* ctx, Group& g, const TensorScratch* cap, uint
             blocks += cdiv(static_cast<uint64_t>(t.m) * (RP / 4), 256);
             bytes += 4.0 * t.m * g.r * (t.sp + 1);
         }
-        EDGC_LAUNCH(ctx, st, KID_REDUCE_Q, bytes, 0.0, k_reduce_q<<<blocks, 256, 0, st>>>(g, RP, 1));
+        EDGC_LAUNCH(ctx, st, KID_REDUCE_Q, bytes, 0.0, (k_reduce_q<1><<<blocks, 256, 0, st>>>(g, RP, 1)));
         EDGC_HIP_TRY(ctx, hipGetLastError());
         return EDGC_OK;
     }

@@ -416,3 +416,25 @@ def test_measure_device_peaks_copies_and_reports_physical_figures():
         c.measure_device_peaks(a[1:1 + (1 << 22)], b[: 1 << 22], reps=3)   # misaligned
     with pytest.raises(edgc.EdgcError):
         c.measure_device_peaks(a, b, reps=0)
+
+
+@pytest.mark.parametrize("m,n,r", [(20000, 130, 3), (9000, 62, 13), (16384, 256, 40), (20000, 33, 30), (12345, 257, 32), (2048, 2048, 1),
+                                   (20000, 40, 20), (10000, 1024, 4)])
+def test_sums_of_many_partials_in_few_columns(m, n, r):
+    """Many row splits and Gram sets over few columns: the sums whose blocks share them in groups.  P^ is orthonormal and
+    Q = D^T P^ of the D and P^ the call returns (operands of 17 bits: 2^-16 of |D| |P^| per column)."""
+    g = torch.Generator(device="cuda").manual_seed(m + n + r)
+    G = torch.randn(m, n, device="cuda", generator=g)
+    ld = (r + 3) // 4 * 4
+    D, P, Q = torch.zeros(m, n, device="cuda"), torch.zeros(m, ld, device="cuda"), torch.zeros(n, ld, device="cuda")
+    Q[:, :r] = torch.randn(n, r, device="cuda", generator=g)
+    c = edgc.Context(0, max_bins=256, max_rank=64, max_rows=20000, max_cols=2048)
+    c.compress(G, D, True, Q, P, r)
+    torch.cuda.synchronize()
+    assert torch.equal(D, G) and not Q[:, r:].any() and not P[:, r:].any()
+    p, q = P[:, :r].double(), Q[:, :r].double()
+    # P^ is rounded to fp32 once: 2^-24 per entry, and the factor's 1e-11
+    assert float((p.t() @ p - torch.eye(r, device="cuda", dtype=torch.float64)).abs().max()) < 1e-6
+    want = D.double().t() @ p
+    assert float((q - want).norm(dim=0).max() / D.double().norm()) < 2.0 ** -16
+    c.close()
