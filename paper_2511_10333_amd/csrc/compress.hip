@@ -422,40 +422,57 @@ __global__ __launch_bounds__(256) void k_reduce_gram(const Group grp, uint32_t R
     }
 }
 
-// out[e] = sum over blocks of gp[b][e], in block order within each of GROUPS interleaved
-// groups and then over the groups: a fixed tree, so the result is reproducible.  256 / GROUPS entries per block.
-template <uint32_t GROUPS>
+// out[e] = sum over blocks of gp[b][e], in block order within each of four interleaved groups and then over the groups: a
+// fixed tree, the same for every W, so the result is reproducible and does not depend on what else is in the launch.
+// W: entries per block.  64: a thread sums a group's sets of an entry as it loads them.  16: all 256 threads load, eight
+// sets each at a time, and one wave adds them up from LDS in the order of the tree.
+template <uint32_t W>
 __global__ __launch_bounds__(256) void k_gram_sum(const Group grps, uint32_t ne)
 {
-    constexpr uint32_t W = 256 / GROUPS;
     const TensorArgs& ta = grps.t[locate(grps, blockIdx.x)];
     const double* __restrict__ gp = ta.gram_part;
     double* __restrict__ out = ta.gram;
     const uint32_t nb = ta.d0;
-    __shared__ double red[GROUPS][W];
-    const uint32_t e = (blockIdx.x - ta.first) * W + threadIdx.x % W;
-    const uint32_t grp = threadIdx.x / W;
+    __shared__ double red[4][W];
+    const uint32_t at = threadIdx.x % W, grp = threadIdx.x / W;
+    const uint32_t e = (blockIdx.x - ta.first) * W + at;          // (ne is a multiple of 256: no block is partial)
+    const double* p = gp + e;
     double s = 0.0;
-    if (e < ne) {
-        const double* p = gp + e;
+    if constexpr (W == 64) {
         uint32_t b = grp;
-        for (; b + 7 * GROUPS < nb; b += 8 * GROUPS) {
+        for (; b + 28 < nb; b += 32) {
             double x[8];
 #pragma unroll
-            for (uint32_t u = 0; u < 8; ++u) x[u] = p[static_cast<size_t>(b + GROUPS * u) * ne];
+            for (uint32_t u = 0; u < 8; ++u) x[u] = p[static_cast<size_t>(b + 4 * u) * ne];
 #pragma unroll
             for (int u = 0; u < 8; ++u) s += x[u];
         }
-        for (; b < nb; b += GROUPS) s += p[static_cast<size_t>(b) * ne];
-    }
-    red[grp][threadIdx.x % W] = s;
-    __syncthreads();
-    if (grp == 0 && e < ne) {
-        double sum = red[0][threadIdx.x];
+        for (; b < nb; b += 4) s += p[static_cast<size_t>(b) * ne];
+    } else {
+        constexpr uint32_t LOADERS = 256 / W, SETS = 8 * LOADERS;
+        __shared__ double tile[SETS][W];
+        double x[8];
+        auto load = [&](uint32_t b0) {
 #pragma unroll
-        for (uint32_t q = 1; q < GROUPS; ++q) sum += red[q][threadIdx.x];
-        out[e] = sum;
+            for (uint32_t u = 0; u < 8; ++u) x[u] = p[static_cast<size_t>(min(b0 + grp + LOADERS * u, nb - 1)) * ne];
+        };
+        load(0);
+        for (uint32_t b0 = 0; b0 < nb; b0 += SETS) {
+            __syncthreads();                                       // the tile before has been added up
+#pragma unroll
+            for (uint32_t u = 0; u < 8; ++u)
+                tile[grp + LOADERS * u][at] = b0 + grp + LOADERS * u < nb ? x[u] : 0.0;     // (a sum is never -0: + 0 keeps it)
+            __syncthreads();
+            if (b0 + SETS < nb) load(b0 + SETS);
+            if (grp < 4) {
+#pragma unroll
+                for (uint32_t i = 0; i < SETS / 4; ++i) s += tile[grp + 4 * i][at];
+            }
+        }
     }
+    if (grp < 4) red[grp][at] = s;
+    __syncthreads();
+    if (grp == 0) out[e] = ((red[0][at] + red[1][at]) + red[2][at]) + red[3][at];
 }
 
 // ---------------------------------------------------------------------------
@@ -1220,61 +1237,78 @@ __global__ __launch_bounds__(256, (NP == 2 && RT == 4) ? 2 : 1) void k_pass_q(co
             }
 }
 
-// Q = sum of the row-split partials (or, of_p, P = sum of the column-split ones: the first phase of a split call,
-// which needs no Gram matrix), four independent loads in flight.  GROUPS 1: in split order.  8: every eighth split by one group
-// of 32 threads, the groups' sums in their order.
-template <uint32_t GROUPS>
+// Q = sum of the row-split partials (or, of_p, P = sum of the column-split ones: the first phase of a split call, which needs
+// no Gram matrix), in split order in either form.  An item is four adjacent factor columns of a row.  W: items per block.
+// 256: a thread sums its item, four independent loads in flight.  32: all 256 threads load, four splits each at a time, and
+// 128 of them add up one column each from LDS.
+template <uint32_t W>
 __global__ __launch_bounds__(256) void k_reduce_q(const Group grp, uint32_t RP, int of_p)
 {
-    constexpr uint32_t W = 256 / GROUPS;
     const TensorArgs& ta = grp.t[locate(grp, blockIdx.x)];
     const float* __restrict__ part = ta.part;
     float* __restrict__ Q = of_p ? ta.P : ta.Q;
     const uint32_t S = of_p ? ta.sp : ta.sq, n = of_p ? ta.m : ta.n, r = grp.r, ldq = of_p ? ta.ldp : ta.ldq;
-    // one thread (of each group) per four adjacent factor columns of one row of Q
-    const uint32_t q4 = RP / 4, at = threadIdx.x % W, group = threadIdx.x / W;
-    const uint64_t t = static_cast<uint64_t>(blockIdx.x - ta.first) * W + at;
-    const uint32_t j = static_cast<uint32_t>(t / q4), c = static_cast<uint32_t>(t % q4) * 4;
-    const bool live = t < static_cast<uint64_t>(n) * q4 && c < r;
-    if (GROUPS == 1 && !live) return;
+    const uint32_t q4 = RP / 4;
+    const uint64_t item0 = static_cast<uint64_t>(blockIdx.x - ta.first) * W, items = static_cast<uint64_t>(n) * q4;
     const size_t stride = static_cast<size_t>(n) * RP;
-    const float* p = part + static_cast<size_t>(j) * RP + c;
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (live) {
-        uint32_t s = group;
-        for (; s + 3 * GROUPS < S; s += 4 * GROUPS) {
-            const float4 x0 = *reinterpret_cast<const float4*>(p + (s + 0 * GROUPS) * stride);
-            const float4 x1 = *reinterpret_cast<const float4*>(p + (s + 1 * GROUPS) * stride);
-            const float4 x2 = *reinterpret_cast<const float4*>(p + (s + 2 * GROUPS) * stride);
-            const float4 x3 = *reinterpret_cast<const float4*>(p + (s + 3 * GROUPS) * stride);
+    if constexpr (W == 256) {
+        const uint64_t t = item0 + threadIdx.x;
+        const uint32_t j = static_cast<uint32_t>(t / q4), c = static_cast<uint32_t>(t % q4) * 4;
+        if (t >= items || c >= r) return;
+        const float* p = part + static_cast<size_t>(j) * RP + c;
+        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+        uint32_t s = 0;
+        for (; s + 4 <= S; s += 4) {
+            const float4 x0 = *reinterpret_cast<const float4*>(p + (s + 0) * stride);
+            const float4 x1 = *reinterpret_cast<const float4*>(p + (s + 1) * stride);
+            const float4 x2 = *reinterpret_cast<const float4*>(p + (s + 2) * stride);
+            const float4 x3 = *reinterpret_cast<const float4*>(p + (s + 3) * stride);
             v.x += x0.x; v.y += x0.y; v.z += x0.z; v.w += x0.w;
             v.x += x1.x; v.y += x1.y; v.z += x1.z; v.w += x1.w;
             v.x += x2.x; v.y += x2.y; v.z += x2.z; v.w += x2.w;
             v.x += x3.x; v.y += x3.y; v.z += x3.z; v.w += x3.w;
         }
-        for (; s < S; s += GROUPS) {
+        for (; s < S; ++s) {
             const float4 x0 = *reinterpret_cast<const float4*>(p + s * stride);
             v.x += x0.x; v.y += x0.y; v.z += x0.z; v.w += x0.w;
         }
-    }
-    if constexpr (GROUPS > 1) {
-        __shared__ float4 red[GROUPS][W];
-        red[group][at] = v;
-        __syncthreads();
-        if (group != 0 || !live) return;
-#pragma unroll
-        for (uint32_t q = 1; q < GROUPS; ++q) {
-            const float4 x = red[q][at];
-            v.x += x.x; v.y += x.y; v.z += x.z; v.w += x.w;
+        float* dst = Q + static_cast<size_t>(j) * ldq + c;
+        if (c + 4 <= r) {
+            *reinterpret_cast<float4*>(dst) = v;
+        } else {
+            if (c + 0 < r) dst[0] = v.x;
+            if (c + 1 < r) dst[1] = v.y;
+            if (c + 2 < r) dst[2] = v.z;
         }
-    }
-    float* dst = Q + static_cast<size_t>(j) * ldq + c;
-    if (c + 4 <= r) {
-        *reinterpret_cast<float4*>(dst) = v;              // ldq is a multiple of 4, Q 16-byte aligned
     } else {
-        dst[0] = v.x;
-        if (c + 1 < r) dst[1] = v.y;
-        if (c + 2 < r) dst[2] = v.z;
+        constexpr uint32_t LOADERS = 256 / W, SPLITS = 4 * LOADERS;
+        __shared__ float4 tile[SPLITS][W];
+        const uint32_t at = threadIdx.x % W, loader = threadIdx.x / W;
+        // the partials are contiguous over the items of a split: item t at 4 t (a block's items past the last load the last)
+        const float* p = part + min(item0 + at, items - 1) * 4;
+        float4 x[4];
+        auto load = [&](uint32_t s0) {
+#pragma unroll
+            for (uint32_t u = 0; u < 4; ++u)
+                x[u] = *reinterpret_cast<const float4*>(p + min(s0 + loader + LOADERS * u, S - 1) * stride);
+        };
+        float v = 0.0f;
+        load(0);
+        for (uint32_t s0 = 0; s0 < S; s0 += SPLITS) {
+            __syncthreads();                                       // the tile before has been added up
+#pragma unroll
+            for (uint32_t u = 0; u < 4; ++u)                       // (a sum is never -0: + 0 keeps it)
+                tile[loader + LOADERS * u][at] = s0 + loader + LOADERS * u < S ? x[u] : make_float4(0.f, 0.f, 0.f, 0.f);
+            __syncthreads();
+            if (s0 + SPLITS < S) load(s0 + SPLITS);
+            if (threadIdx.x < 4 * W) {
+#pragma unroll
+                for (uint32_t i = 0; i < SPLITS; ++i) v += reinterpret_cast<const float*>(tile[i])[threadIdx.x];
+            }
+        }
+        const uint64_t t = item0 + threadIdx.x / 4;
+        const uint32_t j = static_cast<uint32_t>(t / q4), c = static_cast<uint32_t>(t % q4) * 4 + threadIdx.x % 4;
+        if (threadIdx.x < 4 * W && t < items && c < r) Q[static_cast<size_t>(j) * ldq + c] = v;
     }
 }
 
@@ -2487,8 +2521,9 @@ static int run_orthonormalise(edgc_ctx* ctx, Group& g, const TensorScratch* cap,
     // while the launch is at most four blocks per CU with one tile, two with two tiles (the figures at k_apply)
     const bool factor = t16 <= 2 && apply_blocks <= (t16 == 1 ? 4u : 2u) * static_cast<uint32_t>(ctx->num_cu);
     const uint32_t max_sets = !factor ? 1u : t16 == 1 ? 128u : 8u;
-    // One block sums 64 entries, or 16 in 16 groups where that leaves most CUs idle: a CU fetches some 40 bytes a ns
-    // (50257 x 1024 at rank 32, 786 sets of 6 KB: 12 blocks 12.4 us, 48 5.6)
+    // One block sums 64 entries, or 16 where that leaves most CUs idle.  Between events, whole / narrow: 50257 x 1024 at rank 32
+    // (786 sets of 6 KB, 12 and 48 blocks) 10.0 / 5.9 us, 32000 x 768 (500 sets) 6.7 / 3.2, 100000 x 256 at rank 64 6.6 / 4.5,
+    // 16384 x 1024 3.0 / 1.8, 1536 x 1536 (24 sets) 1.7 / 1.8.
     uint32_t summed_tensors = 0;
     for (uint32_t i = 0; i < g.count; ++i) summed_tensors += g.t[i].nb > max_sets ? 1u : 0u;
     const bool narrow = summed_tensors * cdiv(ne, 64) * 4u <= static_cast<uint32_t>(ctx->num_cu);
@@ -2508,7 +2543,7 @@ static int run_orthonormalise(edgc_ctx* ctx, Group& g, const TensorScratch* cap,
     if (blocks) {
         ProfScope prof_scope_(ctx, st, KID_GRAM_SUM, bytes, 0.0);
         if (narrow) k_gram_sum<16><<<blocks, 256, 0, st>>>(g, ne);
-        else k_gram_sum<4><<<blocks, 256, 0, st>>>(g, ne);
+        else k_gram_sum<64><<<blocks, 256, 0, st>>>(g, ne);
         EDGC_HIP_TRY(ctx, hipGetLastError());
     }
     for (uint32_t i = 0; i < g.count; ++i)
@@ -2634,8 +2669,9 @@ static int run_pass_q(edgc_ctx* ctx, Group& g, const TensorScratch* cap, hipStre
     }
     EDGC_HIP_TRY(ctx, hipGetLastError());
 
-    // 256 items (four columns of a row of Q) per block, or 32 in eight groups where that leaves most CUs idle and there are
-    // sums to share (50257 x 1024 at rank 32, 113 splits: 32 blocks 12.0 us, 256 5.5)
+    // 256 items (four columns of a row of Q) per block, or 32 where that leaves most CUs idle and there are sums to share.
+    // Between events, whole / narrow: 50257 x 1024 at rank 32 (113 splits, 32 and 256 blocks) 9.2 / 3.4 us, 32000 x 768 13.8 / 4.6,
+    // 100000 x 256 at rank 64 31.0 / 8.5, 16384 x 1024 5.2 / 2.4, 4096 x 512 5.3 / 1.8, 1024 x 1024 (16 splits) 1.8 / 1.9.
     uint32_t whole_blocks = 0, most_splits = 0;
     for (uint32_t i = 0; i < g.count; ++i) {
         whole_blocks += cdiv(static_cast<uint64_t>(g.t[i].n) * (RP / 4), 256);
@@ -2651,8 +2687,8 @@ static int run_pass_q(edgc_ctx* ctx, Group& g, const TensorScratch* cap, hipStre
         bytes += 4.0 * t.n * g.r * (t.sq + 1);
     }
     ProfScope prof_scope_(ctx, st, KID_REDUCE_Q, bytes, 0.0);
-    if (narrow) k_reduce_q<8><<<blocks, 256, 0, st>>>(g, RP, 0);
-    else k_reduce_q<1><<<blocks, 256, 0, st>>>(g, RP, 0);
+    if (narrow) k_reduce_q<32><<<blocks, 256, 0, st>>>(g, RP, 0);
+    else k_reduce_q<256><<<blocks, 256, 0, st>>>(g, RP, 0);
     EDGC_HIP_TRY(ctx, hipGetLastError());
     return EDGC_OK;
 }
@@ -2678,7 +2714,7 @@ static int compress_impl(edgc_ctx* ctx, Group& g, const TensorScratch* cap, uint
             blocks += cdiv(static_cast<uint64_t>(t.m) * (RP / 4), 256);
             bytes += 4.0 * t.m * g.r * (t.sp + 1);
         }
-        EDGC_LAUNCH(ctx, st, KID_REDUCE_Q, bytes, 0.0, (k_reduce_q<1><<<blocks, 256, 0, st>>>(g, RP, 1)));
+        EDGC_LAUNCH(ctx, st, KID_REDUCE_Q, bytes, 0.0, (k_reduce_q<256><<<blocks, 256, 0, st>>>(g, RP, 1)));
         EDGC_HIP_TRY(ctx, hipGetLastError());
         return EDGC_OK;
     }

@@ -189,6 +189,34 @@ def test_batch_equals_single_tensor_calls(dtype):
     assert torch.equal(one.t[0].residual, E) and torch.equal(one.t[0].grad_out, out)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("r,m,n", [(40, 20000, 640), (64, 8200, 520), (40, 1000, 600), (100, 16384, 400), (33, 2048, 1023)])
+def test_sums_of_partials_do_not_depend_on_how_many_blocks_share_them(dtype, r, m, n, monkeypatch):
+    """One tensor, whose sums of Q's partials (and, up to rank 64, of Gram sets) are spread over narrow blocks, and the same
+    tensor twice in a batch that aims at twice the blocks: the same splits, summed by whole blocks.  The order is the same."""
+    gen_ = torch.Generator(device="cuda").manual_seed(r + m + n)
+    G = torch.randn(m, n, device="cuda", generator=gen_).to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    Q0 = torch.randn(n, r, device="cuda", generator=gen_)
+    got = []
+    for copies in (1, 2):
+        for knob in ("EDGC_TUNE_P", "EDGC_TUNE_Q"):
+            monkeypatch.setenv(knob, str(copies))
+        c = edgc.Context(0, max_bins=16, max_rank=r, max_rows=64, max_cols=64)
+        c.reserve_batch([(m, n)] * copies)
+        ts = []
+        for _ in range(copies):
+            Q = torch.zeros(n, (r + 3) // 4 * 4, device="cuda")
+            Q[:, :r] = Q0
+            ts.append(edgc.Tensor(G, torch.empty_like(G), torch.empty(m, n, device="cuda"), Q,
+                                  torch.zeros(m, (r + 3) // 4 * 4, device="cuda"), True))
+        c.compress_batch(ts, r)
+        torch.cuda.synchronize()
+        got += [(t.P, t.Q) for t in ts]
+        c.close()
+    for P, Q in got[1:]:
+        assert torch.equal(P, got[0][0]) and torch.equal(Q, got[0][1])
+
+
 @pytest.mark.parametrize("deferred", [False, True])
 def test_prepared_descriptors_give_the_same_bits_as_a_list(deferred):
     """binding.PreparedBatch builds the descriptor array once and rewrites only the two per-call
