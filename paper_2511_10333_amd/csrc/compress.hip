@@ -129,8 +129,11 @@ __device__ __forceinline__ void ld_stream4(const uint16_t* __restrict__ p, float
     v[2] = __uint_as_float(q.y << 16); v[3] = __uint_as_float(q.y & 0xffff0000u);
 }
 
+// Two blocks share a CU.  fp32 above rank 64 needs the compiler told: of its own accord it takes 260 registers, four more than two
+// waves per SIMD leave (one block per CU / two, stored, per launch: hidden-1536 block 112 / 93 us, hidden-3072 360 / 307, 5000 x 1002
+// 53 / 42).
 template <int NP, int RT>
-__global__ __launch_bounds__(256) void k_pass_p(const Group grp)
+__global__ __launch_bounds__(256, (NP == 2 && RT == 4) ? 2 : 1) void k_pass_p(const Group grp)
 {
     const TensorArgs& ta = grp.t[locate(grp, blockIdx.x)];
     const auto* __restrict__ G = static_cast<const typename GradElem<NP>::type*>(ta.G);
