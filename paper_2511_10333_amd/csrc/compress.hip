@@ -1328,9 +1328,8 @@ __global__ __launch_bounds__(256) void k_reduce_q(const Group grp, uint32_t RP, 
 // (E_new alone: the deferred subtraction carried out after all).
 // ---------------------------------------------------------------------------
 template <int NP, int RT, bool DEFER, bool PAST>
-__global__ __launch_bounds__(256) void k_decompress(const Group grp)
+__device__ __forceinline__ void decompress_block(const Group& grp, const TensorArgs& ta)
 {
-    const TensorArgs& ta = grp.t[locate(grp, blockIdx.x)];
     const float* __restrict__ P = ta.P;
     const float* __restrict__ Q = ta.Q;
     float* __restrict__ E = ta.E;
@@ -1553,6 +1552,15 @@ __global__ __launch_bounds__(256) void k_decompress(const Group grp)
     }
 }
 
+// (two waves per SIMD: the form with both bodies would take 262 registers at rank 128)
+template <int NP, int RT, bool DEFER, Caching C>
+__global__ __launch_bounds__(256, (DEFER && C == Caching::by_tensor) ? 2 : 1) void k_decompress(const Group grp)
+{
+    const TensorArgs& ta = grp.t[locate(grp, blockIdx.x)];
+    if (C == Caching::past || (C == Caching::by_tensor && ta.past != 0)) decompress_block<NP, RT, DEFER, true>(grp, ta);
+    else decompress_block<NP, RT, DEFER, false>(grp, ta);
+}
+
 // ---------------------------------------------------------------------------
 // P-pass with the deferred subtraction.  The residual buffer holds D_prev = G_prev + E_prev of
 // the previous step and P, Q hold that step's factors; the residual itself is only formed here:
@@ -1568,13 +1576,12 @@ __global__ __launch_bounds__(256) void k_decompress(const Group grp)
 // tile to become the A operand.
 // ---------------------------------------------------------------------------
 template <int NP, int RT, bool PAST>
-__global__ __launch_bounds__(256, 2) void k_pass_p_deferred(const Group grp)
+__device__ __forceinline__ void pass_p_deferred_block(const Group& grp, const TensorArgs& ta)
 {
     // Two blocks share a CU and each keeps one stage of G and D_prev in flight.  Above rank 64
     // the Q tiles of a 64-column stage would leave LDS for one block only (a version with a
     // second register set for the prefetch ran at 2.7 TB/s): k_pass_p_deferred_narrow.
     static_assert(RT <= 2, "above rank 64: k_pass_p_deferred_narrow");
-    const TensorArgs& ta = grp.t[locate(grp, blockIdx.x)];
     using GT = typename GradElem<NP>::type;
     const GT* __restrict__ G = static_cast<const GT*>(ta.G);
     float* __restrict__ E = ta.E;
@@ -1906,6 +1913,14 @@ __global__ __launch_bounds__(256, 2) void k_pass_p_deferred(const Group grp)
             if (row < m)
                 part[(static_cast<size_t>(s) * m + row) * RP + ct * 32 + jl] = accp[ct][v];
         }
+}
+
+template <int NP, int RT, Caching C>
+__global__ __launch_bounds__(256, 2) void k_pass_p_deferred(const Group grp)
+{
+    const TensorArgs& ta = grp.t[locate(grp, blockIdx.x)];
+    if (C == Caching::past || (C == Caching::by_tensor && ta.past != 0)) pass_p_deferred_block<NP, RT, true>(grp, ta);
+    else pass_p_deferred_block<NP, RT, false>(grp, ta);
 }
 
 // ---------------------------------------------------------------------------
@@ -2282,11 +2297,14 @@ template <int NP, int RT>
 static hipError_t allow_lds_pass_p_deferred()
 {
     constexpr int lds = static_cast<int>(deferred_lds<NP, RT>());
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pass_p_deferred<NP, RT, true>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e != hipSuccess) return e;
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pass_p_deferred<NP, RT, false>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    const void* const kernels[] = {reinterpret_cast<const void*>(&k_pass_p_deferred<NP, RT, Caching::past>),
+                                   reinterpret_cast<const void*>(&k_pass_p_deferred<NP, RT, Caching::through>),
+                                   reinterpret_cast<const void*>(&k_pass_p_deferred<NP, RT, Caching::by_tensor>)};
+    for (const void* k : kernels) {
+        const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 template <int NP>
@@ -2420,12 +2438,11 @@ static int run_pass_p(edgc_ctx* ctx, Group& g, const TensorScratch* cap, bool wi
     }
     const uint32_t step = pass_p_step(g.count, across, along, most, rows_per_block, RP, d_bytes,
                                       static_cast<uint32_t>(ctx->num_cu), ctx->tune_p);
-    // The kernels of the deferred form read G past the caches if its rows are whole cache lines: the two stages that share a
+    // The kernels of the deferred form read a G past the caches if its rows are whole cache lines: the two stages that share a
     // line would fetch it twice (per pass, past them always / by this rule: 373 x 7423 bf16 76.8 / 73.6 us, 8191 x 4097 fp32
     // 230.4 / 223.5, hidden-3001 bf16 block 567 / 548).  k_pass_p reads four columns per lane, and gains nothing by it (hidden-2056
     // fp32 block stored 344 / 353, hidden-1000 112.8 / 116.9).
-    bool past = true;
-    uint32_t blocks = 0;
+    uint32_t blocks = 0, n_past = 0;
     double bytes = 0.0, flops = 0.0;
     for (uint32_t i = 0; i < g.count; ++i) {
         TensorArgs& t = g.t[i];
@@ -2438,7 +2455,8 @@ static int run_pass_p(edgc_ctx* ctx, Group& g, const TensorScratch* cap, bool wi
         t.sp = S;
         t.first = g.first[i] = blocks;
         blocks += RB * S;
-        past = past && (t.ldg * sizeof(GT)) % 128 == 0 && reinterpret_cast<uintptr_t>(t.G) % 128 == 0;
+        t.past = whole_lines(t.G, t.ldg * sizeof(GT)) ? 1 : 0;
+        n_past += t.past;
         // algorithmic traffic: read G and write D (where there is a G), read E_old (if any)
         const double mn = static_cast<double>(t.m) * t.n;
         bytes += mn * ((with_grad ? sizeof(GT) + 4 : 0) + (t.e_zero ? 0 : 4));
@@ -2461,8 +2479,11 @@ static int run_pass_p(edgc_ctx* ctx, Group& g, const TensorScratch* cap, bool wi
         } else {
             constexpr size_t lds = deferred_lds<NP, RT>();
             ProfScope prof_scope_(ctx, st, KID_PASS_P_DEFERRED, bytes, fl);
-            if (past) k_pass_p_deferred<NP, RT, true><<<blocks, 256, lds, st>>>(g);
-            else k_pass_p_deferred<NP, RT, false><<<blocks, 256, lds, st>>>(g);
+            switch (group_caching(n_past, g.count)) {
+            case Caching::past: k_pass_p_deferred<NP, RT, Caching::past><<<blocks, 256, lds, st>>>(g); break;
+            case Caching::through: k_pass_p_deferred<NP, RT, Caching::through><<<blocks, 256, lds, st>>>(g); break;
+            default: k_pass_p_deferred<NP, RT, Caching::by_tensor><<<blocks, 256, lds, st>>>(g); break;
+            }
         }
     } else
         EDGC_LAUNCH(ctx, st, KID_PASS_P, bytes, flops, (k_pass_p<NP, RT><<<blocks, 256, 0, st>>>(g)));
@@ -2784,16 +2805,15 @@ static int decompress_impl(edgc_ctx* ctx, Group& g, hipStream_t st)
     const uint32_t target = static_cast<uint32_t>(ctx->num_cu) * per_cu;
     uint32_t tgt[kMaxGroup];
     share_targets(g, target, tgt);
-    // The reconstruction is not read again here and goes past the caches, unless its rows are not whole cache lines: then half
+    // A reconstruction is not read again here and goes past the caches, unless its rows are not whole cache lines: then half
     // a line written past them at a time costs more (the kernel alone, deferred hidden-2056 fp32 block 73.5 past them, 41.8 us
     // through them).  In the stored form lines of the reconstruction push out D, which the kernel reads from the last-level cache,
     // so that only small groups take them through (past / through, per pass: hidden-500 fp32 block, 12 MB, 68.5 / 66.7 us;
     // hidden-1000, 48 MB, 113 / 127; hidden-2056 344 / 391).
-    bool past = true;
     uint64_t d_bytes = 0;
     for (uint32_t i = 0; i < g.count; ++i) d_bytes += 4ull * g.t[i].m * g.t[i].n;
     const bool by_line = g.defer || d_bytes <= (24ull << 20);
-    uint32_t blocks = 0;
+    uint32_t blocks = 0, n_past = 0;
     double bytes = 0.0, flops = 0.0;
     for (uint32_t i = 0; i < g.count; ++i) {
         TensorArgs& t = g.t[i];
@@ -2805,7 +2825,8 @@ static int decompress_impl(edgc_ctx* ctx, Group& g, hipStream_t st)
         t.d1 = JS;
         t.first = g.first[i] = blocks;
         blocks += RB * JS;
-        if (by_line) past = past && (t.ldo * esz) % 128 == 0 && reinterpret_cast<uintptr_t>(t.out) % 128 == 0;
+        t.past = !by_line || whole_lines(t.out, t.ldo * esz) ? 1 : 0;
+        n_past += t.past;
         // algorithmic traffic: write M^ (if asked for); read D and write E_new unless deferred
         bytes += static_cast<double>(t.m) * t.n * ((g.defer ? 0 : 8) + (t.out ? esz : 0));
         flops += 2.0 * t.m * t.n * g.r;
@@ -2816,10 +2837,16 @@ static int decompress_impl(edgc_ctx* ctx, Group& g, hipStream_t st)
         return EDGC_OK;
     }
     ProfScope prof_scope_(ctx, st, KID_DECOMPRESS, bytes, flops);
-    if (g.defer && past) k_decompress<NP, RT, true, true><<<blocks, 256, lds, st>>>(g);
-    else if (g.defer) k_decompress<NP, RT, true, false><<<blocks, 256, lds, st>>>(g);
-    else if (past) k_decompress<NP, RT, false, true><<<blocks, 256, lds, st>>>(g);
-    else k_decompress<NP, RT, false, false><<<blocks, 256, lds, st>>>(g);
+    auto launch = [&](auto defer_tag) {
+        constexpr bool DEFER = decltype(defer_tag)::value;
+        switch (group_caching(n_past, g.count)) {
+        case Caching::past: k_decompress<NP, RT, DEFER, Caching::past><<<blocks, 256, lds, st>>>(g); break;
+        case Caching::through: k_decompress<NP, RT, DEFER, Caching::through><<<blocks, 256, lds, st>>>(g); break;
+        default: k_decompress<NP, RT, DEFER, Caching::by_tensor><<<blocks, 256, lds, st>>>(g); break;
+        }
+    };
+    if (g.defer) launch(std::true_type{});
+    else launch(std::false_type{});
     EDGC_HIP_TRY(ctx, hipGetLastError());
     return EDGC_OK;
 }

@@ -82,6 +82,7 @@ struct TensorArgs {
     uint32_t nb;            // Gram sets in `tiles`
     uint32_t d0, d1;        // decomposition of the launch at hand (set by the host before it)
     uint32_t first;         // first block of this tensor in the grouped grid
+    uint32_t past;          // 1: the launch at hand moves its gradient (decompress: its reconstruction) past the caches
 };
 
 struct Group {

@@ -81,4 +81,21 @@ inline uint32_t decompress_step(uint32_t stages, uint32_t splits, bool as_asked)
     return as_asked ? step : std::min(step, 8u);
 }
 
+// Whether a launch moves its tensors' gradients (reconstructions) past the caches: all of them, none, or each as its
+// TensorArgs::past says.  Only mixed groups get the kernel that holds both forms: it has twice the code and some registers more.
+// One form for a whole mixed group, that of the worst tensor, costs the other tensors.  Per pass, past for all / through for all /
+// each its own: hidden-4096 fp32 block with a 2056 x 1028 matrix beside it, rank 64, deferred 975 / 1043 / 972 us, bf16 786 / 824 /
+// 776; hidden-2048 with 2048 x 2054, rank 32, fp32 291 / 305 / 287, bf16 stored 307 / 303 / 293.
+enum class Caching { past, through, by_tensor };
+inline Caching group_caching(uint32_t n_past, uint32_t count)
+{
+    return n_past == count ? Caching::past : n_past == 0 ? Caching::through : Caching::by_tensor;
+}
+
+// rows that begin and end with a line of the caches
+inline bool whole_lines(const void* p, uint64_t row_bytes)
+{
+    return row_bytes % 128 == 0 && reinterpret_cast<uintptr_t>(p) % 128 == 0;
+}
+
 }  // namespace edgc

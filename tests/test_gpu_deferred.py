@@ -272,3 +272,37 @@ def test_any_element_address_gives_the_same_bits(dtype, r, deferred):
         view.fill_(7.0)
         assert bool((flat == 7.0).all())
     c.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("r,deferred", [(13, True), (13, False), (40, True), (40, False), (100, False), (100, True)])
+def test_rows_of_whole_lines_and_others_in_one_group_give_the_same_bits(dtype, r, deferred):
+    """Gradients and reconstructions in rows of whole cache lines beside ones in ragged rows, against the same numbers in whole
+    lines throughout: the tensors of one launch go past the caches or through them each by itself."""
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    gen_ = torch.Generator(device="cuda").manual_seed(77 * r)
+    shapes = [(512, 512), (512, 511), (385, 577), (448, 768), (1024, 257)]
+    pair = ([], [])
+    for i, (m, n) in enumerate(shapes):
+        G = (torch.randn(m, n, device="cuda", generator=gen_) * 1e-2).to(tdt)
+        D = torch.randn(m, n, device="cuda", generator=gen_) * 1e-2
+        P, Q = (torch.randn(k, (r + 3) // 4 * 4, device="cuda", generator=gen_) for k in (m, n))
+        P[:, r:] = 0
+        Q[:, r:] = 0
+        for which in (0, 1):
+            whole = (n + 63) // 64 * 64
+            # the second group: ragged gradients, ragged reconstructions, both, neither
+            ld_in, ld_out = (whole + 1 if which and i % 2 else whole), (whole + 1 if which and i // 2 % 2 else whole)
+            grad, out = torch.zeros(m, ld_in, device="cuda", dtype=tdt)[:, :n], torch.zeros(m, ld_out, device="cuda", dtype=tdt)[:, :n]
+            grad.copy_(G)
+            pair[which].append(edgc.Tensor(grad, out, D.clone(), Q.clone(), P.clone(), False))
+    c = edgc.Context(0, max_bins=256, max_rank=128, max_rows=1024, max_cols=1024)
+    c.reserve_batch(shapes)
+    for group in pair:
+        c.compress_batch(group, r, deferred=deferred)
+        c.decompress_batch(group, r, deferred=deferred)
+    torch.cuda.synchronize()
+    for a, b in zip(*pair):
+        for x, y in ((a.grad_out, b.grad_out), (a.residual, b.residual), (a.P, b.P), (a.Q, b.Q)):
+            assert torch.isfinite(x.float()).all() and torch.equal(x, y), tuple(a.grad.shape)
+    c.close()

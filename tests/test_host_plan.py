@@ -115,3 +115,29 @@ def test_decompress_plan_is_the_one_asked_for(tmp_path):
     for line in subprocess.run([str(tmp_path / "d")], check=True, capture_output=True, text=True).stdout.splitlines():
         stages, splits, rule, asked = map(int, line.split())
         assert asked == _cdiv(stages, splits) and rule == min(asked, 8)
+
+
+CACHING = r"""
+#include <cstdio>
+#include "pass_plan.h"
+int main()
+{
+    using edgc::Caching;
+    const auto at = [](uint64_t a) { return reinterpret_cast<const void*>(a); };
+    std::printf("%d %d %d %d %d\n", edgc::whole_lines(at(4096), 256), edgc::whole_lines(at(4096), 8224), edgc::whole_lines(at(4100), 256),
+                edgc::whole_lines(at(4096 + 64), 128), edgc::whole_lines(at(128), 1u << 30));
+    for (uint32_t count = 1; count <= 16; ++count)
+        for (uint32_t past = 0; past <= count; ++past)
+            if (edgc::group_caching(past, count) != (past == 0 ? Caching::through : past == count ? Caching::past : Caching::by_tensor))
+                return 1;
+}
+"""
+
+
+def test_a_tensor_of_ragged_rows_does_not_decide_for_its_group(tmp_path):
+    """Each tensor's rows are looked at by themselves, and only groups of one kind get one form for all."""
+    (tmp_path / "c.cpp").write_text(CACHING)
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I" + os.path.join(ROOT, "paper_2511_10333_amd", "csrc"),
+                    str(tmp_path / "c.cpp"), "-o", str(tmp_path / "c")], check=True)
+    out = subprocess.run([str(tmp_path / "c")], check=True, capture_output=True, text=True).stdout
+    assert out.split() == ["1", "0", "0", "0", "1"]
