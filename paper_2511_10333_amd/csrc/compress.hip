@@ -135,7 +135,7 @@ __device__ __forceinline__ void ld_stream4(const uint16_t* __restrict__ p, float
 template <int NP, int RT>
 __global__ __launch_bounds__(256, (NP == 2 && RT == 4) ? 2 : 1) void k_pass_p(const Group grp)
 {
-    const TensorArgs& ta = grp.t[locate(grp, blockIdx.x)];
+    const TensorArgs& ta = tensor_of(grp, blockIdx.x);
     const auto* __restrict__ G = static_cast<const typename GradElem<NP>::type*>(ta.G);
     float* __restrict__ E = ta.E;
     const float* __restrict__ Q = ta.Q;
@@ -306,7 +306,7 @@ __host__ __device__ inline void tri_tile(int t, int T, int& ta, int& tb)
 template <int T16, bool FROM_P>
 __global__ __launch_bounds__(256) void k_reduce_gram(const Group grp, uint32_t RP)
 {
-    const TensorArgs& ta_ = grp.t[locate(grp, blockIdx.x)];
+    const TensorArgs& ta_ = tensor_of(grp, blockIdx.x);
     const float* __restrict__ part = ta_.part;
     float* __restrict__ P = ta_.P;
     double* __restrict__ gram_part = ta_.gram_part;
@@ -432,7 +432,7 @@ __global__ __launch_bounds__(256) void k_reduce_gram(const Group grp, uint32_t R
 template <uint32_t W>
 __global__ __launch_bounds__(256) void k_gram_sum(const Group grps, uint32_t ne)
 {
-    const TensorArgs& ta = grps.t[locate(grps, blockIdx.x)];
+    const TensorArgs& ta = tensor_of(grps, blockIdx.x);
     const double* __restrict__ gp = ta.gram_part;
     double* __restrict__ out = ta.gram;
     const uint32_t nb = ta.d0;
@@ -943,7 +943,7 @@ __device__ __forceinline__ void small_factor(const double* W, double* Rs, double
 template <int T16, int NP, int WAVES, bool FACTOR>
 __global__ __launch_bounds__(64 * WAVES) void k_apply(const Group grp, uint32_t RP)
 {
-    const TensorArgs& ta = grp.t[locate(grp, blockIdx.x)];
+    const TensorArgs& ta = tensor_of(grp, blockIdx.x);
     float* __restrict__ P = ta.P;
     const double* __restrict__ rinv = ta.rinv;
     __bf16* __restrict__ pt = static_cast<__bf16*>(ta.pt);
@@ -1122,7 +1122,7 @@ __device__ __forceinline__ void load_d_rows(const float* __restrict__ D, uint32_
 template <int NP, int RT, int NT>
 __global__ __launch_bounds__(256, (NP == 2 && RT == 4) ? 2 : 1) void k_pass_q(const Group grp)
 {
-    const TensorArgs& ta = grp.t[locate(grp, blockIdx.x)];
+    const TensorArgs& ta = tensor_of(grp, blockIdx.x);
     const float* __restrict__ D = ta.E;
     const __bf16* __restrict__ pt = static_cast<const __bf16*>(ta.pt);
     float* __restrict__ part = ta.part;
@@ -1247,7 +1247,7 @@ __global__ __launch_bounds__(256, (NP == 2 && RT == 4) ? 2 : 1) void k_pass_q(co
 template <uint32_t W>
 __global__ __launch_bounds__(256) void k_reduce_q(const Group grp, uint32_t RP, int of_p)
 {
-    const TensorArgs& ta = grp.t[locate(grp, blockIdx.x)];
+    const TensorArgs& ta = tensor_of(grp, blockIdx.x);
     const float* __restrict__ part = ta.part;
     float* __restrict__ Q = of_p ? ta.P : ta.Q;
     const uint32_t S = of_p ? ta.sp : ta.sq, n = of_p ? ta.m : ta.n, r = grp.r, ldq = of_p ? ta.ldp : ta.ldq;
@@ -1556,7 +1556,7 @@ __device__ __forceinline__ void decompress_block(const Group& grp, const TensorA
 template <int NP, int RT, bool DEFER, Caching C>
 __global__ __launch_bounds__(256, (DEFER && C == Caching::by_tensor) ? 2 : 1) void k_decompress(const Group grp)
 {
-    const TensorArgs& ta = grp.t[locate(grp, blockIdx.x)];
+    const TensorArgs& ta = tensor_of(grp, blockIdx.x);
     if (C == Caching::past || (C == Caching::by_tensor && ta.past != 0)) decompress_block<NP, RT, DEFER, true>(grp, ta);
     else decompress_block<NP, RT, DEFER, false>(grp, ta);
 }
@@ -1918,7 +1918,7 @@ __device__ __forceinline__ void pass_p_deferred_block(const Group& grp, const Te
 template <int NP, int RT, Caching C>
 __global__ __launch_bounds__(256, 2) void k_pass_p_deferred(const Group grp)
 {
-    const TensorArgs& ta = grp.t[locate(grp, blockIdx.x)];
+    const TensorArgs& ta = tensor_of(grp, blockIdx.x);
     if (C == Caching::past || (C == Caching::by_tensor && ta.past != 0)) pass_p_deferred_block<NP, RT, true>(grp, ta);
     else pass_p_deferred_block<NP, RT, false>(grp, ta);
 }
@@ -1935,7 +1935,7 @@ template <int NP, int RT>
 __global__ __launch_bounds__(256, 2) void k_pass_p_deferred_narrow(const Group grp)
 {
     static_assert(RT == 4, "built for ranks above 64");
-    const TensorArgs& ta = grp.t[locate(grp, blockIdx.x)];
+    const TensorArgs& ta = tensor_of(grp, blockIdx.x);
     using GT = typename GradElem<NP>::type;
     const GT* __restrict__ G = static_cast<const GT*>(ta.G);
     float* __restrict__ E = ta.E;
@@ -2247,9 +2247,12 @@ __device__ __forceinline__ void copy_units(const unsigned char* __restrict__ src
 
 __global__ __launch_bounds__(256) void k_copy_rows(const CopyGroup grp)
 {
+    static_assert(offsetof(CopyGroup, t) / 64 == (offsetof(CopyGroup, t) + sizeof(CopyArgs) - 1) / 64, "the first copy's line");
+    const uint64_t first_copy = reinterpret_cast<uint64_t>(grp.t[0].src);      // as in tensor_of
     uint32_t t = 0;
 #pragma unroll
     for (uint32_t i = 1; i < kMaxCopies; ++i) t += (blockIdx.x >= grp.first[i]) ? 1u : 0u;
+    asm volatile("" :: "s"(first_copy));
     const CopyArgs& c = grp.t[t];
     const uint64_t first = static_cast<uint64_t>(blockIdx.x - c.first) * kCopyUnits;
     const uint64_t stride = static_cast<uint64_t>(c.blocks) * kCopyUnits;

@@ -9,6 +9,8 @@
 
 #include "edgc_internal.h"
 
+#include <cstddef>
+
 namespace edgc {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -87,12 +89,21 @@ __device__ __forceinline__ f32x16 mma(const bf16x8 (&a)[NP], const bf16x8 (&b)[N
 // 256-byte pieces of a DRAM page are requested at about the same time (measured 5 to 20 %
 // faster on small matrices than giving each XCD a contiguous range of tiles; the factor
 // slices the blocks share are small enough to sit in every XCD's L2).
-__device__ __forceinline__ uint32_t locate(const Group& g, uint32_t bid)
+// The lines of the first tensor are asked for together with the list of first blocks, so that a group of one (every
+// single-tensor call) does not wait for memory twice in a row at the head of every launch.  Without: 0.3 us per launch more,
+// 256 x 256 fp32 at rank 64 through the single calls 52.7 us in eight launches.
+__device__ __forceinline__ const TensorArgs& tensor_of(const Group& g, uint32_t bid)
 {
+    constexpr size_t at = offsetof(Group, t);
+    static_assert(at / 64 == 1 && (at + offsetof(TensorArgs, gram)) / 64 == 2 && (at + offsetof(TensorArgs, m_pad)) / 64 == 3 &&
+                  at + sizeof(TensorArgs) <= 256, "a word of each of the first tensor's lines");
+    const uint64_t line1 = reinterpret_cast<uint64_t>(g.t[0].G), line2 = reinterpret_cast<uint64_t>(g.t[0].gram);
+    const uint32_t line3 = g.t[0].m_pad;
     uint32_t t = 0;
 #pragma unroll
     for (int i = 1; i < kMaxGroup; ++i) t += (bid >= g.first[i]) ? 1u : 0u;
-    return t;
+    asm volatile("" :: "s"(line1), "s"(line2), "s"(line3));
+    return g.t[t];
 }
 
 // element type of the gradient: one bf16 plane <=> bf16 gradients (raw bits), two planes <=> fp32

@@ -19,7 +19,7 @@ constexpr size_t decompress_full_lds() { return static_cast<size_t>(2) * 64 * (N
 template <int NP, int RT, int WAVES>
 __global__ __launch_bounds__(64 * WAVES, (NP == 2 && RT == 4) ? 2 : ((RT == 4 && WAVES == 4) ? 3 : 4)) void k_decompress_full(const Group grp)
 {
-    const TensorArgs& ta = grp.t[locate(grp, blockIdx.x)];
+    const TensorArgs& ta = tensor_of(grp, blockIdx.x);
     const float* __restrict__ P = ta.P;
     const float* __restrict__ Q = ta.Q;
     void* __restrict__ out_ = ta.out;

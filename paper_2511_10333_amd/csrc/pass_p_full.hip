@@ -30,7 +30,7 @@ constexpr size_t pass_p_full_lds()
 template <int NP, int RT, bool QLATE, int WAVES, bool SUB>
 __global__ __launch_bounds__(64 * WAVES, 2) void k_pass_p_deferred_full(const Group grp)
 {
-    const TensorArgs& ta = grp.t[locate(grp, blockIdx.x)];
+    const TensorArgs& ta = tensor_of(grp, blockIdx.x);
     using GT = typename GradElem<NP>::type;
     const GT* __restrict__ G = static_cast<const GT*>(ta.G);
     float* __restrict__ E = ta.E;

@@ -18,7 +18,7 @@ constexpr size_t pass_q_full_lds() { return static_cast<size_t>(2) * RT * 32 * (
 template <int NP, int RT, bool STREAM, int WAVES>
 __global__ __launch_bounds__(64 * WAVES, 2) void k_pass_q_full(const Group grp)
 {
-    const TensorArgs& ta = grp.t[locate(grp, blockIdx.x)];
+    const TensorArgs& ta = tensor_of(grp, blockIdx.x);
     const float* __restrict__ D = ta.E;
     const __bf16* __restrict__ pt = static_cast<const __bf16*>(ta.pt);
     float* __restrict__ part = ta.part;
