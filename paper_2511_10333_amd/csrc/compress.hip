@@ -116,15 +116,29 @@ __device__ __forceinline__ void store_f32x4(float* __restrict__ base, uint64_t l
     }
 }
 
-// streaming load of four elements that does not pollute the caches (the matrix is read once per pass)
-__device__ __forceinline__ void ld_stream4(const float* __restrict__ p, float (&v)[4])
+// the next four elements of a gradient row; PAST: read once, past the caches
+template <bool PAST>
+__device__ __forceinline__ void load_quad(const float* __restrict__ p, float (&v)[4])
 {
-    const f32x4_any q = __builtin_nontemporal_load(reinterpret_cast<const f32x4_any*>(p));
+    Floats4 q;
+    if constexpr (PAST) {
+        const f32x4_any x = __builtin_nontemporal_load(reinterpret_cast<const f32x4_any*>(p));
+        q = {x.x, x.y, x.z, x.w};
+    } else {
+        q = at_any<Floats4>(p);
+    }
     v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
 }
-__device__ __forceinline__ void ld_stream4(const uint16_t* __restrict__ p, float (&v)[4])
+template <bool PAST>
+__device__ __forceinline__ void load_quad(const uint16_t* __restrict__ p, float (&v)[4])
 {
-    const bf16x4_any q = __builtin_nontemporal_load(reinterpret_cast<const bf16x4_any*>(p));
+    Bf16Quad q;
+    if constexpr (PAST) {
+        const bf16x4_any x = __builtin_nontemporal_load(reinterpret_cast<const bf16x4_any*>(p));
+        q = {x.x, x.y};
+    } else {
+        q = at_any<Bf16Quad>(p);
+    }
     v[0] = __uint_as_float(q.x << 16); v[1] = __uint_as_float(q.x & 0xffff0000u);
     v[2] = __uint_as_float(q.y << 16); v[3] = __uint_as_float(q.y & 0xffff0000u);
 }
@@ -132,7 +146,7 @@ __device__ __forceinline__ void ld_stream4(const uint16_t* __restrict__ p, float
 // Two blocks share a CU.  fp32 above rank 64 needs the compiler told: of its own accord it takes 260 registers, four more than two
 // waves per SIMD leave (one block per CU / two, stored, per launch: hidden-1536 block 112 / 93 us, hidden-3072 360 / 307, 5000 x 1002
 // 53 / 42).
-template <int NP, int RT>
+template <int NP, int RT, bool PAST>
 __global__ __launch_bounds__(256, (NP == 2 && RT == 4) ? 2 : 1) void k_pass_p(const Group grp)
 {
     const TensorArgs& ta = tensor_of(grp, blockIdx.x);
@@ -176,7 +190,7 @@ __global__ __launch_bounds__(256, (NP == 2 && RT == 4) ? 2 : 1) void k_pass_p(co
             const uint32_t row = row0 + p * RPP + a_row, col = k0 + a_col;
             float g[4] = {0.f, 0.f, 0.f, 0.f}, e[4] = {0.f, 0.f, 0.f, 0.f};
             if constexpr (FULL) {
-                if (G) ld_stream4(G + static_cast<uint64_t>(row) * ldg + col, g);
+                if (G) load_quad<PAST>(G + static_cast<uint64_t>(row) * ldg + col, g);
                 if (!e_zero) {
                     const float* pe = E + static_cast<uint64_t>(row) * n + col;
                     const Floats4 q4 = at_any<Floats4>(pe);
@@ -204,15 +218,20 @@ __global__ __launch_bounds__(256, (NP == 2 && RT == 4) ? 2 : 1) void k_pass_p(co
     };
     auto commit = [&](uint32_t k0, auto full_tag) {
         constexpr bool FULL = decltype(full_tag)::value;
+        // (a later power iteration has no G: D is in the buffer as it stands; 4096 x 4096 at rank 32 24.6 us with the store, 16.3
+        // without.  One branch for all rows: one in each of them made the edge tiles slower, 1001 x 777 at rank 64 13.6 / 11.4 us)
+        if (G) {
+#pragma unroll
+            for (int p = 0; p < PA; ++p) {
+                const uint32_t row = row0 + p * RPP + a_row, col = k0 + a_col;
+                if constexpr (FULL)
+                    put_any(E + static_cast<uint64_t>(row) * n + col, Floats4{d[p][0], d[p][1], d[p][2], d[p][3]});
+                else
+                    store_f32x4(E, n, row, col, m, k_end, d[p]);
+            }
+        }
 #pragma unroll
         for (int p = 0; p < PA; ++p) {
-            const uint32_t row = row0 + p * RPP + a_row, col = k0 + a_col;
-            if (!G) {                      // a later power iteration: D is in the buffer as it stands (24.6 us with the
-                                           // store, 4096 x 4096 at rank 32; 16.3 without)
-            } else if constexpr (FULL)
-                put_any(E + static_cast<uint64_t>(row) * n + col, Floats4{d[p][0], d[p][1], d[p][2], d[p][3]});
-            else
-                store_f32x4(E, n, row, col, m, k_end, d[p]);
             bf16x4 w[NP];
             pack4<NP>(d[p], w);
 #pragma unroll
@@ -2441,10 +2460,7 @@ static int run_pass_p(edgc_ctx* ctx, Group& g, const TensorScratch* cap, bool wi
     }
     const uint32_t step = pass_p_step(g.count, across, along, most, rows_per_block, RP, d_bytes,
                                       static_cast<uint32_t>(ctx->num_cu), ctx->tune_p);
-    // The kernels of the deferred form read a G past the caches if its rows are whole cache lines: the two stages that share a
-    // line would fetch it twice (per pass, past them always / by this rule: 373 x 7423 bf16 76.8 / 73.6 us, 8191 x 4097 fp32
-    // 230.4 / 223.5, hidden-3001 bf16 block 567 / 548).  k_pass_p reads four columns per lane, and gains nothing by it (hidden-2056
-    // fp32 block stored 344 / 353, hidden-1000 112.8 / 116.9).
+    // A G goes past the caches if its rows are whole lines of them, or by the size of its group (gradient_past)
     uint32_t blocks = 0, n_past = 0;
     double bytes = 0.0, flops = 0.0;
     for (uint32_t i = 0; i < g.count; ++i) {
@@ -2458,7 +2474,7 @@ static int run_pass_p(edgc_ctx* ctx, Group& g, const TensorScratch* cap, bool wi
         t.sp = S;
         t.first = g.first[i] = blocks;
         blocks += RB * S;
-        t.past = whole_lines(t.G, t.ldg * sizeof(GT)) ? 1 : 0;
+        t.past = gradient_past(d_bytes, sizeof(GT), use_wide, g.defer != 0) || whole_lines(t.G, t.ldg * sizeof(GT)) ? 1 : 0;
         n_past += t.past;
         // algorithmic traffic: read G and write D (where there is a G), read E_old (if any)
         const double mn = static_cast<double>(t.m) * t.n;
@@ -2488,8 +2504,11 @@ static int run_pass_p(edgc_ctx* ctx, Group& g, const TensorScratch* cap, bool wi
             default: k_pass_p_deferred<NP, RT, Caching::by_tensor><<<blocks, 256, lds, st>>>(g); break;
             }
         }
-    } else
-        EDGC_LAUNCH(ctx, st, KID_PASS_P, bytes, flops, (k_pass_p<NP, RT><<<blocks, 256, 0, st>>>(g)));
+    } else {
+        ProfScope prof_scope_(ctx, st, KID_PASS_P, bytes, flops);
+        if (n_past == g.count) k_pass_p<NP, RT, true><<<blocks, 256, 0, st>>>(g);
+        else k_pass_p<NP, RT, false><<<blocks, 256, 0, st>>>(g);
+    }
     EDGC_HIP_TRY(ctx, hipGetLastError());
     return EDGC_OK;
 }

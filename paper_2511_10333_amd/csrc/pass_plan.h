@@ -92,6 +92,26 @@ inline Caching group_caching(uint32_t n_past, uint32_t count)
     return n_past == count ? Caching::past : n_past == 0 ? Caching::through : Caching::by_tensor;
 }
 
+// Whether the P-pass reads a gradient past the caches whose rows are not whole lines of them.  Through them, the two stages that
+// share a line fetch it once; but a group's gradients beside its D (`d_bytes`) then push D out of the 256 MB last-level cache,
+// where the Q-pass or the decompress would find it.  `pairs`: the kernels whose lanes read two columns (k_pass_p_deferred); k_pass_p's
+// read four and share fewer lines.  Per pass without an estimate, past / through, in us, by the size of D:
+//  * k_pass_p: 16 MB (2047 x 2049 fp32 at rank 13) 68.3 / 65.8, 19 MB (5000 x 1002, rank 64) 113.0 / 105.8, 29 MB (hidden-777 block)
+//    91.8 / 87.8, 34 MB 90.1 / 84.8, 42 MB (3300 x 3302) 98.9 / 98.1 and at rank 64 129.9 / 130.2, 46 MB 135.2 / 137.2, 64 MB 161.0 /
+//    165.9, 103 MB 231.9 / 239.4.
+//  * pairs, stored, bf16: 46 MB 101.4 / 91.1, 64 MB (4097 x 4095) 121.1 / 111.9, 66 MB (hidden-1200) 117.9 / 121.1, 103 MB 203.8 / 216.7,
+//    194 MB (hidden-2056) 289.3 / 300.2, 412 MB (hidden-3001) 785 / 778.
+//  * pairs, deferred (D is not read again after the Q-pass), fp32: 46 MB 84.9 / 84.9, 66 MB at rank 64 151.7 / 156.7, 69 MB (3002 x
+//    6002) 111.3 / 116.3, 103 MB 167.5 / 166.7, 128 MB (8191 x 4097) 210.4 / 204.2, 194 MB 278.8 / 274.1; bf16: 46 MB 82.9 / 76.4,
+//    69 MB 105.0 / 121.9, 103 MB 170.6 / 183.0, 132 MB 172.8 / 179.1, 194 MB 244.9 / 235.4, 412 MB 546 / 529.
+inline bool gradient_past(double d_bytes, uint32_t elem_bytes, bool pairs, bool defer)
+{
+    constexpr double MB = 1024.0 * 1024.0;
+    const double both = d_bytes * (1.0 + elem_bytes / 4.0);             // D and G
+    if (!pairs) return both > 80.0 * MB;
+    return both > 96.0 * MB && (defer ? both : d_bytes) <= 256.0 * MB;
+}
+
 // rows that begin and end with a line of the caches
 inline bool whole_lines(const void* p, uint64_t row_bytes)
 {

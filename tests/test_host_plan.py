@@ -124,6 +124,15 @@ int main()
 {
     using edgc::Caching;
     const auto at = [](uint64_t a) { return reinterpret_cast<const void*>(a); };
+    // k_pass_p by the size of its group; the kernels of the deferred form where D is to stay cached and cannot beside G
+    const auto past = [](double mb, uint32_t esz, bool pairs, bool defer) { return edgc::gradient_past(mb * 1048576.0, esz, pairs, defer); };
+    for (double mb : {0.001, 16.0, 40.0, 41.0, 53.0, 54.0, 63.9, 64.1, 127.9, 128.1, 170.0, 171.0, 256.0, 257.0, 4000.0}) {
+        const bool want[] = {mb > 40.0, mb > 80.0 / 1.5, mb > 64.0 && mb <= 256.0, mb > 48.0 && mb <= 128.0, mb > 64.0 && mb <= 170.5};
+        const bool got[] = {past(mb, 4, false, false), past(mb, 2, false, false), past(mb, 2, true, false), past(mb, 4, true, true),
+                            past(mb, 2, true, true)};
+        for (int i = 0; i < 5; ++i)
+            if (want[i] != got[i]) return 2;
+    }
     std::printf("%d %d %d %d %d\n", edgc::whole_lines(at(4096), 256), edgc::whole_lines(at(4096), 8224), edgc::whole_lines(at(4100), 256),
                 edgc::whole_lines(at(4096 + 64), 128), edgc::whole_lines(at(128), 1u << 30));
     for (uint32_t count = 1; count <= 16; ++count)
