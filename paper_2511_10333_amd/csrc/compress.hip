@@ -1549,7 +1549,10 @@ __device__ __forceinline__ void decompress_block(const Group& grp, const TensorA
     // (the two D register sets swap roles)
     // (fp32 above rank 64: the second copy of the loop costs the two registers that let two waves
     // share a SIMD, 128 instead of 103 us on the hidden-4096 layer: left out there)
-    constexpr bool FAST = !(NP == 2 && RT == 4);
+    // stored form through the caches: small groups, which two waves per SIMD serve better than the loop whose second copy
+    // takes the registers of one of them (D is in the last-level cache; with it / without: 2047 x 2049 bf16 at rank 64 18.8 / 14.0 us,
+    // fp32 at rank 13 16.7 / 13.4, 5000 x 1002 bf16 19.8 / 14.6, hidden-500 bf16 block 12.2 / 9.3)
+    constexpr bool FAST = !(NP == 2 && RT == 4) && (DEFER || PAST);
     const uint32_t whole_end = (FAST && rows_full) ? min(st_end, n / 64) : 0;
     uint32_t st = st_begin;
     if (FAST && whole_end > st_begin + 2) {
@@ -2830,11 +2833,13 @@ static int decompress_impl(edgc_ctx* ctx, Group& g, hipStream_t st)
     // A reconstruction is not read again here and goes past the caches, unless its rows are not whole cache lines: then half
     // a line written past them at a time costs more (the kernel alone, deferred hidden-2056 fp32 block 73.5 past them, 41.8 us
     // through them).  In the stored form lines of the reconstruction push out D, which the kernel reads from the last-level cache,
-    // so that only small groups take them through (past / through, per pass: hidden-500 fp32 block, 12 MB, 68.5 / 66.7 us;
-    // hidden-1000, 48 MB, 113 / 127; hidden-2056 344 / 391).
+    // so that only small groups take them through.  Stored, per pass without an estimate, past / through, by the size of D: 17 MB
+    // (2047 x 2049) fp32 at rank 13 66.4 / 61.7 us, bf16 at rank 64 99.3 / 94.9; 20 MB (5000 x 1002) 68.3 / 62.9, 101.3 / 96.3; 28 MB
+    // (777 x 9001) 83.2 / 78.0, 117.8 / 111.8, at rank 100 169.7 / 168.8; 36 MB (3002 x 3002) 85.3 / 82.5, 119.2 / 115.7, at rank 100
+    // 161.1 / 168.2; 48 MB (hidden-1000 block) 101.0 / 101.9, 126.1 / 127.6, 182.8 / 186.9; 108 MB 183 / 200.
     uint64_t d_bytes = 0;
     for (uint32_t i = 0; i < g.count; ++i) d_bytes += 4ull * g.t[i].m * g.t[i].n;
-    const bool by_line = g.defer || d_bytes <= (24ull << 20);
+    const bool by_line = g.defer || d_bytes <= (28ull << 20);
     uint32_t blocks = 0, n_past = 0;
     double bytes = 0.0, flops = 0.0;
     for (uint32_t i = 0; i < g.count; ++i) {
