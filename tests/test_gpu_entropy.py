@@ -432,6 +432,29 @@ def test_one_round_kernels_on_strided_samples_of_many_buffers(dtype, stride, chu
             assert abs(got.H_bits - ref.H_bits) <= H_TOL
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n", [40_001, 600_011, 3_000_007])
+def test_last_block_sums_many_bins(dtype, n):
+    """Bin counts at the lines between few and many bins per thread, between sets of 32-bit counters and none, and no multiple of
+    the bins of an iteration; samples with one set of counters, with eight, of blocks of 512 and 1024 threads."""
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen_ = torch.Generator(device="cuda").manual_seed(n)
+    x = ((torch.rand(n, generator=gen_, device="cuda") - 0.25) ** 3).to(tdt)
+    x[5] = float("nan")
+    fin = x.float()[torch.isfinite(x)]
+    c = edgc.Context(0, max_bins=200_000, max_rank=4, max_rows=64, max_cols=64)
+    lo, hi = fin.min(), fin.max()
+    for bins in (2048, 2049, 4096, 4097, 8195, 16383, 16384, 16385, 32769, 65535, 65536, 100_001):
+        counts = torch.full((bins,), -1, dtype=torch.int64, device="cuda")
+        got = c.entropy_estimate(x, 1, 64, 0, 0, bins, None, counts)
+        scale = torch.tensor(float(bins), dtype=torch.float32) / (hi - lo).cpu()
+        want = torch.bincount(((fin - lo) * scale.cuda()).long().clamp_(0, bins - 1), minlength=bins)
+        assert torch.equal(counts, want), bins
+        p = want[want > 0].double() / fin.numel()
+        assert got.n_nonfinite == 1 and abs(got.H_bits - float(-(p * torch.log2(p)).sum())) <= H_TOL, bins
+    c.close()
+
+
 def to_host_any(x):
     if x.dtype == torch.bfloat16:
         return x.view(torch.int16).cpu().numpy().view(np.uint16)
