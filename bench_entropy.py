@@ -20,7 +20,7 @@ def entropy_sweep(args, torch, edgc, metric, hbm_peak_gbs) -> int:
     100, 10 and 1 (0.1 % to 100 %) times 256, 4096 and 65536 bins.  One "step" is one estimate
     (range, histogram, entropy) of one cell; the JSON line carries every cell and, as `value`, the
     100 % / 4096-bin cell of the fp32 buffer, whose two passes read the whole buffer twice.  A cell's
-    `reads_of_sample` says how often its kernels read the sample (bf16 samples of 32 Mi elements or
+    `reads_of_sample` says how often its kernels read the sample (bf16 samples of 8 Mi elements or
     more are read once), `sample_gbs` = those reads x sample bytes / time."""
     from paper_2511_10333_amd.binding import ENTROPY_RESULT_BYTES, EntropyResult
     n, chunk, seed = 1_000_000_000, args.ent_chunk, 0

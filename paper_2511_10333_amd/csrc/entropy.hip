@@ -1256,12 +1256,21 @@ static int run_entropy(edgc_ctx* ctx, const EntScratch& s, const EntGroup& g, ui
     // for the blocks' fields: every bf16 sample of some size (no range pass, any number of bins), and
     // fp32 samples on more bins than 32-bit counters hold in LDS at once.
     const bool wide_ok = s.part16 != nullptr && ctx->tune_pattern != 0;
-    // (measured on samples of a 1e9-element bf16 buffer, 4096 bins, one read against two passes: 1e7
-    // elements 0.067 against 0.061 ms, 1e8 0.115 against 0.171, 1e9 0.57 against 0.85; on 65536 bins: 1e7
-    // 0.103 against 0.155 ms, 1e9 0.61 against 1.87)
+    // The line for bf16 lies at 8 Mi elements, where the two passes meet on most bin counts and where two-pass samples leave the
+    // kernels of short blocks; at half of that above 16384 bins.  Per estimate in us, two passes / one read, every element of a
+    // buffer (1 sampled in 3 and in 10: the same within 2):
+    //                  256 bins      4096 bins     16384 bins    20000 bins    65536 bins
+    //      4 M         18.1 / 23.0   22.9 / 26.3   32.8 / 32.5   30 / 33       55.2 / 53.5
+    //      7 M         22.0 / 24.1   27.1 / 26.9   35.6 / 33.6   35.7 / 35.5
+    //    8.3 M         24.2 / 25.6   28.8 / 28.4   36.6 / 35.2   36.6 / 37.1   58.3 / 56.3
+    //    9.0 M         26.7 / 26.2   29.3 / 29.0   39.2 / 35.8   74.9 / 37.7
+    //     12 M         28.3 / 27.5   30.9 / 30.5   41.1 / 37.6   78 / 38       96.2 / 60.0
+    //     24 M         39.1 / 32.9   43.4 / 35.8   53.7 / 43.0   84 / 43      101.2 / 65.8
+    //     64 M         66.5 / 46.8   71.8 / 49.8   85.1 / 57.8   98 / 58      118.1 / 81.6
+    // Buffers off 16-byte boundaries: 2 M 24.3 / 23.4 on 256 bins, 8 M 47.0 / 28.8.
     const uint64_t pattern_min = static_cast<uint64_t>(ctx->tune_pattern_min);
     const bool by_pattern = sizeof(T) == 2 && wide_ok &&
-                            (g.n_sampled >= pattern_min || (bins > 16384 && g.n_sampled >= pattern_min / 8));
+                            (g.n_sampled >= pattern_min || (bins > 16384 && g.n_sampled >= pattern_min / 2));
     const bool by_wide_bins = sizeof(T) == 4 && wide_ok && bins > 16384 && bins <= kWideKeys;
     const uint32_t wide_blocks = grid_for(g.n_items, kWideBlock, 4, min(ctx->num_cu, static_cast<int>(s.part16_blocks)));
     uint32_t nparts = 0;                                   // blocks' (lo, hi) in s.mm_part

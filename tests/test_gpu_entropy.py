@@ -455,6 +455,22 @@ def test_last_block_sums_many_bins(dtype, n):
     c.close()
 
 
+def _kernels_of(c, x, bins):
+    c.profile_begin(64)
+    c.entropy_estimate(x, 1, 64, 0, 0, bins)
+    return c.profile_end()
+
+
+@pytest.mark.parametrize("bins,line", [(256, 8 << 20), (4096, 8 << 20), (16384, 8 << 20), (16385, 4 << 20), (65536, 4 << 20)])
+def test_bf16_samples_are_counted_by_pattern_from_where_one_read_is_the_faster(bins, line):
+    """The kernels on both sides of the line between two passes and one read."""
+    x = (torch.randn(line, device="cuda") * 1e-3).bfloat16()
+    c = _context_with()
+    assert "k_hist" in _kernels_of(c, x[:-8], bins)
+    assert set(_kernels_of(c, x, bins)) == {"k_wide_hist", "k_wide_reduce"}
+    c.close()
+
+
 def to_host_any(x):
     if x.dtype == torch.bfloat16:
         return x.view(torch.int16).cpu().numpy().view(np.uint16)
