@@ -1273,6 +1273,8 @@ static int run_entropy(edgc_ctx* ctx, const EntScratch& s, const EntGroup& g, ui
                             (g.n_sampled >= pattern_min || (bins > 16384 && g.n_sampled >= pattern_min / 2));
     const bool by_wide_bins = sizeof(T) == 4 && wide_ok && bins > 16384 && bins <= kWideKeys;
     const uint32_t wide_blocks = grid_for(g.n_items, kWideBlock, 4, min(ctx->num_cu, static_cast<int>(s.part16_blocks)));
+    // of k_wide_reduce, what is moved whatever the sample holds: marks, credits and bins (the host does not know which fields)
+    const double reduce_bytes = 4.0 * kOccupiedWords * wide_blocks + 8.0 * kWideKeys + 8.0 * bins;
     uint32_t nparts = 0;                                   // blocks' (lo, hi) in s.mm_part
     double* const pair_part = reinterpret_cast<double*>(s.mm_part + kMaxReduceBlocks / 2);
     if constexpr (sizeof(T) == 2) {
@@ -1280,7 +1282,7 @@ static int run_entropy(edgc_ctx* ctx, const EntScratch& s, const EntGroup& g, ui
             EDGC_LAUNCH(ctx, st, KID_WIDE_HIST, sample_bytes, 0.0,
                         k_wide_hist<T, VEC, true><<<wide_blocks, kWideBlock, kWideKeys * 2, st>>>(
                             g, s.mm_part, nparts, bins, s.part16, s.occupied, s.wide, counts));
-            EDGC_LAUNCH(ctx, st, KID_WIDE_REDUCE, 2.0 * kWideKeys * wide_blocks, 0.0,
+            EDGC_LAUNCH(ctx, st, KID_WIDE_REDUCE, reduce_bytes, 0.0,
                         k_wide_reduce<true><<<kWideKeys / kReduceKeys, kWideBlock, kWideReduceLds, st>>>(
                             s.part16, s.occupied, wide_blocks, s.wide, bins, range ? 1 : 0, range ? range[0] : 0.0f,
                             range ? range[1] : 0.0f, counts, s.mm_part, wide_blocks, pair_part, s.ticket, g.n_sampled, res));
@@ -1369,7 +1371,7 @@ static int run_entropy(edgc_ctx* ctx, const EntScratch& s, const EntGroup& g, ui
             EDGC_LAUNCH(ctx, st, KID_WIDE_HIST, sample_bytes, 0.0,
                         k_wide_hist<T, VEC, false><<<wide_blocks, kWideBlock, kWideKeys * 2, st>>>(
                             g, s.mm_part, nparts, bins, s.part16, s.occupied, s.wide, counts));
-            EDGC_LAUNCH(ctx, st, KID_WIDE_REDUCE, 2.0 * kWideKeys * wide_blocks, 0.0,
+            EDGC_LAUNCH(ctx, st, KID_WIDE_REDUCE, reduce_bytes, 0.0,
                         k_wide_reduce<false><<<(bins + kReduceKeys - 1) / kReduceKeys, kWideBlock, kWideReduceLds, st>>>(
                             s.part16, s.occupied, wide_blocks, s.wide, bins, 0, 0.0f, 0.0f, counts, s.mm_part, nparts,
                             pair_part, s.ticket, g.n_sampled, res));
