@@ -100,7 +100,7 @@ extern "C" int edgc_create(edgc_ctx** out, int hip_device, uint32_t max_bins, ui
     const size_t at_mm = place(2 * kMaxReduceBlocks * sizeof(float));
     const size_t at_copies = place(8 * kCopyBins * sizeof(uint32_t));
     const size_t at_counts = place(static_cast<size_t>(max_bins) * sizeof(unsigned long long));
-    s.part16_blocks = static_cast<uint32_t>(std::min(ctx->num_cu, 1024));
+    s.part16_blocks = std::min(static_cast<uint32_t>(ctx->num_cu), kMaxPart16Blocks);
     const size_t at_occupied = place(static_cast<size_t>(s.part16_blocks) * 8 * sizeof(uint32_t));
     const size_t at_result = place(sizeof(edgc_entropy_result));
     const size_t at_gram = place(static_cast<size_t>(36) * 256 * sizeof(double));

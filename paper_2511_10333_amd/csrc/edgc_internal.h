@@ -19,7 +19,7 @@ struct Scratch {
     unsigned int*       ticket       = nullptr;  // [kTicketWords] last-block ticket, zero between calls
     uint32_t*           copies       = nullptr;  // [8][kCopyBins] histogram counters, a set per XCD
     uint16_t*           part16       = nullptr;  // [part16_blocks][65536] 16-bit counters per block
-    uint32_t            part16_blocks = 0;       // at most 1024: k_wide_reduce looks at one block's marks per thread
+    uint32_t            part16_blocks = 0;       // at most kMaxPart16Blocks
     uint32_t*           occupied     = nullptr;  // [part16_blocks][8] which of a block's fields were stored, a bit per 256 keys
     unsigned long long* wide         = nullptr;  // [65536] 64-bit credits per key, zero between calls
     unsigned long long* counts       = nullptr;  // [max_bins] histogram when the caller gives none
@@ -36,6 +36,7 @@ struct Scratch {
 };
 
 constexpr int kMaxReduceBlocks = 4096;
+constexpr uint32_t kMaxPart16Blocks = 1024;
 constexpr uint32_t kTicketWords = 64;      // the last-block ticket, on a cache line of its own
 constexpr uint32_t kCopyBins = 16384;      // largest histogram that is accumulated in one set of counters per XCD
 

@@ -1058,6 +1058,8 @@ __global__ __launch_bounds__(kWideBlock) void k_wide_hist(
 // 33 MB of fields read and the patterns binned by the last block alone 86.0 us, marked fields only 80.4, binned by every block
 // and k_wide_hist's short sweep 73.8; 10 M fp32 elements on 65536 bins (range kernel included) 43.7 us, marked fields only 35.5.
 constexpr uint32_t kReduceGroups = kWideBlock / (kReduceKeys / 8);        // 32 groups of 32 threads
+static_assert(kMaxPart16Blocks <= kWideBlock && kMaxPart16Blocks * 65535ull < (1ull << 32),
+              "k_wide_reduce: a thread looks at one block's marks, and a key's fields are summed in 32 bits");
 constexpr size_t kWideReduceLds = (kReduceGroups + 4) * kReduceKeys * sizeof(uint32_t);
 
 template <bool PATTERN>
@@ -1093,7 +1095,7 @@ __global__ __launch_bounds__(kWideBlock) void k_wide_reduce(
         const uint32_t col = threadIdx.x & 31u, grp = threadIdx.x >> 5;
         const uint4* __restrict__ src = reinterpret_cast<const uint4*>(part16 + blockIdx.x * kReduceKeys) + col;
         constexpr size_t kRow = kWideKeys / 8;                             // 16-byte items per block's fields
-        uint32_t sm[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};                 // at most 256 fields of 16 bits
+        uint32_t sm[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};                 // of at most 32 fields; 1024 per key: below 2^26
         for (uint32_t b = grp; b < nfrom; b += 8 * kReduceGroups) {
             uint4 v[8];
 #pragma unroll
