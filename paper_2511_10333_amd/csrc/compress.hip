@@ -2405,6 +2405,9 @@ int CopyList::flush(hipStream_t st)
 // inputs, cached / streamed: deferred, hidden-2048 fp32 block (201 MB) 253 / 236 us, hidden-3584 shard (154 MB) 214 / 200,
 // hidden-1536 (113 MB) 200 / 195, two hidden-768 blocks (57 MB) 109 / 112; stored, 50257 x 1024 (206 MB) 334 / 339,
 // hidden-2048 at rank 64 (201 MB) 356 / 364, hidden-4096 fp32 block (805 MB) 1221 / 1186.
+// Rows that are not whole cache lines take the same line: the Q-pass alone loses there (8191 x 4097 fp32, deferred, 28 us through the
+// caches, 38 past them), but the pass gains from 128 MB on (fp32 at rank 13, through / past: 103 MB 165.0 / 166.7 us, 128 MB 207.7 /
+// 204.2, 194 MB 281.3 / 274.1, 412 MB 624.7 / 610.7; bf16 103 MB 177.7 / 170.6, 132 MB 173.0 / 172.8, 194 MB 243.9 / 235.4).
 // The P-pass reads the residual with ordinary loads in every case (non-temporal ones: hidden-2048 246 against 236 us,
 // the shard 210 against 200, 50257 x 1024 349 against 339, hidden-4096 1197 against 1186).
 static uint32_t group_streams(const edgc_ctx* ctx, const Group& g)

@@ -13,7 +13,7 @@
 // (1 % of a transformer block), k_minmax_small and k_hist_small.
 // What bounds them at a 1 % sample (0.01 to 0.5 M items): latency.  Both kernels, one after the other, for 2 M fp32
 // elements of four buffers on 4096 bins: 20.3 us (22.8 before they had kernels of their own); in the passes that they are a part
-// of: two hidden-768 bf16 blocks, 24 buffers, 100 -> 87 us per pass, hidden-2048 block 232 -> 228, hidden-5120 1173 -> 1164.
+// of: two hidden-768 bf16 blocks, 24 buffers, 100 -> 87 us per pass, hidden-2048 block 232 -> 228.
 // The chunk-strided sample is read with 16-byte loads whenever chunks are a
 // multiple of the vector width, so a wavefront touches whole cache lines.
 // Both kernels take a list of buffers (EntGroup): the estimate is over the union

@@ -29,11 +29,13 @@ import re
 import sys
 
 ALIASES = {"k_pass_p_deferred_full": "k_pass_p_deferred", "k_pass_p_deferred_narrow": "k_pass_p_deferred",
-           "k_decompress_full": "k_decompress", "k_pass_q_full": "k_pass_q"}
+           "k_decompress_full": "k_decompress", "k_pass_q_full": "k_pass_q",
+           "k_minmax_small": "k_minmax", "k_hist_small": "k_hist"}
 
 
 def bench_name(kernel: str) -> str:
     k = re.sub(r"^void\s+", "", kernel).replace("(anonymous namespace)::", "")
+    k = re.sub(r"\((?:edgc::)?Caching\)(\d)", lambda e: ("past", "through", "by_tensor")[int(e[1])], k)   # an enumerator
     k = re.sub(r"\(.*$", "", k)
     full = k.replace("edgc::", "")
     base = re.sub(r"<.*$", "", full)
@@ -183,7 +185,8 @@ def cmd_cells(a) -> int:
     out.extend(["```\n",
                 "`ms`: one whole estimate, from a pair of events around back-to-back estimates.  `reads`: how often the "
                 "estimate's kernels read the sample.  Kernel columns: microseconds per launch from a second pass with every "
-                "launch between its own events.\n",
+                "launch between its own events (`k_minmax` and `k_hist` stand for their one-round forms `k_minmax_small` and "
+                "`k_hist_small` too).\n",
                 "| dtype | stride | bins | sampled | ms | reads | sample GB/s | buffer GB/s | kernels (us) |",
                 "|---|---|---|---|---|---|---|---|---|"])
     for c in d["cells"]:
