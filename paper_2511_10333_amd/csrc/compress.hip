@@ -1346,7 +1346,7 @@ __global__ __launch_bounds__(256) void k_reduce_q(const Group grp, uint32_t RP, 
 // M^ itself (k_pass_p_deferred).  Without DEFER a null `out` leaves the reconstruction unwritten
 // (E_new alone: the deferred subtraction carried out after all).
 // ---------------------------------------------------------------------------
-template <int NP, int RT, bool DEFER, bool PAST>
+template <int NP, int RT, bool DEFER, bool PAST, bool LOOP>
 __device__ __forceinline__ void decompress_block(const Group& grp, const TensorArgs& ta)
 {
     const float* __restrict__ P = ta.P;
@@ -1549,10 +1549,7 @@ __device__ __forceinline__ void decompress_block(const Group& grp, const TensorA
     // (the two D register sets swap roles)
     // (fp32 above rank 64: the second copy of the loop costs the two registers that let two waves
     // share a SIMD, 128 instead of 103 us on the hidden-4096 layer: left out there)
-    // stored form through the caches: small groups, which two waves per SIMD serve better than the loop whose second copy
-    // takes the registers of one of them (D is in the last-level cache; with it / without: 2047 x 2049 bf16 at rank 64 18.8 / 14.0 us,
-    // fp32 at rank 13 16.7 / 13.4, 5000 x 1002 bf16 19.8 / 14.6, hidden-500 bf16 block 12.2 / 9.3)
-    constexpr bool FAST = !(NP == 2 && RT == 4) && (DEFER || PAST);
+    constexpr bool FAST = !(NP == 2 && RT == 4) && LOOP;
     const uint32_t whole_end = (FAST && rows_full) ? min(st_end, n / 64) : 0;
     uint32_t st = st_begin;
     if (FAST && whole_end > st_begin + 2) {
@@ -1579,8 +1576,8 @@ template <int NP, int RT, bool DEFER, Caching C>
 __global__ __launch_bounds__(256, (DEFER && C == Caching::by_tensor) ? 2 : 1) void k_decompress(const Group grp)
 {
     const TensorArgs& ta = tensor_of(grp, blockIdx.x);
-    if (C == Caching::past || (C == Caching::by_tensor && ta.past != 0)) decompress_block<NP, RT, DEFER, true>(grp, ta);
-    else decompress_block<NP, RT, DEFER, false>(grp, ta);
+    if (C == Caching::past || (C == Caching::by_tensor && ta.past != 0)) decompress_block<NP, RT, DEFER, true, true>(grp, ta);
+    else decompress_block<NP, RT, DEFER, false, DEFER && C != Caching::small>(grp, ta);
 }
 
 // ---------------------------------------------------------------------------
@@ -1597,7 +1594,7 @@ __global__ __launch_bounds__(256, (DEFER && C == Caching::by_tensor) ? 2 : 1) vo
 // (B operand of M^) and [rank][column] (B operand of D Q); D goes through a wave-private LDS
 // tile to become the A operand.
 // ---------------------------------------------------------------------------
-template <int NP, int RT, bool PAST>
+template <int NP, int RT, bool PAST, bool LOOP>
 __device__ __forceinline__ void pass_p_deferred_block(const Group& grp, const TensorArgs& ta)
 {
     // Two blocks share a CU and each keeps one stage of G and D_prev in flight.  Above rank 64
@@ -1905,7 +1902,7 @@ __device__ __forceinline__ void pass_p_deferred_block(const Group& grp, const Te
 
     // stages [0, n_fast) are full and followed by a full stage.  (fp32 at ranks 33 to 64 has no
     // registers to spare for the second copy of the loop: it spills there and gets slower.)
-    constexpr bool FAST = !(NP == 2 && RT == 2);
+    constexpr bool FAST = !(NP == 2 && RT == 2) && LOOP;
     const uint32_t n_whole = (FAST && rows_full && !e_zero) ? (k_end - k_begin) / 64 : 0;
     const uint32_t n_fast = n_whole > 1 ? n_whole - 1 : 0;
     uint32_t st = 0;
@@ -1941,8 +1938,8 @@ template <int NP, int RT, Caching C>
 __global__ __launch_bounds__(256, 2) void k_pass_p_deferred(const Group grp)
 {
     const TensorArgs& ta = tensor_of(grp, blockIdx.x);
-    if (C == Caching::past || (C == Caching::by_tensor && ta.past != 0)) pass_p_deferred_block<NP, RT, true>(grp, ta);
-    else pass_p_deferred_block<NP, RT, false>(grp, ta);
+    if (C == Caching::past || (C == Caching::by_tensor && ta.past != 0)) pass_p_deferred_block<NP, RT, true, true>(grp, ta);
+    else pass_p_deferred_block<NP, RT, false, C != Caching::small>(grp, ta);
 }
 
 // ---------------------------------------------------------------------------
@@ -2324,6 +2321,7 @@ static hipError_t allow_lds_pass_p_deferred()
     constexpr int lds = static_cast<int>(deferred_lds<NP, RT>());
     const void* const kernels[] = {reinterpret_cast<const void*>(&k_pass_p_deferred<NP, RT, Caching::past>),
                                    reinterpret_cast<const void*>(&k_pass_p_deferred<NP, RT, Caching::through>),
+                                   reinterpret_cast<const void*>(&k_pass_p_deferred<NP, RT, Caching::small>),
                                    reinterpret_cast<const void*>(&k_pass_p_deferred<NP, RT, Caching::by_tensor>)};
     for (const void* k : kernels) {
         const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -2504,9 +2502,10 @@ static int run_pass_p(edgc_ctx* ctx, Group& g, const TensorScratch* cap, bool wi
         } else {
             constexpr size_t lds = deferred_lds<NP, RT>();
             ProfScope prof_scope_(ctx, st, KID_PASS_P_DEFERRED, bytes, fl);
-            switch (group_caching(n_past, g.count)) {
+            switch (group_caching(n_past, g.count, d_bytes)) {
             case Caching::past: k_pass_p_deferred<NP, RT, Caching::past><<<blocks, 256, lds, st>>>(g); break;
             case Caching::through: k_pass_p_deferred<NP, RT, Caching::through><<<blocks, 256, lds, st>>>(g); break;
+            case Caching::small: k_pass_p_deferred<NP, RT, Caching::small><<<blocks, 256, lds, st>>>(g); break;
             default: k_pass_p_deferred<NP, RT, Caching::by_tensor><<<blocks, 256, lds, st>>>(g); break;
             }
         }
@@ -2869,9 +2868,12 @@ static int decompress_impl(edgc_ctx* ctx, Group& g, hipStream_t st)
     ProfScope prof_scope_(ctx, st, KID_DECOMPRESS, bytes, flops);
     auto launch = [&](auto defer_tag) {
         constexpr bool DEFER = decltype(defer_tag)::value;
-        switch (group_caching(n_past, g.count)) {
+        switch (group_caching(n_past, g.count, static_cast<double>(d_bytes))) {
         case Caching::past: k_decompress<NP, RT, DEFER, Caching::past><<<blocks, 256, lds, st>>>(g); break;
-        case Caching::through: k_decompress<NP, RT, DEFER, Caching::through><<<blocks, 256, lds, st>>>(g); break;
+        case Caching::through:                                     // (stored: never, through the caches only where small)
+            if constexpr (DEFER) k_decompress<NP, RT, DEFER, Caching::through><<<blocks, 256, lds, st>>>(g);
+            break;
+        case Caching::small: k_decompress<NP, RT, DEFER, Caching::small><<<blocks, 256, lds, st>>>(g); break;
         default: k_decompress<NP, RT, DEFER, Caching::by_tensor><<<blocks, 256, lds, st>>>(g); break;
         }
     };

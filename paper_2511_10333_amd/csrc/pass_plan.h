@@ -86,10 +86,18 @@ inline uint32_t decompress_step(uint32_t stages, uint32_t splits, bool as_asked)
 // One form for a whole mixed group, that of the worst tensor, costs the other tensors.  Per pass, past for all / through for all /
 // each its own: hidden-4096 fp32 block with a 2056 x 1028 matrix beside it, rank 64, deferred 975 / 1043 / 972 us, bf16 786 / 824 /
 // 776; hidden-2048 with 2048 x 2054, rank 32, fp32 291 / 305 / 287, bf16 stored 307 / 303 / 293.
-enum class Caching { past, through, by_tensor };
-inline Caching group_caching(uint32_t n_past, uint32_t count)
+// Small groups through the caches take kernels without the loop whose loads can be counted: they are bound by latencies, and its second
+// copy costs code, registers and, in the stored decompress, one of two waves per SIMD.  Per pass with / without it: 501 x 501 bf16 at
+// rank 64 61.5 / 58.7 us, 2047 x 2049 (16 MB) 89.5 / 85.7 and stored 94.9 / 90.0, 3002 x 3002 (34 MB) 101.2 / 96.6, 3300 x 3302 (42 MB) 1.5 % less,
+// hidden-1000 block (46 MB) 1 % more, hidden-1200 (66 MB) 5 % more, hidden-2056 fp32 5 % more; the stored decompress alone 2047 x 2049
+// 18.8 / 14.0, 5000 x 1002 19.8 / 14.6, hidden-500 block 12.2 / 9.3.
+enum class Caching { past, through, by_tensor, small };
+constexpr double kSmallGroup = 40.0 * 1024 * 1024;                       // bytes of D
+inline Caching group_caching(uint32_t n_past, uint32_t count, double d_bytes)
 {
-    return n_past == count ? Caching::past : n_past == 0 ? Caching::through : Caching::by_tensor;
+    if (n_past == count) return Caching::past;
+    if (n_past) return Caching::by_tensor;
+    return d_bytes <= kSmallGroup ? Caching::small : Caching::through;
 }
 
 // Whether the P-pass reads a gradient past the caches whose rows are not whole lines of them.  Through them, the two stages that

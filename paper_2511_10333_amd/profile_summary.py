@@ -35,7 +35,7 @@ ALIASES = {"k_pass_p_deferred_full": "k_pass_p_deferred", "k_pass_p_deferred_nar
 
 def bench_name(kernel: str) -> str:
     k = re.sub(r"^void\s+", "", kernel).replace("(anonymous namespace)::", "")
-    k = re.sub(r"\((?:edgc::)?Caching\)(\d)", lambda e: ("past", "through", "by_tensor")[int(e[1])], k)   # an enumerator
+    k = re.sub(r"\((?:edgc::)?Caching\)(\d)", lambda e: ("past", "through", "by_tensor", "small")[int(e[1])], k)   # an enumerator
     k = re.sub(r"\(.*$", "", k)
     full = k.replace("edgc::", "")
     base = re.sub(r"<.*$", "", full)

@@ -137,8 +137,10 @@ int main()
                 edgc::whole_lines(at(4096 + 64), 128), edgc::whole_lines(at(128), 1u << 30));
     for (uint32_t count = 1; count <= 16; ++count)
         for (uint32_t past = 0; past <= count; ++past)
-            if (edgc::group_caching(past, count) != (past == 0 ? Caching::through : past == count ? Caching::past : Caching::by_tensor))
-                return 1;
+            for (double mb : {1.0, 40.0, 40.1})
+                if (edgc::group_caching(past, count, mb * 1048576.0) !=
+                    (past == count ? Caching::past : past ? Caching::by_tensor : mb <= 40.0 ? Caching::small : Caching::through))
+                    return 1;
 }
 """
 
