@@ -950,8 +950,8 @@ __device__ __forceinline__ void small_factor(const double* W, double* Rs, double
 
 // ---------------------------------------------------------------------------
 // P^ = P R^-1 on fp64 MFMA (64 rows per block, 16 per wave), fp32 result in place,
-// and the bf16 operand copy Pt[plane][c][i] (i contiguous, rows padded to a
-// multiple of 64) that the Q-pass reads as MFMA B-fragments.
+// and the bf16 operand copy, rows padded to a multiple of 64, in the order in which the
+// Q-pass reads it as MFMA B-fragments (pt_unit).
 // FACTOR: every block sums the Gram tiles (`nb` sets, in the order of k_gram_sum) and factors them itself: a launch of
 // k_chol for one block per matrix costs more than the chain of one or two diagonal tiles (1.7 us each).  Per pass,
 // k_chol / this: 1024 x 1024 at rank 4 50 / 47 us, two hidden-768 blocks at rank 16 114 / 110, three odd matrices at rank 13
@@ -960,12 +960,12 @@ __device__ __forceinline__ void small_factor(const double* W, double* Rs, double
 // the same, 131072 x 128 (2048) 152 / 155, eight 100000 x 96 (12500, 64 sets each) 533 / 605.
 // ---------------------------------------------------------------------------
 template <int T16, int NP, int WAVES, bool FACTOR>
-__global__ __launch_bounds__(64 * WAVES) void k_apply(const Group grp, uint32_t RP)
+__global__ __launch_bounds__(64 * WAVES) void k_apply(const Group grp)
 {
     const TensorArgs& ta = tensor_of(grp, blockIdx.x);
     float* __restrict__ P = ta.P;
     const double* __restrict__ rinv = ta.rinv;
-    __bf16* __restrict__ pt = static_cast<__bf16*>(ta.pt);
+    bf16x8* __restrict__ pt = static_cast<bf16x8*>(ta.pt);
     const uint32_t ldp = ta.ldp, m = ta.m, r = grp.r, m_pad = ta.m_pad;
     constexpr int CW = 16 * T16;
     constexpr int LD = CW + 4;             // floats; 16 rows x 4 columns per read: 2-way at worst
@@ -1082,20 +1082,20 @@ __global__ __launch_bounds__(64 * WAVES) void k_apply(const Group grp, uint32_t 
             }
         }
     }
-    // transposed operand copy: 8 consecutive rows of one column per 16-byte store (the copy's rows are
-    // padded to a multiple of 64, which a block of more rows may reach past)
-    constexpr uint32_t SEG = ROWS / 8;
-    for (uint32_t idx = tid; idx < RP * SEG; idx += NTH) {
-        const uint32_t cc = idx / SEG, q = idx % SEG;
-        if (row0 + 8 * q >= m_pad) continue;
+    // operand copy in fragment order (pt_unit): a half wave stores 32 columns of the same eight rows, 512 bytes (the copy's rows
+    // are padded to a multiple of 64, which a block of more rows may reach past)
+    constexpr int RT = T16 <= 2 ? 1 : T16 / 2;
+    for (uint32_t idx = tid; idx < RT * 4 * ROWS; idx += NTH) {
+        const uint32_t unit = idx & 63u, ct = (idx >> 6) % RT, q16 = (idx >> 6) / RT;
+        const uint32_t row = 16 * q16 + 8 * (unit >> 5), cc = 32 * ct + (unit & 31u);
+        if (row0 + row >= m_pad) continue;
         bf16x8 w[NP];
         float v8[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v8[e] = (cc < static_cast<uint32_t>(CW)) ? Ps[(8 * q + e) * LD + cc] : 0.0f;
+        for (int e = 0; e < 8; ++e) v8[e] = (cc < static_cast<uint32_t>(CW)) ? Ps[(row + e) * LD + cc] : 0.0f;
         pack8<NP>(v8, w);
 #pragma unroll
-        for (int p = 0; p < NP; ++p)
-            *reinterpret_cast<bf16x8*>(pt + (static_cast<size_t>(p) * RP + cc) * m_pad + row0 + 8 * q) = w[p];
+        for (int p = 0; p < NP; ++p) pt[pt_unit<NP, RT>(row0 / 16 + q16, ct, p, unit)] = w[p];
     }
 }
 
@@ -1105,7 +1105,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_apply(const Group grp, uint32_t 
 // of the block's 128*NT-column strip.  Lane (jl, g) loads rows 8g..8g+7 of a
 // 16-row step at columns NT*jl..NT*jl+NT-1: these are MFMA A-fragments
 // (M = column, K = row) as they stand, so D is never transposed.  The P^
-// operand comes from the transposed bf16 copy through a double-buffered LDS
+// operand comes from the bf16 copy in fragment order through a double-buffered LDS
 // tile shared by the four waves (one barrier per stage).
 // ---------------------------------------------------------------------------
 template <int NT, bool FULL, bool STREAM>
@@ -1143,16 +1143,14 @@ __global__ __launch_bounds__(256, (NP == 2 && RT == 4) ? 2 : 1) void k_pass_q(co
 {
     const TensorArgs& ta = tensor_of(grp, blockIdx.x);
     const float* __restrict__ D = ta.E;
-    const __bf16* __restrict__ pt = static_cast<const __bf16*>(ta.pt);
+    const bf16x8* __restrict__ pt = static_cast<const bf16x8*>(ta.pt);
     float* __restrict__ part = ta.part;
     const uint32_t m_pad = ta.m_pad, m = ta.m, n = ta.n, stages_per_split = ta.d0, CB = ta.d1;
     constexpr int RP = RT * 32;
-    constexpr int ROWB = NP * 128 + 16;              // LDS bytes per factor column: 64 rows x NP planes + pad
-    constexpr int TILE = RP * ROWB;
     constexpr int W = 32 * NT;
-    constexpr int NSEG = RP * NP * 8;                // 16-byte segments of one P^ tile
+    constexpr int NSEG = RP * NP * 8;                // 16-byte units of one P^ tile: the fragments of 64 rows, in their order
     constexpr int PS = (NSEG + 255) / 256;
-    extern __shared__ __attribute__((aligned(16))) unsigned char qlds[];   // 2 tiles
+    extern __shared__ bf16x8 qlds[];                 // 2 tiles
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int jl = lane & 31, g = lane >> 5;
@@ -1177,21 +1175,14 @@ __global__ __launch_bounds__(256, (NP == 2 && RT == 4) ? 2 : 1) void k_pass_q(co
 #pragma unroll
         for (int p = 0; p < PS; ++p) {
             const int it = tid + p * 256;
-            if (it < NSEG) {
-                const int sg = it % 8, cp = it / 8, c = cp % RP, pl = cp / RP;
-                seg[p] = *reinterpret_cast<const bf16x8*>(
-                    pt + (static_cast<size_t>(pl) * RP + c) * m_pad + st * 64 + sg * 8);
-            }
+            if (it < NSEG) seg[p] = pt[static_cast<size_t>(st) * NSEG + it];
         }
     };
     auto store_pt = [&](int buf) {
 #pragma unroll
         for (int p = 0; p < PS; ++p) {
             const int it = tid + p * 256;
-            if (it < NSEG) {
-                const int sg = it % 8, cp = it / 8, c = cp % RP, pl = cp / RP;
-                *reinterpret_cast<bf16x8*>(qlds + buf * TILE + c * ROWB + pl * 128 + sg * 16) = seg[p];
-            }
+            if (it < NSEG) qlds[buf * NSEG + it] = seg[p];
         }
     };
 
@@ -1203,7 +1194,7 @@ __global__ __launch_bounds__(256, (NP == 2 && RT == 4) ? 2 : 1) void k_pass_q(co
         if (st + 1 < st_end) fetch_pt(st + 1);
         const uint32_t i0 = st * 64;
         const bool full = cols_full && (i0 + 64 <= m);
-        const unsigned char* tile = qlds + buf * TILE;
+        const bf16x8* tile = qlds + buf * NSEG;
         // The stage's D loads are issued at once (the other waves of the SIMD compute meanwhile);
         // fp32 above rank 64 issues them in two halves: with all 64 registers of a stage in
         // flight the kernel is 12 registers over what lets two waves share a SIMD.
@@ -1237,7 +1228,7 @@ __global__ __launch_bounds__(256, (NP == 2 && RT == 4) ? 2 : 1) void k_pass_q(co
                     bf16x8 b[NP];
 #pragma unroll
                     for (int p = 0; p < NP; ++p)
-                        b[p] = *reinterpret_cast<const bf16x8*>(tile + (ct * 32 + jl) * ROWB + p * 128 + u * 32 + g * 16);
+                        b[p] = tile[pt_unit<NP, RT>(u, ct, p, lane)];
 #pragma unroll
                     for (int t = 0; t < NT; ++t) acc[ct][t] = mma<NP>(a[t], b, acc[ct][t]);
                 }
@@ -2302,14 +2293,6 @@ size_t compress_part_elems(uint64_t max_rows, uint64_t max_cols, uint32_t max_ra
 
 // Kernels that may need more than 64 KiB of dynamic LDS get the limit raised once, at context
 // creation, so that hot calls make no attribute calls.
-template <int NP, int RT, int NT>
-static hipError_t allow_lds_pass_q()
-{
-    constexpr int lds = 2 * RT * 32 * (NP * 128 + 16);
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pass_q<NP, RT, NT>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-}
-
 template <int NP, int RT>
 static constexpr size_t deferred_lds()
 {
@@ -2341,9 +2324,6 @@ int prepare_compress_kernels(edgc_ctx* ctx)
     constexpr int chol_max = (128 * (128 + kCholPad) + 8 * 16 * 17 + 128 + 16) * 8 + (8 + 36) * 4;
     EDGC_HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(&k_chol),
                                           hipFuncAttributeMaxDynamicSharedMemorySize, chol_max));
-    EDGC_HIP_TRY(ctx, (allow_lds_pass_q<1, 4, 2>()));
-    EDGC_HIP_TRY(ctx, (allow_lds_pass_q<2, 4, 2>()));
-    EDGC_HIP_TRY(ctx, (allow_lds_pass_q<2, 2, 2>()));
     EDGC_HIP_TRY(ctx, (allow_lds_pass_p_deferred<2, 2>()));
     EDGC_HIP_TRY(ctx, prepare_pass_p_full());
     EDGC_HIP_TRY(ctx, prepare_decompress_full());
@@ -2638,20 +2618,20 @@ static int run_orthonormalise(edgc_ctx* ctx, Group& g, const TensorScratch* cap,
         ProfScope prof_scope_(ctx, st, KID_APPLY, bytes, flops);
         switch (t16) {
         case 1:
-            if (factor) k_apply<1, NP, 4, true><<<blocks, 256, 0, st>>>(g, RP);
-            else k_apply<1, NP, 4, false><<<blocks, 256, 0, st>>>(g, RP);
+            if (factor) k_apply<1, NP, 4, true><<<blocks, 256, 0, st>>>(g);
+            else k_apply<1, NP, 4, false><<<blocks, 256, 0, st>>>(g);
             break;
         case 2:
-            if (factor) k_apply<2, NP, 4, true><<<blocks, 256, 0, st>>>(g, RP);
-            else k_apply<2, NP, 4, false><<<blocks, 256, 0, st>>>(g, RP);
+            if (factor) k_apply<2, NP, 4, true><<<blocks, 256, 0, st>>>(g);
+            else k_apply<2, NP, 4, false><<<blocks, 256, 0, st>>>(g);
             break;
-        case 4: k_apply<4, NP, 4, false><<<blocks, 256, 0, st>>>(g, RP); break;
+        case 4: k_apply<4, NP, 4, false><<<blocks, 256, 0, st>>>(g); break;
         default:
             switch (apply_waves) {
-            case 4: k_apply<8, NP, 4, false><<<blocks, 256, 0, st>>>(g, RP); break;
-            case 9: k_apply<8, NP, 9, false><<<blocks, 576, 0, st>>>(g, RP); break;
-            case 10: k_apply<8, NP, 10, false><<<blocks, 640, 0, st>>>(g, RP); break;
-            default: k_apply<8, NP, 8, false><<<blocks, 512, 0, st>>>(g, RP); break;
+            case 4: k_apply<8, NP, 4, false><<<blocks, 256, 0, st>>>(g); break;
+            case 9: k_apply<8, NP, 9, false><<<blocks, 576, 0, st>>>(g); break;
+            case 10: k_apply<8, NP, 10, false><<<blocks, 640, 0, st>>>(g); break;
+            default: k_apply<8, NP, 8, false><<<blocks, 512, 0, st>>>(g); break;
             }
             break;
         }
@@ -2667,7 +2647,8 @@ template <int NP, int RT, int NT>
 static int run_pass_q(edgc_ctx* ctx, Group& g, const TensorScratch* cap, hipStream_t st)
 {
     constexpr uint32_t RP = RT * 32;
-    constexpr size_t lds = static_cast<size_t>(2) * RP * (NP * 128 + 16);
+    constexpr size_t lds = static_cast<size_t>(2) * RP * NP * 128;
+    static_assert(lds <= 64 * 1024, "fits the default dynamic LDS limit");
     constexpr edgc_dtype DT = (NP == 1) ? EDGC_BF16 : EDGC_F32;
     // whole-tile groups: the pipelined kernel (pass_q_full.hip), 4 or 8 waves of 64 columns per block
     // (measured per launch, general kernel / 4 waves / 8 waves: hidden-5120 bf16 block at rank 128: 144 / 142 /

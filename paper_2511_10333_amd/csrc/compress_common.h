@@ -83,6 +83,17 @@ __device__ __forceinline__ f32x16 mma(const bf16x8 (&a)[NP], const bf16x8 (&b)[N
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[0], acc, 0, 0, 0);
 }
 
+// Where the bf16 operand copy of P^ holds eight rows of one factor column (one 16-byte unit): in the order of the Q-pass's
+// B-fragments, 16 rows x 32 columns each, so that a wave's lanes (unit = lane: 8 (lane / 32) rows on, column lane % 32) store and
+// load a fragment as 1 KB in a row, and the fragments of a 64-row stage are one contiguous tile.  Per pass, as
+// [plane][column][row] (16-byte stores apart, LDS reads eight rows apart in k_apply) / in this order: hidden-5120 bf16 block at
+// rank 128 1163 / 1145 us, two hidden-768 bf16 blocks at rank 16 87.7 / 86.0.
+template <int NP, int RT>
+__device__ __forceinline__ size_t pt_unit(uint32_t row16, uint32_t ct, uint32_t plane, uint32_t unit)
+{
+    return ((static_cast<size_t>(row16) * RT + ct) * NP + plane) * 64 + unit;
+}
+
 // Tensor of a grouped launch that owns block `bid` (tensors with no blocks are skipped).
 // Blocks keep the order of the grid: consecutive blocks, which the dispatcher spreads
 // round-robin over the 8 XCDs, walk along the rows of the matrix, so that neighbouring

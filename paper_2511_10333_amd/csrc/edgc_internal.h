@@ -31,7 +31,7 @@ struct Scratch {
     size_t  gram_part_elems = 0;
     double* gram      = nullptr;   // [rank_pad*rank_pad]
     double* rinv      = nullptr;   // rinv_elems(max_rank): upper-triangle tiles of R^-1
-    void*   pt        = nullptr;   // operand copy of P^ transposed: [planes][rank_pad][rows_pad] bf16
+    void*   pt        = nullptr;   // bf16 operand copy of P^: planes * rank_pad * rows_pad elements
     size_t  pt_bytes  = 0;
 };
 
@@ -73,7 +73,7 @@ struct TensorArgs {
     double* gram_part;      // per-block upper-triangle Gram tiles
     double* gram;           // summed Gram tiles
     double* rinv;           // inverse factor R^-1: upper-triangle 16x16 tiles, row-major over (tk <= tc)
-    void*   pt;             // transposed bf16 copy of P^: [planes][rank_pad][m_pad]
+    void*   pt;             // bf16 operand copy of P^, rows padded to m_pad, in fragment order (pt_unit)
     const double* tiles;    // what k_chol reads: gram_part (nb sets) or gram (one set)
     uint64_t ldg, ldo;
     uint32_t ldq, ldp, m, n, m_pad;

@@ -13,26 +13,24 @@
 namespace edgc {
 
 template <int NP, int RT>
-constexpr size_t pass_q_full_lds() { return static_cast<size_t>(2) * RT * 32 * (NP * 128 + 16); }
+constexpr size_t pass_q_full_lds() { return static_cast<size_t>(2) * RT * 32 * NP * 128; }
 
 template <int NP, int RT, bool STREAM, int WAVES>
 __global__ __launch_bounds__(64 * WAVES, 2) void k_pass_q_full(const Group grp)
 {
     const TensorArgs& ta = tensor_of(grp, blockIdx.x);
     const float* __restrict__ D = ta.E;
-    const __bf16* __restrict__ pt = static_cast<const __bf16*>(ta.pt);
+    const bf16x8* __restrict__ pt = static_cast<const bf16x8*>(ta.pt);
     float* __restrict__ part = ta.part;
     const uint32_t m_pad = ta.m_pad, n = ta.n, stages_per_split = ta.d0, CB = ta.d1;
     constexpr int NT = 2;                            // columns per lane
     constexpr int RP = RT * 32;
-    constexpr int ROWB = NP * 128 + 16;              // LDS bytes per factor column: 64 rows x NP planes + pad
-    constexpr int TILE = RP * ROWB;
     constexpr int W = 32 * NT;
-    constexpr int NSEG = RP * NP * 8;                // 16-byte segments of one P^ tile
+    constexpr int NSEG = RP * NP * 8;                // 16-byte units of one P^ tile: the fragments of 64 rows, in their order
     constexpr int NTH = 64 * WAVES;
     static_assert(NSEG % NTH == 0, "the P^ tile divides evenly among the threads");
     constexpr int PS = NSEG / NTH;
-    extern __shared__ __attribute__((aligned(16))) unsigned char qlds[];   // 2 tiles
+    extern __shared__ bf16x8 qlds[];                 // 2 tiles
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -59,20 +57,12 @@ __global__ __launch_bounds__(64 * WAVES, 2) void k_pass_q_full(const Group grp)
 
 #define EDGC_QFULL_FETCH_PT(ST)                                                                           \
     {                                                                                                     \
-        _Pragma("unroll") for (int p = 0; p < PS; ++p) {                                                  \
-            const int it = tid + p * NTH;                                                                 \
-            const int sg = it % 8, cp = it / 8, c = cp % RP, pl = cp / RP;                                \
-            seg[p] = *reinterpret_cast<const bf16x8*>(                                                    \
-                pt + (static_cast<size_t>(pl) * RP + c) * m_pad + (ST) * 64 + sg * 8);                    \
-        }                                                                                                 \
+        _Pragma("unroll") for (int p = 0; p < PS; ++p)                                                    \
+            seg[p] = pt[static_cast<size_t>(ST) * NSEG + tid + p * NTH];                                  \
     }
 #define EDGC_QFULL_STORE_PT(BUF)                                                                          \
     {                                                                                                     \
-        _Pragma("unroll") for (int p = 0; p < PS; ++p) {                                                  \
-            const int it = tid + p * NTH;                                                                 \
-            const int sg = it % 8, cp = it / 8, c = cp % RP, pl = cp / RP;                                \
-            *reinterpret_cast<bf16x8*>(qlds + (BUF) * TILE + c * ROWB + pl * 128 + sg * 16) = seg[p];     \
-        }                                                                                                 \
+        _Pragma("unroll") for (int p = 0; p < PS; ++p) qlds[(BUF) * NSEG + tid + p * NTH] = seg[p];       \
     }
     // the 16-row steps U0 and U0 + 1 of stage ST: rows 8g + q of each step, two adjacent columns
 #define EDGC_QFULL_FETCH_D(ST, U0)                                                                        \
@@ -106,7 +96,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void k_pass_q_full(const Group grp)
             _Pragma("unroll") for (int ct = 0; ct < RT; ++ct) {                                           \
                 bf16x8 b[NP];                                                                             \
                 _Pragma("unroll") for (int p = 0; p < NP; ++p)                                            \
-                    b[p] = *reinterpret_cast<const bf16x8*>(tile + (ct * 32 + jl) * ROWB + p * 128 + (2 * (H) + uu) * 32 + g * 16); \
+                    b[p] = tile[pt_unit<NP, RT>(2 * (H) + uu, ct, p, lane)];                              \
                 _Pragma("unroll") for (int t = 0; t < NT; ++t) acc[ct][t] = mma<NP>(a[uu][t], b, acc[ct][t]); \
             }                                                                                             \
         }                                                                                                 \
@@ -116,7 +106,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void k_pass_q_full(const Group grp)
         EDGC_QFULL_STORE_PT(buf)                                                                          \
         __syncthreads(); /* tile `buf` is complete; every wave is past its reads of stage ST-2 */         \
         if constexpr (MORE) EDGC_QFULL_FETCH_PT((ST) + 1)                                                 \
-        const unsigned char* tile = qlds + buf * TILE;                                                    \
+        const bf16x8* tile = qlds + buf * NSEG;                                                           \
         EDGC_QFULL_HALF(ST, MORE, 0)                                                                      \
         EDGC_QFULL_HALF(ST, MORE, 1)                                                                      \
         buf ^= 1;                                                                                         \
