@@ -2653,22 +2653,31 @@ static int run_pass_q(edgc_ctx* ctx, Group& g, const TensorScratch* cap, hipStre
     // whole-tile groups: the pipelined kernel (pass_q_full.hip), 4 or 8 waves of 64 columns per block
     // (measured per launch, general kernel / 4 waves / 8 waves: hidden-5120 bf16 block at rank 128: 144 / 142 /
     // 132 us, at rank 64: 128 / 134 / 124, at rank 32: 128 / 132 / -; hidden-4096 fp32 block at rank 64:
-    // 96 / 86 / 90; hidden-2048 fp32 block at rank 16: 21.4 / 20.5 / -)
+    // 96 / 86 / 90)
     uint32_t qwaves = 0;
     if (NT == 2 && ctx->tune_qfull != 0) {
         const uint32_t want = ctx->tune_qfull > 0 ? (ctx->tune_qfull == 8 ? 8u : 4u)
                                                   : (NP == 1 ? (RT >= 2 ? 8u : 0u) : 4u);
         if (want && pass_q_full_applies(g, DT, RT, want)) qwaves = want;
     }
-    const uint32_t W4 = (qwaves ? qwaves : 4u) * 32 * NT;
     // launches that read a gigabyte or more (a 32-tensor stage: 16 tensors share the blocks, most of them left
     // with one row split) aim at three blocks per CU: 594 against 649 us
     uint64_t d_bytes = 0;
     for (uint32_t i = 0; i < g.count; ++i) d_bytes += 4ull * g.t[i].m * g.t[i].n;
-    // one block per CU where D is small and the partials of more row splits weigh: 4096 x 4096 fp32 at rank 32 (two
-    // iterations) 202 against 210 us, three odd matrices of 14 M elements 125 against 127, hidden-2048 block (201 MB) 237
-    // against 232
-    const uint32_t per_cu = ctx->tune_q ? ctx->tune_q
+    // Up to rank 64, and while the last-level cache can hold D, waves by themselves (pass_q_direct.hip); `groups`: column groups of
+    // 64 per block of it.  One, four waves on the rows; two where rows are not whole lines and a wave's strips share lines.
+    uint32_t groups = 0;
+    if constexpr (RT <= 2) {
+        bool lines = true;
+        for (uint32_t i = 0; i < g.count; ++i) lines = lines && whole_lines(g.t[i].E, 4ull * g.t[i].n);
+        groups = ctx->tune_qdirect >= 0 ? static_cast<uint32_t>(ctx->tune_qdirect) : q_direct_groups(static_cast<double>(d_bytes), RP, lines);
+        if (groups) qwaves = 0;
+    }
+    const uint32_t W4 = groups ? 64u * groups : (qwaves ? qwaves : 4u) * 32 * NT;
+    const uint32_t turn = groups ? 4u / groups : 1u;   // stages that a block's waves take side by side
+    // the other kernels: one block per CU where D is small and the partials of more row splits weigh (rank 100, one / two: 4096 x 4096
+    // fp32 180 / 192 us, hidden-768 block bf16 131 / 136)
+    const uint32_t per_cu = ctx->tune_q ? ctx->tune_q : groups ? q_direct_per_cu(groups, RP)
                           : ((qwaves == 8 || d_bytes <= (80ull << 20)) ? 1u : (d_bytes >= (1ull << 30) ? 3u : 2u));
     const uint32_t target = static_cast<uint32_t>(ctx->num_cu) * per_cu;
     uint32_t tgt[kMaxGroup];
@@ -2678,11 +2687,12 @@ static int run_pass_q(edgc_ctx* ctx, Group& g, const TensorScratch* cap, hipStre
     for (uint32_t i = 0; i < g.count; ++i) {
         TensorArgs& t = g.t[i];
         const uint32_t CB = cdiv(t.n, W4), stages = t.m_pad / 64;
-        uint32_t S = std::max(1u, std::min(stages, tgt[i] / CB));
+        uint32_t S = std::max(1u, std::min(cdiv(stages, turn), tgt[i] / CB));
+        if (groups && !ctx->tune_q) S = q_direct_splits(S, per_cu);
         const uint64_t lim = cap[i].part_elems / (static_cast<uint64_t>(t.n) * RP);
         if (lim == 0) return fail(ctx, EDGC_EINVAL, "partial-factor scratch too small for this shape");
         S = static_cast<uint32_t>(std::min<uint64_t>(S, lim));
-        const uint32_t sps = cdiv(stages, S);
+        const uint32_t sps = cdiv(cdiv(stages, S), turn) * turn;
         S = cdiv(stages, sps);
         t.d0 = sps;
         t.d1 = CB;
@@ -2692,7 +2702,10 @@ static int run_pass_q(edgc_ctx* ctx, Group& g, const TensorScratch* cap, hipStre
         bytes += 4.0 * t.m * t.n;
         flops += 2.0 * t.m * t.n * g.r;
     }
-    if (qwaves) {
+    if (groups) {
+        ProfScope prof_scope_(ctx, st, KID_PASS_Q, bytes, flops);
+        EDGC_HIP_TRY(ctx, launch_pass_q_direct(g, DT, RT, blocks, groups, st));
+    } else if (qwaves) {
         ProfScope prof_scope_(ctx, st, KID_PASS_Q, bytes, flops);
         EDGC_HIP_TRY(ctx, launch_pass_q_full(g, DT, RT, blocks, qwaves, st));
     } else {

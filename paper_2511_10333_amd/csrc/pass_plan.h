@@ -69,6 +69,29 @@ inline uint32_t pass_p_step(uint32_t count, const uint32_t* across, const uint32
     return step;
 }
 
+// The Q-pass of waves by themselves (pass_q_direct.hip), up to rank 64.  Column groups per block, 0 where the other kernels stay:
+// that is a D that the last-level cache cannot hold, where every form waits for HBM (per pass without an estimate, others / this:
+// hidden-4096 fp32 block at rank 16 824 / 824 to 831 us, stored at rank 64 1157 / 1159 to 1168, hidden-3001 bf16 783 / 800, the Q-pass of
+// hidden-5120 bf16 at rank 64 238 / 243; stored hidden-2304 (255 MB) at rank 64 58 / 65), while hidden-2048 (201 MB) takes 215 / 209
+// and stored in bf16 236 / 228.  Two groups where rows are not whole lines and strips of one group would share them: three odd fp32
+// matrices at rank 13 99.0 / 96.3 with one / 94.5 with two; above rank 32 the sums of two weigh more: 8191 x 4097 bf16 at rank 64 252 /
+// 251 / 257, 2047 x 2049 89.8 / 87.4 / 89.9.
+inline uint32_t q_direct_groups(double d_bytes, uint32_t rp, bool lines)
+{
+    if (d_bytes > 224.0 * 1024 * 1024) return 0;
+    return lines || rp > 32 ? 1 : 2;
+}
+// Blocks (of four waves) per CU.  Two / three / four: 4096 x 4096 fp32 at rank 32, two iterations, 150.9 / 152.0 / 149.8, two hidden-768
+// bf16 blocks 65.8 / 65.7 / 64.9, hidden-2048 fp32 214.2 / 210.9 / 209.4; above rank 32 three waves per SIMD have no registers: 3072 x
+// 3072 bf16 at rank 64 96.2 / 98.0 / 97.8; two groups: three odd matrices 94.5 / 94.4 / 97.3.
+inline uint32_t q_direct_per_cu(uint32_t groups, uint32_t rp) { return groups == 1 && rp <= 32 ? 4 : 2; }
+// ... but beyond 32 row splits no more than two per CU are worth their partials (tall matrices of few columns): 50257 x 1024 bf16 at
+// rank 32 280.6 / 282.3 / 285.3, 50257 x 768 fp32 220.9 / 222.9 / 225.2, 100000 x 96 bf16 87.6 / 87.4 / 92.2, 16384 x 1024 92.3 / 92.4 / 93.9.
+inline uint32_t q_direct_splits(uint32_t splits, uint32_t per_cu)
+{
+    return per_cu > 2 && splits > 32 ? std::max(32u, splits * 2 / per_cu) : splits;
+}
+
 // Stages (of 64 columns) per block of the decompress.  `splits`: into how many its share of the blocks aimed at would cut the
 // tensor; `as_asked`: the whole-tile kernel, or a count of blocks per CU that was asked for.
 // Otherwise at most eight stages: many rounds of short blocks keep every CU busy to the end.  Stored form, per pass: hidden-4096

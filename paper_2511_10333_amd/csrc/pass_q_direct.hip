@@ -1,0 +1,163 @@
+// Q-pass  Q_partial[s] = D[row range s, :]^T P^[row range s, :]  (Sec. II-B: the second product of the PowerSGD step)
+// up to rank 64, any shape: every wave by itself.  A lane's loads of D are A-fragments as they stand, as in k_pass_q
+// (compress.hip); the B-fragments of P^ come straight from memory, where k_apply has laid them out in the order of a wave's
+// lanes (pt_unit): 1 KB loads that the XCD's L2 serves, no LDS tile and no barrier in the loop.  The waves of a block take
+// the stages of its row range in turn (WR of them to a column group of 64, WC groups) and add their sums up in LDS at the end,
+// in wave order, so that a block of four waves writes one partial where four blocks would write four.
+// What bounds it: the last-level cache for a D of some size (a read of it without arithmetic: 64 MB 13.6 us between events),
+// launch and latency for a small one.  k_pass_q and k_pass_q_full keep one to two waves per SIMD in step by a barrier
+// per stage.  Between events, these / this, D just written: 4096 x 4096 fp32 at rank 32 22.8 / 15.9 us, hidden-2048 fp32 block at
+// rank 16 39.1 / 34.5, hidden-3584 bf16, one of four shards, at rank 64 32.9 / 30.0; the sums of the partials 5.3 / 3.6 and less.
+#include "compress_common.h"
+#include "pass_plan.h"
+
+namespace edgc {
+
+template <int NP, int RT, bool STREAM, int WR, int WC>
+__global__ __launch_bounds__(64 * WR * WC, 2) void k_pass_q_direct(const Group grp)
+{
+    const TensorArgs& ta = tensor_of(grp, blockIdx.x);
+    const float* __restrict__ D = ta.E;
+    const bf16x8* __restrict__ pt = static_cast<const bf16x8*>(ta.pt);
+    float* __restrict__ part = ta.part;
+    const uint32_t m = ta.m, n = ta.n, sps = ta.d0, CB = ta.d1;
+    constexpr int RP = RT * 32;
+    __shared__ __attribute__((aligned(16))) float sums[WR * WC * 64 * 32];      // [column group][wave][column][factor column]
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wr = wave % WR, wc = wave / WR;
+    const int jl = lane & 31, g = lane >> 5;
+    const uint32_t lid = blockIdx.x - ta.first;
+    const uint32_t s = lid / CB, cb = lid % CB;
+    const uint32_t jw0 = (cb * WC + wc) * 64u;                       // first column of this wave
+    const uint32_t st_end = min((m + 63u) / 64u, (s + 1u) * sps);
+    const uint32_t whole = min(st_end, m / 64u);                     // the stages before it have all their 64 rows
+    // Columns jw0 + 2jl and + 1.  Past the last column a lane reads the last pair of the row again (n >= 2), and where the last
+    // column is the first of a pair its value is the second of that one: what does not exist is not written below, and
+    // a column's sums depend on that column alone.
+    const uint32_t col = min(jw0 + 2u * jl, n - 2u);
+    const bool odd_last = jw0 + 2u * jl == n - 1u;
+    const uint32_t off = 8u * g * n + col;                           // element offset in a 16-row step (n < 2^28: fits 32 bits)
+
+    f32x16 acc[RT][2];
+#pragma unroll
+    for (int ct = 0; ct < RT; ++ct)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[ct][t][v] = 0.0f;
+    float dv[4][8][2];
+
+    // the 16-row steps U0 and U0 + 1 of stage ST: rows 8g + q of each step
+#define EDGC_QDIRECT_FETCH_D(ST, U0)                                                                      \
+    _Pragma("unroll") for (int uu = 0; uu < 2; ++uu) {                                                    \
+        _Pragma("unroll") for (int q = 0; q < 8; ++q) {                                                   \
+            const float* p_ = D + static_cast<uint64_t>((ST) * 64 + 16 * ((U0) + uu) + q) * n + off;       \
+            const Floats2 x = load_pair<STREAM>(p_);                                                      \
+            dv[(U0) + uu][q][0] = x.x; dv[(U0) + uu][q][1] = x.y;                                         \
+        }                                                                                                 \
+    }
+    // half H of stage ST: to fragments; the same half of this wave's next stage is requested into the registers; multiplied
+#define EDGC_QDIRECT_HALF(ST, MORE, H)                                                                    \
+    {                                                                                                     \
+        bf16x8 b[2][RT][NP];                                                                              \
+        _Pragma("unroll") for (int uu = 0; uu < 2; ++uu)                                                  \
+            _Pragma("unroll") for (int ct = 0; ct < RT; ++ct)                                             \
+                _Pragma("unroll") for (int p = 0; p < NP; ++p)                                            \
+                    b[uu][ct][p] = pt[pt_unit<NP, RT>((ST) * 4 + 2 * (H) + uu, ct, p, lane)];             \
+        bf16x8 a[2][2][NP];                                                                               \
+        _Pragma("unroll") for (int uu = 0; uu < 2; ++uu) {                                                \
+            _Pragma("unroll") for (int t = 0; t < 2; ++t) {                                               \
+                float col8[8];                                                                            \
+                _Pragma("unroll") for (int q = 0; q < 8; ++q)                                             \
+                    col8[q] = (t == 0 && odd_last) ? dv[2 * (H) + uu][q][1] : dv[2 * (H) + uu][q][t];     \
+                pack8<NP>(col8, a[uu][t]);                                                                \
+            }                                                                                             \
+        }                                                                                                 \
+        if constexpr (MORE) EDGC_QDIRECT_FETCH_D((ST) + WR, 2 * (H))                                      \
+        _Pragma("unroll") for (int uu = 0; uu < 2; ++uu)                                                  \
+            _Pragma("unroll") for (int ct = 0; ct < RT; ++ct)                                             \
+                _Pragma("unroll") for (int t = 0; t < 2; ++t) acc[ct][t] = mma<NP>(a[uu][t], b[uu][ct], acc[ct][t]); \
+    }
+
+    uint32_t st = s * sps + wr;
+    if (jw0 < n && st < st_end) {
+        if (st < whole) {
+            EDGC_QDIRECT_FETCH_D(st, 0)
+            EDGC_QDIRECT_FETCH_D(st, 2)
+            for (; st + WR < whole; st += WR) {
+                EDGC_QDIRECT_HALF(st, true, 0)
+                EDGC_QDIRECT_HALF(st, true, 1)
+            }
+            EDGC_QDIRECT_HALF(st, false, 0)
+            EDGC_QDIRECT_HALF(st, false, 1)
+            st += WR;
+        }
+        if (st < st_end) {                                           // the last rows; those past them as zeros
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    const uint32_t row = st * 64u + 16u * u + 8u * g + q;
+                    const Floats2 x = load_pair<STREAM>(D + static_cast<uint64_t>(min(row, m - 1u)) * n + col);
+                    dv[u][q][0] = row < m ? x.x : 0.0f;
+                    dv[u][q][1] = row < m ? x.y : 0.0f;
+                }
+            EDGC_QDIRECT_HALF(st, false, 0)
+            EDGC_QDIRECT_HALF(st, false, 1)
+        }
+    }
+#undef EDGC_QDIRECT_HALF
+#undef EDGC_QDIRECT_FETCH_D
+
+    // accumulator (ct, t, v) of lane l: column j = jw0 + 2 rho + t with rho = 8*(v/4) + 4*g + v%4, factor column
+    // c = ct*32 + jl  ->  part[s][j][c], 32 factor columns at a time through LDS
+    constexpr int ITEMS = WC * 64 * 8, NTH = 64 * WR * WC;           // of four factor columns
+    float4* const s4 = reinterpret_cast<float4*>(sums);
+#pragma unroll
+    for (int ct = 0; ct < RT; ++ct) {
+        if (ct) __syncthreads();                                     // the sums before are read
+        float* mine = sums + (wc * WR + wr) * 64 * 32;
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) mine[(2 * (8 * (v / 4) + 4 * g + v % 4) + t) * 32 + jl] = acc[ct][t][v];
+        __syncthreads();
+#pragma unroll
+        for (int i0 = 0; i0 < ITEMS; i0 += NTH) {
+            static_assert(ITEMS % NTH == 0, "the items divide evenly among the threads");
+            const int i = i0 + tid, c = i / (64 * 8), e = i % (64 * 8);
+            float4 x = s4[c * WR * 64 * 8 + e];
+#pragma unroll
+            for (int w = 1; w < WR; ++w) {
+                const float4 y = s4[(c * WR + w) * 64 * 8 + e];
+                x.x += y.x; x.y += y.y; x.z += y.z; x.w += y.w;
+            }
+            const uint32_t j = (cb * WC + c) * 64u + e / 8;
+            if (j < n) *reinterpret_cast<float4*>(part + (static_cast<size_t>(s) * n + j) * RP + ct * 32 + e % 8 * 4) = x;
+        }
+    }
+}
+
+template <int NP, int RT, int WR, int WC>
+static hipError_t launch_qdirect(const Group& g, uint32_t blocks, hipStream_t st)
+{
+    if (g.stream) k_pass_q_direct<NP, RT, true, WR, WC><<<blocks, 64 * WR * WC, 0, st>>>(g);
+    else k_pass_q_direct<NP, RT, false, WR, WC><<<blocks, 64 * WR * WC, 0, st>>>(g);
+    return hipGetLastError();
+}
+
+template <int WR, int WC>
+static hipError_t launch_qdirect_w(const Group& g, edgc_dtype dt, int rt, uint32_t blocks, hipStream_t st)
+{
+    if (dt == EDGC_BF16) return rt == 1 ? launch_qdirect<1, 1, WR, WC>(g, blocks, st) : launch_qdirect<1, 2, WR, WC>(g, blocks, st);
+    return rt == 1 ? launch_qdirect<2, 1, WR, WC>(g, blocks, st) : launch_qdirect<2, 2, WR, WC>(g, blocks, st);
+}
+
+hipError_t launch_pass_q_direct(const Group& g, edgc_dtype dt, int rt, uint32_t blocks, uint32_t column_groups, hipStream_t st)
+{
+    return column_groups == 1 ? launch_qdirect_w<4, 1>(g, dt, rt, blocks, st) : launch_qdirect_w<2, 2>(g, dt, rt, blocks, st);
+}
+
+}  // namespace edgc

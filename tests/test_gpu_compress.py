@@ -438,3 +438,32 @@ def test_sums_of_many_partials_in_few_columns(m, n, r):
     want = D.double().t() @ p
     assert float((q - want).norm(dim=0).max() / D.double().norm()) < 2.0 ** -16
     c.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("m,n,r", [(64, 64, 8), (40, 33, 3), (33, 65, 32), (65, 127, 16), (257, 1001, 20), (1000, 66, 33), (4100, 70, 64),
+                                   (515, 4160, 40), (256, 128, 1), (321, 130, 64), (9000, 40, 5)])
+def test_q_pass_of_waves_by_themselves(m, n, r, dtype, monkeypatch):
+    """k_pass_q_direct, with one column group per block and with two, against k_pass_q: edges of stages and strips, rows at odd
+    addresses, fewer rows than a block's waves take.  The products are the same and exact in fp32; what differs is the order of
+    at most 3 m additions a value."""
+    g = torch.Generator(device="cuda").manual_seed(m * n + r)
+    G = torch.randn(m, n, device="cuda", generator=g)
+    G = G.to(torch.bfloat16) if dtype == "bf16" else G
+    Q0 = torch.zeros(n, (r + 3) // 4 * 4, device="cuda")
+    Q0[:, :r] = torch.randn(n, r, device="cuda", generator=g)
+    out = {}
+    for form in ("0", "1", "2"):
+        monkeypatch.setenv("EDGC_TUNE_QDIRECT", form)
+        c = edgc.Context(0, max_bins=256, max_rank=64, max_rows=9000, max_cols=5000)
+        D, P, Q = torch.zeros(m, n, device="cuda"), torch.zeros(m, Q0.shape[1], device="cuda"), Q0.clone()
+        c.compress(G, D, True, Q, P, r)
+        torch.cuda.synchronize()
+        c.close()
+        out[form] = (D, P, Q)
+    D, P, Q = out["0"]
+    bound = 2 * 3 * m * 2.0 ** -23 * (1 + 2.0 ** -7) * (D.double().abs().t() @ P.double().abs())
+    for form in ("1", "2"):
+        assert torch.equal(out[form][0], D) and torch.equal(out[form][1], P)
+        assert bool(((out[form][2].double() - Q.double()).abs() <= bound).all())
+        assert not out[form][2][:, r:].any()
