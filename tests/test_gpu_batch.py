@@ -509,3 +509,12 @@ def test_batched_step_replays_from_a_hip_graph(deferred):
             assert torch.equal(a.grad_out, b.grad_out), step
             if a.residual is not None:
                 assert torch.equal(a.residual, b.residual) and torch.equal(a.Q, b.Q) and torch.equal(a.P, b.P), step
+
+
+def test_calls_without_a_stream_use_torchs_current_one():
+    from paper_2511_10333_amd.binding import _stream_handle
+    assert _stream_handle(None) == torch.cuda.current_stream().cuda_stream
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        assert _stream_handle(None) == side.cuda_stream
+    assert _stream_handle(side) == side.cuda_stream and _stream_handle(None) == torch.cuda.current_stream().cuda_stream
