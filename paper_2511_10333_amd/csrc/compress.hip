@@ -1326,6 +1326,60 @@ __global__ __launch_bounds__(256) void k_reduce_q(const Group grp, uint32_t RP, 
 }
 
 // ---------------------------------------------------------------------------
+// Copies of the tensors that are sent as they stand (decompress hands the gradient on), all of them at the head of
+// k_decompress's grid: a transformer stage has a dozen norm weights and biases of some kilobytes each, and a launch
+// costs more than any of them (16 of them in the stage of two hidden-768 blocks: 16 launches 37 to 60 us, one 5; the pass
+// 82.7 us with one, 77.1 in k_decompress).  k_copy_rows where there is no such launch.  A unit is the widest
+// access that the tensor's pointers, row length and strides allow; a contiguous tensor may end inside a unit.
+template <typename U>
+__device__ __forceinline__ void copy_units(const unsigned char* __restrict__ src, unsigned char* __restrict__ dst,
+                                           uint64_t row_bytes, uint64_t ld_src, uint64_t ld_dst, uint32_t m, uint64_t first,
+                                           uint64_t stride)
+{
+    constexpr int N = kCopyUnits / 256;
+    const uint64_t whole = row_bytes / sizeof(U), total = whole * m;      // units
+    // what the last unit of a contiguous tensor leaves: 16-bit pieces, one per thread of its first block
+    const uint64_t at = whole * sizeof(U) + 2u * threadIdx.x;
+    if (first == 0 && m == 1 && at < row_bytes)
+        *reinterpret_cast<uint16_t*>(dst + at) = *reinterpret_cast<const uint16_t*>(src + at);
+    for (; first < total; first += stride) {
+        U v[N] = {};
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            const uint64_t i = first + threadIdx.x + k * 256u, row = m == 1 ? 0 : i / whole;
+            if (i < total) v[k] = *reinterpret_cast<const U*>(src + row * ld_src + (i - row * whole) * sizeof(U));
+        }
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            const uint64_t i = first + threadIdx.x + k * 256u, row = m == 1 ? 0 : i / whole;
+            if (i < total) *reinterpret_cast<U*>(dst + row * ld_dst + (i - row * whole) * sizeof(U)) = v[k];
+        }
+    }
+}
+
+// block `bid` of a list's copies
+__device__ __forceinline__ void copy_block(const CopyGroup& grp, uint32_t bid)
+{
+    static_assert(offsetof(CopyGroup, t) / 64 == (offsetof(CopyGroup, t) + sizeof(CopyArgs) - 1) / 64, "the first copy's line");
+    const uint64_t first_copy = reinterpret_cast<uint64_t>(grp.t[0].src);      // as in tensor_of
+    uint32_t t = 0;
+#pragma unroll
+    for (uint32_t i = 1; i < kMaxCopies; ++i) t += (bid >= grp.first[i]) ? 1u : 0u;
+    asm volatile("" :: "s"(first_copy));
+    const CopyArgs& c = grp.t[t];
+    const uint64_t first = static_cast<uint64_t>(bid - c.first) * kCopyUnits;
+    const uint64_t stride = static_cast<uint64_t>(c.blocks) * kCopyUnits;
+    switch (c.unit) {
+    case 16: copy_units<uint4>(c.src, c.dst, c.row_bytes, c.ld_src, c.ld_dst, c.m, first, stride); break;
+    case 8: copy_units<uint2>(c.src, c.dst, c.row_bytes, c.ld_src, c.ld_dst, c.m, first, stride); break;
+    case 4: copy_units<uint32_t>(c.src, c.dst, c.row_bytes, c.ld_src, c.ld_dst, c.m, first, stride); break;
+    default: copy_units<uint16_t>(c.src, c.dst, c.row_bytes, c.ld_src, c.ld_dst, c.m, first, stride); break;
+    }
+}
+
+__global__ __launch_bounds__(256) void k_copy_rows(const CopyGroup grp) { copy_block(grp, blockIdx.x); }
+
+// ---------------------------------------------------------------------------
 // Decompress:  M^ = P^ Q^T -> grad_out,  E_new = D - M^ (as transmitted), in place.
 // Block: 4 waves x 32 rows; the wave's P^ rows stay in registers as A-fragments;
 // Q rows of a 64-column stage go through LDS, row 2*jl + ct of the stage at LDS
@@ -1564,9 +1618,10 @@ __device__ __forceinline__ void decompress_block(const Group& grp, const TensorA
 
 // (two waves per SIMD: the form with both bodies would take 262 registers at rank 128)
 template <int NP, int RT, bool DEFER, Caching C>
-__global__ __launch_bounds__(256, (DEFER && C == Caching::by_tensor) ? 2 : 1) void k_decompress(const Group grp)
+__global__ __launch_bounds__(256, (DEFER && C == Caching::by_tensor) ? 2 : 1) void k_decompress(const Group grp, const CopyGroup copies)
 {
     const TensorArgs& ta = tensor_of(grp, blockIdx.x);
+    if (blockIdx.x < grp.first[0]) { copy_block(copies, blockIdx.x); return; }
     if (C == Caching::past || (C == Caching::by_tensor && ta.past != 0)) decompress_block<NP, RT, DEFER, true, true>(grp, ta);
     else decompress_block<NP, RT, DEFER, false, DEFER && C != Caching::small>(grp, ta);
 }
@@ -2225,55 +2280,6 @@ __global__ __launch_bounds__(256, 2) void k_pass_p_deferred_narrow(const Group g
         }
 }
 
-// Copies of the tensors that are sent as they stand (decompress hands the gradient on), all of them in one launch: a
-// transformer stage has a dozen norm weights and biases of some kilobytes each, and a launch costs more than any of
-// them (16 of them in the stage of two hidden-768 blocks: 16 launches 37 to 60 us, one 5).  A unit is the widest
-// access that the tensor's pointers, row length and strides allow; a contiguous tensor may end inside a unit.
-template <typename U>
-__device__ __forceinline__ void copy_units(const unsigned char* __restrict__ src, unsigned char* __restrict__ dst,
-                                           uint64_t row_bytes, uint64_t ld_src, uint64_t ld_dst, uint32_t m, uint64_t first,
-                                           uint64_t stride)
-{
-    constexpr int N = kCopyUnits / 256;
-    const uint64_t whole = row_bytes / sizeof(U), total = whole * m;      // units
-    // what the last unit of a contiguous tensor leaves: 16-bit pieces, one per thread of its first block
-    const uint64_t at = whole * sizeof(U) + 2u * threadIdx.x;
-    if (first == 0 && m == 1 && at < row_bytes)
-        *reinterpret_cast<uint16_t*>(dst + at) = *reinterpret_cast<const uint16_t*>(src + at);
-    for (; first < total; first += stride) {
-        U v[N] = {};
-#pragma unroll
-        for (int k = 0; k < N; ++k) {
-            const uint64_t i = first + threadIdx.x + k * 256u, row = m == 1 ? 0 : i / whole;
-            if (i < total) v[k] = *reinterpret_cast<const U*>(src + row * ld_src + (i - row * whole) * sizeof(U));
-        }
-#pragma unroll
-        for (int k = 0; k < N; ++k) {
-            const uint64_t i = first + threadIdx.x + k * 256u, row = m == 1 ? 0 : i / whole;
-            if (i < total) *reinterpret_cast<U*>(dst + row * ld_dst + (i - row * whole) * sizeof(U)) = v[k];
-        }
-    }
-}
-
-__global__ __launch_bounds__(256) void k_copy_rows(const CopyGroup grp)
-{
-    static_assert(offsetof(CopyGroup, t) / 64 == (offsetof(CopyGroup, t) + sizeof(CopyArgs) - 1) / 64, "the first copy's line");
-    const uint64_t first_copy = reinterpret_cast<uint64_t>(grp.t[0].src);      // as in tensor_of
-    uint32_t t = 0;
-#pragma unroll
-    for (uint32_t i = 1; i < kMaxCopies; ++i) t += (blockIdx.x >= grp.first[i]) ? 1u : 0u;
-    asm volatile("" :: "s"(first_copy));
-    const CopyArgs& c = grp.t[t];
-    const uint64_t first = static_cast<uint64_t>(blockIdx.x - c.first) * kCopyUnits;
-    const uint64_t stride = static_cast<uint64_t>(c.blocks) * kCopyUnits;
-    switch (c.unit) {
-    case 16: copy_units<uint4>(c.src, c.dst, c.row_bytes, c.ld_src, c.ld_dst, c.m, first, stride); break;
-    case 8: copy_units<uint2>(c.src, c.dst, c.row_bytes, c.ld_src, c.ld_dst, c.m, first, stride); break;
-    case 4: copy_units<uint32_t>(c.src, c.dst, c.row_bytes, c.ld_src, c.ld_dst, c.m, first, stride); break;
-    default: copy_units<uint16_t>(c.src, c.dst, c.row_bytes, c.ld_src, c.ld_dst, c.m, first, stride); break;
-    }
-}
-
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
@@ -2803,7 +2809,7 @@ int launch_compress(edgc_ctx* ctx, Group& g, const TensorScratch* cap, edgc_dtyp
 }
 
 template <int NP, int RT>
-static int decompress_impl(edgc_ctx* ctx, Group& g, hipStream_t st)
+static int decompress_impl(edgc_ctx* ctx, Group& g, CopyList& copies, hipStream_t st)
 {
     constexpr uint32_t RP = RT * 32;
     constexpr size_t lds = static_cast<size_t>(64) * (NP * RP * 2 + 16);
@@ -2836,7 +2842,9 @@ static int decompress_impl(edgc_ctx* ctx, Group& g, hipStream_t st)
     uint64_t d_bytes = 0;
     for (uint32_t i = 0; i < g.count; ++i) d_bytes += 4ull * g.t[i].m * g.t[i].n;
     const bool by_line = g.defer || d_bytes <= (28ull << 20);
-    uint32_t blocks = 0, n_past = 0;
+    if (use_full)
+        if (int rc = copies.flush(st)) return rc;
+    uint32_t blocks = copies.blocks, n_past = 0;       // the copies' blocks come first
     double bytes = 0.0, flops = 0.0;
     for (uint32_t i = 0; i < g.count; ++i) {
         TensorArgs& t = g.t[i];
@@ -2860,32 +2868,34 @@ static int decompress_impl(edgc_ctx* ctx, Group& g, hipStream_t st)
         return EDGC_OK;
     }
     ProfScope prof_scope_(ctx, st, KID_DECOMPRESS, bytes, flops);
+    std::fill(copies.g.first + copies.g.count, copies.g.first + kMaxCopies, ~0u);
     auto launch = [&](auto defer_tag) {
         constexpr bool DEFER = decltype(defer_tag)::value;
         switch (group_caching(n_past, g.count, static_cast<double>(d_bytes))) {
-        case Caching::past: k_decompress<NP, RT, DEFER, Caching::past><<<blocks, 256, lds, st>>>(g); break;
+        case Caching::past: k_decompress<NP, RT, DEFER, Caching::past><<<blocks, 256, lds, st>>>(g, copies.g); break;
         case Caching::through:                                     // (stored: never, through the caches only where small)
-            if constexpr (DEFER) k_decompress<NP, RT, DEFER, Caching::through><<<blocks, 256, lds, st>>>(g);
+            if constexpr (DEFER) k_decompress<NP, RT, DEFER, Caching::through><<<blocks, 256, lds, st>>>(g, copies.g);
             break;
-        case Caching::small: k_decompress<NP, RT, DEFER, Caching::small><<<blocks, 256, lds, st>>>(g); break;
-        default: k_decompress<NP, RT, DEFER, Caching::by_tensor><<<blocks, 256, lds, st>>>(g); break;
+        case Caching::small: k_decompress<NP, RT, DEFER, Caching::small><<<blocks, 256, lds, st>>>(g, copies.g); break;
+        default: k_decompress<NP, RT, DEFER, Caching::by_tensor><<<blocks, 256, lds, st>>>(g, copies.g); break;
         }
     };
     if (g.defer) launch(std::true_type{});
     else launch(std::false_type{});
+    copies.g.count = copies.blocks = 0;
     EDGC_HIP_TRY(ctx, hipGetLastError());
     return EDGC_OK;
 }
 
-int launch_decompress(edgc_ctx* ctx, Group& g, edgc_dtype dt, hipStream_t st)
+int launch_decompress(edgc_ctx* ctx, Group& g, CopyList& copies, edgc_dtype dt, hipStream_t st)
 {
     const int rt = rank_tiles(g.r);
     std::fill(g.first + g.count, g.first + kMaxGroup, ~0u);
 #define EDGC_DISPATCH(NP_)                                              \
     switch (rt) {                                                       \
-    case 1: return decompress_impl<NP_, 1>(ctx, g, st);                 \
-    case 2: return decompress_impl<NP_, 2>(ctx, g, st);                 \
-    default: return decompress_impl<NP_, 4>(ctx, g, st);                \
+    case 1: return decompress_impl<NP_, 1>(ctx, g, copies, st);                 \
+    case 2: return decompress_impl<NP_, 2>(ctx, g, copies, st);                 \
+    default: return decompress_impl<NP_, 4>(ctx, g, copies, st);                \
     }
     if (dt == EDGC_BF16) { EDGC_DISPATCH(1) }
     EDGC_DISPATCH(2)

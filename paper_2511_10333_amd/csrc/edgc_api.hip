@@ -410,7 +410,8 @@ int decompress_one(edgc_ctx* ctx, const float* P, uint32_t ldp, const float* Q, 
     TensorArgs& t = g.t[0];
     t.E = residual; t.Q = const_cast<float*>(Q); t.ldq = ldq; t.P = const_cast<float*>(P); t.ldp = ldp;
     t.out = grad_out; t.ldo = ld; t.m = m; t.n = n;
-    return launch_decompress(ctx, g, dtype, static_cast<hipStream_t>(hip_stream));
+    CopyList none{ctx};
+    return launch_decompress(ctx, g, none, dtype, static_cast<hipStream_t>(hip_stream));
 }
 
 }  // namespace
@@ -618,16 +619,16 @@ int decompress_batch_impl(edgc_ctx* ctx, const edgc_tensor* tensors, uint32_t co
     Group g{};
     g.r = r;
     g.defer = static_cast<uint32_t>(defer);
+    CopyList copies{ctx};
     auto flush = [&]() -> int {
-        if (g.count == 0) return EDGC_OK;
-        const int rc = launch_decompress(ctx, g, dtype, st);
+        if (g.count == 0) return copies.flush(st);
+        const int rc = launch_decompress(ctx, g, copies, dtype, st);
         g = Group{};
         g.r = r;
         g.defer = static_cast<uint32_t>(defer);
         return rc;
     };
     const uint32_t esz = dtype == EDGC_F32 ? 4 : 2;
-    CopyList copies{ctx};
     for (uint32_t i = 0; i < count; ++i) {
         const edgc_tensor& d = tensors[i];
         if (kind[i] == 1) {                      // sent as it stands: hand the gradient on
@@ -641,7 +642,6 @@ int decompress_batch_impl(edgc_ctx* ctx, const edgc_tensor* tensors, uint32_t co
         if (++g.count == kMaxGroup)
             if (int rc = flush()) return rc;
     }
-    if (int rc = copies.flush(st)) return rc;
     return flush();
 }
 

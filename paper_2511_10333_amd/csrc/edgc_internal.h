@@ -265,10 +265,9 @@ int launch_init_q(edgc_ctx* ctx, float* Q, uint32_t n, uint32_t ldq, uint32_t c0
 // phase 0: whole step; 1: up to P = D Q (not orthonormalised); 2: orthonormalise P as it stands, Q-pass
 int launch_compress(edgc_ctx* ctx, Group& g, const TensorScratch* cap, edgc_dtype dt,
                     uint32_t power_iters, hipStream_t st, int phase = 0);
-int launch_decompress(edgc_ctx* ctx, Group& g, edgc_dtype dt, hipStream_t st);
 
 // Copies of tensors that are sent as they stand, collected and launched together (compress.hip).
-constexpr uint32_t kMaxCopies = 32, kCopyUnits = 1024;      // tensors per launch; units that a block copies at a time
+constexpr uint32_t kMaxCopies = 16, kCopyUnits = 1024;      // tensors per launch; units that a block copies at a time
 // Blocks of 256 threads for one tensor: a launch takes fewer than 2^32 threads, so beyond 2^18 blocks each copies several runs.
 constexpr uint32_t copy_blocks(uint64_t units)
 {
@@ -294,6 +293,8 @@ struct CopyList {
             hipStream_t st);                // strides in elements
     int flush(hipStream_t st);
 };
+// `copies`: made by the same launch, or by one before it
+int launch_decompress(edgc_ctx* ctx, Group& g, CopyList& copies, edgc_dtype dt, hipStream_t st);
 int prepare_compress_kernels(edgc_ctx* ctx);
 int prepare_entropy_kernels(edgc_ctx* ctx);
 size_t compress_part_elems(uint64_t max_rows, uint64_t max_cols, uint32_t max_rank, int num_cu);

@@ -511,6 +511,41 @@ def test_batched_step_replays_from_a_hip_graph(deferred):
                 assert torch.equal(a.residual, b.residual) and torch.equal(a.Q, b.Q) and torch.equal(a.P, b.P), step
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("r,count,deferred", [(8, 1, False), (8, 16, True), (40, 17, False), (100, 5, True), (100, 33, False), (8, 0, True)])
+def test_copies_at_the_head_of_the_decompress(dtype, r, count, deferred):
+    """Tensors sent as they stand between compressed ones, fewer and more than one launch takes, before the general kernel and
+    (rank 100, deferred) the whole-tile one: every copy is the gradient, and the compressed ones get what they get without copies."""
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(count + r)
+    rand = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    ld = (r + 3) // 4 * 4
+
+    def matrix(m, n):
+        D, P, Q = rand(m, n), torch.zeros(m, ld, device="cuda"), torch.zeros(n, ld, device="cuda")
+        P[:, :r], Q[:, :r] = rand(m, r), rand(n, r)
+        return edgc.Tensor(None, torch.empty(m, n, device="cuda", dtype=tdt), D, Q, P)
+
+    def vector(i):
+        n, off = [1, 768, 3071, 16387][i % 4], [0, 1, 2, 8][i // 4 % 4]
+        src, dst = rand(n + off).to(tdt)[off:], torch.empty(n + off + 8, device="cuda", dtype=tdt)[off:off + n]
+        return edgc.Tensor(src, dst)
+
+    mats = [matrix(512, 640), matrix(768, 512)]
+    alone = [edgc.Tensor(None, torch.empty_like(t.grad_out), t.residual.clone(), t.Q, t.P) for t in mats]
+    vecs = [vector(i) for i in range(count)]
+    ts = vecs[:count // 2] + mats[:1] + vecs[count // 2:] + mats[1:]
+    c = edgc.Context(0, max_bins=16, max_rank=128, max_rows=64, max_cols=64)
+    for batch in (ts, alone):
+        c.reserve_batch([tuple(t.grad_out.shape) if t.grad_out.dim() == 2 else (1, t.grad_out.numel()) for t in batch])
+        c.decompress_batch(batch, r, deferred=deferred)
+    for t in vecs:
+        assert torch.equal(t.grad_out, t.grad)
+    for t, u in zip(mats, alone):
+        assert torch.equal(t.grad_out, u.grad_out) and torch.equal(t.residual, u.residual)
+    c.close()
+
+
 def test_calls_without_a_stream_use_torchs_current_one():
     from paper_2511_10333_amd.binding import _stream_handle
     assert _stream_handle(None) == torch.cuda.current_stream().cuda_stream
