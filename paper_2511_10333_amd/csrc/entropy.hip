@@ -12,8 +12,9 @@
 // or, where one block holds the sample in one round, k_estimate_one alone; where every block of a grid takes one round
 // (1 % of a transformer block), k_minmax_small and k_hist_small.
 // What bounds them at a 1 % sample (0.01 to 0.5 M items): latency.  Both kernels, one after the other, for 2 M fp32
-// elements of four buffers on 4096 bins: 20.3 us (22.8 before they had kernels of their own); in the passes that they are a part
-// of: two hidden-768 bf16 blocks, 24 buffers, 100 -> 87 us per pass, hidden-2048 block 232 -> 228.
+// elements of four buffers on 4096 bins: 15.8 us (22.8 before they had kernels of their own, 20.3 with a release per block and the
+// library's logarithms); clock stamps in the second: 1.4 us until the items are requested, 1.0 range, 1.4 bins, 2.3 until the
+// counters are added, 1.6 ticket, 2.2 the counters and their logarithms, 1.1 the block's sum and the result.
 // The chunk-strided sample is read with 16-byte loads whenever chunks are a
 // multiple of the vector width, so a wavefront touches whole cache lines.
 // Both kernels take a list of buffers (EntGroup): the estimate is over the union
@@ -419,17 +420,50 @@ __device__ __forceinline__ bool finite_f32(float x)
     return (__float_as_uint(x) & 0x7f800000u) != 0x7f800000u;
 }
 
-// log of a bin's width: what the differential entropy adds.  Formed before the sums are there (a lone wave's fp64 logarithm
-// takes some 0.3 us, its code from a cold cache included).
-__device__ __forceinline__ double log_bin_width(const RangeParams& rp, uint32_t bins)
+// The logarithms that do not depend on the bins: of the sample's size (less e0, see entropy_base), and of a bin's width (what the
+// differential entropy adds).  Formed by a wave that would otherwise wait.
+struct EstimateLogs {
+    double log2_n, log_w;
+};
+// All logarithms of an estimate are taken less this integer, the binary exponent of the sample's size:
+// H = (log2 n - e0) - (1/n) sum c (log2 c - e0), without the cancellation of log2 n.
+__device__ __forceinline__ int entropy_base(unsigned long long n_sampled) { return __builtin_amdgcn_frexp_exp(static_cast<double>(n_sampled)); }
+// log2 of a positive integer (some finite value for 0) less the integer e0, in fp64: x = 2^e m with m in [sqrt 1/2, sqrt 2), log2 m
+// from the series of artanh at s = (m - 1) / (m + 1), s^2 < 0.0295, to s^19 (what is left out is below 2^-56 of it).  Some 25 dependent
+// operations and short code, which the last block of a grid runs alone and from a cold cache: the library's function, one bin after
+// the other, was 3 to 4 of the 17 us that the histogram kernel of a 1 % sample took on 4096 bins.
+__device__ __forceinline__ double log2_count(double x, int e0)
+{
+    double m = __builtin_amdgcn_frexp_mant(x);                       // [1/2, 1)
+    int e = __builtin_amdgcn_frexp_exp(x);
+    if (m < 0.70710678118654752440) { m += m; e -= 1; }
+    const double f = m - 1.0, a = m + 1.0;
+    double y = __builtin_amdgcn_rcp(a);                              // an estimate; two Newton steps, and one on the quotient
+    y = fma(fma(-a, y, 1.0), y, y);
+    y = fma(fma(-a, y, 1.0), y, y);
+    double q = f * y;
+    q = fma(fma(-a, q, f), y, q);
+    const double z = q * q;
+    double p = 1.0 / 19.0;
+    p = fma(p, z, 1.0 / 17.0);
+    p = fma(p, z, 1.0 / 15.0);
+    p = fma(p, z, 1.0 / 13.0);
+    p = fma(p, z, 1.0 / 11.0);
+    p = fma(p, z, 1.0 / 9.0);
+    p = fma(p, z, 1.0 / 7.0);
+    p = fma(p, z, 1.0 / 5.0);
+    p = fma(p, z, 1.0 / 3.0);
+    return fma(fma(q * z, p, q), 2.88539008177792681472, static_cast<double>(e - e0));       // 2 / ln 2
+}
+__device__ __forceinline__ EstimateLogs estimate_logs(const RangeParams& rp, uint32_t bins, unsigned long long n_sampled)
 {
     const double w = static_cast<double>(rp.w);
-    return w > 0.0 ? log(w / static_cast<double>(bins)) : 0.0;
+    return {log2_count(static_cast<double>(n_sampled), entropy_base(n_sampled)), w > 0.0 ? log(w / static_cast<double>(bins)) : 0.0};
 }
 
-// The estimate from sum c log2 c (`acc`) and sum c (`tot`) over the bins, by one thread:
-// H = log2 n - (1/n) sum c log2 c in fp64, and the result record.  `log_w`: log_bin_width.
-__device__ __forceinline__ void emit_result(double acc, double tot, double log_w, const RangeParams& rp,
+// The estimate from sum c (log2 c - e0) (`acc`) and sum c (`tot`) over the bins, by one thread, in fp64, and the result record.  `res` may be the caller's pinned host memory: the end of the
+// kernel makes it visible.
+__device__ __forceinline__ void emit_result(double acc, double tot, const EstimateLogs& logs, const RangeParams& rp,
                                             unsigned long long n_sampled, edgc_entropy_result* res)
 {
     edgc_entropy_result r;
@@ -441,25 +475,37 @@ __device__ __forceinline__ void emit_result(double acc, double tot, double log_w
     r.n_nonfinite = n_sampled - static_cast<unsigned long long>(tot);
     r._pad = 0;
     if (tot > 0.0) {
-        double H = log2(tot) - acc / tot;
+        // (the product is rounded as a bin's is: with one bin only the difference is zero)
+        double H = (tot * (r.n_nonfinite == 0 ? logs.log2_n : log2_count(tot, entropy_base(n_sampled))) - acc) / tot;
         if (H < 0.0) H = 0.0;
         r.H_bits = H;
-        r.h_diff_nats = (rp.w > 0.0f) ? H * 0.69314718055994530942 + log_w : -INFINITY;
+        r.h_diff_nats = (rp.w > 0.0f) ? H * 0.69314718055994530942 + logs.log_w : -INFINITY;
         r.status = EDGC_OK;
     } else {
         r.H_bits = NAN; r.h_diff_nats = NAN;
         r.status = EDGC_ENONFINITE;
     }
     *res = r;
-    __threadfence_system();       // `res` may be the caller's pinned host memory
 }
 
-__device__ __forceinline__ void entropy_term(unsigned long long c, double& acc, double& tot)
+__device__ __forceinline__ void entropy_term(unsigned long long c, int e0, double& acc, double& tot)
 {
     if (c) {
         const double d = static_cast<double>(c);
-        acc += d * log2(d);
+        acc = fma(d, log2_count(d, e0), acc);
         tot += d;
+    }
+}
+// four bins at a time, their logarithms side by side; a wave passes over bins that hold nothing
+__device__ __forceinline__ void entropy_terms(const unsigned long long (&c)[4], int e0, double& acc, double& tot)
+{
+    if (c[0] | c[1] | c[2] | c[3]) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const double d = static_cast<double>(c[e]);
+            acc = fma(d, log2_count(d, e0), acc);
+            tot += d;
+        }
     }
 }
 
@@ -639,22 +685,24 @@ __device__ __forceinline__ RangeParams fold_range(const float2* __restrict__ par
     return make_range(lo, hi, fbins);
 }
 
-// True in every thread of the block that finishes last of the grid (the ticket is zero before and after).
-// Every wave waits for its own stores and atomics, then ONE thread makes them visible device-wide: an agent-scope
-// release writes this XCD's L2 back, and with one in every wave of every block these queue up behind each other (the
-// histogram kernel of a 1 % sample: 384 blocks 59 us, 48 blocks 27 us; with one per block 20 and 18).
-template <int BLOCK>
-__device__ __forceinline__ bool last_block(unsigned int* ticket)
+// True in every thread of the block that finishes last of the grid (the ticket is zero before and after); the block's last
+// wave does `meanwhile` while the ticket is on its way.
+// What the blocks hand to the last one they have written by device-scope atomics, which take effect where every XCD sees them:
+// every wave waits for its own, and no release is needed.  (A release writes the XCD's L2 back, some 0.1 us that the blocks of an
+// XCD queue up for: one per wave, the histogram kernel of a 1 % sample took 59 us on 384 blocks; one per block, the ticket
+// of 246 blocks came back 3.5 us after the last of them had asked, without 1.6.)
+template <int BLOCK, typename F>
+__device__ __forceinline__ bool last_block(unsigned int* ticket, F&& meanwhile)
 {
     __shared__ bool s_last;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (threadIdx.x == 0) {
-        __threadfence();
         const bool last = atomicAdd(ticket, 1u) == gridDim.x * gridDim.y - 1u;
         if (last) *ticket = 0u;
         s_last = last;
     }
+    if (threadIdx.x >= BLOCK - 64) meanwhile();
     __syncthreads();
     const bool last = s_last;
     if (last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
@@ -663,98 +711,58 @@ __device__ __forceinline__ bool last_block(unsigned int* ticket)
 
 __host__ __device__ constexpr uint32_t copy_stride(uint32_t bins) { return (bins + 3u) & ~3u; }   // words per set
 
-// The last block's part: the histogram from the sets of counters, H = log2 n - (1/n) sum c log2 c (== -sum p log2 p) and the
-// result.  Its code is fetched from a cold cache by one block, so it is short (with a loop over 32 bins written out 32 times
-// this took 7.7 us where one set of counters was summed); a thread has the counters of four bins in flight, bins BLOCK
-// apart, so that few bins are spread over all threads.
-template <int BLOCK>
-__device__ __forceinline__ void finish_hist(const uint32_t* copies, uint32_t sets, unsigned long long* counts, uint32_t bins,
-                                            const RangeParams& rp, unsigned long long n_sampled, edgc_entropy_result* res)
+// The last block's part: the histogram from the sets of 32-bit counters (S of them; 0: from the 64-bit counters themselves),
+// and H = log2 n - (1/n) sum c log2 c (== -sum p log2 p).  A thread has the counters of 4 U bins in flight: four
+// neighbours a load from a set, which is padded to a multiple of four counters that stay zero, and bins BLOCK apart where they are
+// 64-bit words at any address.
+template <int BLOCK, int S, int U>
+__device__ __forceinline__ void sum_bins(const uint32_t* copies, unsigned long long* counts, uint32_t bins, int e0, double& acc, double& tot)
 {
-    constexpr uint32_t B = 4;
-    double acc = 0.0, tot = 0.0;
-    for (uint32_t i0 = threadIdx.x; i0 < bins; i0 += BLOCK * B) {
-        unsigned long long c[B] = {0, 0, 0, 0};
-        if (sets) {
-            uint32_t x[8][B];
+    if constexpr (S > 0) {
+        for (uint32_t i0 = threadIdx.x * 4u; i0 < bins; i0 += BLOCK * 4u * U) {
+            uint4 x[U][S];
 #pragma unroll
-            for (uint32_t k = 0; k < 8; ++k) {
+            for (int u = 0; u < U; ++u)
 #pragma unroll
-                for (uint32_t e = 0; e < B; ++e) x[k][e] = 0u;
-                if (k < sets) {
+                for (int k = 0; k < S; ++k)
+                    x[u][k] = *reinterpret_cast<const uint4*>(copies + static_cast<size_t>(k) * copy_stride(bins) +
+                                                              min(i0 + BLOCK * 4u * u, copy_stride(bins) - 4u));
 #pragma unroll
-                    for (uint32_t e = 0; e < B; ++e)
-                        x[k][e] = copies[static_cast<size_t>(k) * copy_stride(bins) + min(i0 + e * BLOCK, bins - 1u)];
-                }
+            for (int u = 0; u < U; ++u) {
+                const uint32_t i = i0 + BLOCK * 4u * u;
+                if (i >= bins) break;
+                unsigned long long c[4] = {0, 0, 0, 0};
+#pragma unroll
+                for (int k = 0; k < S; ++k) { c[0] += x[u][k].x; c[1] += x[u][k].y; c[2] += x[u][k].z; c[3] += x[u][k].w; }
+#pragma unroll
+                for (uint32_t e = 0; e < 4; ++e)
+                    if (i + e < bins) counts[i + e] = c[e];
+                entropy_terms(c, e0, acc, tot);
             }
-#pragma unroll
-            for (uint32_t k = 0; k < 8; ++k)
-#pragma unroll
-                for (uint32_t e = 0; e < B; ++e) c[e] += x[k][e];
-        } else {
-#pragma unroll
-            for (uint32_t e = 0; e < B; ++e) c[e] = counts[min(i0 + e * BLOCK, bins - 1u)];
-        }
-#pragma unroll 1
-        for (uint32_t e = 0; e < B; ++e) {
-            const uint32_t i = i0 + e * BLOCK;
-            if (i >= bins) break;
-            const unsigned long long v = e == 0 ? c[0] : e == 1 ? c[1] : e == 2 ? c[2] : c[3];
-            if (sets) counts[i] = v;
-            entropy_term(v, acc, tot);
-        }
-    }
-    const double log_w = log_bin_width(rp, bins);
-    block_sum_pair<BLOCK>(acc, tot);
-    if (threadIdx.x == BLOCK - 1) emit_result(acc, tot, log_w, rp, n_sampled, res);
-}
-
-// The same for more than four bins per thread: the time is that of the logarithms, some hundred dependent operations each, and
-// of the loads, so the bins of an iteration are written out.  A set's counters of four neighbouring bins are one load; without
-// sets a thread has eight bins' counters in flight.  k_hist, between events, one logarithm at a time / this: 16384 bins, 1 M fp32
-// elements 27.4 / 23.9 us, 10 M bf16 34.3 / 29.8, 10 M fp32 37.0 / 32.9; 65536 bins, 10 K bf16 elements 29.3 / 20.5, 1 M 51.1 / 41.8.
-template <int BLOCK>
-__device__ __forceinline__ void finish_many(const uint32_t* copies, uint32_t sets, unsigned long long* counts, uint32_t bins,
-                                            const RangeParams& rp, unsigned long long n_sampled, edgc_entropy_result* res)
-{
-    double acc = 0.0, tot = 0.0;
-    auto four_bins = [&](uint32_t i, const unsigned long long (&c)[4]) {
-#pragma unroll
-        for (uint32_t e = 0; e < 4; ++e)
-            if (i + e < bins) {
-                counts[i + e] = c[e];
-                entropy_term(c[e], acc, tot);
-            }
-    };
-    if (sets == 8) {
-        for (uint32_t i = threadIdx.x * 4u; i < bins; i += BLOCK * 4u) {
-            uint4 x[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) x[k] = *reinterpret_cast<const uint4*>(copies + static_cast<size_t>(k) * copy_stride(bins) + i);
-            unsigned long long c[4] = {0, 0, 0, 0};
-#pragma unroll
-            for (int k = 0; k < 8; ++k) { c[0] += x[k].x; c[1] += x[k].y; c[2] += x[k].z; c[3] += x[k].w; }
-            four_bins(i, c);
-        }
-    } else if (sets) {
-        for (uint32_t i = threadIdx.x * 4u; i < bins; i += BLOCK * 4u) {
-            const uint4 x = *reinterpret_cast<const uint4*>(copies + i);
-            const unsigned long long c[4] = {x.x, x.y, x.z, x.w};
-            four_bins(i, c);
         }
     } else {
-        for (uint32_t i = threadIdx.x; i < bins; i += BLOCK * 8u) {
-            unsigned long long c[8];
+        for (uint32_t i0 = threadIdx.x; i0 < bins; i0 += BLOCK * 4u * U) {
+            unsigned long long c[U][4];
 #pragma unroll
-            for (uint32_t e = 0; e < 8; ++e) c[e] = counts[min(i + e * BLOCK, bins - 1u)];
+            for (uint32_t u = 0; u < U; ++u)
 #pragma unroll
-            for (uint32_t e = 0; e < 8; ++e)
-                if (i + e * BLOCK < bins) entropy_term(c[e], acc, tot);
+                for (uint32_t e = 0; e < 4; ++e) c[u][e] = counts[min(i0 + BLOCK * (4u * u + e), bins - 1u)];
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) {
+#pragma unroll
+                for (uint32_t e = 0; e < 4; ++e)
+                    if (i0 + BLOCK * (4u * u + e) >= bins) c[u][e] = 0ull;
+                entropy_terms(c[u], e0, acc, tot);
+            }
         }
     }
-    const double log_w = log_bin_width(rp, bins);
+}
+template <int BLOCK>
+__device__ __forceinline__ void finish(double acc, double tot, const EstimateLogs& logs, const RangeParams& rp,
+                                       unsigned long long n_sampled, edgc_entropy_result* res)
+{
     block_sum_pair<BLOCK>(acc, tot);
-    if (threadIdx.x == BLOCK - 1) emit_result(acc, tot, log_w, rp, n_sampled, res);
+    if (threadIdx.x == BLOCK - 1) emit_result(acc, tot, logs, rp, n_sampled, res);
 }
 
 // `sets` = 8: the blocks of equal id modulo 8, which the dispatcher places on one XCD, share a set of 32-bit counters at
@@ -793,9 +801,13 @@ __global__ __launch_bounds__(BLOCK) void k_hist(
         if (copy) atomicAdd(&copy[i], s);
         else atomicAdd(&counts[bin_base + i], static_cast<unsigned long long>(s));
     }
-    if (!last_block<BLOCK>(ticket)) return;
-    if (bins > 4 * BLOCK) finish_many<BLOCK>(copies, sets, counts, bins, rp, grp.n_sampled, res);
-    else finish_hist<BLOCK>(copies, sets, counts, bins, rp, grp.n_sampled, res);
+    EstimateLogs logs{};
+    if (!last_block<BLOCK>(ticket, [&] { logs = estimate_logs(rp, bins, grp.n_sampled); })) return;
+    double acc = 0.0, tot = 0.0;
+    if (sets == 8) sum_bins<BLOCK, 8, 1>(copies, counts, bins, entropy_base(grp.n_sampled), acc, tot);
+    else if (sets) sum_bins<BLOCK, 1, 2>(copies, counts, bins, entropy_base(grp.n_sampled), acc, tot);
+    else sum_bins<BLOCK, 0, 2>(copies, counts, bins, entropy_base(grp.n_sampled), acc, tot);
+    finish<BLOCK>(acc, tot, logs, rp, grp.n_sampled, res);
 }
 
 // The same for a sample of which every block takes one round of loads: 1 % of a transformer block and less.  What bounds it
@@ -841,8 +853,12 @@ __global__ __launch_bounds__(BLOCK) void k_hist_small(const EntGroup grp, const 
         for (uint32_t r = 0; r < (1u << rep_shift); ++r) s += h[(i << rep_shift) | r];
         if (s) atomicAdd(&copy[i], s);
     }
-    if (!last_block<BLOCK>(ticket)) return;
-    finish_hist<BLOCK>(copies, sets, counts, bins, rp, grp.n_sampled, res);
+    EstimateLogs logs{};
+    if (!last_block<BLOCK>(ticket, [&] { logs = estimate_logs(rp, bins, grp.n_sampled); })) return;
+    double acc = 0.0, tot = 0.0;
+    if (sets == 2) sum_bins<BLOCK, 2, 2>(copies, counts, bins, entropy_base(grp.n_sampled), acc, tot);
+    else sum_bins<BLOCK, 1, 2>(copies, counts, bins, entropy_base(grp.n_sampled), acc, tot);
+    finish<BLOCK>(acc, tot, logs, rp, grp.n_sampled, res);
 }
 
 // The whole estimate of a small sample by one block: range, histogram and entropy without a second launch, global
@@ -876,11 +892,11 @@ __global__ __launch_bounds__(kOneBlock) void k_estimate_one(const EntGroup grp, 
         uint32_t s = 0;
         for (uint32_t r = 0; r < (1u << rep_shift); ++r) s += h[(i << rep_shift) | r];
         counts[i] = s;
-        entropy_term(s, acc, tot);
+        entropy_term(s, entropy_base(grp.n_sampled), acc, tot);
     }
-    const double log_w = log_bin_width(rp, bins);
-    block_sum_pair<kOneBlock>(acc, tot);
-    if (threadIdx.x == kOneBlock - 1) emit_result(acc, tot, log_w, rp, grp.n_sampled, res);
+    EstimateLogs logs{};
+    if (threadIdx.x >= kOneBlock - 64) logs = estimate_logs(rp, bins, grp.n_sampled);
+    finish<kOneBlock>(acc, tot, logs, rp, grp.n_sampled, res);
 }
 
 // ---------------------------------------------------------------------------
@@ -907,6 +923,7 @@ __global__ __launch_bounds__(kOneBlock) void k_estimate_one(const EntGroup grp, 
 // middle and a few outliers of 65536 bins.
 // ---------------------------------------------------------------------------
 constexpr int kWideBlock = 1024;
+constexpr uint32_t kFoldedRange = kMaxReduceBlocks - 1;                   // where k_wide_hist leaves the range for k_wide_reduce (bins as keys)
 constexpr uint32_t kWideKeys = 65536;
 constexpr uint32_t kReduceKeys = 256;                                     // keys that one block of k_wide_reduce sums
 constexpr uint32_t kOccupiedWords = kWideKeys / kReduceKeys / 32;         // 32-bit words of a block's marks
@@ -952,6 +969,7 @@ __global__ __launch_bounds__(kWideBlock) void k_wide_hist(
         const RangeParams rp = fold_range<kWideBlock>(part, nparts, fbins);
         lo = rp.lo; scale = rp.scale;
         top = __uint_as_float(__float_as_uint(fbins) - 1u);     // largest float below the bin count
+        if (blockIdx.x == 0 && threadIdx.x == 0) part[kFoldedRange] = make_float2(rp.lo, rp.hi);
     }
     auto add = [&](uint32_t key, uint32_t k) { atomicAdd(&h[key >> 1], k << ((key & 1u) << 4)); };
     // bin = trunc((x - lo) * scale), each operation rounded on its own, clamped to [0, bins - 1]
@@ -1054,9 +1072,10 @@ __global__ __launch_bounds__(kWideBlock) void k_wide_hist(
 //  bf16 (keys are bit patterns): every block folds the range of the patterns that k_wide_hist's blocks saw and adds its
 //  256 totals to the bins of their patterns.
 // What bounds it: latency, of the marks, the marked blocks' fields (all of a thread's eight 16-byte loads in flight together),
-// the one release per block and the last block's loads of the bins.  134 M bf16 elements of a gradient, both kernels: all of
+// the ticket and the last block's loads of the bins.  134 M bf16 elements of a gradient, both kernels: all of
 // 33 MB of fields read and the patterns binned by the last block alone 86.0 us, marked fields only 80.4, binned by every block
-// and k_wide_hist's short sweep 73.8; 10 M fp32 elements on 65536 bins (range kernel included) 43.7 us, marked fields only 35.5.
+// and k_wide_hist's short sweep 73.8, without releases and with short logarithms 65.9; 10 M fp32 elements on 65536 bins (range
+// kernel included) 43.7 us, marked fields only 35.5, and 30.6.
 constexpr uint32_t kReduceGroups = kWideBlock / (kReduceKeys / 8);        // 32 groups of 32 threads
 static_assert(kMaxPart16Blocks <= kWideBlock && kMaxPart16Blocks * 65535ull < (1ull << 32),
               "k_wide_reduce: a thread looks at one block's marks, and a key's fields are summed in 32 bits");
@@ -1066,7 +1085,7 @@ template <bool PATTERN>
 __global__ __launch_bounds__(kWideBlock) void k_wide_reduce(
     const uint16_t* __restrict__ part16, const uint32_t* __restrict__ occupied, uint32_t nblocks, unsigned long long* __restrict__ wide,
     uint32_t bins, int has_range, float range_lo, float range_hi, unsigned long long* counts,
-    const float2* __restrict__ mm_part, uint32_t nparts, double* part_d, unsigned int* ticket, unsigned long long n_sampled,
+    const float2* __restrict__ mm_part, double* part_d, unsigned int* ticket, unsigned long long n_sampled,
     edgc_entropy_result* res)
 {
     extern __shared__ __align__(256) uint32_t red[];                  // the groups' sums: [kReduceGroups][kReduceKeys], then [4][kReduceKeys]
@@ -1080,7 +1099,10 @@ __global__ __launch_bounds__(kWideBlock) void k_wide_reduce(
     if ((marks >> (blockIdx.x & 31u)) & 1u) s_from[atomicAdd(&s_nfrom, 1u)] = threadIdx.x;
     if (c) wide[key] = 0ull;                          // zero between estimates
     RangeParams rp{};
-    if constexpr (PATTERN) {
+    if constexpr (!PATTERN) {
+        const float2 v = mm_part[kFoldedRange];
+        rp = make_range(v.x, v.y, static_cast<float>(bins));
+    } else {
         float lo = INFINITY, hi = -INFINITY;
         if (threadIdx.x < nblocks) { lo = mm_part[threadIdx.x].x; hi = mm_part[threadIdx.x].y; }
         block_range_minmax<kWideBlock>(lo, hi);
@@ -1128,10 +1150,13 @@ __global__ __launch_bounds__(kWideBlock) void k_wide_reduce(
         double acc = 0.0, tot = 0.0;
         if (mine && key < bins) {
             counts[key] = c;
-            entropy_term(c, acc, tot);
+            entropy_term(c, entropy_base(n_sampled), acc, tot);
         }
         block_sum_pair<kWideBlock>(acc, tot);
-        if (threadIdx.x == kWideBlock - 1) { part_d[2 * blockIdx.x] = acc; part_d[2 * blockIdx.x + 1] = tot; }
+        if (threadIdx.x == kWideBlock - 1) {
+            __hip_atomic_store(&part_d[2 * blockIdx.x], acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&part_d[2 * blockIdx.x + 1], tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
     } else if (threadIdx.x < kReduceKeys) {           // whole waves
         const float x = __uint_as_float(key << 16);
         if (!finite_f32(x)) c = 0ull;
@@ -1156,21 +1181,16 @@ __global__ __launch_bounds__(kWideBlock) void k_wide_reduce(
         const unsigned long long run = sum - (head ? before : 0ull);
         if (tail && run) atomicAdd(&counts[bin], run);
     }
-    if (!last_block<kWideBlock>(ticket)) return;
-    if constexpr (PATTERN) {
-        finish_hist<kWideBlock>(nullptr, 0u, counts, bins, rp, n_sampled, res);
-        return;
-    }
-
-    rp = fold_range<kWideBlock>(mm_part, nparts, static_cast<float>(bins));
+    EstimateLogs logs{};
+    if (!last_block<kWideBlock>(ticket, [&] { logs = estimate_logs(rp, bins, n_sampled); })) return;
     double acc = 0.0, tot = 0.0;
-    if (threadIdx.x < gridDim.x) {
+    if constexpr (PATTERN) {
+        sum_bins<kWideBlock, 0, 1>(nullptr, counts, bins, entropy_base(n_sampled), acc, tot);
+    } else if (threadIdx.x < gridDim.x) {
         acc = part_d[2 * threadIdx.x];
         tot = part_d[2 * threadIdx.x + 1];
     }
-    const double log_w = log_bin_width(rp, bins);
-    block_sum_pair<kWideBlock>(acc, tot);
-    if (threadIdx.x == kWideBlock - 1) emit_result(acc, tot, log_w, rp, n_sampled, res);
+    finish<kWideBlock>(acc, tot, logs, rp, n_sampled, res);
 }
 
 // ---------------------------------------------------------------------------
@@ -1258,18 +1278,17 @@ static int run_entropy(edgc_ctx* ctx, const EntScratch& s, const EntGroup& g, ui
     // for the blocks' fields: every bf16 sample of some size (no range pass, any number of bins), and
     // fp32 samples on more bins than 32-bit counters hold in LDS at once.
     const bool wide_ok = s.part16 != nullptr && ctx->tune_pattern != 0;
-    // The line for bf16 lies at 8 Mi elements, where the two passes meet on most bin counts and where two-pass samples leave the
-    // kernels of short blocks; at half of that above 16384 bins.  Per estimate in us, two passes / one read, every element of a
-    // buffer (1 sampled in 3 and in 10: the same within 2):
-    //                  256 bins      4096 bins     16384 bins    20000 bins    65536 bins
-    //      4 M         18.1 / 23.0   22.9 / 26.3   32.8 / 32.5   30 / 33       55.2 / 53.5
-    //      7 M         22.0 / 24.1   27.1 / 26.9   35.6 / 33.6   35.7 / 35.5
-    //    8.3 M         24.2 / 25.6   28.8 / 28.4   36.6 / 35.2   36.6 / 37.1   58.3 / 56.3
-    //    9.0 M         26.7 / 26.2   29.3 / 29.0   39.2 / 35.8   74.9 / 37.7
-    //     12 M         28.3 / 27.5   30.9 / 30.5   41.1 / 37.6   78 / 38       96.2 / 60.0
-    //     24 M         39.1 / 32.9   43.4 / 35.8   53.7 / 43.0   84 / 43      101.2 / 65.8
-    //     64 M         66.5 / 46.8   71.8 / 49.8   85.1 / 57.8   98 / 58      118.1 / 81.6
-    // Buffers off 16-byte boundaries: 2 M 24.3 / 23.4 on 256 bins, 8 M 47.0 / 28.8.
+    // The line for bf16 lies at 8 Mi elements, where two-pass samples leave the kernels of short blocks; at half of that above 16384
+    // bins.  Per estimate in us, two passes / one read, every element of a buffer (1 sampled in 3 and in 10: the same within 2):
+    //                  256 bins      4096 bins     16384 bins    16385 bins    65536 bins
+    //      4 M         15.7 / 18.5   18.1 / 19.7   29.2 / 24.5   26.8 / 24.7   48.3 / 38.1
+    //      6 M         18.6 / 19.2   21.8 / 19.9   31.3 / 25.1   29.0 / 25.0   49.7 / 39.0
+    //      8 M         20.3 / 20.0   23.4 / 20.8   32.3 / 25.2   29.3 / 25.4   49.9 / 39.3
+    //     12 M         25.7 / 22.1   28.1 / 23.1   37.3 / 28.2   74.8 / 28.5   88.1 / 41.7
+    //     24 M         36.2 / 28.0   38.5 / 28.8   47.9 / 33.7   80.2 / 34.1   92.9 / 47.8
+    //     64 M         58.8 / 40.8   63.8 / 42.0   73.5 / 47.2   93.5 / 47.8  109.8 / 62.8
+    // (The line was drawn when the sums over the bins took longer in the one read; now the two meet at 6 M on few bins, and the one
+    // read is the faster from 1 M on above 4096 bins: 28.1 / 22.8 on 16384, 45.1 / 35.6 on 65536.)
     const uint64_t pattern_min = static_cast<uint64_t>(ctx->tune_pattern_min);
     const bool by_pattern = sizeof(T) == 2 && wide_ok &&
                             (g.n_sampled >= pattern_min || (bins > 16384 && g.n_sampled >= pattern_min / 2));
@@ -1287,7 +1306,7 @@ static int run_entropy(edgc_ctx* ctx, const EntScratch& s, const EntGroup& g, ui
             EDGC_LAUNCH(ctx, st, KID_WIDE_REDUCE, reduce_bytes, 0.0,
                         k_wide_reduce<true><<<kWideKeys / kReduceKeys, kWideBlock, kWideReduceLds, st>>>(
                             s.part16, s.occupied, wide_blocks, s.wide, bins, range ? 1 : 0, range ? range[0] : 0.0f,
-                            range ? range[1] : 0.0f, counts, s.mm_part, wide_blocks, pair_part, s.ticket, g.n_sampled, res));
+                            range ? range[1] : 0.0f, counts, s.mm_part, pair_part, s.ticket, g.n_sampled, res));
             EDGC_HIP_TRY(ctx, hipGetLastError());
             return EDGC_OK;
         }
@@ -1375,7 +1394,7 @@ static int run_entropy(edgc_ctx* ctx, const EntScratch& s, const EntGroup& g, ui
                             g, s.mm_part, nparts, bins, s.part16, s.occupied, s.wide, counts));
             EDGC_LAUNCH(ctx, st, KID_WIDE_REDUCE, reduce_bytes, 0.0,
                         k_wide_reduce<false><<<(bins + kReduceKeys - 1) / kReduceKeys, kWideBlock, kWideReduceLds, st>>>(
-                            s.part16, s.occupied, wide_blocks, s.wide, bins, 0, 0.0f, 0.0f, counts, s.mm_part, nparts,
+                            s.part16, s.occupied, wide_blocks, s.wide, bins, 0, 0.0f, 0.0f, counts, s.mm_part,
                             pair_part, s.ticket, g.n_sampled, res));
             EDGC_HIP_TRY(ctx, hipGetLastError());
             return EDGC_OK;

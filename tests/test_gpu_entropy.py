@@ -478,3 +478,31 @@ def to_host_any(x):
     if x.dtype == torch.bfloat16:
         return x.view(torch.int16).cpu().numpy().view(np.uint16)
     return x.cpu().numpy()
+
+
+@pytest.mark.parametrize("dtype,bins,n", [("f32", 1, 3000), ("f32", 2, 40000), ("f32", 255, 3000), ("f32", 1000, 60001), ("f32", 1023, 300000),
+                                          ("f32", 4096, 2000000), ("f32", 4095, 9000000), ("f32", 5003, 200000), ("f32", 16384, 3000),
+                                          ("f32", 16384, 5000000), ("f32", 20001, 700000), ("f32", 65536, 3000000), ("f32", 100000, 400000),
+                                          ("bf16", 128, 3000), ("bf16", 100, 50000), ("bf16", 128, 12000000), ("bf16", 40000, 60000)])
+def test_entropy_of_given_counts(dtype, bins, n):
+    """Every kernel that ends in the sum over the bins, on a histogram that is known: single, odd and empty bins, a bin with half
+    of the sample.  The logarithms are taken less the exponent of n, so that a term c/n (log2 c - e0) is at most
+    c/n (log2(n/c) + 1) and the terms' magnitudes add up to H + 1 at most; a few roundings of 2^-53 of each: 1e-15 (H + 1)."""
+    rng = np.random.default_rng(bins + n)
+    top = min(bins, 128) if dtype == "bf16" else bins                       # i + 1/2 is a bf16 value below 128
+    c = np.floor(rng.exponential(1.0, top) * rng.integers(0, 2, top) * (n / (2.0 * top))).astype(np.int64)
+    c[rng.integers(0, top, 1 + top // 8)] = 1
+    c[top // 2] += max(0, n - int(c.sum()))
+    c = np.minimum(c, n)
+    n = int(c.sum())
+    x = torch.from_numpy(np.repeat(np.arange(top, dtype=np.float32) + 0.5, c)).cuda()
+    x = x[torch.randperm(n, device="cuda", generator=torch.Generator(device="cuda").manual_seed(1))]
+    x = x.to(torch.bfloat16) if dtype == "bf16" else x
+    counts = torch.empty(bins, dtype=torch.int64, device="cuda")
+    e = edgc.Context(0, max_bins=bins, max_rank=32, max_rows=64, max_cols=64)
+    got = e.entropy_estimate(x, 1, 64, 0, 0, bins, value_range=(0.0, float(bins)), counts_out=counts)
+    e.close()
+    assert np.array_equal(counts.cpu().numpy()[:top], c) and int(counts.sum()) == n and got.n_sampled == n
+    want = math.fsum(k / n * math.log2(n / k) for k in c.tolist() if k)
+    assert abs(got.H_bits - want) <= 1e-15 * (want + 1.0)
+    assert want != 0.0 or got.H_bits == 0.0
