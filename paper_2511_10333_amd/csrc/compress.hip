@@ -1326,11 +1326,38 @@ __global__ __launch_bounds__(256) void k_reduce_q(const Group grp, uint32_t RP, 
 }
 
 // ---------------------------------------------------------------------------
-// Copies of the tensors that are sent as they stand (decompress hands the gradient on), all of them at the head of
-// k_decompress's grid: a transformer stage has a dozen norm weights and biases of some kilobytes each, and a launch
+// Copies of the tensors that are sent as they stand (decompress hands the gradient on).  Contiguous ones, and a transformer stage
+// has a dozen norm weights and biases of some kilobytes each, ride at the head of the decompress's grid, since a launch
 // costs more than any of them (16 of them in the stage of two hidden-768 blocks: 16 launches 37 to 60 us, one 5; the pass
-// 82.7 us with one, 77.1 in k_decompress).  k_copy_rows where there is no such launch.  A unit is the widest
-// access that the tensor's pointers, row length and strides allow; a contiguous tensor may end inside a unit.
+// 82.7 us with one, 77.1 in k_decompress_copies).  16-byte accesses at any element address, so that the kernels that carry this code carry
+// little of it (with a case per alignment and strides it was 5500 instructions and 80 bytes of scratch).
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
+__device__ __forceinline__ void copy_run(const CopyRuns& runs, uint32_t bid)
+{
+    uint32_t t = 0;
+#pragma unroll
+    for (uint32_t i = 1; i < kMaxCopies; ++i) t += (bid >= runs.first[i]) ? 1u : 0u;
+    const CopyRun& c = runs.t[t];
+    const unsigned char* __restrict__ src = c.src;
+    unsigned char* __restrict__ dst = c.dst;
+    const uint64_t whole = c.bytes / 16, stride = static_cast<uint64_t>(c.blocks) * kCopyUnits;
+    uint64_t i = static_cast<uint64_t>(bid - c.first) * kCopyUnits + threadIdx.x;
+    // what the last unit leaves: 16-bit pieces, one per thread of the first block
+    const uint64_t rest = whole * 16 + 2u * threadIdx.x;
+    if (bid == c.first && rest < c.bytes) *reinterpret_cast<uint16_t*>(dst + rest) = *reinterpret_cast<const uint16_t*>(src + rest);
+    constexpr uint32_t N = kCopyUnits / 256;
+    for (; i < whole; i += stride) {
+        u32x4 v[N];
+#pragma unroll
+        for (uint32_t k = 0; k < N; ++k) v[k] = *reinterpret_cast<const u32x4_any*>(src + min(i + k * 256u, whole - 1u) * 16);
+#pragma unroll
+        for (uint32_t k = 0; k < N; ++k)
+            if (i + k * 256u < whole) *reinterpret_cast<u32x4_any*>(dst + (i + k * 256u) * 16) = v[k];
+    }
+}
+__global__ __launch_bounds__(256) void k_copy_runs(const CopyRuns runs) { copy_run(runs, blockIdx.x); }
+
+// Copies whose rows are apart, all in one launch.  A unit is the widest access that pointers, row length and strides allow.
 template <typename U>
 __device__ __forceinline__ void copy_units(const unsigned char* __restrict__ src, unsigned char* __restrict__ dst,
                                            uint64_t row_bytes, uint64_t ld_src, uint64_t ld_dst, uint32_t m, uint64_t first,
@@ -1338,36 +1365,28 @@ __device__ __forceinline__ void copy_units(const unsigned char* __restrict__ src
 {
     constexpr int N = kCopyUnits / 256;
     const uint64_t whole = row_bytes / sizeof(U), total = whole * m;      // units
-    // what the last unit of a contiguous tensor leaves: 16-bit pieces, one per thread of its first block
-    const uint64_t at = whole * sizeof(U) + 2u * threadIdx.x;
-    if (first == 0 && m == 1 && at < row_bytes)
-        *reinterpret_cast<uint16_t*>(dst + at) = *reinterpret_cast<const uint16_t*>(src + at);
     for (; first < total; first += stride) {
         U v[N] = {};
 #pragma unroll
         for (int k = 0; k < N; ++k) {
-            const uint64_t i = first + threadIdx.x + k * 256u, row = m == 1 ? 0 : i / whole;
+            const uint64_t i = first + threadIdx.x + k * 256u, row = i / whole;
             if (i < total) v[k] = *reinterpret_cast<const U*>(src + row * ld_src + (i - row * whole) * sizeof(U));
         }
 #pragma unroll
         for (int k = 0; k < N; ++k) {
-            const uint64_t i = first + threadIdx.x + k * 256u, row = m == 1 ? 0 : i / whole;
+            const uint64_t i = first + threadIdx.x + k * 256u, row = i / whole;
             if (i < total) *reinterpret_cast<U*>(dst + row * ld_dst + (i - row * whole) * sizeof(U)) = v[k];
         }
     }
 }
 
-// block `bid` of a list's copies
-__device__ __forceinline__ void copy_block(const CopyGroup& grp, uint32_t bid)
+__global__ __launch_bounds__(256) void k_copy_rows(const CopyGroup grp)
 {
-    static_assert(offsetof(CopyGroup, t) / 64 == (offsetof(CopyGroup, t) + sizeof(CopyArgs) - 1) / 64, "the first copy's line");
-    const uint64_t first_copy = reinterpret_cast<uint64_t>(grp.t[0].src);      // as in tensor_of
     uint32_t t = 0;
 #pragma unroll
-    for (uint32_t i = 1; i < kMaxCopies; ++i) t += (bid >= grp.first[i]) ? 1u : 0u;
-    asm volatile("" :: "s"(first_copy));
+    for (uint32_t i = 1; i < kMaxCopies; ++i) t += (blockIdx.x >= grp.first[i]) ? 1u : 0u;
     const CopyArgs& c = grp.t[t];
-    const uint64_t first = static_cast<uint64_t>(bid - c.first) * kCopyUnits;
+    const uint64_t first = static_cast<uint64_t>(blockIdx.x - c.first) * kCopyUnits;
     const uint64_t stride = static_cast<uint64_t>(c.blocks) * kCopyUnits;
     switch (c.unit) {
     case 16: copy_units<uint4>(c.src, c.dst, c.row_bytes, c.ld_src, c.ld_dst, c.m, first, stride); break;
@@ -1376,8 +1395,6 @@ __device__ __forceinline__ void copy_block(const CopyGroup& grp, uint32_t bid)
     default: copy_units<uint16_t>(c.src, c.dst, c.row_bytes, c.ld_src, c.ld_dst, c.m, first, stride); break;
     }
 }
-
-__global__ __launch_bounds__(256) void k_copy_rows(const CopyGroup grp) { copy_block(grp, blockIdx.x); }
 
 // ---------------------------------------------------------------------------
 // Decompress:  M^ = P^ Q^T -> grad_out,  E_new = D - M^ (as transmitted), in place.
@@ -1618,12 +1635,21 @@ __device__ __forceinline__ void decompress_block(const Group& grp, const TensorA
 
 // (two waves per SIMD: the form with both bodies would take 262 registers at rank 128)
 template <int NP, int RT, bool DEFER, Caching C>
-__global__ __launch_bounds__(256, (DEFER && C == Caching::by_tensor) ? 2 : 1) void k_decompress(const Group grp, const CopyGroup copies)
+__global__ __launch_bounds__(256, (DEFER && C == Caching::by_tensor) ? 2 : 1) void k_decompress(const Group grp)
 {
     const TensorArgs& ta = tensor_of(grp, blockIdx.x);
-    if (blockIdx.x < grp.first[0]) { copy_block(copies, blockIdx.x); return; }
     if (C == Caching::past || (C == Caching::by_tensor && ta.past != 0)) decompress_block<NP, RT, DEFER, true, true>(grp, ta);
     else decompress_block<NP, RT, DEFER, false, DEFER && C != Caching::small>(grp, ta);
+}
+// Copies in its first blocks.  A kernel of its own: with the copies' code the one without is some registers larger, which can cost
+// a wave per SIMD (2047 x 2049 fp32 at rank 64, through the caches: 8.1 / 9.3 us); and for rows of whole cache lines only, which
+// the matrices that come with vectors have.
+template <int NP, int RT, bool DEFER>
+__global__ __launch_bounds__(256) void k_decompress_copies(const Group grp, const CopyRuns copies)
+{
+    const TensorArgs& ta = tensor_of(grp, blockIdx.x);
+    if (blockIdx.x < grp.first[0]) copy_run(copies, blockIdx.x);
+    else decompress_block<NP, RT, DEFER, true, true>(grp, ta);
 }
 
 // ---------------------------------------------------------------------------
@@ -2351,35 +2377,53 @@ int CopyList::add(const void* src, uint64_t ld_src, void* dst, uint64_t ld_dst, 
                   uint32_t elem_bytes, hipStream_t st)
 {
     if (static_cast<uint64_t>(m) * n == 0 || src == dst) return EDGC_OK;
-    CopyArgs c{};
+    static_assert(static_cast<uint64_t>(kMaxCopies) * copy_blocks(~0ull >> 16) * 256 < (1ull << 31), "threads of a launch, others beside them");
+    const uint64_t row_bytes = static_cast<uint64_t>(n) * elem_bytes;
+    if (m == 1 || (ld_src == n && ld_dst == n)) {
+        if (runs.count == kMaxCopies)
+            if (int rc = flush(st)) return rc;
+        CopyRun& c = runs.t[runs.count];
+        c.src = static_cast<const unsigned char*>(src);
+        c.dst = static_cast<unsigned char*>(dst);
+        c.bytes = row_bytes * m;
+        c.first = runs.first[runs.count++] = run_blocks;
+        run_blocks += c.blocks = copy_blocks((c.bytes + 15) / 16);
+        return EDGC_OK;
+    }
+    if (rows.count == kMaxCopies)
+        if (int rc = flush_rows(st)) return rc;
+    CopyArgs& c = rows.t[rows.count];
     c.src = static_cast<const unsigned char*>(src);
     c.dst = static_cast<unsigned char*>(dst);
     c.m = m;
-    c.row_bytes = static_cast<uint64_t>(n) * elem_bytes;
+    c.row_bytes = row_bytes;
     c.ld_src = ld_src * elem_bytes;
     c.ld_dst = ld_dst * elem_bytes;
-    if (ld_src == n && ld_dst == n) { c.row_bytes *= m; c.m = 1; }
-    uint64_t bits = reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst);
-    if (c.m > 1) bits |= c.row_bytes | c.ld_src | c.ld_dst;
+    const uint64_t bits = reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst) | row_bytes | c.ld_src | c.ld_dst;
     c.unit = 16;
     while (c.unit > elem_bytes && bits % c.unit) c.unit /= 2;
-    static_assert(static_cast<uint64_t>(kMaxCopies) * copy_blocks(~0ull >> 16) * 256 < (1ull << 32), "threads of a launch");
-    c.blocks = copy_blocks((c.row_bytes + c.unit - 1) / c.unit * c.m);
-    if (g.count == kMaxCopies)
-        if (int rc = flush(st)) return rc;
-    c.first = g.first[g.count] = blocks;
-    blocks += c.blocks;
-    g.t[g.count++] = c;
+    c.first = rows.first[rows.count++] = row_blocks;
+    row_blocks += c.blocks = copy_blocks(row_bytes / c.unit * m);
+    return EDGC_OK;
+}
+
+int CopyList::flush_rows(hipStream_t st)
+{
+    if (rows.count == 0) return EDGC_OK;
+    std::fill(rows.first + rows.count, rows.first + kMaxCopies, ~0u);
+    k_copy_rows<<<row_blocks, 256, 0, st>>>(rows);
+    rows.count = row_blocks = 0;
+    EDGC_HIP_TRY(ctx, hipGetLastError());
     return EDGC_OK;
 }
 
 int CopyList::flush(hipStream_t st)
 {
-    if (g.count == 0) return EDGC_OK;
-    std::fill(g.first + g.count, g.first + kMaxCopies, ~0u);
-    k_copy_rows<<<blocks, 256, 0, st>>>(g);
-    g.count = 0;
-    blocks = 0;
+    if (int rc = flush_rows(st)) return rc;
+    if (runs.count == 0) return EDGC_OK;
+    std::fill(runs.first + runs.count, runs.first + kMaxCopies, ~0u);
+    k_copy_runs<<<run_blocks, 256, 0, st>>>(runs);
+    runs.count = run_blocks = 0;
     EDGC_HIP_TRY(ctx, hipGetLastError());
     return EDGC_OK;
 }
@@ -2842,9 +2886,7 @@ static int decompress_impl(edgc_ctx* ctx, Group& g, CopyList& copies, hipStream_
     uint64_t d_bytes = 0;
     for (uint32_t i = 0; i < g.count; ++i) d_bytes += 4ull * g.t[i].m * g.t[i].n;
     const bool by_line = g.defer || d_bytes <= (28ull << 20);
-    if (use_full)
-        if (int rc = copies.flush(st)) return rc;
-    uint32_t blocks = copies.blocks, n_past = 0;       // the copies' blocks come first
+    uint32_t blocks = 0, n_past = 0;
     double bytes = 0.0, flops = 0.0;
     for (uint32_t i = 0; i < g.count; ++i) {
         TensorArgs& t = g.t[i];
@@ -2863,26 +2905,37 @@ static int decompress_impl(edgc_ctx* ctx, Group& g, CopyList& copies, hipStream_
         flops += 2.0 * t.m * t.n * g.r;
     }
     if (use_full) {
+        if (int rc = copies.flush(st)) return rc;
         ProfScope prof_scope_(ctx, st, KID_DECOMPRESS, bytes, flops);
         EDGC_HIP_TRY(ctx, launch_decompress_full(g, DT, RT, blocks, waves, st));
         return EDGC_OK;
     }
+    const Caching caching = group_caching(n_past, g.count, static_cast<double>(d_bytes));
+    const bool with_copies = copies.runs.count != 0 && caching == Caching::past;
+    if (int rc = with_copies ? copies.flush_rows(st) : copies.flush(st)) return rc;
+    if (with_copies) {                                 // the copies' blocks come first
+        for (uint32_t i = 0; i < g.count; ++i) g.t[i].first = g.first[i] += copies.run_blocks;
+        blocks += copies.run_blocks;
+        std::fill(copies.runs.first + copies.runs.count, copies.runs.first + kMaxCopies, ~0u);
+    }
     ProfScope prof_scope_(ctx, st, KID_DECOMPRESS, bytes, flops);
-    std::fill(copies.g.first + copies.g.count, copies.g.first + kMaxCopies, ~0u);
     auto launch = [&](auto defer_tag) {
         constexpr bool DEFER = decltype(defer_tag)::value;
-        switch (group_caching(n_past, g.count, static_cast<double>(d_bytes))) {
-        case Caching::past: k_decompress<NP, RT, DEFER, Caching::past><<<blocks, 256, lds, st>>>(g, copies.g); break;
-        case Caching::through:                                     // (stored: never, through the caches only where small)
-            if constexpr (DEFER) k_decompress<NP, RT, DEFER, Caching::through><<<blocks, 256, lds, st>>>(g, copies.g);
+        switch (caching) {
+        case Caching::past:
+            if (with_copies) k_decompress_copies<NP, RT, DEFER><<<blocks, 256, lds, st>>>(g, copies.runs);
+            else k_decompress<NP, RT, DEFER, Caching::past><<<blocks, 256, lds, st>>>(g);
             break;
-        case Caching::small: k_decompress<NP, RT, DEFER, Caching::small><<<blocks, 256, lds, st>>>(g, copies.g); break;
-        default: k_decompress<NP, RT, DEFER, Caching::by_tensor><<<blocks, 256, lds, st>>>(g, copies.g); break;
+        case Caching::through:                                     // (stored: never, through the caches only where small)
+            if constexpr (DEFER) k_decompress<NP, RT, DEFER, Caching::through><<<blocks, 256, lds, st>>>(g);
+            break;
+        case Caching::small: k_decompress<NP, RT, DEFER, Caching::small><<<blocks, 256, lds, st>>>(g); break;
+        default: k_decompress<NP, RT, DEFER, Caching::by_tensor><<<blocks, 256, lds, st>>>(g); break;
         }
     };
     if (g.defer) launch(std::true_type{});
     else launch(std::false_type{});
-    copies.g.count = copies.blocks = 0;
+    copies.runs.count = copies.run_blocks = 0;
     EDGC_HIP_TRY(ctx, hipGetLastError());
     return EDGC_OK;
 }

@@ -274,23 +274,36 @@ constexpr uint32_t copy_blocks(uint64_t units)
     const uint64_t runs = (units + kCopyUnits - 1) / kCopyUnits;
     return runs < (1u << 18) ? static_cast<uint32_t>(runs) : 1u << 18;
 }
-struct CopyArgs {
+struct CopyRun {                            // contiguous
+    const unsigned char* src;
+    unsigned char* dst;
+    uint64_t bytes;
+    uint32_t first, blocks;                 // first block; blocks
+};
+struct CopyRuns {
+    uint32_t first[kMaxCopies];             // as in Group
+    uint32_t count;
+    CopyRun t[kMaxCopies];
+};
+struct CopyArgs {                           // rows apart
     const unsigned char* src;
     unsigned char* dst;
     uint64_t row_bytes, ld_src, ld_dst;     // bytes
     uint32_t m, unit, first, blocks;        // rows; bytes per access; first block; blocks
 };
 struct CopyGroup {
-    uint32_t first[kMaxCopies];             // as in Group
+    uint32_t first[kMaxCopies];
     uint32_t count;
     CopyArgs t[kMaxCopies];
 };
 struct CopyList {
     edgc_ctx* ctx;
-    CopyGroup g{};
-    uint32_t blocks = 0;
+    CopyRuns runs{};
+    CopyGroup rows{};
+    uint32_t run_blocks = 0, row_blocks = 0;
     int add(const void* src, uint64_t ld_src, void* dst, uint64_t ld_dst, uint32_t m, uint32_t n, uint32_t elem_bytes,
             hipStream_t st);                // strides in elements
+    int flush_rows(hipStream_t st);
     int flush(hipStream_t st);
 };
 // `copies`: made by the same launch, or by one before it
