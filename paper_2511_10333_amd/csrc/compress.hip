@@ -288,14 +288,15 @@ __global__ __launch_bounds__(256, (NP == 2 && RT == 4) ? 2 : 1) void k_pass_p(co
         }
     }
 
-    // partial P of this k-range: part[s][row][c], c over the padded rank
+    // partial P of this k-range: part[s][row][c], c < part_width
+    const uint32_t pw = part_width<RT>(grp.r);
 #pragma unroll
     for (int ct = 0; ct < RT; ++ct)
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const uint32_t row = row0 + wave * 32 + 8 * (v / 4) + 4 * (lane >> 5) + (v % 4);
-            if (row < m)
-                part[(static_cast<size_t>(s) * m + row) * RP + ct * 32 + (lane & 31)] = acc[ct][v];
+            if (row < m && (RT > 1 || static_cast<uint32_t>(lane & 31) < pw))
+                part[(static_cast<size_t>(s) * m + row) * pw + ct * 32 + (lane & 31)] = acc[ct][v];
         }
 }
 
@@ -323,7 +324,7 @@ __host__ __device__ inline void tri_tile(int t, int T, int& ta, int& tb)
 // FROM_P: P is in the caller's buffer and not in partials (the second phase of a split call).  A template: as a branch it
 // costs the rank-128 kernel 24 registers (46 against 42 us on the hidden-5120 block).
 template <int T16, bool FROM_P>
-__global__ __launch_bounds__(256) void k_reduce_gram(const Group grp, uint32_t RP)
+__global__ __launch_bounds__(256) void k_reduce_gram(const Group grp, uint32_t pw)
 {
     const TensorArgs& ta_ = tensor_of(grp, blockIdx.x);
     const float* __restrict__ part = ta_.part;
@@ -351,7 +352,7 @@ __global__ __launch_bounds__(256) void k_reduce_gram(const Group grp, uint32_t R
     const uint32_t total_chunks = (m + 63) / 64;
     const uint32_t ch_begin = bid * chunks_per_block;
     const uint32_t ch_end = min(total_chunks, ch_begin + chunks_per_block);
-    const size_t sstride = static_cast<size_t>(m) * RP;
+    const size_t sstride = static_cast<size_t>(m) * pw;
     for (uint32_t ch = ch_begin; ch < ch_end; ++ch) {
         const uint32_t row0 = ch * 64;
         __syncthreads();                             // previous chunk's Gram reads are done
@@ -366,7 +367,7 @@ __global__ __launch_bounds__(256) void k_reduce_gram(const Group grp, uint32_t R
             const int i = idx / (CW / 4), c4 = (idx % (CW / 4)) * 4;
             const uint32_t row = min(row0 + i, m - 1);       // rows past the end are loaded but not used
             v[it] = make_float4(0.f, 0.f, 0.f, 0.f);
-            src[it] = part + static_cast<size_t>(row) * RP + c4;
+            src[it] = part + static_cast<size_t>(row) * pw + c4;
             if (FROM_P && static_cast<uint32_t>(c4) < r) {   // P as the caller holds it, columns from r on masked
                 const float4 x = *reinterpret_cast<const float4*>(P + static_cast<size_t>(row) * ldp + c4);
                 v[it].x = x.x;
@@ -1238,7 +1239,8 @@ __global__ __launch_bounds__(256, (NP == 2 && RT == 4) ? 2 : 1) void k_pass_q(co
     }
 
     // accumulator (ct, t, v) of lane l: column j = jw0 + NT*rho + t with rho = 8*(v/4) + 4*g + v%4,
-    // factor column c = ct*32 + jl  ->  part[s][j][c]
+    // factor column c = ct*32 + jl  ->  part[s][j][c], c < part_width
+    const uint32_t pw = part_width<RT>(grp.r);
 #pragma unroll
     for (int ct = 0; ct < RT; ++ct)
 #pragma unroll
@@ -1246,7 +1248,8 @@ __global__ __launch_bounds__(256, (NP == 2 && RT == 4) ? 2 : 1) void k_pass_q(co
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const uint32_t j = jw0 + NT * (8 * (v / 4) + 4 * g + (v % 4)) + t;
-                if (j < n) part[(static_cast<size_t>(s) * n + j) * RP + ct * 32 + jl] = acc[ct][t][v];
+                if (j < n && (RT > 1 || static_cast<uint32_t>(jl) < pw))
+                    part[(static_cast<size_t>(s) * n + j) * pw + ct * 32 + jl] = acc[ct][t][v];
             }
 }
 
@@ -1255,20 +1258,20 @@ __global__ __launch_bounds__(256, (NP == 2 && RT == 4) ? 2 : 1) void k_pass_q(co
 // 256: a thread sums its item, four independent loads in flight.  32: all 256 threads load, four splits each at a time, and
 // 128 of them add up one column each from LDS.
 template <uint32_t W>
-__global__ __launch_bounds__(256) void k_reduce_q(const Group grp, uint32_t RP, int of_p)
+__global__ __launch_bounds__(256) void k_reduce_q(const Group grp, uint32_t pw, int of_p)
 {
     const TensorArgs& ta = tensor_of(grp, blockIdx.x);
     const float* __restrict__ part = ta.part;
     float* __restrict__ Q = of_p ? ta.P : ta.Q;
     const uint32_t S = of_p ? ta.sp : ta.sq, n = of_p ? ta.m : ta.n, r = grp.r, ldq = of_p ? ta.ldp : ta.ldq;
-    const uint32_t q4 = RP / 4;
+    const uint32_t q4 = pw / 4;
     const uint64_t item0 = static_cast<uint64_t>(blockIdx.x - ta.first) * W, items = static_cast<uint64_t>(n) * q4;
-    const size_t stride = static_cast<size_t>(n) * RP;
+    const size_t stride = static_cast<size_t>(n) * pw;
     if constexpr (W == 256) {
         const uint64_t t = item0 + threadIdx.x;
         const uint32_t j = static_cast<uint32_t>(t / q4), c = static_cast<uint32_t>(t % q4) * 4;
         if (t >= items || c >= r) return;
-        const float* p = part + static_cast<size_t>(j) * RP + c;
+        const float* p = part + static_cast<size_t>(j) * pw + c;
         float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
         uint32_t s = 0;
         for (; s + 4 <= S; s += 4) {
@@ -1995,14 +1998,15 @@ __device__ __forceinline__ void pass_p_deferred_block(const Group& grp, const Te
 #undef EDGC_DEFERRED_STAGE
 #undef EDGC_DEFERRED_COMBINE
 
-    // partial P of this k-range: part[s][row][c], c over the padded rank
+    // partial P of this k-range: part[s][row][c], c < part_width
+    const uint32_t pw = part_width<RT>(r);
 #pragma unroll
     for (int ct = 0; ct < RT; ++ct)
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const uint32_t row = row0 + 8 * (v / 4) + 4 * g + (v % 4);
-            if (row < m)
-                part[(static_cast<size_t>(s) * m + row) * RP + ct * 32 + jl] = accp[ct][v];
+            if (row < m && (RT > 1 || static_cast<uint32_t>(jl) < pw))
+                part[(static_cast<size_t>(s) * m + row) * pw + ct * 32 + jl] = accp[ct][v];
         }
 }
 
@@ -2556,7 +2560,7 @@ static int run_orthonormalise(edgc_ctx* ctx, Group& g, const TensorScratch* cap,
     if (from_p)
         for (uint32_t i = 0; i < g.count; ++i) g.t[i].sp = 0;
     const uint32_t r = g.r;
-    const uint32_t RP = rank_tiles(r) * 32;
+    const uint32_t RP = rank_tiles(r) * 32, pw = r <= 16 ? 16u : RP;       // pw: part_width
     const uint32_t t16 = gram_tiles(r);
     const uint32_t ntile = t16 * (t16 + 1) / 2, ne = ntile * 256;
     uint32_t tgt[kMaxGroup];
@@ -2583,8 +2587,8 @@ static int run_orthonormalise(edgc_ctx* ctx, Group& g, const TensorScratch* cap,
     {
         ProfScope prof_scope_(ctx, st, KID_REDUCE_GRAM, bytes, flops);
 #define EDGC_GRAM(T_)                                                       \
-    if (from_p) k_reduce_gram<T_, true><<<blocks, 256, 0, st>>>(g, RP);     \
-    else k_reduce_gram<T_, false><<<blocks, 256, 0, st>>>(g, RP);
+    if (from_p) k_reduce_gram<T_, true><<<blocks, 256, 0, st>>>(g, pw);     \
+    else k_reduce_gram<T_, false><<<blocks, 256, 0, st>>>(g, pw);
         switch (t16) {
         case 1: EDGC_GRAM(1) break;
         case 2: EDGC_GRAM(2) break;
@@ -2767,9 +2771,10 @@ static int run_pass_q(edgc_ctx* ctx, Group& g, const TensorScratch* cap, hipStre
     // 256 items (four columns of a row of Q) per block, or 32 where that leaves most CUs idle and there are sums to share.
     // Between events, whole / narrow: 50257 x 1024 at rank 32 (113 splits, 32 and 256 blocks) 9.2 / 3.4 us, 32000 x 768 13.8 / 4.6,
     // 100000 x 256 at rank 64 31.0 / 8.5, 16384 x 1024 5.2 / 2.4, 4096 x 512 5.3 / 1.8, 1024 x 1024 (16 splits) 1.8 / 1.9.
+    const uint32_t pw = g.r <= 16 ? 16u : RP;          // part_width
     uint32_t whole_blocks = 0, most_splits = 0;
     for (uint32_t i = 0; i < g.count; ++i) {
-        whole_blocks += cdiv(static_cast<uint64_t>(g.t[i].n) * (RP / 4), 256);
+        whole_blocks += cdiv(static_cast<uint64_t>(g.t[i].n) * (pw / 4), 256);
         most_splits = std::max(most_splits, g.t[i].sq);
     }
     const bool narrow = most_splits >= 16 && whole_blocks * 4u <= static_cast<uint32_t>(ctx->num_cu);
@@ -2778,12 +2783,12 @@ static int run_pass_q(edgc_ctx* ctx, Group& g, const TensorScratch* cap, hipStre
     for (uint32_t i = 0; i < g.count; ++i) {
         TensorArgs& t = g.t[i];
         t.first = g.first[i] = blocks;
-        blocks += cdiv(static_cast<uint64_t>(t.n) * (RP / 4), narrow ? 32 : 256);
+        blocks += cdiv(static_cast<uint64_t>(t.n) * (pw / 4), narrow ? 32 : 256);
         bytes += 4.0 * t.n * g.r * (t.sq + 1);
     }
     ProfScope prof_scope_(ctx, st, KID_REDUCE_Q, bytes, 0.0);
-    if (narrow) k_reduce_q<32><<<blocks, 256, 0, st>>>(g, RP, 0);
-    else k_reduce_q<256><<<blocks, 256, 0, st>>>(g, RP, 0);
+    if (narrow) k_reduce_q<32><<<blocks, 256, 0, st>>>(g, pw, 0);
+    else k_reduce_q<256><<<blocks, 256, 0, st>>>(g, pw, 0);
     EDGC_HIP_TRY(ctx, hipGetLastError());
     return EDGC_OK;
 }
@@ -2800,16 +2805,16 @@ static int compress_impl(edgc_ctx* ctx, Group& g, const TensorScratch* cap, uint
     if (phase == 1) {
         int rc = run_pass_p<NP, RT>(ctx, g, cap, true, st);
         if (rc != EDGC_OK) return rc;
-        constexpr uint32_t RP = RT * 32;
+        const uint32_t pw = g.r <= 16 ? 16u : RT * 32u;                    // part_width
         uint32_t blocks = 0;
         double bytes = 0.0;
         for (uint32_t i = 0; i < g.count; ++i) {
             TensorArgs& t = g.t[i];
             t.first = g.first[i] = blocks;
-            blocks += cdiv(static_cast<uint64_t>(t.m) * (RP / 4), 256);
+            blocks += cdiv(static_cast<uint64_t>(t.m) * (pw / 4), 256);
             bytes += 4.0 * t.m * g.r * (t.sp + 1);
         }
-        EDGC_LAUNCH(ctx, st, KID_REDUCE_Q, bytes, 0.0, (k_reduce_q<256><<<blocks, 256, 0, st>>>(g, RP, 1)));
+        EDGC_LAUNCH(ctx, st, KID_REDUCE_Q, bytes, 0.0, (k_reduce_q<256><<<blocks, 256, 0, st>>>(g, pw, 1)));
         EDGC_HIP_TRY(ctx, hipGetLastError());
         return EDGC_OK;
     }

@@ -94,6 +94,17 @@ __device__ __forceinline__ size_t pt_unit(uint32_t row16, uint32_t ct, uint32_t 
     return ((static_cast<size_t>(row16) * RT + ct) * NP + plane) * 64 + unit;
 }
 
+// Columns of a split partial: the padded rank, but 16 up to rank 16 (the accumulators hold 32 there, of which the upper half is
+// zero): half the bytes to write and to sum.  Between events, 32 / 16: hidden-2048 fp32 block at rank 16, the Q-pass 33.4 to 35.5 /
+// 30.5 us, the sums of P 3.0 / 2.3; three odd fp32 matrices at rank 13 3.8 / 3.0 and 2.5 / 2.1.  (Stores under a condition, not an
+// early end of the lanes without: that one changed the registers of the kernels for small groups, 18.4 / 20.9 us.)
+template <int RT>
+__device__ __forceinline__ uint32_t part_width(uint32_t r)
+{
+    if constexpr (RT == 1) return r <= 16 ? 16u : 32u;
+    return RT * 32u;
+}
+
 // Tensor of a grouped launch that owns block `bid` (tensors with no blocks are skipped).
 // Blocks keep the order of the grid: consecutive blocks, which the dispatcher spreads
 // round-robin over the 8 XCDs, walk along the rows of the matrix, so that neighbouring

@@ -234,13 +234,15 @@ __global__ __launch_bounds__(64 * WAVES, 2) void k_pass_p_deferred_full(const Gr
 #undef EDGC_FULL_FETCH_DG
 #undef EDGC_FULL_FETCH_Q
 
-    // partial P of this k-range: part[s][row][c], c over the padded rank
+    // partial P of this k-range: part[s][row][c], c < part_width
+    const uint32_t pw = part_width<RT>(r);
 #pragma unroll
     for (int ct = 0; ct < RT; ++ct)
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const uint32_t row = row0 + 8 * (v / 4) + 4 * g + (v % 4);
-            part[(static_cast<size_t>(s) * m + row) * RP + ct * 32 + jl] = accp[ct][v];
+            if (RT > 1 || static_cast<uint32_t>(jl) < pw)
+                part[(static_cast<size_t>(s) * m + row) * pw + ct * 32 + jl] = accp[ct][v];
         }
 }
 

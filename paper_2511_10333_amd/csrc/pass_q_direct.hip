@@ -21,7 +21,6 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void k_pass_q_direct(const Group g
     const bf16x8* __restrict__ pt = static_cast<const bf16x8*>(ta.pt);
     float* __restrict__ part = ta.part;
     const uint32_t m = ta.m, n = ta.n, sps = ta.d0, CB = ta.d1;
-    constexpr int RP = RT * 32;
     __shared__ __attribute__((aligned(16))) float sums[WR * WC * 64 * 32];      // [column group][wave][column][factor column]
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -112,7 +111,8 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void k_pass_q_direct(const Group g
 #undef EDGC_QDIRECT_FETCH_D
 
     // accumulator (ct, t, v) of lane l: column j = jw0 + 2 rho + t with rho = 8*(v/4) + 4*g + v%4, factor column
-    // c = ct*32 + jl  ->  part[s][j][c], 32 factor columns at a time through LDS
+    // c = ct*32 + jl  ->  part[s][j][c], c < part_width, 32 factor columns at a time through LDS
+    const uint32_t pw = part_width<RT>(grp.r);
     constexpr int ITEMS = WC * 64 * 8, NTH = 64 * WR * WC;           // of four factor columns
     float4* const s4 = reinterpret_cast<float4*>(sums);
 #pragma unroll
@@ -135,7 +135,8 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void k_pass_q_direct(const Group g
                 x.x += y.x; x.y += y.y; x.z += y.z; x.w += y.w;
             }
             const uint32_t j = (cb * WC + c) * 64u + e / 8;
-            if (j < n) *reinterpret_cast<float4*>(part + (static_cast<size_t>(s) * n + j) * RP + ct * 32 + e % 8 * 4) = x;
+            if (j < n && (RT > 1 || e % 8 * 4u < pw))
+                *reinterpret_cast<float4*>(part + (static_cast<size_t>(s) * n + j) * pw + ct * 32 + e % 8 * 4) = x;
         }
     }
 }

@@ -128,7 +128,8 @@ __global__ __launch_bounds__(64 * WAVES, 2) void k_pass_q_full(const Group grp)
 #undef EDGC_QFULL_FETCH_PT
 
     // accumulator (ct, t, v) of lane l: column j = jw0 + NT*rho + t with rho = 8*(v/4) + 4*g + v%4,
-    // factor column c = ct*32 + jl  ->  part[s][j][c]
+    // factor column c = ct*32 + jl  ->  part[s][j][c], c < part_width
+    const uint32_t pw = part_width<RT>(grp.r);
 #pragma unroll
     for (int ct = 0; ct < RT; ++ct)
 #pragma unroll
@@ -136,7 +137,8 @@ __global__ __launch_bounds__(64 * WAVES, 2) void k_pass_q_full(const Group grp)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const uint32_t j = jw0 + NT * (8 * (v / 4) + 4 * g + (v % 4)) + t;
-                part[(static_cast<size_t>(s) * n + j) * RP + ct * 32 + jl] = acc[ct][t][v];
+                if (RT > 1 || static_cast<uint32_t>(jl) < pw)
+                    part[(static_cast<size_t>(s) * n + j) * pw + ct * 32 + jl] = acc[ct][t][v];
             }
 }
 
