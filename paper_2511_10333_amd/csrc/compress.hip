@@ -323,8 +323,14 @@ __host__ __device__ inline void tri_tile(int t, int T, int& ta, int& tb)
 
 // FROM_P: P is in the caller's buffer and not in partials (the second phase of a split call).  A template: as a branch it
 // costs the rank-128 kernel 24 registers (46 against 42 us on the hidden-5120 block).
-template <int T16, bool FROM_P>
-__global__ __launch_bounds__(256) void k_reduce_gram(const Group grp, uint32_t pw)
+// What bounds it: a block's chain of the partials' loads (a CU's fetch rate: 32 KB times the splits for 64 rows above rank 64), LDS and
+// MFMA.  Above rank 32 eight waves share a chunk of 64 rows, and a chunk is of 32 or 16 rows where 64 would leave most CUs
+// without one.  Between events, always four waves of 64 rows / this: 1024 x 1024 fp32 at rank 100 14.7 / 4.7 us, 300 x 3000 23.8 / 8.0,
+// 8191 x 4097 bf16 16.5 / 11.5 (and 1.3 more to add up its 256 sets), 2047 x 2049 at rank 48 11.0 / 4.9, hidden-768 block at
+// rank 64 9.0 / 4.8, hidden-1024 block at rank 48 7.6 / 4.3, 512 x 512 at rank 40 5.6 / 2.1; with chunks of 64: hidden-2048 block at
+// rank 128 25.9 / 24.3, hidden-4096 block at rank 64 14.5 / 13.3, hidden-5120 block at rank 128 35.1 / 34.1.
+template <int T16, bool FROM_P, int WAVES, int ROWS>
+__global__ __launch_bounds__(64 * WAVES) void k_reduce_gram(const Group grp, uint32_t pw)
 {
     const TensorArgs& ta_ = tensor_of(grp, blockIdx.x);
     const float* __restrict__ part = ta_.part;
@@ -335,35 +341,37 @@ __global__ __launch_bounds__(256) void k_reduce_gram(const Group grp, uint32_t p
     constexpr int CW = 16 * T16;
     constexpr int LD = CW + 16;                      // floats; 4 rows x 16 columns per read: 2-way at worst
     constexpr int NTILE = T16 * (T16 + 1) / 2;
-    constexpr int TPW = (NTILE + 3) / 4;             // Gram tiles per wave
-    __shared__ __attribute__((aligned(16))) float Ps[64 * LD];
+    constexpr int NTH = 64 * WAVES, IT = ROWS * CW / 4 / NTH;     // items of four columns per thread
+    static_assert(IT * NTH * 4 == ROWS * CW, "the chunk divides evenly among the threads");
+    constexpr int TPW = (NTILE + WAVES - 1) / WAVES; // Gram tiles per wave
+    __shared__ __attribute__((aligned(16))) float Ps[ROWS * LD];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 
     int ta[TPW], tb[TPW];
 #pragma unroll
     for (int q = 0; q < TPW; ++q) {
-        const int t = wave + 4 * q;
+        const int t = wave + WAVES * q;
         tri_tile(t < NTILE ? t : 0, T16, ta[q], tb[q]);
     }
     f64x4 acc[TPW];
 #pragma unroll
     for (int q = 0; q < TPW; ++q) acc[q] = f64x4{0.0, 0.0, 0.0, 0.0};
 
-    const uint32_t total_chunks = (m + 63) / 64;
+    const uint32_t total_chunks = (m + ROWS - 1) / ROWS;
     const uint32_t ch_begin = bid * chunks_per_block;
     const uint32_t ch_end = min(total_chunks, ch_begin + chunks_per_block);
     const size_t sstride = static_cast<size_t>(m) * pw;
     for (uint32_t ch = ch_begin; ch < ch_end; ++ch) {
-        const uint32_t row0 = ch * 64;
+        const uint32_t row0 = ch * ROWS;
         __syncthreads();                             // previous chunk's Gram reads are done
-        // the sums of all T16 items of a thread advance together, DEP splits at a time, so that
-        // DEP * T16 independent 16-byte loads are in flight (the order of the additions per element
+        // the sums of all IT items of a thread advance together, DEP splits at a time, so that
+        // DEP * IT independent 16-byte loads are in flight (the order of the additions per element
         // is the split order, whatever the grouping)
-        float4 v[T16];
-        const float* src[T16];
+        float4 v[IT];
+        const float* src[IT];
 #pragma unroll
-        for (int it = 0; it < T16; ++it) {
-            const int idx = tid + 256 * it;
+        for (int it = 0; it < IT; ++it) {
+            const int idx = tid + NTH * it;
             const int i = idx / (CW / 4), c4 = (idx % (CW / 4)) * 4;
             const uint32_t row = min(row0 + i, m - 1);       // rows past the end are loaded but not used
             v[it] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -376,32 +384,32 @@ __global__ __launch_bounds__(256) void k_reduce_gram(const Group grp, uint32_t p
                 if (static_cast<uint32_t>(c4) + 3 < r) v[it].w = x.w;
             }
         }
-        constexpr int DEP = T16 >= 4 ? 2 : 4;            // splits per round
+        constexpr int DEP = T16 >= 4 && IT > 1 ? 2 : 4;  // splits per round
         uint32_t sp = 0;
         for (; sp + DEP <= S; sp += DEP) {
-            float4 x[DEP][T16];
+            float4 x[DEP][IT];
 #pragma unroll
             for (int u = 0; u < DEP; ++u)
 #pragma unroll
-                for (int it = 0; it < T16; ++it)
+                for (int it = 0; it < IT; ++it)
                     x[u][it] = *reinterpret_cast<const float4*>(src[it] + (sp + u) * sstride);
 #pragma unroll
             for (int u = 0; u < DEP; ++u)
 #pragma unroll
-                for (int it = 0; it < T16; ++it) {
+                for (int it = 0; it < IT; ++it) {
                     v[it].x += x[u][it].x; v[it].y += x[u][it].y; v[it].z += x[u][it].z; v[it].w += x[u][it].w;
                 }
         }
         for (; sp < S; ++sp) {
 #pragma unroll
-            for (int it = 0; it < T16; ++it) {
+            for (int it = 0; it < IT; ++it) {
                 const float4 x0 = *reinterpret_cast<const float4*>(src[it] + sp * sstride);
                 v[it].x += x0.x; v[it].y += x0.y; v[it].z += x0.z; v[it].w += x0.w;
             }
         }
 #pragma unroll
-        for (int it = 0; it < T16; ++it) {
-            const int idx = tid + 256 * it;
+        for (int it = 0; it < IT; ++it) {
+            const int idx = tid + NTH * it;
             const int i = idx / (CW / 4), c4 = (idx % (CW / 4)) * 4;
             const uint32_t row = row0 + i;
             if (!FROM_P && row < m) {
@@ -422,7 +430,7 @@ __global__ __launch_bounds__(256) void k_reduce_gram(const Group grp, uint32_t p
         __syncthreads();
         const float* pk = Ps + (lane >> 4) * LD + (lane & 15);
 #pragma unroll 4
-        for (int k0 = 0; k0 < 64; k0 += 4) {
+        for (int k0 = 0; k0 < ROWS; k0 += 4) {
 #pragma unroll
             for (int q = 0; q < TPW; ++q) {
                 // rows from column tile tb, columns from column tile ta: the tile below the diagonal
@@ -436,7 +444,7 @@ __global__ __launch_bounds__(256) void k_reduce_gram(const Group grp, uint32_t p
     // i = lane/16 + 4v, j = lane%16 (the lower triangle, which is the one k_chol factors)
 #pragma unroll
     for (int q = 0; q < TPW; ++q) {
-        const int t = wave + 4 * q;
+        const int t = wave + WAVES * q;
         if (t < NTILE) {
             double* out = gram_part + (static_cast<size_t>(bid) * NTILE + t) * 256;
 #pragma unroll
@@ -2566,12 +2574,16 @@ static int run_orthonormalise(edgc_ctx* ctx, Group& g, const TensorScratch* cap,
     uint32_t tgt[kMaxGroup];
     share_targets(g, static_cast<uint32_t>(ctx->num_cu) * 2, tgt);
 
-    // P = sum of the partials, per-block Gram tiles
-    uint32_t blocks = 0;
+    // P = sum of the partials, per-block Gram tiles; above rank 32 half chunks while they fit one round over the CUs, and
+    // quarters while they fit half of one
+    uint32_t blocks = 0, whole_chunks = 0;
+    for (uint32_t i = 0; i < g.count; ++i) whole_chunks += cdiv(g.t[i].m, 64u);
+    const uint32_t cu = static_cast<uint32_t>(ctx->num_cu);
+    const uint32_t chunk = t16 < 4 || 2 * whole_chunks > cu ? 64u : 8 * whole_chunks > cu ? 32u : 16u;
     double bytes = 0.0, flops = 0.0;
     for (uint32_t i = 0; i < g.count; ++i) {
         TensorArgs& t = g.t[i];
-        const uint32_t chunks = cdiv(t.m, 64);
+        const uint32_t chunks = cdiv(t.m, chunk);
         const uint32_t cpb = std::max(1u, chunks / tgt[i]);
         const uint32_t NB = cdiv(chunks, cpb);
         if (static_cast<uint64_t>(NB) * ne > cap[i].gram_part_elems)
@@ -2586,14 +2598,14 @@ static int run_orthonormalise(edgc_ctx* ctx, Group& g, const TensorScratch* cap,
     }
     {
         ProfScope prof_scope_(ctx, st, KID_REDUCE_GRAM, bytes, flops);
-#define EDGC_GRAM(T_)                                                       \
-    if (from_p) k_reduce_gram<T_, true><<<blocks, 256, 0, st>>>(g, pw);     \
-    else k_reduce_gram<T_, false><<<blocks, 256, 0, st>>>(g, pw);
+#define EDGC_GRAM(T_, W_, R_)                                                              \
+    if (from_p) k_reduce_gram<T_, true, W_, R_><<<blocks, 64 * W_, 0, st>>>(g, pw);        \
+    else k_reduce_gram<T_, false, W_, R_><<<blocks, 64 * W_, 0, st>>>(g, pw);
         switch (t16) {
-        case 1: EDGC_GRAM(1) break;
-        case 2: EDGC_GRAM(2) break;
-        case 4: EDGC_GRAM(4) break;
-        default: EDGC_GRAM(8) break;
+        case 1: EDGC_GRAM(1, 4, 64) break;
+        case 2: EDGC_GRAM(2, 4, 64) break;
+        case 4: if (chunk == 64) { EDGC_GRAM(4, 8, 64) } else if (chunk == 32) { EDGC_GRAM(4, 8, 32) } else { EDGC_GRAM(4, 4, 16) } break;
+        default: if (chunk == 64) { EDGC_GRAM(8, 8, 64) } else if (chunk == 32) { EDGC_GRAM(8, 8, 32) } else { EDGC_GRAM(8, 8, 16) } break;
         }
 #undef EDGC_GRAM
     }

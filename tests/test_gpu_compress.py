@@ -467,3 +467,25 @@ def test_q_pass_of_waves_by_themselves(m, n, r, dtype, monkeypatch):
         assert torch.equal(out[form][0], D) and torch.equal(out[form][1], P)
         assert bool(((out[form][2].double() - Q.double()).abs() <= bound).all())
         assert not out[form][2][:, r:].any()
+
+
+@pytest.mark.parametrize("m,n,r", [(40, 500, 33), (129, 300, 64), (300, 3000, 100), (2047, 140, 100), (2049, 140, 70), (8192, 140, 40),
+                                   (8193, 140, 128), (4097, 150, 128), (17, 40, 17), (1040, 66, 65)])
+def test_orthonormalisation_of_few_rows_at_high_rank(m, n, r):
+    """Chunks of 16, 32 and 64 rows on both sides of where one takes over from the other, and rows that end inside one: P^ is
+    orthonormal and spans D Q, and Q = D^T P^ (operands of 17 bits: 2^-16 of |D| |P^| per column)."""
+    g = torch.Generator(device="cuda").manual_seed(m + n + r)
+    G = torch.randn(m, n, device="cuda", generator=g)
+    ld = (r + 3) // 4 * 4
+    D, P, Q = torch.zeros(m, n, device="cuda"), torch.zeros(m, ld, device="cuda"), torch.zeros(n, ld, device="cuda")
+    q0 = torch.linalg.qr(torch.randn(n, r, device="cuda", generator=g)).Q
+    Q[:, :r] = q0
+    c = edgc.Context(0, max_bins=256, max_rank=128, max_rows=m, max_cols=n)
+    c.compress(G, D, True, Q, P, r)
+    torch.cuda.synchronize()
+    c.close()
+    p, q, y = P[:, :r].double(), Q[:, :r].double(), G.double() @ q0.double()
+    assert float((p.t() @ p - torch.eye(r, device="cuda", dtype=torch.float64)).abs().max()) < 1e-6
+    # D Q in operands of 17 bits: each column within 2^-16 of |D| |q| of the span
+    assert float((y - p @ (p.t() @ y)).norm(dim=0).max() / G.double().norm()) < 2.0 ** -16
+    assert float((q - G.double().t() @ p).norm(dim=0).max() / G.double().norm()) < 2.0 ** -16
