@@ -2734,9 +2734,12 @@ static int run_pass_q(edgc_ctx* ctx, Group& g, const TensorScratch* cap, hipStre
     // 64 per block of it.  One, four waves on the rows; two where rows are not whole lines and a wave's strips share lines.
     uint32_t groups = 0;
     if constexpr (RT <= 2) {
-        bool lines = true;
-        for (uint32_t i = 0; i < g.count; ++i) lines = lines && whole_lines(g.t[i].E, 4ull * g.t[i].n);
-        groups = ctx->tune_qdirect >= 0 ? static_cast<uint32_t>(ctx->tune_qdirect) : q_direct_groups(static_cast<double>(d_bytes), RP, lines);
+        bool lines = true, pairs = true;               // (its lanes read two columns: a matrix of one keeps k_pass_q)
+        for (uint32_t i = 0; i < g.count; ++i) {
+            lines = lines && whole_lines(g.t[i].E, 4ull * g.t[i].n);
+            pairs = pairs && g.t[i].n >= 2;
+        }
+        if (pairs) groups = ctx->tune_qdirect >= 0 ? static_cast<uint32_t>(ctx->tune_qdirect) : q_direct_groups(static_cast<double>(d_bytes), RP, lines);
         if (groups) qwaves = 0;
     }
     const uint32_t W4 = groups ? 64u * groups : (qwaves ? qwaves : 4u) * 32 * NT;

@@ -1,9 +1,10 @@
 // Q-pass  Q_partial[s] = D[row range s, :]^T P^[row range s, :]  (Sec. II-B: the second product of the PowerSGD step)
-// up to rank 64, any shape: every wave by itself.  A lane's loads of D are A-fragments as they stand, as in k_pass_q
-// (compress.hip); the B-fragments of P^ come straight from memory, where k_apply has laid them out in the order of a wave's
-// lanes (pt_unit): 1 KB loads that the XCD's L2 serves, no LDS tile and no barrier in the loop.  The waves of a block take
-// the stages of its row range in turn (WR of them to a column group of 64, WC groups) and add their sums up in LDS at the end,
-// in wave order, so that a block of four waves writes one partial where four blocks would write four.
+// up to rank 64, any shape of at least two columns (checked on the host): every wave by itself.  A lane's loads of D are
+// A-fragments as they stand, as in k_pass_q (compress.hip); the B-fragments of P^ come straight from memory, where
+// k_apply has laid them out in the order of a wave's lanes (pt_unit): 1 KB loads that the XCD's L2 serves, no LDS tile
+// and no barrier in the loop.  The waves of a block take the stages of its row range in turn (WR of them to a column group
+// of 64, WC groups) and add their sums up in LDS at the end, in wave order, so that a block of four waves writes one
+// partial where four blocks would write four.
 // What bounds it: the last-level cache for a D of some size (a read of it without arithmetic: 64 MB 13.6 us between events),
 // launch and latency for a small one.  k_pass_q and k_pass_q_full keep one to two waves per SIMD in step by a barrier
 // per stage.  Between events, these / this, D just written: 4096 x 4096 fp32 at rank 32 22.8 / 15.9 us, hidden-2048 fp32 block at

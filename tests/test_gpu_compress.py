@@ -442,7 +442,7 @@ def test_sums_of_many_partials_in_few_columns(m, n, r):
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("m,n,r", [(64, 64, 8), (40, 33, 3), (33, 65, 32), (65, 127, 16), (257, 1001, 20), (1000, 66, 33), (4100, 70, 64),
-                                   (515, 4160, 40), (256, 128, 1), (321, 130, 64), (9000, 40, 5)])
+                                   (515, 4160, 40), (256, 128, 1), (321, 130, 64), (9000, 40, 5), (70, 1, 1), (70, 2, 2), (2, 70, 1)])
 def test_q_pass_of_waves_by_themselves(m, n, r, dtype, monkeypatch):
     """k_pass_q_direct, with one column group per block and with two, against k_pass_q: edges of stages and strips, rows at odd
     addresses, fewer rows than a block's waves take.  The products are the same and exact in fp32; what differs is the order of
