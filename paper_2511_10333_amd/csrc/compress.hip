@@ -2578,8 +2578,8 @@ static int run_orthonormalise(edgc_ctx* ctx, Group& g, const TensorScratch* cap,
     // quarters while they fit half of one
     uint32_t blocks = 0, whole_chunks = 0;
     for (uint32_t i = 0; i < g.count; ++i) whole_chunks += cdiv(g.t[i].m, 64u);
-    const uint32_t cu = static_cast<uint32_t>(ctx->num_cu);
-    const uint32_t chunk = t16 < 4 || 2 * whole_chunks > cu ? 64u : 8 * whole_chunks > cu ? 32u : 16u;
+    const uint32_t most = std::min(static_cast<uint32_t>(ctx->num_cu), kGramSets);
+    const uint32_t chunk = t16 < 4 || 2 * whole_chunks > most ? 64u : 8 * whole_chunks > most ? 32u : 16u;
     double bytes = 0.0, flops = 0.0;
     for (uint32_t i = 0; i < g.count; ++i) {
         TensorArgs& t = g.t[i];
