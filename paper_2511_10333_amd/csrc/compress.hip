@@ -2730,16 +2730,22 @@ static int run_pass_q(edgc_ctx* ctx, Group& g, const TensorScratch* cap, hipStre
     // with one row split) aim at three blocks per CU: 594 against 649 us
     uint64_t d_bytes = 0;
     for (uint32_t i = 0; i < g.count; ++i) d_bytes += 4ull * g.t[i].m * g.t[i].n;
-    // Up to rank 64, and while the last-level cache can hold D, waves by themselves (pass_q_direct.hip); `groups`: column groups of
-    // 64 per block of it.  One, four waves on the rows; two where rows are not whole lines and a wave's strips share lines.
-    uint32_t groups = 0;
+    // Up to rank 64, and while the last-level cache can hold D, waves by themselves (pass_q_direct.hip).  fp32: `groups` column groups
+    // of 64 per block, on row splits of their own.  bf16: strips of `strip` columns per wave, on those of the other kernels.
+    uint32_t groups = 0, strip = 0;
     if constexpr (RT <= 2) {
-        bool lines = true, pairs = true;               // (its lanes read two columns: a matrix of one keeps k_pass_q)
+        bool lines = true, pairs = true;               // (a lane reads two columns: a matrix of one keeps k_pass_q)
         for (uint32_t i = 0; i < g.count; ++i) {
             lines = lines && whole_lines(g.t[i].E, 4ull * g.t[i].n);
             pairs = pairs && g.t[i].n >= 2;
         }
-        if (pairs) groups = ctx->tune_qdirect >= 0 ? static_cast<uint32_t>(ctx->tune_qdirect) : q_direct_groups(static_cast<double>(d_bytes), RP, lines);
+        if (pairs) {
+            if constexpr (NP == 2)
+                groups = ctx->tune_qdirect >= 0 ? static_cast<uint32_t>(ctx->tune_qdirect) : q_direct_groups(static_cast<double>(d_bytes), RP, lines);
+            else
+                strip = ctx->tune_qdirect >= 0 ? (ctx->tune_qdirect == 0 ? 0u : ctx->tune_qdirect == 2 && RT == 1 ? 32u : 64u)
+                                               : q_ring_strip(static_cast<double>(d_bytes), RP, qwaves != 0);
+        }
         if (groups) qwaves = 0;
     }
     const uint32_t W4 = groups ? 64u * groups : (qwaves ? qwaves : 4u) * 32 * NT;
@@ -2767,13 +2773,16 @@ static int run_pass_q(edgc_ctx* ctx, Group& g, const TensorScratch* cap, hipStre
         t.d1 = CB;
         t.sq = S;
         t.first = g.first[i] = blocks;
-        blocks += CB * S;
+        blocks += (strip ? cdiv(t.n, 4u * strip) : CB) * S;
         bytes += 4.0 * t.m * t.n;
         flops += 2.0 * t.m * t.n * g.r;
     }
     if (groups) {
         ProfScope prof_scope_(ctx, st, KID_PASS_Q, bytes, flops);
-        EDGC_HIP_TRY(ctx, launch_pass_q_direct(g, DT, RT, blocks, groups, st));
+        EDGC_HIP_TRY(ctx, launch_pass_q_direct(g, RT, blocks, groups, st));
+    } else if (strip) {
+        ProfScope prof_scope_(ctx, st, KID_PASS_Q, bytes, flops);
+        EDGC_HIP_TRY(ctx, launch_pass_q_ring(g, RT, blocks, strip, st));
     } else if (qwaves) {
         ProfScope prof_scope_(ctx, st, KID_PASS_Q, bytes, flops);
         EDGC_HIP_TRY(ctx, launch_pass_q_full(g, DT, RT, blocks, qwaves, st));

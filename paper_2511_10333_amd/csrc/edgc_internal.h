@@ -336,8 +336,9 @@ hipError_t prepare_decompress_full();
 bool pass_q_full_applies(const Group& g, edgc_dtype dt, int rank_tiles, uint32_t waves);
 hipError_t launch_pass_q_full(const Group& g, edgc_dtype dt, int rank_tiles, uint32_t blocks, uint32_t waves,
                               hipStream_t st);
-// pass_q_direct.hip: the Q-pass up to rank 64, waves by themselves; a block of four takes one column group of 64 or two
-hipError_t launch_pass_q_direct(const Group& g, edgc_dtype dt, int rank_tiles, uint32_t blocks, uint32_t column_groups,
-                                hipStream_t st);
+// pass_q_direct.hip: the Q-pass up to rank 64, waves by themselves.  fp32: a block of four takes one column group of 64 or two;
+// bf16: each of four a strip of 64 columns or (rank 32) of 32, on the row splits of the kernels with barriers
+hipError_t launch_pass_q_direct(const Group& g, int rank_tiles, uint32_t blocks, uint32_t column_groups, hipStream_t st);
+hipError_t launch_pass_q_ring(const Group& g, int rank_tiles, uint32_t blocks, uint32_t strip, hipStream_t st);
 
 }  // namespace edgc

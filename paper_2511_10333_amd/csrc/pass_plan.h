@@ -69,27 +69,43 @@ inline uint32_t pass_p_step(uint32_t count, const uint32_t* across, const uint32
     return step;
 }
 
-// The Q-pass of waves by themselves (pass_q_direct.hip), up to rank 64.  Column groups per block, 0 where the other kernels stay:
-// that is a D that the last-level cache cannot hold, where every form waits for HBM (per pass without an estimate, others / this:
-// hidden-4096 fp32 block at rank 16 824 / 824 to 831 us, stored at rank 64 1157 / 1159 to 1168, hidden-3001 bf16 783 / 800, the Q-pass of
-// hidden-5120 bf16 at rank 64 238 / 243; stored hidden-2304 (255 MB) at rank 64 58 / 65), while hidden-2048 (201 MB) takes 215 / 209
-// and stored in bf16 236 / 228.  Two groups where rows are not whole lines and strips of one group would share them: three odd fp32
-// matrices at rank 13 99.0 / 96.3 with one / 94.5 with two; above rank 32 the sums of two weigh more: 8191 x 4097 bf16 at rank 64 252 /
-// 251 / 257, 2047 x 2049 89.8 / 87.4 / 89.9.
+// The Q-pass of waves by themselves (pass_q_direct.hip), up to rank 64, fp32 gradients.  Column groups per block, 0 where the other
+// kernels stay: that is a D that the last-level cache cannot hold, where every form waits for HBM (per pass without an estimate, others /
+// this: hidden-4096 block at rank 16 824 / 824 to 831 us, stored at rank 64 1157 / 1159 to 1168; stored hidden-2304 (255 MB) at rank
+// 64 58 / 65, the Q-pass alone), while hidden-2048 (201 MB) takes 215 / 209.  Two groups where rows are not whole lines and strips of one
+// group would share them: three odd matrices at rank 13 95.8 / 93.6 with one / 92.1 with two, 3002 x 5002 91.4 / 90.6 / 90.8;
+// above rank 32 the sums of two weigh more: 8191 x 4097 at rank 64 261.0 / 261.5 / 263.9, 2047 x 2049 82.3 / 80.1 / 81.7.
 inline uint32_t q_direct_groups(double d_bytes, uint32_t rp, bool lines)
 {
     if (d_bytes > 224.0 * 1024 * 1024) return 0;
     return lines || rp > 32 ? 1 : 2;
 }
-// Blocks (of four waves) per CU.  Two / three / four: 4096 x 4096 fp32 at rank 32, two iterations, 150.9 / 152.0 / 149.8, two hidden-768
-// bf16 blocks 65.8 / 65.7 / 64.9, hidden-2048 fp32 214.2 / 210.9 / 209.4; above rank 32 three waves per SIMD have no registers: 3072 x
-// 3072 bf16 at rank 64 96.2 / 98.0 / 97.8; two groups: three odd matrices 94.5 / 94.4 / 97.3.
+// Blocks (of four waves) per CU aimed at.  Three are resident up to rank 32 (150 registers) and two above (190); a fourth, which begins
+// as others end, is worth its row splits where a block would have few: two / three / four, two hidden-768 blocks at rank 16 77.3 / 76.9 /
+// 75.2, 4096 x 4096 at rank 32 148.8 / 149.1 / 149.1, hidden-2048 block at rank 16 207.2 / 204.6 / 205.0; above rank 32 3072 x
+// 3072 at rank 64 91.6 / 93.2 / 93.4; two groups: three odd matrices 92.8 / 93.2 / 95.8.
 inline uint32_t q_direct_per_cu(uint32_t groups, uint32_t rp) { return groups == 1 && rp <= 32 ? 4 : 2; }
 // ... but beyond 32 row splits no more than two per CU are worth their partials (tall matrices of few columns): 50257 x 1024 bf16 at
 // rank 32 280.6 / 282.3 / 285.3, 50257 x 768 fp32 220.9 / 222.9 / 225.2, 100000 x 96 bf16 87.6 / 87.4 / 92.2, 16384 x 1024 92.3 / 92.4 / 93.9.
 inline uint32_t q_direct_splits(uint32_t splits, uint32_t per_cu)
 {
     return per_cu > 2 && splits > 32 ? std::max(32u, splits * 2 / per_cu) : splits;
+}
+
+// bf16: columns per wave of k_pass_q_ring, 0 where k_pass_q and k_pass_q_full stay.  It takes their row splits, which give one wave of 64
+// columns per SIMD up to 80 MB of D: there strips of 32, twice the waves, are the fastest.  Between events, those / 64 / 32 at rank 32:
+// 1024 x 1024 4.0 / 3.3 / 2.3 us, 2048 x 2048 7.3 / 6.5 / 5.8, 4096 x 4096 16.3 / 12.4 / 12.7, 16384 x 1024 12.9 / 13.1 / 10.8,
+// hidden-1024 block 12.5 / 10.1 / 8.5, two hidden-768 blocks 12.6 / 11.8 / 9.7, 3002 x 5002 13.2 / 12.9 / 12.1.  With two waves per SIMD, above
+// that, the passes of all forms are the same, and of ragged rows the ones here the slower (hidden-1500 block at rank 16 160 / 175 / 175,
+// hidden-768 block and 50257 x 768 190 / 206 / 207).  Above rank 32 there are registers for 64 columns only, and groups of whole
+// tiles of some size, which k_pass_q_full takes, gain nothing: 4096 x 4096 at rank 64 15.5 / 15.5, hidden-1024 block 12.0 / 13.0, but 2048 x 2048
+// 11.9 / 9.4, 1024 x 1024 5.8 / 4.8, two hidden-768 blocks 15.7 / 13.9.
+inline uint32_t q_ring_strip(double d_bytes, uint32_t rp, bool whole_tiles)
+{
+    constexpr double MB = 1024.0 * 1024;
+    if (d_bytes > 80 * MB) return 0;
+    if (rp > 32) return whole_tiles && d_bytes > 32 * MB ? 0 : 64;
+    return 32;
 }
 
 // Stages (of 64 columns) per block of the decompress.  `splits`: into how many its share of the blocks aimed at would cut the

@@ -2,21 +2,27 @@
 // up to rank 64, any shape of at least two columns (checked on the host): every wave by itself.  A lane's loads of D are
 // A-fragments as they stand, as in k_pass_q (compress.hip); the B-fragments of P^ come straight from memory, where
 // k_apply has laid them out in the order of a wave's lanes (pt_unit): 1 KB loads that the XCD's L2 serves, no LDS tile
-// and no barrier in the loop.  The waves of a block take the stages of its row range in turn (WR of them to a column group
+// and no barrier in the loop.
+//   fp32 gradients, k_pass_q_direct: the waves of a block take the stages of its row range in turn (WR of them to a column group
 // of 64, WC groups) and add their sums up in LDS at the end, in wave order, so that a block of four waves writes one
 // partial where four blocks would write four.
-// What bounds it: the last-level cache for a D of some size (a read of it without arithmetic: 64 MB 13.6 us between events),
-// launch and latency for a small one.  k_pass_q and k_pass_q_full keep one to two waves per SIMD in step by a barrier
-// per stage.  Between events, these / this, D just written: 4096 x 4096 fp32 at rank 32 22.8 / 15.9 us, hidden-2048 fp32 block at
-// rank 16 39.1 / 34.5, hidden-3584 bf16, one of four shards, at rank 64 32.9 / 30.0; the sums of the partials 5.3 / 3.6 and less.
+//   bf16 gradients, k_pass_q_ring: a wave has a row range to itself, on the splits of k_pass_q and k_pass_q_full, and writes its partial: Q is
+// theirs bit for bit.  (In another order of the sums a last bit of Q turns the bf16 rounding of operands and of the
+// reconstruction: 2e-4 to 7e-4 of the result's norm.  In fp32 it stays a last bit.)
+// What bounds them: the last-level cache for a D of some size (a read of it without arithmetic: 64 MB 13.6 us between events),
+// launch, latency and the partials for a small one.  k_pass_q and k_pass_q_full keep one to two waves per SIMD in step by a barrier
+// per stage.  Between events, those / these, D just written, fp32: 4096 x 4096 at rank 32 18.0 / 11.5 us, hidden-2048 block at
+// rank 16 35 / 31; bf16 (pass_plan.h) two hidden-768 blocks at rank 16 12.6 / 9.5, where row ranges and partials of its own would save
+// nothing, but 2048 x 2048 at rank 32 7.3 / 5.8 where they would save 3.5 more.
 #include "compress_common.h"
 #include "pass_plan.h"
 
 namespace edgc {
 
-template <int NP, int RT, bool STREAM, int WR, int WC>
+template <int RT, bool STREAM, int WR, int WC>
 __global__ __launch_bounds__(64 * WR * WC, 2) void k_pass_q_direct(const Group grp)
 {
+    constexpr int NP = 2;
     const TensorArgs& ta = tensor_of(grp, blockIdx.x);
     const float* __restrict__ D = ta.E;
     const bf16x8* __restrict__ pt = static_cast<const bf16x8*>(ta.pt);
@@ -142,24 +148,162 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void k_pass_q_direct(const Group g
     }
 }
 
-template <int NP, int RT, int WR, int WC>
+template <int NT, bool STREAM>
+__device__ __forceinline__ void load_columns(const float* p, float (&v)[NT])
+{
+    if constexpr (NT == 2) {
+        const Floats2 x = load_pair<STREAM>(p);
+        v[0] = x.x; v[1] = x.y;
+    } else {
+        v[0] = STREAM ? __builtin_nontemporal_load(p) : *p;
+    }
+}
+
+// NT: columns per lane, 32 NT per wave.  Blocks go through the row ranges first, so that the blocks that read the same rows of P^
+// and neighbouring columns of D are a multiple of the number of ranges apart, mostly on one XCD: the other way round 16384 x 1024
+// at rank 32 15.8 / 10.8 us, hidden-1024 block 10.3 / 8.5, but 4096 x 4096 11.1 / 12.7.
+template <int RT, int NT, bool STREAM>
+__global__ __launch_bounds__(256, NT == 1 ? 4 : 2) void k_pass_q_ring(const Group grp)
+{
+    const TensorArgs& ta = tensor_of(grp, blockIdx.x);
+    const float* __restrict__ D = ta.E;
+    const bf16x8* __restrict__ pt = static_cast<const bf16x8*>(ta.pt);
+    float* __restrict__ part = ta.part;
+    const uint32_t m = ta.m, n = ta.n, sps = ta.d0, S = ta.sq;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int jl = lane & 31, g = lane >> 5;
+    const uint32_t lid = blockIdx.x - ta.first;
+    const uint32_t s = lid % S, cb = lid / S;
+    const uint32_t jw0 = (cb * 4u + wave) * (32u * NT);              // first column of this wave
+    if (jw0 >= n) return;
+    const uint32_t st0 = s * sps;                                    // (below the number of stages: S = ceil(stages / sps))
+    const uint32_t st_end = min((m + 63u) / 64u, st0 + sps);
+    const uint32_t whole = min(st_end, m / 64u);                     // the stages before it have all their 64 rows
+    // the lane's columns, past the last one and where that is the first of a pair: as in k_pass_q_direct
+    const uint32_t col = min(jw0 + NT * jl, n - NT);
+    const bool odd_last = NT == 2 && jw0 + NT * jl == n - 1u;
+    const uint32_t off = 8u * g * n + col;                           // element offset in a 16-row step (n < 2^28: fits 32 bits)
+
+    f32x16 acc[RT][NT];
+#pragma unroll
+    for (int ct = 0; ct < RT; ++ct)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[ct][t][v] = 0.0f;
+    // Two places for the halves (32 rows) of a stage: what is requested of D, and the fragments of P^ for it.  Both are requested when the
+    // half before the last has been consumed: loads complete in order, so that fragments requested just before their use would
+    // wait for all of D requested before them (4096 x 4096 at rank 32, strips of 64, the fp32 operands: 22.2 us, so 16.3).
+    // With three or four halves in flight the kernel is no faster.
+    float dv[2][2][8][NT];
+    bf16x8 b[2][2][RT][1];
+
+#define EDGC_QRING_FETCH_D(HALF, H)                                                                       \
+    _Pragma("unroll") for (int u = 0; u < 2; ++u) {                                                       \
+        _Pragma("unroll") for (int q = 0; q < 8; ++q)                                                     \
+            load_columns<NT, STREAM>(D + static_cast<uint64_t>((HALF) * 32u + 16 * u + q) * n + off, dv[H][u][q]); \
+    }
+#define EDGC_QRING_FETCH_P(HALF, H)                                                                       \
+    _Pragma("unroll") for (int u = 0; u < 2; ++u) {                                                       \
+        _Pragma("unroll") for (int ct = 0; ct < RT; ++ct)                                                 \
+            b[H][u][ct][0] = pt[pt_unit<1, RT>((HALF) * 2u + u, ct, 0, lane)];                            \
+    }
+    // half HALF, in place H: to fragments; the half after the next is requested into the registers; multiplied
+#define EDGC_QRING_HALF(HALF, MORE, H)                                                                    \
+    {                                                                                                     \
+        bf16x8 a[2][NT][1];                                                                               \
+        _Pragma("unroll") for (int u = 0; u < 2; ++u) {                                                   \
+            _Pragma("unroll") for (int t = 0; t < NT; ++t) {                                              \
+                float col8[8];                                                                            \
+                _Pragma("unroll") for (int q = 0; q < 8; ++q)                                             \
+                    col8[q] = (t == 0 && odd_last) ? dv[H][u][q][NT - 1] : dv[H][u][q][t];                \
+                pack8<1>(col8, a[u][t]);                                                                  \
+            }                                                                                             \
+        }                                                                                                 \
+        if constexpr (MORE) EDGC_QRING_FETCH_D((HALF) + 2, H)                                             \
+        _Pragma("unroll") for (int u = 0; u < 2; ++u)                                                     \
+            _Pragma("unroll") for (int ct = 0; ct < RT; ++ct)                                             \
+                _Pragma("unroll") for (int t = 0; t < NT; ++t) acc[ct][t] = mma<1>(a[u][t], b[H][u][ct], acc[ct][t]); \
+        if constexpr (MORE) EDGC_QRING_FETCH_P((HALF) + 2, H)                                             \
+    }
+
+    uint32_t st = st0;
+    if (st < whole) {
+        EDGC_QRING_FETCH_D(2 * st, 0)
+        EDGC_QRING_FETCH_P(2 * st, 0)
+        EDGC_QRING_FETCH_D(2 * st + 1, 1)
+        EDGC_QRING_FETCH_P(2 * st + 1, 1)
+        for (; st + 1 < whole; ++st) {
+            EDGC_QRING_HALF(2 * st, true, 0)
+            EDGC_QRING_HALF(2 * st + 1, true, 1)
+        }
+        EDGC_QRING_HALF(2 * st, false, 0)
+        EDGC_QRING_HALF(2 * st + 1, false, 1)
+        ++st;
+    }
+    if (st < st_end) {                                               // the last rows; those past them as zeros
+#pragma unroll 1
+        for (uint32_t half = 2 * st; half < 2 * st + 2; ++half) {
+            EDGC_QRING_FETCH_P(half, 0)
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    const uint32_t row = half * 32u + 16u * u + 8u * g + q;
+                    load_columns<NT, STREAM>(D + static_cast<uint64_t>(min(row, m - 1u)) * n + col, dv[0][u][q]);
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) dv[0][u][q][t] = row < m ? dv[0][u][q][t] : 0.0f;
+                }
+            EDGC_QRING_HALF(half, false, 0)
+        }
+    }
+#undef EDGC_QRING_HALF
+#undef EDGC_QRING_FETCH_P
+#undef EDGC_QRING_FETCH_D
+
+    // accumulator (ct, t, v) of lane l: column j = jw0 + NT*rho + t with rho = 8*(v/4) + 4*g + v%4,
+    // factor column c = ct*32 + jl  ->  part[s][j][c], c < part_width
+    const uint32_t pw = part_width<RT>(grp.r);
+#pragma unroll
+    for (int ct = 0; ct < RT; ++ct)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const uint32_t j = jw0 + NT * (8 * (v / 4) + 4 * g + v % 4) + t;
+                if (j < n && (RT > 1 || static_cast<uint32_t>(jl) < pw))
+                    part[(static_cast<size_t>(s) * n + j) * pw + ct * 32 + jl] = acc[ct][t][v];
+            }
+}
+
+template <int RT, int WR, int WC>
 static hipError_t launch_qdirect(const Group& g, uint32_t blocks, hipStream_t st)
 {
-    if (g.stream) k_pass_q_direct<NP, RT, true, WR, WC><<<blocks, 64 * WR * WC, 0, st>>>(g);
-    else k_pass_q_direct<NP, RT, false, WR, WC><<<blocks, 64 * WR * WC, 0, st>>>(g);
+    if (g.stream) k_pass_q_direct<RT, true, WR, WC><<<blocks, 64 * WR * WC, 0, st>>>(g);
+    else k_pass_q_direct<RT, false, WR, WC><<<blocks, 64 * WR * WC, 0, st>>>(g);
     return hipGetLastError();
 }
 
-template <int WR, int WC>
-static hipError_t launch_qdirect_w(const Group& g, edgc_dtype dt, int rt, uint32_t blocks, hipStream_t st)
+hipError_t launch_pass_q_direct(const Group& g, int rt, uint32_t blocks, uint32_t column_groups, hipStream_t st)
 {
-    if (dt == EDGC_BF16) return rt == 1 ? launch_qdirect<1, 1, WR, WC>(g, blocks, st) : launch_qdirect<1, 2, WR, WC>(g, blocks, st);
-    return rt == 1 ? launch_qdirect<2, 1, WR, WC>(g, blocks, st) : launch_qdirect<2, 2, WR, WC>(g, blocks, st);
+    if (column_groups == 1) return rt == 1 ? launch_qdirect<1, 4, 1>(g, blocks, st) : launch_qdirect<2, 4, 1>(g, blocks, st);
+    return rt == 1 ? launch_qdirect<1, 2, 2>(g, blocks, st) : launch_qdirect<2, 2, 2>(g, blocks, st);
 }
 
-hipError_t launch_pass_q_direct(const Group& g, edgc_dtype dt, int rt, uint32_t blocks, uint32_t column_groups, hipStream_t st)
+template <int RT, int NT>
+static hipError_t launch_qring(const Group& g, uint32_t blocks, hipStream_t st)
 {
-    return column_groups == 1 ? launch_qdirect_w<4, 1>(g, dt, rt, blocks, st) : launch_qdirect_w<2, 2>(g, dt, rt, blocks, st);
+    if (g.stream) k_pass_q_ring<RT, NT, true><<<blocks, 256, 0, st>>>(g);
+    else k_pass_q_ring<RT, NT, false><<<blocks, 256, 0, st>>>(g);
+    return hipGetLastError();
+}
+
+hipError_t launch_pass_q_ring(const Group& g, int rt, uint32_t blocks, uint32_t strip, hipStream_t st)
+{
+    if (rt == 2) return launch_qring<2, 2>(g, blocks, st);
+    return strip == 32 ? launch_qring<1, 1>(g, blocks, st) : launch_qring<1, 2>(g, blocks, st);
 }
 
 }  // namespace edgc

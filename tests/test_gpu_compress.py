@@ -489,3 +489,36 @@ def test_orthonormalisation_of_few_rows_at_high_rank(m, n, r):
     # D Q in operands of 17 bits: each column within 2^-16 of |D| |q| of the span
     assert float((y - p @ (p.t() @ y)).norm(dim=0).max() / G.double().norm()) < 2.0 ** -16
     assert float((q - G.double().t() @ p).norm(dim=0).max() / G.double().norm()) < 2.0 ** -16
+
+
+def _q_pass_forms(m, n, r, dtype, forms, monkeypatch, **env):
+    """(D, P, Q) of one compress from the same inputs under each EDGC_TUNE_QDIRECT."""
+    g = torch.Generator(device="cuda").manual_seed(m * n + r)
+    G = torch.randn(m, n, device="cuda", generator=g)
+    G = G.to(torch.bfloat16) if dtype == "bf16" else G
+    Q0 = torch.zeros(n, (r + 3) // 4 * 4, device="cuda")
+    Q0[:, :r] = torch.randn(n, r, device="cuda", generator=g)
+    for k, v in env.items():
+        monkeypatch.setenv("EDGC_TUNE_" + k, v)
+    out = {}
+    for form in forms:
+        monkeypatch.setenv("EDGC_TUNE_QDIRECT", form)
+        c = edgc.Context(0, max_bins=256, max_rank=64, max_rows=m, max_cols=n)
+        D, P, Q = torch.zeros(m, n, device="cuda"), torch.zeros(m, Q0.shape[1], device="cuda"), Q0.clone()
+        c.compress(G, D, True, Q, P, r)
+        torch.cuda.synchronize()
+        c.close()
+        out[form] = (D, P, Q)
+    return out
+
+
+@pytest.mark.parametrize("stream", ["0", "1"])
+@pytest.mark.parametrize("m,n,r", [(64, 64, 8), (33, 65, 32), (65, 127, 16), (1000, 66, 33), (700, 16387, 5), (700, 16387, 20), (700, 8195, 64),
+                                   (1500, 8194, 40), (640, 4096, 16), (4096, 512, 64), (16384, 64, 3), (9000, 41, 32), (1, 2, 1)])
+def test_q_of_bf16_gradients_does_not_depend_on_the_form_of_the_q_pass(m, n, r, stream, monkeypatch):
+    """k_pass_q_ring, in strips of 64 columns and of 32, is k_pass_q (k_pass_q_full where tiles are whole) bit for bit: one and
+    several stages per wave, rows and columns that end inside a stage and a strip, odd rows, cached and streamed reads."""
+    out = _q_pass_forms(m, n, r, "bf16", ("0", "1", "2"), monkeypatch, STREAM=stream)
+    for form in ("1", "2"):
+        for got, want in zip(out[form], out["0"]):
+            assert torch.equal(got, want)
