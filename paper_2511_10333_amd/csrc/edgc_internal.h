@@ -165,7 +165,8 @@ struct edgc_ctx {
     int tune_pwaves = -1;   // waves per block of that kernel: -1 built-in choice (8 above rank 64), 4 or 8
     int tune_qfull = -1;    // Q-pass of whole-tile groups: -1 built-in choice; 0 the general kernel; 4 / 8 the
                             // pipelined kernel with that many waves per block
-    int tune_qdirect = -1;  // Q-pass of waves by themselves: -1 built-in choice; 0 not; 1 / 2 with that many column groups per block
+    int tune_qdirect = -1;  // Q-pass of waves by themselves: -1 built-in choice; 0 not; 1 / 2: fp32 that many column groups per block,
+                            // bf16 strips of 64 columns / of 32 (above rank 32 of 64)
     int tune_apply = -1;    // k_apply above rank 64: waves (of 16 rows) per block, 4, 8, 9 or 10
     int tune_ept = 0;       // items per thread of the histogram and, twice as many, of the range pass; 0: built-in choice
     int tune_pattern = 1;   // entropy estimate: 1 one read into 16-bit counters per block where that applies

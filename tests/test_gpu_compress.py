@@ -522,3 +522,12 @@ def test_q_of_bf16_gradients_does_not_depend_on_the_form_of_the_q_pass(m, n, r, 
     for form in ("1", "2"):
         for got, want in zip(out[form], out["0"]):
             assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("given,meant", [("3", "2"), ("4", "2"), ("1000", "2"), ("-7", "-1")])
+def test_override_of_the_q_pass_form_out_of_range(given, meant, dtype, monkeypatch):
+    """Taken as the nearest form that there is: every column of Q is computed."""
+    out = _q_pass_forms(700, 515, 20, dtype, (meant, given), monkeypatch)
+    for got, want in zip(out[given], out[meant]):
+        assert torch.equal(got, want)
