@@ -79,6 +79,7 @@ extern "C" int edgc_create(edgc_ctx** out, int hip_device, uint32_t max_bins, ui
     if (const char* e = getenv("EDGC_TUNE_PATTERN")) ctx->tune_pattern = atoi(e);
     if (const char* e = getenv("EDGC_TUNE_QDIRECT")) ctx->tune_qdirect = std::clamp(atoi(e), -1, 2);
     if (const char* e = getenv("EDGC_TUNE_QFULL")) ctx->tune_qfull = atoi(e);
+    if (ctx->tune_qfull >= 0 && ctx->tune_qdirect < 0) ctx->tune_qdirect = 0;       // (a choice among the kernels with a barrier per stage)
     if (const char* e = getenv("EDGC_TUNE_PWAVES")) ctx->tune_pwaves = atoi(e);
     if (const char* e = getenv("EDGC_TUNE_APPLY")) ctx->tune_apply = atoi(e);
     if (const char* e = getenv("EDGC_TUNE_EPT")) ctx->tune_ept = atoi(e);

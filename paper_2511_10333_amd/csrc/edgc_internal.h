@@ -164,7 +164,7 @@ struct edgc_ctx {
                             // 1 / 2 the whole-tile kernel with the Q rows requested early / late
     int tune_pwaves = -1;   // waves per block of that kernel: -1 built-in choice (8 above rank 64), 4 or 8
     int tune_qfull = -1;    // Q-pass of whole-tile groups: -1 built-in choice; 0 the general kernel; 4 / 8 the
-                            // pipelined kernel with that many waves per block
+                            // pipelined kernel with that many waves per block; given, tune_qdirect is 0 unless given too
     int tune_qdirect = -1;  // Q-pass of waves by themselves: -1 built-in choice; 0 not; 1 / 2: fp32 that many column groups per block,
                             // bf16 strips of 64 columns / of 32 (above rank 32 of 64)
     int tune_apply = -1;    // k_apply above rank 64: waves (of 16 rows) per block, 4, 8, 9 or 10

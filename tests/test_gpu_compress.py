@@ -491,8 +491,8 @@ def test_orthonormalisation_of_few_rows_at_high_rank(m, n, r):
     assert float((q - G.double().t() @ p).norm(dim=0).max() / G.double().norm()) < 2.0 ** -16
 
 
-def _q_pass_forms(m, n, r, dtype, forms, monkeypatch, **env):
-    """(D, P, Q) of one compress from the same inputs under each EDGC_TUNE_QDIRECT."""
+def _q_pass_forms(m, n, r, dtype, forms, monkeypatch, knob="QDIRECT", **env):
+    """(D, P, Q) of one compress from the same inputs under each value of EDGC_TUNE_QDIRECT, or of another override."""
     g = torch.Generator(device="cuda").manual_seed(m * n + r)
     G = torch.randn(m, n, device="cuda", generator=g)
     G = G.to(torch.bfloat16) if dtype == "bf16" else G
@@ -502,7 +502,7 @@ def _q_pass_forms(m, n, r, dtype, forms, monkeypatch, **env):
         monkeypatch.setenv("EDGC_TUNE_" + k, v)
     out = {}
     for form in forms:
-        monkeypatch.setenv("EDGC_TUNE_QDIRECT", form)
+        monkeypatch.setenv("EDGC_TUNE_" + knob, form)
         c = edgc.Context(0, max_bins=256, max_rank=64, max_rows=m, max_cols=n)
         D, P, Q = torch.zeros(m, n, device="cuda"), torch.zeros(m, Q0.shape[1], device="cuda"), Q0.clone()
         c.compress(G, D, True, Q, P, r)
@@ -531,3 +531,15 @@ def test_override_of_the_q_pass_form_out_of_range(given, meant, dtype, monkeypat
     out = _q_pass_forms(700, 515, 20, dtype, (meant, given), monkeypatch)
     for got, want in zip(out[given], out[meant]):
         assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("m,n,r", [(1280, 4096, 20), (2560, 2048, 64), (704, 16384, 7)])
+def test_overrides_of_the_whole_tile_q_pass_reach_it(m, n, r, monkeypatch):
+    """EDGC_TUNE_QFULL alone selects among the kernels with a barrier per stage, also where the built-in choice is the one without:
+    whole tiles through the general kernel (0) and through the pipelined one are the same bits, in fp32 others than that one's."""
+    direct = _q_pass_forms(m, n, r, "f32", ("1",), monkeypatch)["1"][2]
+    monkeypatch.delenv("EDGC_TUNE_QDIRECT")
+    out = _q_pass_forms(m, n, r, "f32", ("0", "4"), monkeypatch, knob="QFULL")
+    assert torch.equal(out["0"][2], out["4"][2]) and not torch.equal(out["0"][2], direct)
+    monkeypatch.setenv("EDGC_TUNE_QDIRECT", "1")
+    assert torch.equal(_q_pass_forms(m, n, r, "f32", ("0",), monkeypatch, knob="QFULL")["0"][2], direct)
