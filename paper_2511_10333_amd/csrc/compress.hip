@@ -324,12 +324,10 @@ __host__ __device__ inline void tri_tile(int t, int T, int& ta, int& tb)
 // FROM_P: P is in the caller's buffer and not in partials (the second phase of a split call).  A template: as a branch it
 // costs the rank-128 kernel 24 registers (46 against 42 us on the hidden-5120 block).
 // What bounds it: a block's chain of the partials' loads (a CU's fetch rate: 32 KB times the splits for 64 rows above rank 64), LDS and
-// MFMA.  Above rank 32 eight waves share a chunk of 64 rows, and a chunk is of 32 or 16 rows where 64 would leave most CUs
-// without one.  Between events, always four waves of 64 rows / this: 1024 x 1024 fp32 at rank 100 14.7 / 4.7 us, 300 x 3000 23.8 / 8.0,
-// 8191 x 4097 bf16 16.5 / 11.5 (and 1.3 more to add up its 256 sets), 2047 x 2049 at rank 48 11.0 / 4.9, hidden-768 block at
-// rank 64 9.0 / 4.8, hidden-1024 block at rank 48 7.6 / 4.3, 512 x 512 at rank 40 5.6 / 2.1; with chunks of 64: hidden-2048 block at
-// rank 128 25.9 / 24.3, hidden-4096 block at rank 64 14.5 / 13.3, hidden-5120 block at rank 128 35.1 / 34.1.
-template <int T16, bool FROM_P, int WAVES, int ROWS>
+// MFMA.  Above rank 32 eight waves share a chunk of 64 rows.  Between events, four / eight: hidden-2048 block at rank 128 25.9 / 24.3,
+// hidden-4096 block at rank 64 14.5 / 13.3, hidden-5120 block at rank 128 35.1 / 34.1, 8191 x 4097 at rank 100 16.6 / 13.6.
+// (Chunks of fewer rows, which give the chip more blocks, change the order of the sums with what is in the launch.)
+template <int T16, bool FROM_P, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void k_reduce_gram(const Group grp, uint32_t pw)
 {
     const TensorArgs& ta_ = tensor_of(grp, blockIdx.x);
@@ -338,6 +336,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_reduce_gram(const Group grp, uin
     double* __restrict__ gram_part = ta_.gram_part;
     const uint32_t S = FROM_P ? 0 : ta_.sp, m = ta_.m, r = grp.r, ldp = ta_.ldp, chunks_per_block = ta_.d0;
     const uint32_t bid = blockIdx.x - ta_.first;
+    constexpr int ROWS = 64;
     constexpr int CW = 16 * T16;
     constexpr int LD = CW + 16;                      // floats; 4 rows x 16 columns per read: 2-way at worst
     constexpr int NTILE = T16 * (T16 + 1) / 2;
@@ -2560,30 +2559,62 @@ static int run_pass_p(edgc_ctx* ctx, Group& g, const TensorScratch* cap, bool wi
     return EDGC_OK;
 }
 
+// P = sum of the P-pass's partials, by itself
+static int run_reduce_p(edgc_ctx* ctx, Group& g, uint32_t pw, hipStream_t st)
+{
+    uint32_t whole_blocks = 0, most_splits = 0, blocks = 0;
+    for (uint32_t i = 0; i < g.count; ++i) {
+        whole_blocks += cdiv(static_cast<uint64_t>(g.t[i].m) * (pw / 4), 256);
+        most_splits = std::max(most_splits, g.t[i].sp);
+    }
+    const bool narrow = most_splits >= 16 && whole_blocks * 4u <= static_cast<uint32_t>(ctx->num_cu);      // as in run_pass_q
+    double bytes = 0.0;
+    for (uint32_t i = 0; i < g.count; ++i) {
+        TensorArgs& t = g.t[i];
+        t.first = g.first[i] = blocks;
+        blocks += cdiv(static_cast<uint64_t>(t.m) * (pw / 4), narrow ? 32 : 256);
+        bytes += 4.0 * t.m * g.r * (t.sp + 1);
+    }
+    ProfScope prof_scope_(ctx, st, KID_REDUCE_Q, bytes, 0.0);
+    if (narrow) k_reduce_q<32><<<blocks, 256, 0, st>>>(g, pw, 1);
+    else k_reduce_q<256><<<blocks, 256, 0, st>>>(g, pw, 1);
+    EDGC_HIP_TRY(ctx, hipGetLastError());
+    return EDGC_OK;
+}
+
 // from_p: P is in the caller's buffer and not in partials (the second phase of a split call)
 template <int NP>
 static int run_orthonormalise(edgc_ctx* ctx, Group& g, const TensorScratch* cap, hipStream_t st,
                               bool from_p = false)
 {
-    if (from_p)
-        for (uint32_t i = 0; i < g.count; ++i) g.t[i].sp = 0;
     const uint32_t r = g.r;
     const uint32_t RP = rank_tiles(r) * 32, pw = r <= 16 ? 16u : RP;       // pw: part_width
     const uint32_t t16 = gram_tiles(r);
     const uint32_t ntile = t16 * (t16 + 1) / 2, ne = ntile * 256;
+    // Above rank 32 a block of few has many partials to fetch: there P is summed by a launch of its own, over all CUs, and the Gram
+    // matrix taken from P.  The bits are the same.  k_reduce_gram alone / both: 1024 x 1024 at rank 100 (16 splits) 12.7 / 10.8 us, 300 x
+    // 3000 (47) 22.0 / 11.0, 2047 x 2049 (33) 18.5 / 13.4, at rank 48 9.6 / 7.2, hidden-768 block at rank 64 (24) 8.0 / 7.0, but 1024 x
+    // 1024 at rank 48 (16) 6.1 / 5.6 for a launch more, 8191 x 4097 at rank 100 (8) 13.8 / 14.3.
+    uint32_t all_chunks = 0, most_splits = 0;
+    for (uint32_t i = 0; i < g.count; ++i) {
+        all_chunks += cdiv(g.t[i].m, 64u);
+        most_splits = std::max(most_splits, g.t[i].sp);
+    }
+    if (!from_p && t16 >= 4 && 2 * all_chunks <= static_cast<uint32_t>(ctx->num_cu) && most_splits * RP >= 1536) {
+        if (int rc = run_reduce_p(ctx, g, pw, st)) return rc;
+        from_p = true;
+    }
+    if (from_p)
+        for (uint32_t i = 0; i < g.count; ++i) g.t[i].sp = 0;
     uint32_t tgt[kMaxGroup];
     share_targets(g, static_cast<uint32_t>(ctx->num_cu) * 2, tgt);
 
-    // P = sum of the partials, per-block Gram tiles; above rank 32 half chunks while they fit one round over the CUs, and
-    // quarters while they fit half of one
-    uint32_t blocks = 0, whole_chunks = 0;
-    for (uint32_t i = 0; i < g.count; ++i) whole_chunks += cdiv(g.t[i].m, 64u);
-    const uint32_t most = std::min(static_cast<uint32_t>(ctx->num_cu), kGramSets);
-    const uint32_t chunk = t16 < 4 || 2 * whole_chunks > most ? 64u : 8 * whole_chunks > most ? 32u : 16u;
+    // P = sum of the partials, per-block Gram tiles
+    uint32_t blocks = 0;
     double bytes = 0.0, flops = 0.0;
     for (uint32_t i = 0; i < g.count; ++i) {
         TensorArgs& t = g.t[i];
-        const uint32_t chunks = cdiv(t.m, chunk);
+        const uint32_t chunks = cdiv(t.m, 64);
         const uint32_t cpb = std::max(1u, chunks / tgt[i]);
         const uint32_t NB = cdiv(chunks, cpb);
         if (static_cast<uint64_t>(NB) * ne > cap[i].gram_part_elems)
@@ -2598,14 +2629,14 @@ static int run_orthonormalise(edgc_ctx* ctx, Group& g, const TensorScratch* cap,
     }
     {
         ProfScope prof_scope_(ctx, st, KID_REDUCE_GRAM, bytes, flops);
-#define EDGC_GRAM(T_, W_, R_)                                                              \
-    if (from_p) k_reduce_gram<T_, true, W_, R_><<<blocks, 64 * W_, 0, st>>>(g, pw);        \
-    else k_reduce_gram<T_, false, W_, R_><<<blocks, 64 * W_, 0, st>>>(g, pw);
+#define EDGC_GRAM(T_, W_)                                                              \
+    if (from_p) k_reduce_gram<T_, true, W_><<<blocks, 64 * W_, 0, st>>>(g, pw);        \
+    else k_reduce_gram<T_, false, W_><<<blocks, 64 * W_, 0, st>>>(g, pw);
         switch (t16) {
-        case 1: EDGC_GRAM(1, 4, 64) break;
-        case 2: EDGC_GRAM(2, 4, 64) break;
-        case 4: if (chunk == 64) { EDGC_GRAM(4, 8, 64) } else if (chunk == 32) { EDGC_GRAM(4, 8, 32) } else { EDGC_GRAM(4, 4, 16) } break;
-        default: if (chunk == 64) { EDGC_GRAM(8, 8, 64) } else if (chunk == 32) { EDGC_GRAM(8, 8, 32) } else { EDGC_GRAM(8, 8, 16) } break;
+        case 1: EDGC_GRAM(1, 4) break;
+        case 2: EDGC_GRAM(2, 4) break;
+        case 4: EDGC_GRAM(4, 8) break;
+        default: EDGC_GRAM(8, 8) break;
         }
 #undef EDGC_GRAM
     }
@@ -2829,18 +2860,7 @@ static int compress_impl(edgc_ctx* ctx, Group& g, const TensorScratch* cap, uint
     if (phase == 1) {
         int rc = run_pass_p<NP, RT>(ctx, g, cap, true, st);
         if (rc != EDGC_OK) return rc;
-        const uint32_t pw = g.r <= 16 ? 16u : RT * 32u;                    // part_width
-        uint32_t blocks = 0;
-        double bytes = 0.0;
-        for (uint32_t i = 0; i < g.count; ++i) {
-            TensorArgs& t = g.t[i];
-            t.first = g.first[i] = blocks;
-            blocks += cdiv(static_cast<uint64_t>(t.m) * (pw / 4), 256);
-            bytes += 4.0 * t.m * g.r * (t.sp + 1);
-        }
-        EDGC_LAUNCH(ctx, st, KID_REDUCE_Q, bytes, 0.0, (k_reduce_q<256><<<blocks, 256, 0, st>>>(g, pw, 1)));
-        EDGC_HIP_TRY(ctx, hipGetLastError());
-        return EDGC_OK;
+        return run_reduce_p(ctx, g, g.r <= 16 ? 16u : RT * 32u, st);       // (part_width)
     }
     if (phase == 2) {
         int rc = run_orthonormalise<NP>(ctx, g, cap, st, true);

@@ -89,8 +89,8 @@ extern "C" int edgc_create(edgc_ctx** out, int hip_device, uint32_t max_bins, ui
     const uint64_t rp = (max_rank <= 32) ? 32 : (max_rank <= 64 ? 64 : 128);
     const uint64_t rows_pad = (max_rows + 63) / 64 * 64;
     s.part_elems = compress_part_elems(max_rows, max_cols, max_rank, ctx->num_cu);
-    // per-block upper-triangle 16x16 Gram tiles: at most 36 tiles of 256 doubles per chunk
-    s.gram_part_elems = gram_sets(rows_pad) * 36ull * 256ull;
+    // per-block upper-triangle 16x16 Gram tiles: at most 36 tiles of 256 doubles per 64-row chunk
+    s.gram_part_elems = (rows_pad / 64) * 36ull * 256ull;
     s.pt_bytes = 2ull * rp * rows_pad * 2ull;
     bool ok = true;
     // everything but the large buffers in one allocation; what has to be zero between calls comes first
@@ -463,7 +463,7 @@ extern "C" int edgc_reserve_batch(edgc_ctx* ctx, const uint32_t* rows, const uin
         }
         const uint64_t rows_pad = (static_cast<uint64_t>(rows[i]) + 63) / 64 * 64;
         b.cap.part_elems = compress_part_elems(rows[i], cols[i], ctx->max_rank, ctx->num_cu);
-        b.cap.gram_part_elems = gram_sets(rows_pad) * 36ull * 256ull;
+        b.cap.gram_part_elems = (rows_pad / 64) * 36ull * 256ull;
         ok = ok && dev_alloc(&b.part, b.cap.part_elems) == hipSuccess;
         ok = ok && dev_alloc(&b.gram_part, b.cap.gram_part_elems) == hipSuccess;
         ok = ok && dev_alloc(&b.gram, static_cast<size_t>(36) * 256) == hipSuccess;

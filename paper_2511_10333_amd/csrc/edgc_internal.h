@@ -3,7 +3,6 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
-#include <algorithm>
 #include <stdint.h>
 #include <string>
 #include <vector>
@@ -44,14 +43,6 @@ constexpr uint32_t kCopyBins = 16384;      // largest histogram that is accumula
 // 16-wide tiles per side of the Gram matrix and of R^-1 at a rank: the orthonormalisation kernels are built for
 // 1, 2, 4 and 8, and work on (and store) every tile of the size they are built for.
 constexpr uint32_t gram_tiles(uint32_t r) { return r <= 16 ? 1 : r <= 32 ? 2 : r <= 64 ? 4 : 8; }
-
-// Gram sets that a matrix of up to that many rows can need (k_reduce_gram): one per 64 rows, or of fewer rows per 32 while they are
-// at most kGramSets, per 16 while they are at most half of that.
-constexpr uint32_t kGramSets = 256;
-constexpr uint64_t gram_sets(uint64_t rows_pad)
-{
-    return std::max({rows_pad / 64, std::min<uint64_t>(rows_pad / 32, kGramSets), std::min<uint64_t>(rows_pad / 16, kGramSets / 2)});
-}
 
 // Doubles behind `rinv`: the upper-triangle 16x16 tiles of R^-1 at any rank up to max_rank
 constexpr size_t rinv_elems(uint32_t max_rank)

@@ -217,6 +217,37 @@ def test_sums_of_partials_do_not_depend_on_how_many_blocks_share_them(dtype, r, 
         assert torch.equal(P, got[0][0]) and torch.equal(Q, got[0][1])
 
 
+@pytest.mark.parametrize("r,m,n,most", [(40, 2048, 1023, 2), (100, 2000, 640, 2), (100, 300, 3000, 9), (64, 8192, 512, 2), (48, 1000, 600, 3),
+                                        (40, 1024, 1600, 9)])
+def test_sums_of_gram_matrices_do_not_depend_on_the_neighbours(r, m, n, most, monkeypatch):
+    """A matrix of few rows alone and beside copies of itself, on the same splits (the last one alone with its P summed by a launch of its
+    own, the nine not).  Three quarters of P's directions are of small
+    length, so that the last bits of a Gram matrix reach P^ (a condition number of some 1e4, squared, of 2^-53 is more than 2^-30)."""
+    gen_ = torch.Generator(device="cuda").manual_seed(r + m + n)
+    k = r // 4
+    G = torch.randn(m, k, device="cuda", generator=gen_) @ torch.randn(k, n, device="cuda", generator=gen_)
+    G += 1e-3 * torch.randn(m, n, device="cuda", generator=gen_)
+    Q0 = torch.randn(n, r, device="cuda", generator=gen_)
+    got = []
+    for copies in (1, most):
+        for knob in ("EDGC_TUNE_P", "EDGC_TUNE_Q"):
+            monkeypatch.setenv(knob, str(copies))
+        c = edgc.Context(0, max_bins=16, max_rank=r, max_rows=64, max_cols=64)
+        c.reserve_batch([(m, n)] * copies)
+        ts = []
+        for _ in range(copies):
+            Q = torch.zeros(n, (r + 3) // 4 * 4, device="cuda")
+            Q[:, :r] = Q0
+            ts.append(edgc.Tensor(G, torch.empty_like(G), torch.empty(m, n, device="cuda"), Q,
+                                  torch.zeros(m, (r + 3) // 4 * 4, device="cuda"), True))
+        c.compress_batch(ts, r)
+        torch.cuda.synchronize()
+        got += [(t.P, t.Q) for t in ts]
+        c.close()
+    for P, Q in got[1:]:
+        assert torch.equal(P, got[0][0]) and torch.equal(Q, got[0][1])
+
+
 @pytest.mark.parametrize("deferred", [False, True])
 def test_prepared_descriptors_give_the_same_bits_as_a_list(deferred):
     """binding.PreparedBatch builds the descriptor array once and rewrites only the two per-call
