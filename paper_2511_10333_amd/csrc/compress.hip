@@ -1339,14 +1339,16 @@ __global__ __launch_bounds__(256) void k_reduce_q(const Group grp, uint32_t pw, 
 // Copies of the tensors that are sent as they stand (decompress hands the gradient on).  Contiguous ones, and a transformer stage
 // has a dozen norm weights and biases of some kilobytes each, ride at the head of the decompress's grid, since a launch
 // costs more than any of them (16 of them in the stage of two hidden-768 blocks: 16 launches 37 to 60 us, one 5; the pass
-// 82.7 us with one, 77.1 in k_decompress_copies).  16-byte accesses at any element address, so that the kernels that carry this code carry
+// 82.7 us with one, 77.1 in k_decompress_copies).  No more than kHeadCopies of them, which every block of that grid looks
+// through; more go as one launch before it, as do all of them before the other forms of the decompress.  16-byte accesses at any element address, so that the kernels that carry this code carry
 // little of it (with a case per alignment and strides it was 5500 instructions and 80 bytes of scratch).
 typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
-__device__ __forceinline__ void copy_run(const CopyRuns& runs, uint32_t bid)
+template <uint32_t N_RUNS>
+__device__ __forceinline__ void copy_run(const CopyRuns<N_RUNS>& runs, uint32_t bid)
 {
     uint32_t t = 0;
 #pragma unroll
-    for (uint32_t i = 1; i < kMaxCopies; ++i) t += (bid >= runs.first[i]) ? 1u : 0u;
+    for (uint32_t i = 1; i < N_RUNS; ++i) t += (bid >= runs.first[i]) ? 1u : 0u;
     const CopyRun& c = runs.t[t];
     const unsigned char* __restrict__ src = c.src;
     unsigned char* __restrict__ dst = c.dst;
@@ -1365,7 +1367,7 @@ __device__ __forceinline__ void copy_run(const CopyRuns& runs, uint32_t bid)
             if (i + k * 256u < whole) *reinterpret_cast<u32x4_any*>(dst + (i + k * 256u) * 16) = v[k];
     }
 }
-__global__ __launch_bounds__(256) void k_copy_runs(const CopyRuns runs) { copy_run(runs, blockIdx.x); }
+__global__ __launch_bounds__(256) void k_copy_runs(const CopyRuns<kMaxCopies> runs) { copy_run(runs, blockIdx.x); }
 
 // Copies whose rows are apart, all in one launch.  A unit is the widest access that pointers, row length and strides allow.
 template <typename U>
@@ -1655,7 +1657,7 @@ __global__ __launch_bounds__(256, (DEFER && C == Caching::by_tensor) ? 2 : 1) vo
 // a wave per SIMD (2047 x 2049 fp32 at rank 64, through the caches: 8.1 / 9.3 us); and for rows of whole cache lines only, which
 // the matrices that come with vectors have.
 template <int NP, int RT, bool DEFER>
-__global__ __launch_bounds__(256) void k_decompress_copies(const Group grp, const CopyRuns copies)
+__global__ __launch_bounds__(256) void k_decompress_copies(const Group grp, const CopyRuns<kHeadCopies> copies)
 {
     const TensorArgs& ta = tensor_of(grp, blockIdx.x);
     if (blockIdx.x < grp.first[0]) copy_run(copies, blockIdx.x);
@@ -2388,22 +2390,23 @@ int CopyList::add(const void* src, uint64_t ld_src, void* dst, uint64_t ld_dst, 
                   uint32_t elem_bytes, hipStream_t st)
 {
     if (static_cast<uint64_t>(m) * n == 0 || src == dst) return EDGC_OK;
-    static_assert(static_cast<uint64_t>(kMaxCopies) * copy_blocks(~0ull >> 16) * 256 < (1ull << 31), "threads of a launch, others beside them");
+    static_assert(static_cast<uint64_t>(kMaxCopies) * copy_blocks(~0ull >> 16) * 256 < (1ull << 32), "threads of a launch");
+    static_assert(static_cast<uint64_t>(kHeadCopies) * copy_blocks(~0ull >> 16) * 256 < (1ull << 31), "threads of a launch, others beside them");
     const uint64_t row_bytes = static_cast<uint64_t>(n) * elem_bytes;
     if (m == 1 || (ld_src == n && ld_dst == n)) {
-        if (runs.count == kMaxCopies)
+        if (run_count == kMaxCopies)
             if (int rc = flush(st)) return rc;
-        CopyRun& c = runs.t[runs.count];
+        CopyRun& c = runs.t[run_count];
         c.src = static_cast<const unsigned char*>(src);
         c.dst = static_cast<unsigned char*>(dst);
         c.bytes = row_bytes * m;
-        c.first = runs.first[runs.count++] = run_blocks;
+        c.first = runs.first[run_count++] = run_blocks;
         run_blocks += c.blocks = copy_blocks((c.bytes + 15) / 16);
         return EDGC_OK;
     }
-    if (rows.count == kMaxCopies)
+    if (row_count == kMaxCopies)
         if (int rc = flush_rows(st)) return rc;
-    CopyArgs& c = rows.t[rows.count];
+    CopyArgs& c = rows.t[row_count];
     c.src = static_cast<const unsigned char*>(src);
     c.dst = static_cast<unsigned char*>(dst);
     c.m = m;
@@ -2413,17 +2416,17 @@ int CopyList::add(const void* src, uint64_t ld_src, void* dst, uint64_t ld_dst, 
     const uint64_t bits = reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst) | row_bytes | c.ld_src | c.ld_dst;
     c.unit = 16;
     while (c.unit > elem_bytes && bits % c.unit) c.unit /= 2;
-    c.first = rows.first[rows.count++] = row_blocks;
+    c.first = rows.first[row_count++] = row_blocks;
     row_blocks += c.blocks = copy_blocks(row_bytes / c.unit * m);
     return EDGC_OK;
 }
 
 int CopyList::flush_rows(hipStream_t st)
 {
-    if (rows.count == 0) return EDGC_OK;
-    std::fill(rows.first + rows.count, rows.first + kMaxCopies, ~0u);
+    if (row_count == 0) return EDGC_OK;
+    std::fill(rows.first + row_count, rows.first + kMaxCopies, ~0u);
     k_copy_rows<<<row_blocks, 256, 0, st>>>(rows);
-    rows.count = row_blocks = 0;
+    row_count = row_blocks = 0;
     EDGC_HIP_TRY(ctx, hipGetLastError());
     return EDGC_OK;
 }
@@ -2431,10 +2434,10 @@ int CopyList::flush_rows(hipStream_t st)
 int CopyList::flush(hipStream_t st)
 {
     if (int rc = flush_rows(st)) return rc;
-    if (runs.count == 0) return EDGC_OK;
-    std::fill(runs.first + runs.count, runs.first + kMaxCopies, ~0u);
+    if (run_count == 0) return EDGC_OK;
+    std::fill(runs.first + run_count, runs.first + kMaxCopies, ~0u);
     k_copy_runs<<<run_blocks, 256, 0, st>>>(runs);
-    runs.count = run_blocks = 0;
+    run_count = run_blocks = 0;
     EDGC_HIP_TRY(ctx, hipGetLastError());
     return EDGC_OK;
 }
@@ -2960,19 +2963,22 @@ static int decompress_impl(edgc_ctx* ctx, Group& g, CopyList& copies, hipStream_
         return EDGC_OK;
     }
     const Caching caching = group_caching(n_past, g.count, static_cast<double>(d_bytes));
-    const bool with_copies = copies.runs.count != 0 && caching == Caching::past;
+    const bool with_copies = copies.run_count != 0 && copies.run_count <= kHeadCopies && caching == Caching::past;
+    CopyRuns<kHeadCopies> head;
     if (int rc = with_copies ? copies.flush_rows(st) : copies.flush(st)) return rc;
     if (with_copies) {                                 // the copies' blocks come first
         for (uint32_t i = 0; i < g.count; ++i) g.t[i].first = g.first[i] += copies.run_blocks;
         blocks += copies.run_blocks;
-        std::fill(copies.runs.first + copies.runs.count, copies.runs.first + kMaxCopies, ~0u);
+        std::copy_n(copies.runs.first, kHeadCopies, head.first);
+        std::copy_n(copies.runs.t, kHeadCopies, head.t);
+        std::fill(head.first + copies.run_count, head.first + kHeadCopies, ~0u);
     }
     ProfScope prof_scope_(ctx, st, KID_DECOMPRESS, bytes, flops);
     auto launch = [&](auto defer_tag) {
         constexpr bool DEFER = decltype(defer_tag)::value;
         switch (caching) {
         case Caching::past:
-            if (with_copies) k_decompress_copies<NP, RT, DEFER><<<blocks, 256, lds, st>>>(g, copies.runs);
+            if (with_copies) k_decompress_copies<NP, RT, DEFER><<<blocks, 256, lds, st>>>(g, head);
             else k_decompress<NP, RT, DEFER, Caching::past><<<blocks, 256, lds, st>>>(g);
             break;
         case Caching::through:                                     // (stored: never, through the caches only where small)
@@ -2984,7 +2990,7 @@ static int decompress_impl(edgc_ctx* ctx, Group& g, CopyList& copies, hipStream_
     };
     if (g.defer) launch(std::true_type{});
     else launch(std::false_type{});
-    copies.runs.count = copies.run_blocks = 0;
+    copies.run_count = copies.run_blocks = 0;
     EDGC_HIP_TRY(ctx, hipGetLastError());
     return EDGC_OK;
 }

@@ -268,7 +268,8 @@ int launch_compress(edgc_ctx* ctx, Group& g, const TensorScratch* cap, edgc_dtyp
                     uint32_t power_iters, hipStream_t st, int phase = 0);
 
 // Copies of tensors that are sent as they stand, collected and launched together (compress.hip).
-constexpr uint32_t kMaxCopies = 16, kCopyUnits = 1024;      // tensors per launch; units that a block copies at a time
+constexpr uint32_t kMaxCopies = 32, kHeadCopies = 16;       // tensors per launch; at the head of a decompress's grid
+constexpr uint32_t kCopyUnits = 1024;                       // units that a block copies at a time
 // Blocks of 256 threads for one tensor: a launch takes fewer than 2^32 threads, so beyond 2^18 blocks each copies several runs.
 constexpr uint32_t copy_blocks(uint64_t units)
 {
@@ -281,10 +282,10 @@ struct CopyRun {                            // contiguous
     uint64_t bytes;
     uint32_t first, blocks;                 // first block; blocks
 };
+template <uint32_t N>
 struct CopyRuns {
-    uint32_t first[kMaxCopies];             // as in Group
-    uint32_t count;
-    CopyRun t[kMaxCopies];
+    uint32_t first[N];                      // as in Group
+    CopyRun t[N];
 };
 struct CopyArgs {                           // rows apart
     const unsigned char* src;
@@ -294,14 +295,13 @@ struct CopyArgs {                           // rows apart
 };
 struct CopyGroup {
     uint32_t first[kMaxCopies];
-    uint32_t count;
     CopyArgs t[kMaxCopies];
 };
 struct CopyList {
     edgc_ctx* ctx;
-    CopyRuns runs{};
+    CopyRuns<kMaxCopies> runs{};
     CopyGroup rows{};
-    uint32_t run_blocks = 0, row_blocks = 0;
+    uint32_t run_count = 0, run_blocks = 0, row_count = 0, row_blocks = 0;
     int add(const void* src, uint64_t ld_src, void* dst, uint64_t ld_dst, uint32_t m, uint32_t n, uint32_t elem_bytes,
             hipStream_t st);                // strides in elements
     int flush_rows(hipStream_t st);

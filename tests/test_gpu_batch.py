@@ -577,6 +577,61 @@ def test_copies_at_the_head_of_the_decompress(dtype, r, count, deferred):
     c.close()
 
 
+def _launches(call):
+    """Nodes of the graph that `call(stream)` is captured into."""
+    import ctypes
+    path = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line)
+    hip, side, graph, nodes = ctypes.CDLL(path), torch.cuda.Stream(), ctypes.c_void_p(), ctypes.c_size_t()
+    torch.cuda.synchronize()
+    assert hip.hipStreamBeginCapture(ctypes.c_void_p(side.cuda_stream), 2) == 0
+    try:
+        call(side)
+    finally:
+        assert hip.hipStreamEndCapture(ctypes.c_void_p(side.cuda_stream), ctypes.byref(graph)) == 0
+    assert hip.hipGraphGetNodes(graph, None, ctypes.byref(nodes)) == 0
+    assert hip.hipGraphDestroy(graph) == 0
+    return nodes.value
+
+
+@pytest.mark.parametrize("kind,count,matrices,launches", [
+    ("runs", 16, None, 1), ("runs", 17, None, 1), ("runs", 32, None, 1), ("runs", 33, None, 2),
+    ("rows", 16, None, 1), ("rows", 17, None, 1), ("rows", 32, None, 1), ("rows", 33, None, 2), ("both", 64, None, 2), ("both", 66, None, 4),
+    ("runs", 16, (512, 640), 1), ("runs", 17, (512, 640), 2), ("runs", 32, (512, 640), 2), ("runs", 33, (512, 640), 2), ("runs", 49, (512, 640), 3),
+    ("both", 10, (512, 640), 2), ("both", 40, (512, 640), 3), ("rows", 33, (512, 640), 3), ("both", 10, (511, 641), 3), ("runs", 20, (511, 641), 2)])
+def test_launches_of_the_copies(kind, count, matrices, launches):
+    """Contiguous tensors sent as they stand and ones whose rows are apart: up to 32 of each in a launch, up to 16 contiguous ones in the
+    decompress's own where its rows are whole cache lines.  Every copy is the gradient and nothing around it is written."""
+    g = torch.Generator(device="cuda").manual_seed(count)
+    ts, pads = [], []
+    for i in range(count):
+        rows, cols, extra, off = (7, 3 + i % 5, 1 + i % 8, i % 4) if kind == "rows" or (kind == "both" and i % 2) else (1, 100 + i, 0, i % 4)
+        def view(fill):
+            buf = torch.full((off + rows * (cols + extra) + 8,), fill, device="cuda")
+            return buf, buf[off:off + rows * (cols + extra)].view(rows, cols + extra)[:, :cols]
+        grad, (buf, out) = view(0.0)[1], view(7.0)
+        grad.copy_(torch.randn(rows, cols, generator=g, device="cuda"))
+        ts.append(edgc.Tensor(grad, out)); pads.append(buf)
+    r, mats = 64, []
+    if matrices:
+        m, n = matrices
+        for _ in range(2):
+            D, P, Q = (torch.randn(*s, generator=g, device="cuda") for s in ((m, n), (m, r), (n, r)))
+            mats.append(edgc.Tensor(None, torch.empty(m, n, device="cuda"), D, Q, P))
+    ts = ts[:count // 2] + mats + ts[count // 2:]
+    want = [t.residual - t.P @ t.Q.t() for t in mats]
+    c = edgc.Context(0, max_bins=16, max_rank=r, max_rows=64, max_cols=64)
+    c.reserve_batch([tuple(t.grad_out.shape) for t in ts])
+    assert _launches(lambda s: c.decompress_batch(ts, r, stream=s)) == launches
+    c.decompress_batch(ts, r)
+    copied = [t for t in ts if t.grad is not None]
+    for t, buf in zip(copied, pads):
+        assert torch.equal(t.grad_out, t.grad)
+        assert int((buf != 7.0).sum()) == int((t.grad != 7.0).sum())
+    for t, e in zip(mats, want):
+        assert float((t.residual - e).norm() / e.norm()) < 1e-4        # operands of 17 bits: 2^-16 of |P| |Q|, which |E| exceeds
+    c.close()
+
+
 def test_calls_without_a_stream_use_torchs_current_one():
     from paper_2511_10333_amd.binding import _stream_handle
     assert _stream_handle(None) == torch.cuda.current_stream().cuda_stream
