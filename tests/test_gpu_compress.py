@@ -444,9 +444,9 @@ def test_sums_of_many_partials_in_few_columns(m, n, r):
 @pytest.mark.parametrize("m,n,r", [(64, 64, 8), (40, 33, 3), (33, 65, 32), (65, 127, 16), (257, 1001, 20), (1000, 66, 33), (4100, 70, 64),
                                    (515, 4160, 40), (256, 128, 1), (321, 130, 64), (9000, 40, 5), (70, 1, 1), (70, 2, 2), (2, 70, 1)])
 def test_q_pass_of_waves_by_themselves(m, n, r, dtype, monkeypatch):
-    """k_pass_q_direct, with one column group per block and with two, against k_pass_q: edges of stages and strips, rows at odd
-    addresses, fewer rows than a block's waves take.  The products are the same and exact in fp32; what differs is the order of
-    at most 3 m additions a value."""
+    """The Q-pass of waves by themselves in both forms (fp32: one column group per block and two) against k_pass_q: edges of
+    stages and strips, rows at odd addresses, fewer rows than a block's waves take.  The products are the same and exact in fp32; what
+    differs is the order of at most 3 m additions a value."""
     g = torch.Generator(device="cuda").manual_seed(m * n + r)
     G = torch.randn(m, n, device="cuda", generator=g)
     G = G.to(torch.bfloat16) if dtype == "bf16" else G
@@ -510,6 +510,20 @@ def _q_pass_forms(m, n, r, dtype, forms, monkeypatch, knob="QDIRECT", **env):
         c.close()
         out[form] = (D, P, Q)
     return out
+
+
+@pytest.mark.parametrize("stream", ["0", "1"])
+@pytest.mark.parametrize("m,n,r", [(700, 16387, 5), (700, 16387, 20), (733, 16389, 33), (700, 16387, 64), (1472, 8193, 16), (1500, 8194, 48), (1536, 16384, 32)])
+def test_q_pass_of_waves_by_themselves_over_several_stages(m, n, r, stream, monkeypatch):
+    """k_pass_q_direct where a wave takes two stages and more (few row splits: a block per CU aimed at, strips for all of them): the
+    requests for its next stage, then a stage that ends early, an odd last column, cached and streamed reads.  Bound: as above."""
+    out = _q_pass_forms(m, n, r, "f32", ("0", "1", "2"), monkeypatch, STREAM=stream, Q="1")
+    D, P, Q = out["0"]
+    bound = 2 * 3 * m * 2.0 ** -23 * (1 + 2.0 ** -7) * (D.double().abs().t() @ P.double().abs())
+    for form in ("1", "2"):
+        assert torch.equal(out[form][0], D) and torch.equal(out[form][1], P)
+        assert bool(((out[form][2].double() - Q.double()).abs() <= bound).all())
+        assert not out[form][2][:, r:].any()
 
 
 @pytest.mark.parametrize("stream", ["0", "1"])

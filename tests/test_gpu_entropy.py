@@ -462,7 +462,7 @@ def _kernels_of(c, x, bins):
 
 
 @pytest.mark.parametrize("bins,line", [(256, 8 << 20), (4096, 8 << 20), (16384, 8 << 20), (16385, 4 << 20), (65536, 4 << 20)])
-def test_bf16_samples_are_counted_by_pattern_from_where_one_read_is_the_faster(bins, line):
+def test_bf16_samples_are_counted_by_pattern_from_the_line_on(bins, line):
     """The kernels on both sides of the line between two passes and one read."""
     x = (torch.randn(line, device="cuda") * 1e-3).bfloat16()
     c = _context_with()
