@@ -163,7 +163,7 @@ struct edgc_ctx {
     int tune_pattern = 1;   // entropy estimate: 1 one read into 16-bit counters per block where that applies
                             // (bf16 samples, fp32 on more than 16384 bins); 0 the plain kernels only
     long long tune_pattern_min = 8 << 20;   // bf16 samples from this many elements on are counted by bit pattern
-                                            // (on more than 16384 bins: from an eighth of it on)
+                                            // (on more than 16384 bins: from half of it on)
     edgc::Scratch s;
     std::vector<edgc::BatchSlot> batch;
     edgc::Profiler prof;

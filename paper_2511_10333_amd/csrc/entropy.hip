@@ -429,7 +429,7 @@ struct EstimateLogs {
 // H = (log2 n - e0) - (1/n) sum c (log2 c - e0), without the cancellation of log2 n.
 __device__ __forceinline__ int entropy_base(unsigned long long n_sampled) { return __builtin_amdgcn_frexp_exp(static_cast<double>(n_sampled)); }
 // log2 of a positive integer (some finite value for 0) less the integer e0, in fp64: x = 2^e m with m in [sqrt 1/2, sqrt 2), log2 m
-// from the series of artanh at s = (m - 1) / (m + 1), s^2 < 0.0295, to s^19 (what is left out is below 2^-56 of it).  Some 25 dependent
+// from the series of artanh at s = (m - 1) / (m + 1), s^2 < 0.0295, to s^19 (what is left out is below 2^-55 of it).  Some 25 dependent
 // operations and short code, which the last block of a grid runs alone and from a cold cache: the library's function, one bin after
 // the other, was 3 to 4 of the 17 us that the histogram kernel of a 1 % sample took on 4096 bins.
 __device__ __forceinline__ double log2_count(double x, int e0)
@@ -461,8 +461,8 @@ __device__ __forceinline__ EstimateLogs estimate_logs(const RangeParams& rp, uin
     return {log2_count(static_cast<double>(n_sampled), entropy_base(n_sampled)), w > 0.0 ? log(w / static_cast<double>(bins)) : 0.0};
 }
 
-// The estimate from sum c (log2 c - e0) (`acc`) and sum c (`tot`) over the bins, by one thread, in fp64, and the result record.  `res` may be the caller's pinned host memory: the end of the
-// kernel makes it visible.
+// The estimate from sum c (log2 c - e0) (`acc`) and sum c (`tot`) over the bins, by one thread, in fp64, and the result record.
+// `res` may be the caller's pinned host memory: the end of the kernel makes it visible.
 __device__ __forceinline__ void emit_result(double acc, double tot, const EstimateLogs& logs, const RangeParams& rp,
                                             unsigned long long n_sampled, edgc_entropy_result* res)
 {
@@ -1278,17 +1278,25 @@ static int run_entropy(edgc_ctx* ctx, const EntScratch& s, const EntGroup& g, ui
     // for the blocks' fields: every bf16 sample of some size (no range pass, any number of bins), and
     // fp32 samples on more bins than 32-bit counters hold in LDS at once.
     const bool wide_ok = s.part16 != nullptr && ctx->tune_pattern != 0;
-    // The line for bf16 lies at 8 Mi elements, where two-pass samples leave the kernels of short blocks; at half of that above 16384
-    // bins.  Per estimate in us, two passes / one read, every element of a buffer (1 sampled in 3 and in 10: the same within 2):
-    //                  256 bins      4096 bins     16384 bins    16385 bins    65536 bins
-    //      4 M         15.7 / 18.5   18.1 / 19.7   29.2 / 24.5   26.8 / 24.7   48.3 / 38.1
-    //      6 M         18.6 / 19.2   21.8 / 19.9   31.3 / 25.1   29.0 / 25.0   49.7 / 39.0
-    //      8 M         20.3 / 20.0   23.4 / 20.8   32.3 / 25.2   29.3 / 25.4   49.9 / 39.3
-    //     12 M         25.7 / 22.1   28.1 / 23.1   37.3 / 28.2   74.8 / 28.5   88.1 / 41.7
-    //     24 M         36.2 / 28.0   38.5 / 28.8   47.9 / 33.7   80.2 / 34.1   92.9 / 47.8
-    //     64 M         58.8 / 40.8   63.8 / 42.0   73.5 / 47.2   93.5 / 47.8  109.8 / 62.8
-    // (The line was drawn when the sums over the bins took longer in the one read; now the two meet at 6 M on few bins, and the one
-    // read is the faster from 1 M on above 4096 bins: 28.1 / 22.8 on 16384, 45.1 / 35.6 on 65536.)
+    // The line for bf16 lies at 8 Mi elements, where two-pass samples leave the kernels of short blocks, and at half of that above 16384
+    // bins.  It was drawn there when the sums over the bins took longer in the one read, and it is not where the two meet now: without a
+    // caller's range that is at some 6 M elements up to 4096 bins, 3 to 4 M on 8192 and below 0.5 M from 12000 on (up to a fifth of the
+    // estimate is left there); with one, which spares the two passes their first, beyond 8 Mi up to 4096 bins.  Per estimate in us, two passes
+    // / one read, every element of a buffer (1 sampled in 3 and in 10: the same within 2; 12 and 24 buffers within 3):
+    //                  256 bins      4096 bins      8192 bins    16384 bins    16385 bins    65536 bins
+    //      1 M         13.0 / 17.4   15.5 / 18.4   19.9 / 20.0   28.1 / 22.8   25.4 / 22.9   45.3 / 35.5
+    //      4 M         15.4 / 18.3   17.9 / 19.4   22.4 / 20.8   29.3 / 24.7   26.8 / 24.5   48.1 / 38.2
+    //      6 M         18.4 / 19.2   21.6 / 20.5   25.2 / 21.8   31.2 / 25.6   28.5 / 25.7   49.9 / 39.6
+    //      8.4 M       20.8 / 19.8   23.7 / 20.9   28.1 / 22.3   32.4 / 25.5   29.8 / 25.7   50.1 / 39.7
+    //     12 M         25.7 / 22.1   28.1 / 23.1                 37.3 / 28.2   74.8 / 28.5   88.1 / 41.7
+    //     24 M         36.2 / 28.0   38.5 / 28.8                 47.9 / 33.7   80.2 / 34.1   92.9 / 47.8
+    //     64 M         58.8 / 40.8   63.8 / 42.0                 73.5 / 47.2   93.5 / 47.8  109.8 / 62.8
+    //   a range given:
+    //      4 M         13.4 / 18.4   14.6 / 19.6   21.9 / 20.8   26.0 / 24.5   23.3 / 24.7   50.6 / 45.6
+    //      8.4 M       16.8 / 20.0   19.0 / 21.0   28.2 / 22.4   30.5 / 26.2   26.3 / 26.2   52.7 / 45.1
+    //   buffers off 16-byte boundaries:
+    //      1 M         16.4 / 17.7   18.0 / 18.8   24.3 / 20.5   38.0 / 23.4   34.5 / 23.5   64.6 / 35.9
+    //      4 M         30.2 / 20.1   29.1 / 21.1   32.1 / 22.3   38.0 / 26.0   50.0 / 26.4   65.8 / 39.6
     const uint64_t pattern_min = static_cast<uint64_t>(ctx->tune_pattern_min);
     const bool by_pattern = sizeof(T) == 2 && wide_ok &&
                             (g.n_sampled >= pattern_min || (bins > 16384 && g.n_sampled >= pattern_min / 2));
