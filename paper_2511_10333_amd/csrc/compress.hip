@@ -2972,6 +2972,7 @@ static int decompress_impl(edgc_ctx* ctx, Group& g, CopyList& copies, hipStream_
         std::copy_n(copies.runs.first, kHeadCopies, head.first);
         std::copy_n(copies.runs.t, kHeadCopies, head.t);
         std::fill(head.first + copies.run_count, head.first + kHeadCopies, ~0u);
+        for (uint32_t i = 0; i < copies.run_count; ++i) bytes += 2.0 * head.t[i].bytes;
     }
     ProfScope prof_scope_(ctx, st, KID_DECOMPRESS, bytes, flops);
     auto launch = [&](auto defer_tag) {

@@ -632,6 +632,21 @@ def test_launches_of_the_copies(kind, count, matrices, launches):
     c.close()
 
 
+@pytest.mark.parametrize("count", [0, 16, 17])
+def test_profile_credits_the_copies_that_ride_in_the_decompress(count):
+    """Their time is in the decompress's, so their bytes are: read and written; a launch of their own is not profiled."""
+    m, n, r, k = 512, 640, 8, 100_000
+    D, P, Q = torch.zeros(m, n, device="cuda"), torch.zeros(m, r, device="cuda"), torch.zeros(n, r, device="cuda")
+    ts = [edgc.Tensor(torch.zeros(k, device="cuda"), torch.empty(k, device="cuda")) for _ in range(count)]
+    ts.append(edgc.Tensor(None, torch.empty(m, n, device="cuda"), D, Q, P))
+    c = edgc.Context(0, max_bins=16, max_rank=r, max_rows=64, max_cols=64)
+    c.reserve_batch([(1, k)] * count + [(m, n)])
+    c.profile_begin(16)
+    c.decompress_batch(ts, r)
+    assert c.profile_end()["k_decompress"]["bytes"] == 12 * m * n + (8 * k * count if count <= 16 else 0)
+    c.close()
+
+
 def test_calls_without_a_stream_use_torchs_current_one():
     from paper_2511_10333_amd.binding import _stream_handle
     assert _stream_handle(None) == torch.cuda.current_stream().cuda_stream
