@@ -6,9 +6,9 @@
 //   k_gram_sum      Gram = sum of the per-block Grams (only when there are many)
 //   k_chol          scaled Cholesky of the Gram in fp64, inverse factor R^-1 (above rank 32, and in launches
 //                   of many blocks; otherwise k_apply's blocks do it themselves)
-//   k_apply         P^ = P R^-1 (fp64), plus a transposed bf16 operand copy of P^
-//   k_pass_q        Q_partial = D^T P^                                (split over rows)
-//   k_reduce_q      Q = sum of partials
+//   k_apply         P^ = P R^-1 (fp64), plus a bf16 operand copy of P^ in the order of the Q-pass's fragments
+//   k_pass_q        Q_partial = D^T P^                                (split over rows; other forms in pass_q_full.hip and pass_q_direct.hip)
+//   k_reduce_q      Q = sum of partials (and P, where the Gram matrix does not sum them)
 //   k_decompress    M^ = P^ Q^T -> grad_out, E_new = D - M^
 //   k_pass_p_deferred   the P-pass when the residual buffer kept D of the step before instead of E
 //                   (batched calls, deferred = 1): E = D_prev - P^_prev Q_prev^T is formed on the
